@@ -267,27 +267,36 @@ Params derive(const sdf_search_params *p, uint32_t k, uint32_t w) {
 }
 
 
-// Window starts per tile: as many as keep a tile's hits within one target
-// partition (hits per window start run about 1.15 hbar, and splitting a tile
-// into partitions costs a search of every list per partition), at least 512
-// so fixed per-tile costs stay amortised.
-uint32_t auto_tile_core(double hbar, uint32_t hpart, uint32_t cmax) {
-    const double per_win = 1.15 * (hbar > 1.0 ? hbar : 1.0);
-    double c = 0.95 * (double)hpart / per_win;
-    c = std::min(std::max(c, 512.0), (double)cmax);
-    return ((uint32_t)c) & ~63u;
+// Hits per target partition: as many as the layout holds while at most a third
+// of the room for kept hits is taken by hits kept by chance.  A hit is kept
+// when one of three pairs of slots around it counts T hits; by chance the
+// others of a pair are Poisson distributed about their mean number.
+uint32_t auto_hits_per_part(const TileLimits &t, double T) {
+    const double slots = T <= 15.0 ? t.slots : t.slots / 2;
+    uint32_t h = t.hits;
+    for (; h > 4096; h -= 1024) {
+        const double mean = 2.0 * h / slots;
+        double p = std::exp(-mean), tail = 1.0;  // tail: P(others >= T - 1)
+        for (double x = 0; x < T - 1.0; x++) {
+            tail -= p;
+            p *= mean / (x + 1.0);
+        }
+        if (3.0 * h * tail <= t.kept / 3.0) break;
+    }
+    return h;
+}
+
+// Window starts per tile: as many as keep a tile's hits (of its minimizers,
+// the halo of the last window included) within one target partition, since
+// partitions cost a search of every list each.
+uint32_t auto_tile_core(double hits_per_min, double halo, uint32_t hpart, uint32_t cmax) {
+    const double c = 0.85 * (double)hpart / std::max(hits_per_min, 1e-3) - halo;
+    return ((uint32_t)std::min(std::max(c, 128.0), (double)cmax)) & ~63u;
 }
 
 // Most window bases the 512-thread tile layout holds: a window has at most
 // n - k + 1 minimizers, and that layout keeps 1,024 per tile.
 bool fits_tile512(uint32_t n, uint32_t k) { return n <= 1023 + k; }
-
-// Workgroup layout of the tile kernel: 512 threads, two workgroups per CU,
-// when the windows fit it and hits are sparse (mean list length up to 8; its
-// bin table is a quarter of the size), else 1,024 threads, one per CU.
-uint32_t tile_threads_rule(double hbar, uint32_t n, uint32_t k) {
-    return (fits_tile512(n, k) && hbar <= 8.0) ? 512u : 1024u;
-}
 
 int cu_count(int dev) {
     static int cached[64] = {0};
@@ -353,7 +362,7 @@ void check_spans(const sdf_index_s *ix, const sdf_span *qs, uint32_t nq) {
 // device, then each span's window starts and tiles (span set-up).
 struct Prepared {
     uint64_t qbases = 0;
-    uint32_t threads = 1024, core = 512, hpart = 16384, sb = 0, grid = 1;
+    uint32_t threads = 1024, core = 512, halo = 1, hpart = 16384, sb = 0, grid = 1;
     DevBuf<unsigned char> dup;
     const uint16_t *dT = nullptr;
     SpanDesc *dsd = nullptr;
@@ -421,18 +430,31 @@ void prepare(sdf_index_s *ix, const sdf_span *qs, uint32_t nq, const Params &P, 
     // schedule, else the calling thread's settings (sdf_set_tuning, where
     // sdf_autotune's choice goes), else the hit-density rules
     const sdf_tuning &tu = tuning();
-    uint32_t threads = threads_override
-                           ? threads_override
-                           : knob(tu.tile_threads, tile_threads_rule(ix->hbar, P.n, ix->k));
+    // minimizers per window, the least threshold a tile is likely to have, and
+    // hits per minimizer (of which only the eligible ones have any)
+    const double per_win = (double)P.n * (double)ix->nm / (double)std::max<uint64_t>(ix->total, 1);
+    const double t_min = std::ceil(0.8 * P.tau * per_win);
+    const double hits_per_min = ix->hbar * (double)ix->ne / (double)std::max<uint64_t>(ix->nm, 1);
+    // 512 threads, two workgroups per CU, while a tile of 256 window starts and
+    // its halo keeps its hits in one partition of that layout's smaller table,
+    // else 1,024 threads, one per CU (measured: 250 Mbp at 20.7 hits per
+    // minimizer 1.65 against 1.95 ms, 3.1 Gbp at 93 hits 199 ms at 320 starts
+    // in two partitions each against 206 ms at 512 in one)
+    const TileLimits lim512 = tile512::tile_limits();
+    const bool sparse = hits_per_min * (256.0 + per_win) <= 0.85 * auto_hits_per_part(lim512, t_min);
+    uint32_t threads = threads_override ? threads_override : knob(tu.tile_threads, sparse ? 512u : 1024u);
     if (!fits_tile512(P.n, ix->k)) threads = 1024;
-    const uint32_t cmax = threads == 512 ? tile512::tile_core_max() : tile1024::tile_core_max();
+    const TileLimits lim = threads == 512 ? lim512 : tile1024::tile_limits();
+    const uint32_t cmax = lim.core;
     const uint32_t hpart =
-        std::max<uint32_t>(knob(tu.hits_per_part, threads == 512 ? 8192 : 16384), 1024);
-    const uint32_t pick =
-        core_override ? core_override : knob(tu.tile_core, auto_tile_core(ix->hbar, hpart, cmax));
+        std::max<uint32_t>(knob(tu.hits_per_part, auto_hits_per_part(lim, t_min)), 1024);
+    const uint32_t pick = core_override ? core_override
+                                        : knob(tu.tile_core, auto_tile_core(hits_per_min, per_win,
+                                                                            hpart, cmax));
     const uint32_t core = std::min(std::max<uint32_t>(pick, 1), cmax);
     pr.threads = threads;
     pr.core = core;
+    pr.halo = (uint32_t)std::min(1.25 * per_win + 16.0, 4096.0);
     pr.hpart = hpart;
     pr.ntiles.alloc(nq + 1);
     pr.tile0.alloc(nq + 1);
@@ -486,6 +508,7 @@ SearchArgs tile_args(sdf_index_s *ix, const Params &P, const Prepared &pr, uint3
     a.total_tiles = pr.tile0.p + nq;
     a.work = work;
     a.core = pr.core;
+    a.halo = pr.halo;
     a.hpart = pr.hpart;
     a.bin_shift = pr.sb;
     a.seeds = seeds;

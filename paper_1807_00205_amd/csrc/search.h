@@ -43,6 +43,7 @@ struct SearchArgs {
     const uint32_t *total_tiles;  // device: tiles over all spans
     uint32_t *work;          // tile counter (starts at 0)
     uint32_t core;           // window starts per tile
+    uint32_t halo;           // minimizers read past the core (more when a window reaches further)
     uint32_t hpart;          // target hits per partition
     uint32_t bin_shift;      // target bins of 2^bin_shift >= n bases
     uint32_t *seeds;         // 6 u32 per seed
@@ -79,15 +80,22 @@ void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nr
 
 void launch_span_setup(const IndexView &ix, SpanDesc *spans, uint32_t nspans, uint32_t n,
                        uint32_t core, uint32_t *ntiles, uint32_t *tile0, hipStream_t st);
+// What a tile layout holds: window starts, minimizers and hits per partition,
+// kept hits, and the slots of its bin table while counters have 4 bits.
+struct TileLimits {
+    uint32_t core, minimizers, hits, kept, slots;
+};
 // The tile kernel in its two workgroup layouts (search.hip compiled twice):
 // 1,024 threads, one workgroup per CU; 512 threads, two per CU.
 namespace tile1024 {
 void launch_tile_search(const SearchArgs &a, uint32_t grid, hipStream_t st);
 uint32_t tile_core_max();
+TileLimits tile_limits();
 }
 namespace tile512 {
 void launch_tile_search(const SearchArgs &a, uint32_t grid, hipStream_t st);
 uint32_t tile_core_max();
+TileLimits tile_limits();
 }
 
 // Chaining (chain.hip): seeds -> sorted candidates.

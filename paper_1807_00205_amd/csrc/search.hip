@@ -7,25 +7,40 @@
 // One workgroup owns a tile: up to `core` consecutive minimizers of the span
 // as window starts plus the halo of minimizers the last window reaches.  All
 // hits of the tile stay on chip:
-//   1. gather pass 1: every hit (p, p', o) increments a counter for its
-//      (orientation, target bin of 2^SB >= n bases) in an LDS hash table;
-//   2. gather pass 2: a hit is kept only if some pair of adjacent bins around
-//      it holds at least T_min hits.  Hash collisions only raise counts, so
-//      no hit that could matter is dropped (lossless prefilter);
-//   3. kept hits are sorted in LDS by (o, p', q); exact raw counts decide the
+//   1. gather: every hit (p, p', o) is loaded once, increments a small counter
+//      for its (orientation, target bin of 2^SB >= n bases) in an LDS table
+//      indexed by the bin modulo the table size, and stays in a register;
+//   2. the counters become flags: a slot is hot when some pair of adjacent
+//      bins around it holds at least T_min hits;
+//   3. a hit is kept only if its slot is hot.  Bins that share a slot only
+//      raise counts, so no hit that could matter is dropped (lossless);
+//   4. kept hits are sorted in LDS by (o, p', q); exact raw counts decide the
 //      target starts x that could pass for some window of the tile, and the
 //      hits within 2n of such an x are kept;
-//   4. each wave takes windows and walks their candidates in target order,
-//      counting distinct shared hashes exactly with a per-wave bitmask, and
-//      runs the run/argmax logic.
+//   5. each wave takes windows and walks their candidates in target order,
+//      with every window's count of distinct shared hashes kept up to date as
+//      hits enter and leave the target window, and runs the run/argmax logic.
 // Large tiles split the target coordinate range into partitions processed
 // in order (run state of every window is kept across partitions).
 //
+// What bounds it: on dense indexes (3.1 Gbp: 185 hits per minimizer, 39 G per
+// search) the gather's loads and the LDS counters, on sparse ones the latency
+// of the phase sequence.  Counters have 4 bits while the tile has many hits
+// (131,072 slots in 64 KiB: fewer chance hits in a slot than 16-bit counters
+// in a quarter of the slots, so the whole tile fits one partition and every
+// list is read once, in one piece), 8 bits when it has few or when a 4-bit
+// counter overflows, 16 bits when an 8-bit one does.  An overflow shows in
+// the sum of the counters, taken while they become flags: it equals the
+// number of hits counted exactly when none wrapped.
+//
+// Measured against 16-bit counters in 32 KiB, partitions of 16,384 hits, a
+// search per hit for its list and hits gathered twice (tile kernel): 3.1 Gbp
+// all-vs-all 538 -> 205 ms, 4,096 spans on 250 Mbp 4.06 -> 1.65 ms, 50 Mbp
+// 1.31 -> 0.94 ms.
+//
 // The file is compiled twice, for two workgroup layouts (SDF_TILE_THREADS):
-// 1,024 threads with 148 KB of LDS, one workgroup per CU, and 512 threads
-// with 77 KB, two per CU, whose barrier waits overlap each other's work
-// (faster where hits are sparse; its bin table is a quarter of the size, so
-// dense hit sets are kept less selectively).
+// 1,024 threads, one workgroup per CU, and 512 threads with 80 KB of LDS, two
+// per CU, whose barrier waits overlap each other's work.
 #include "kmer.h"
 #include "sdf_impl.h"
 #include "search.h"
@@ -41,27 +56,27 @@ constexpr int TB = 1024;        // threads per tile workgroup
 constexpr int QCAP = 1280;      // query minimizers per tile (core + halo)
 constexpr int CMAX = 1024;      // window starts per tile core
 constexpr int CB = 2048;        // kept hits per partition
-constexpr int TSLOTS = 16384;   // 16-bit counters in the bin table
-constexpr int TSLOT_BITS = 14;
-#define SDF_TILE_WAVES_PER_EU 4
+constexpr uint32_t TLOG = 16;   // bin table of 2^TLOG bytes
+constexpr uint32_t HCAP = 65535;  // hits per partition
 #elif SDF_TILE_THREADS == 512
 namespace tile512 {
 constexpr int TB = 512;
 constexpr int QCAP = 1024;      // holds any window of up to 1,023 + k bases
 constexpr int CMAX = 512;
 constexpr int CB = 1024;
-constexpr int TSLOTS = 4096;
-constexpr int TSLOT_BITS = 12;
-#define SDF_TILE_WAVES_PER_EU 4  // two workgroups per CU: at most 128 VGPRs
+constexpr uint32_t TLOG = 15;
+constexpr uint32_t HCAP = 32767;
 #else
 #error "SDF_TILE_THREADS must be 512 or 1024"
 #endif
+#define SDF_TILE_WAVES_PER_EU 4  // 16 waves per CU: at most 128 VGPRs
 constexpr int NWAVES = TB / 64;
-constexpr int TWORDS = TSLOTS / 2;
+constexpr uint32_t TBYTES = 1u << TLOG;
+constexpr uint32_t TWORDS = TBYTES / 4;
+constexpr uint32_t NCHUNK = (HCAP + 1) / 64;  // 64-hit chunks per partition
 constexpr int SBUF = 32;        // seeds buffered per wave before one global atomic
-constexpr uint32_t HMAX = 65535;  // hits per partition (16-bit counters cannot overflow)
 constexpr int STACK = 40;
-constexpr int QW = QCAP / 64;     // 64-bit words of a bitmask over the query minimizers
+static_assert(CMAX <= TB && CB % TB == 0 && TBYTES % (16 * TB) == 0, "one pass per thread");
 
 enum : uint32_t { EF_CAND = 1 };
 // Packed per kept hit after compaction: its query minimizer, whether it is a
@@ -71,65 +86,79 @@ constexpr uint32_t EI_Q = 0x7FFu;        // bits 0-10
 constexpr uint32_t EI_CAND = 1u << 11;
 constexpr uint32_t EI_SAMEP = 1u << 12;
 static_assert(QCAP <= 2048, "EI_Q field width");
-// Minimizers of one window that share hash and strand have the same hits
-// except each one's own position, so their union is the full list: the
-// first one stands for all of them with its self-hit kept (QM_UNION), the
-// others are left out (QM_SKIP).
-enum : uint8_t { QM_NORMAL = 0, QM_SKIP = 1, QM_UNION = 2 };
+// Flags of a query minimizer: strand and eligibility from the index, whether
+// its hits are in the partition's lists, and its mode while a partition covers
+// a single window.  Minimizers of one window that share hash and strand have
+// the same hits except each one's own position, so their union is the full
+// list: the first one stands for all of them with its self-hit kept (union),
+// the others are left out (skip).
+enum : uint32_t { QF_STRAND = 1, QF_ELIG = 2, QF_LISTED = 4, QF_UNION = 8, QF_SKIP = 16 };
 enum : uint32_t {
     ERR_COLLECT = 2,     // (a partition keeps more than CB hits: split, or listed as dense)
-    ERR_HITS = 4,        // (a partition has more than HMAX hits: split, or listed as dense)
+    ERR_HITS = 4,        // (a partition has more than HCAP hits: split, or listed as dense)
     ERR_STACK = 8,       // partition splits nested deeper than the stack
     ERR_DENSE_FULL = 16  // more dense windows than the list holds
 };
 
-struct RunState {
-    uint32_t prev_j, prev_seq, best_j;
-    uint16_t best_c;
-    uint16_t active;
+// Kept hits after the gather, over the bin table.
+struct PostLds {
+    uint32_t hot[CB];       // last hot start at or before an entry, + 1
+    uint32_t pref[CB + 1];
+    uint32_t etb[CB];       // start of the candidate's sequence
+    uint32_t einfo[CB];     // EI_* fields of each kept hit
+    uint16_t rng_end[CB];
+    uint8_t relf[CB];
+    int16_t qnext[QCAP];    // next minimizer of the tile with the same hash, or -1
+    uint32_t seeds[NWAVES * SBUF * 6];
 };
+static_assert(sizeof(PostLds) <= TBYTES, "kept-hit arrays exceed the table area");
 
 struct TileLds {
-    uint32_t qpos[QCAP + 1];
-    uint32_t qhash[QCAP];
-    int16_t qprev[QCAP];
-    uint8_t qfl[QCAP];
-    uint8_t qmode[QCAP];  // QM_* while a partition covers a single window
-    uint32_t lst_lo[2 * QCAP];
-    uint32_t hoff[2 * QCAP + 4];
-    uint16_t win_T[CMAX];
-    uint16_t win_qend[CMAX];
-    uint16_t win_s[CMAX];
-    uint16_t qT[QCAP];       // smallest threshold among the windows holding q (0xFFFF: none)
-    uint32_t Tblk[CMAX / 32];     // smallest threshold per 32 window starts
-    uint32_t ndup;
-    RunState run[CMAX][2];
-    union {  // bin table in the gather passes; scratch and seed buffers after
+    union {
+        uint4 vec[TBYTES / 16];
         uint32_t table[TWORDS];
-        uint64_t scratch[TWORDS / 2];
-        uint32_t hot_area[(9 * CB) / 4 + 2];  // hot starts, flags, prefix sums
+        PostLds post;
     } u;
-    uint64_t coll[CB];
-    uint32_t eseq[CB];
-    uint16_t rng_end[CB];
-    uint32_t einfo[CB];  // EI_* fields of each kept hit
+    uint64_t coll[CB];      // kept hits; before the gather: minimizers whose hash repeats
+    // the partition's hits in the order of its non-empty lists (one per query
+    // minimizer: strand 0, then strand 1): list l holds the hits [h0, h1), at
+    // epos[base + e] for hit e (strand 1 at epos[base1 + e] when the strands'
+    // pieces are not adjacent)
+    uint2 rec[QCAP];        // base, meta: q (11 bits) | strand of q << 11 | first hit of strand 1 << 12
+    uint32_t rec1[QCAP];    // base1
+    uint64_t marks[NCHUNK]; // bit h0 - 1 of every list but the first
+    uint16_t pre[NCHUNK];   // list of the chunk's first hit
+    uint32_t qpos[QCAP + 1];
+    int16_t qprev[QCAP];    // previous minimizer of the tile with the same hash, or -1
+    uint16_t qT[QCAP];      // smallest threshold among the windows holding q (0xFFFF: none)
+    uint16_t win_qend[CMAX];
+    uint16_t win_s[CMAX];   // sketch size, 0 where no window starts
+    uint32_t run_prev[2 * CMAX], run_best[2 * CMAX];  // run state between partitions
+    uint16_t run_c[2 * CMAX];                         // 0: no run open
+    uint8_t qfl[QCAP];
+    uint16_t Tblk[CMAX / 32];     // smallest threshold per 32 window starts
     uint32_t stackA[STACK], stackB[STACK], stackW[STACK];  // W: first window | end << 16
     uint64_t wtmp[NWAVES + 1];
+    uint32_t wmin[NWAVES];
     uint64_t ph[PH_N];
-    // scalars
-    uint32_t tile, ntiles, c0, c1, Q, C, nwin, Tmin, ncoll, dup;
+    uint32_t tile, ntiles, c0, c1, C, nwin, ncoll, nraw, ndup, dup, csum, nself;
     uint32_t obeg[2], oend[2];
     uint32_t sp;
     uint32_t err;
     uint32_t skip;
-    uint64_t gb, ge;
-    uint32_t qid, qseq;
+    uint32_t qid, qtb;         // query, start of its sequence
+    uint32_t next_tile, next_c0, next_c1, next_qid, next_qtb;
+    uint64_t next_ge;
+    SpanDesc span;             // the span of the tile fetched last,
+    uint32_t span_end;         // the first tile past it
+    uint32_t span_tb;          // and the start of its sequence
     // work counters of this workgroup, added to the global ones once at exit
     // (global atomics on a handful of shared addresses from every CU serialise)
     unsigned long long cnt[CNT_N];
     uint32_t wseeds[NWAVES];   // seeds buffered per wave, then their offsets
     unsigned long long seed_base;
 };
+static_assert(sizeof(TileLds) <= (TB == 512 ? 81920 : 163840), "LDS of the workgroups of a CU");
 
 // ----------------------------------------------------------- block helpers --
 constexpr int DPP_ROW_SHR = 0x110;      // + n: lane reads lane - n of its row of 16
@@ -300,29 +329,31 @@ __device__ void block_sort_runs(uint64_t *keys, uint32_t n) {
     __syncthreads();
 }
 
-// Gap-free segment containing position x: index or -1.
-// Entry range of I_G^{-1} for (hash, strand).
-__device__ __forceinline__ void lookup(const IndexView &ix, uint32_t hash, uint32_t strand,
-                                       uint32_t &lo, uint32_t &hi) {
-    const uint64_t key = ((uint64_t)hash << 1) | strand;
+// Entries of I_G^{-1} for a hash: strand 0 at [lo, mid), strand 1 at [mid, hi).
+__device__ __forceinline__ void lookup(const IndexView &ix, uint32_t hash, uint32_t &lo,
+                                       uint32_t &mid, uint32_t &hi) {
+    const uint64_t key = (uint64_t)hash << 1;
     const uint64_t d = key >> ix.dir_shift;
     lo = ix.dir[d];
-    hi = ix.dir[d + 1];
-    if (ix.dir_shift) {
-        const uint32_t low = (uint32_t)(key & ((1ull << ix.dir_shift) - 1));
-        uint32_t a = lo, b = hi;
-        while (a < b) {
-            uint32_t m = (a + b) >> 1;
-            if (ix.ekeylo[m] < low) a = m + 1; else b = m;
-        }
-        uint32_t c = a, e = hi;
-        while (c < e) {
-            uint32_t m = (c + e) >> 1;
-            if (ix.ekeylo[m] <= low) c = m + 1; else e = m;
-        }
-        lo = a;
-        hi = c;
+    mid = ix.dir[d + 1];
+    if (ix.dir_shift == 0) {
+        hi = ix.dir[d + 2];
+        return;
     }
+    // both keys share the directory entry: their low bits within it
+    const uint32_t low = (uint32_t)(key & ((1ull << ix.dir_shift) - 1));
+    const uint32_t end = mid;
+    auto first = [&](uint32_t from, uint32_t bits) {  // first entry >= bits
+        uint32_t a = from, b = end;
+        while (a < b) {
+            const uint32_t m = (a + b) >> 1;
+            if (ix.ekeylo[m] < bits) a = m + 1; else b = m;
+        }
+        return a;
+    };
+    lo = first(lo, low);
+    mid = first(lo, low + 1);
+    hi = first(mid, low + 2);
 }
 
 // First entries of the ascending positions epos[lo, hi) that are >= x0 and
@@ -367,13 +398,6 @@ __device__ __forceinline__ void lower_pos2(const IndexView &ix, uint32_t lo, uin
     r1 = c1;
 }
 
-__device__ __forceinline__ uint32_t slot_of(uint32_t bin, uint32_t o) {
-    return (((bin << 1) | o) * 0x9E3779B1u) >> (32 - TSLOT_BITS);
-}
-__device__ __forceinline__ uint32_t slot_count(const uint32_t *table, uint32_t slot) {
-    return (table[slot >> 1] >> ((slot & 1) * 16)) & 0xFFFFu;
-}
-
 // Packed kept-hit key: o (1 bit) | p' (32 bits) | q (11 bits).
 __device__ __forceinline__ uint64_t ckey(uint32_t o, uint32_t p, uint32_t q) {
     return ((uint64_t)o << 43) | ((uint64_t)p << 11) | q;
@@ -383,69 +407,61 @@ __device__ __forceinline__ uint32_t ck_p(uint64_t k) { return (uint32_t)(k >> 11
 __device__ __forceinline__ uint32_t ck_q(uint64_t k) { return (uint32_t)(k & 2047); }
 __device__ __forceinline__ uint64_t ck_op(uint64_t k) { return k >> 11; }
 
-// Largest l in [lo, hi) with hoff[l] <= e (hoff[lo] <= e < hoff[hi]).
-__device__ __forceinline__ uint32_t list_of_from(const uint32_t *hoff, uint32_t lo, uint32_t hi,
-                                                 uint32_t e) {
-    while (hi - lo > 1) {
-        uint32_t m = (lo + hi) >> 1;
-        if (hoff[m] <= e) lo = m; else hi = m;
-    }
-    return lo;
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m, uint32_t add) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, add));
+}
+__device__ __forceinline__ uint32_t uni(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ __forceinline__ uint32_t lane_read(uint32_t x, uint32_t l) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)l);
 }
 
-// Largest l in [lo, hi) with hoff[l] <= e, for a hit index e that every lane of the wave holds alike
-// (hoff[lo] <= e < hoff[hi]): the 64 lanes probe 64 evenly spaced lists
-// per round and a ballot narrows the range 64-fold, so 2,560 lists take two
-// rounds of one LDS read each.
-__device__ __forceinline__ uint32_t wave_list_of(const uint32_t *hoff, uint32_t lo, uint32_t hi,
-                                                 uint32_t e) {
-    const uint32_t lane = (uint32_t)(threadIdx.x & 63);
-    while (hi - lo > 1) {
-        const uint32_t step = (hi - lo + 63) / 64;
-        const uint32_t p = lo + lane * step;
-        const bool le = p < hi && hoff[p] <= e;  // a prefix of the lanes (lane 0 always)
-        const uint32_t c = (uint32_t)__popcll(__ballot(le));
-        const uint32_t nhi = min(hi, lo + c * step);
-        lo = lo + (c - 1) * step;
-        hi = nhi;
-    }
-    return lo;
+// A value the compiler does not see through: addresses made from it are
+// computed where they are used, not hoisted out of the tile loop and spilled.
+__device__ __forceinline__ uint32_t opaque(uint32_t x) {
+    asm volatile("" : "+v"(x));
+    return x;
 }
 
-// Hits [cb, cb + 64 * HU) of the tile in lane-interleaved order: lv = list
-// (2q + strand) or NONE32 past the end, pv = target position.  The lists of
-// the block's first and last hit bound each lane's list search, and every
-// position load is issued before any is used.  HU is eight, six in the
-// 512-thread layout, whose 128 registers per lane spill more with eight.
-constexpr int HU = TB == 512 ? 6 : 8;
-// In the 512-thread layout the hits [0, STASH) of a partition that pass 1
-// gathers (position and list) are kept for pass 2 in the arrays that hold
-// kept-hit data only later, so pass 2 reads them from LDS instead of
-// searching the lists and loading positions again (most of its partitions
-// hold fewer).  The 1,024-thread layout gathers twice: there the kept copy
-// cost more in register spills than it saved.
-constexpr uint32_t STASH = TB == 512 ? 1536 : 0;
-static_assert(STASH % (64 * HU) == 0, "the stash holds whole wave rounds");
-__device__ __forceinline__ void gather_hits(const TileLds &L, const IndexView &ix, uint32_t nl,
-                                            uint32_t H, uint32_t cb, uint32_t lane,
-                                            uint32_t (&pv)[HU], uint32_t (&lv)[HU]) {
+// The kernel's arguments, read again from where this is called (scalar loads
+// that hit the constant cache): held in registers over the whole tile loop they
+// spill.  They are the kernel's first and only parameter.
+__device__ __forceinline__ const SearchArgs &kernel_args() {
+    auto p = (const __attribute__((address_space(4))) SearchArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const SearchArgs *)p;
+}
+
+// The list of hit e (marks and pre of its chunk): lists that start at or
+// before it, less one.
+__device__ __forceinline__ uint32_t list_of(const TileLds &L, uint32_t e) {
+    const uint64_t m = L.marks[e >> 6] & ((1ull << (e & 63)) - 1);
+    return L.pre[e >> 6] + (uint32_t)__popcll(m);
+}
+
+constexpr int HU = 8;  // chunks gathered per round: their loads are all in flight together
+constexpr int SG = 6;  // rounds whose hits stay in registers (48 per lane)
+
+// Hits of the chunks [c, c + HU): pv = target position, bit u of the result =
+// orientation.  Lists and chunks are exact, so every load is in range; lanes
+// past the last hit repeat it.
+__device__ __forceinline__ uint32_t gather_hits(const TileLds &L, const uint32_t *epos, uint32_t H,
+                                                uint32_t nch, bool pieces, uint32_t c,
+                                                uint32_t lane, uint32_t (&pv)[HU]) {
+    uint32_t ob = 0;
+    uint32_t at[HU];
 #pragma unroll
     for (int u = 0; u < HU; u++) {
-        pv[u] = 0;
-        lv[u] = NONE32;
+        const uint32_t cc = min(c + (uint32_t)u, nch - 1);
+        const uint32_t l = lanes_below(L.marks[cc], L.pre[cc]);
+        const uint32_t e = min(cc * 64 + lane, H - 1);
+        const uint2 r = L.rec[l];
+        const uint32_t b = e >= (r.y >> 12) ? 1u : 0u;
+        at[u] = (pieces && b ? L.rec1[l] : r.x) + e;
+        ob |= (b ^ ((r.y >> 11) & 1)) << u;
     }
-    if (cb >= H) return;
-    const uint32_t l0 = wave_list_of(L.hoff, 0, nl, cb);
-    const uint32_t l1 = wave_list_of(L.hoff, l0, nl, min(cb + 64 * HU - 1, H - 1));
 #pragma unroll
-    for (int u = 0; u < HU; u++) {
-        const uint32_t e = cb + (uint32_t)u * 64 + lane;
-        if (e < H) {
-            const uint32_t l = (l1 > l0) ? list_of_from(L.hoff, l0, l1 + 1, e) : l0;
-            lv[u] = l;
-            pv[u] = ix.epos[L.lst_lo[l] + (e - L.hoff[l])];
-        }
-    }
+    for (int u = 0; u < HU; u++) pv[u] = epos[at[u]];
+    return ob;
 }
 
 // A window the tile cannot hold goes to the list of dense windows (once)
@@ -472,9 +488,9 @@ __device__ __forceinline__ void split_partition(const SearchArgs &a, TileLds &L,
         const uint32_t mid = WA + (WB - WA) / 2;
         L.stackA[L.sp] = A; L.stackB[L.sp] = B; L.stackW[L.sp] = mid | (WB << 16); L.sp++;
         L.stackA[L.sp] = A; L.stackB[L.sp] = B; L.stackW[L.sp] = WA | (mid << 16); L.sp++;
-    } else if (L.win_T[WA]) {
+    } else if (L.win_s[WA]) {
         list_dense(a, L, L.c0 + WA);
-        L.win_T[WA] = 0;  // no candidates, no runs: its seeds come from the dense pass
+        L.win_s[WA] = 0;  // no candidates, no runs: its seeds come from the dense pass
     }
 }
 
@@ -507,23 +523,6 @@ __device__ __forceinline__ void seeds_flush(const SearchArgs &a, SeedBuf &sb, in
     }
     __builtin_amdgcn_wave_barrier();
     sb.n = 0;
-}
-
-__device__ __forceinline__ void seeds_push(const SearchArgs &a, SeedBuf &sb, int lane,
-                                           uint32_t qid, uint32_t i, uint32_t j, uint32_t o,
-                                           uint32_t c, uint32_t s) {
-    if (lane == 0) {
-        uint32_t *d = sb.buf + sb.n * 6;
-        d[0] = qid;
-        d[1] = i;
-        d[2] = j;
-        d[3] = o;
-        d[4] = c;
-        d[5] = s;
-    }
-    __builtin_amdgcn_wave_barrier();
-    sb.n++;
-    if (sb.n == SBUF) seeds_flush(a, sb, lane);
 }
 
 // Every lane with `mine` set pushes one seed; order within the buffer does
@@ -579,171 +578,650 @@ __device__ __forceinline__ void seeds_flush_block(const SearchArgs &a, TileLds &
     sb.n = 0;
 }
 
+// Hot flags of four adjacent table words at once: bit 0 of every counter field
+// says whether some pair of adjacent slots among (slot - 2, slot - 1),
+// (slot - 1, slot), (slot, slot + 1) sums to at least T.  pw and nw are the
+// words before and after w; `sum` gains the counters of w.
+__device__ __forceinline__ uint32_t hot_nibbles(uint32_t pw, uint32_t w, uint32_t nw, uint32_t T,
+                                                uint32_t &sum) {
+    const uint32_t K = 0x01010101u * (0x80u - T);
+    const uint32_t E = w & 0x0F0F0F0Fu, O = (w >> 4) & 0x0F0F0F0Fu;
+    const uint32_t Se = E + O;                                     // pairs starting at 0, 2, 4, 6
+    const uint32_t So = O + ((E >> 8) | ((nw & 15u) << 24));       // at 1, 3, 5, 7
+    sum = __builtin_amdgcn_sad_u8(Se, 0u, sum);
+    const uint32_t he = ((Se + K) & 0x80808080u) >> 7, ho = ((So + K) & 0x80808080u) >> 7;
+    const uint32_t pe = ((pw >> 28) + ((pw >> 24) & 15u)) >= T ? 1u : 0u;  // at -2
+    const uint32_t po = ((pw >> 28) + (w & 15u)) >= T ? 1u : 0u;           // at -1
+    const uint32_t bo = (ho << 8) | po;
+    return (((he << 8) | pe) | bo | he) | ((bo | he | ho) << 4);
+}
+__device__ __forceinline__ uint32_t hot_bytes(uint32_t pw, uint32_t w, uint32_t nw, uint32_t T,
+                                              uint32_t &sum) {
+    const uint32_t K = 0x00010001u * (0x8000u - T);
+    const uint32_t E = w & 0x00FF00FFu, O = (w >> 8) & 0x00FF00FFu;
+    const uint32_t Se = E + O, So = O + ((E >> 16) | ((nw & 255u) << 16));
+    sum = __builtin_amdgcn_sad_u8(w, 0u, sum);
+    const uint32_t he = ((Se + K) & 0x80008000u) >> 15, ho = ((So + K) & 0x80008000u) >> 15;
+    const uint32_t pe = ((pw >> 24) + ((pw >> 16) & 255u)) >= T ? 1u : 0u;
+    const uint32_t po = ((pw >> 24) + (w & 255u)) >= T ? 1u : 0u;
+    const uint32_t bo = (ho << 16) | po;
+    return (((he << 16) | pe) | bo | he) | ((bo | he | ho) << 8);
+}
+
+// Table slot of position p and orientation o: the bin modulo half the table,
+// so that adjacent bins are adjacent slots.  hl: log2 of the half's slots.
+__device__ __forceinline__ uint32_t slot_of(uint32_t p, uint32_t o, uint32_t SB, uint32_t hl) {
+    return ((p >> SB) & ((1u << hl) - 1u)) | (o << hl);
+}
+
+// Open run of a window and orientation.
+struct RunState {
+    uint32_t prev_j, best_j, best_c;  // best_c 0: none
+};
+// 64 window starts and an orientation, one window per lane: its minimizers are
+// [qc, qc + len), len 0 where no window starts; together they lie in [qlo, qhi).
+struct Block {
+    uint32_t qlo, qhi, o;
+    uint32_t qc, len, i, si, Ti;
+    uint32_t near;      // X - 1 of the excluded overlaps
+    bool runs_out;      // first and last candidate of each run instead of its seed
+};
+// A candidate: its position, the least previous candidate that a run links to
+// (its sequence's start and less than n back), and for the excluded overlaps
+// with the window itself |j - i| < X the range 2X - 1 (0: another sequence).
+struct Cand {
+    uint32_t j, lo, kx;
+};
+__device__ __forceinline__ Cand candidate(const SearchArgs &a, const TileLds &L, uint32_t e) {
+    Cand c;
+    c.j = ck_p(L.coll[e]);
+    const uint32_t tb = L.u.post.etb[e];
+    c.lo = max(tb, c.j >= a.n - 1 ? c.j - (a.n - 1) : 0u);
+    c.kx = tb == L.qtb ? 2 * (a.n - a.max_overlap) - 1 : 0u;
+    return c;
+}
+
+// Seeds of runs that ended, one per lane at most, until they are pushed
+// together (most windows have one run): lanes in m hold (j, v).
+struct EndedRuns {
+    uint64_t m;
+    uint32_t j, v;
+};
+__device__ __forceinline__ void push_ended(const SearchArgs &a, TileLds &L, SeedBuf &sbuf,
+                                           const Block &bk, EndedRuns &er, uint32_t lane) {
+    seeds_push_lanes(a, sbuf, (int)lane, (er.m >> lane) & 1, L.qid, bk.i, er.j, bk.o, er.v, bk.si);
+    er.m = 0;
+}
+
+// Run logic of one candidate: a passing candidate continues the open run when
+// it lies in its sequence less than n after the previous candidate; a run's
+// seed is its largest count, earliest j on ties.  With runs_out a run gives
+// its first and last candidate (the previous one) for the estimate.
+__device__ __forceinline__ void run_step(const SearchArgs &a, TileLds &L, SeedBuf &sbuf,
+                                         const Block &bk, RunState &rs, EndedRuns &er,
+                                         uint32_t lane, bool mine, uint32_t cnt, uint32_t j,
+                                         uint32_t lo, uint32_t kx) {
+    // (& and |, not && and ||: no branches)
+    const bool open = rs.best_c != 0;
+    const bool pass = mine & (cnt >= bk.Ti) & (j + bk.near - bk.i >= kx);
+    const bool link = pass & open & (rs.prev_j >= lo);
+    const bool ends = mine & open & !link;
+    const uint64_t em = __builtin_amdgcn_ballot_w64(ends);
+    if (em & er.m) push_ended(a, L, sbuf, bk, er, lane);
+    er.m |= em;
+    er.j = ends ? rs.best_j : er.j;
+    er.v = ends ? (bk.runs_out ? rs.prev_j : rs.best_c) : er.v;
+    const bool upd = pass & (!link | (!bk.runs_out & (cnt > rs.best_c)));
+    rs.best_c = upd ? cnt : (mine & !pass) ? 0u : rs.best_c;
+    rs.best_j = upd ? j : rs.best_j;
+    rs.prev_j = mine ? j : rs.prev_j;
+}
+
+// Candidates among the kept hits [ob, oe) against the windows of a block whose
+// minimizers fit R per lane.  Lane l holds for each of its minimizers
+// qlo + 64 r + l the last of its hits that has entered (every hit up to
+// j + n - k has entered before candidate j): one at or past the candidate means
+// that the minimizer has a hit in [j, j + n - k], so a ballot per r is the
+// candidate's bitmask over the block's minimizers, and a window's count the
+// popcount of it over the window's own.
+template <int R>
+__device__ __forceinline__ void eval_masks(const SearchArgs &a, TileLds &L, SeedBuf &sbuf,
+                                           const Block &bk, RunState &rs, EndedRuns &er,
+                                           uint32_t ob, uint32_t oe,
+                                           uint32_t lane, bool dup, uint32_t &n_evals,
+                                           uint32_t &n_scan) {
+    const PostLds &F = L.u.post;
+    const uint32_t qlo = bk.qlo, nq = bk.qhi - bk.qlo;
+    uint64_t wm[R];  // the window's minimizers
+    uint32_t last[R] = {};  // hit + 1
+    uint64_t again[R] = {};  // (with repeats) minimizers with an earlier one of their hash in the block
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int from = (int)lane - 64 * r, to = (int)(lane + bk.len) - 64 * r;
+        uint64_t m = from <= 0 ? ~0ull : from < 64 ? ~0ull << from : 0ull;
+        if (to < 64) m = to <= 0 ? 0ull : m & ((1ull << to) - 1);
+        wm[r] = m;
+        const uint32_t q = lane + 64 * r;
+        if (dup) again[r] = __builtin_amdgcn_ballot_w64(q < nq && L.qprev[min(qlo + q, (uint32_t)QCAP - 1)] >= (int)qlo);
+    }
+    // the next hit to enter, its chunk, the chunk's minimizers and the hits of it
+    // still to enter
+    uint32_t next = NONE32, fc = ob & ~63u, frl = 0;
+    uint64_t frel = 0;
+    auto chunk_of_next = [&]() {
+        for (;; fc += 64) {
+            if (fc >= oe) {
+                next = NONE32;
+                return;
+            }
+            const uint32_t fx = fc + lane;
+            frl = fx >= ob && fx < oe ? (F.einfo[fx] & EI_Q) - qlo : NONE32;
+            frel = __builtin_amdgcn_ballot_w64(frl < nq);
+            if (frel) break;
+        }
+        next = fc + (uint32_t)__builtin_ctzll(frel);
+    };
+    chunk_of_next();
+    uint32_t carry_q = EI_Q;  // minimizer of the hit before the chunk
+    for (uint32_t e0 = ob & ~63u; e0 < oe; e0 += 64) {
+        n_scan++;
+        const uint32_t ex = e0 + lane;
+        const bool valid = ex >= ob && ex < oe;
+        const uint32_t info = valid ? F.einfo[ex] : 0u;
+        const uint32_t qx = info & EI_Q;
+        const bool cand = valid && (info & EI_CAND) && qx - qlo < nq;
+        uint64_t mm = __ballot(cand);
+        const uint32_t pq = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_q, (int)qx, DPP_WAVE_SHR1,
+                                                                  0xf, 0xf, false);
+        carry_q = lane_read(qx, 63);
+        if (!mm) continue;
+        // the window's first hit at this position: the one before lies outside it
+        const uint32_t pq1 = (info & EI_SAMEP) ? pq + 1 : 0u;
+        Cand c{0, 0, 0};
+        uint32_t pend = 0;
+        if (cand) {
+            c = candidate(a, L, ex);
+            pend = F.rng_end[ex];
+        }
+        while (mm) {
+            const uint32_t bb = (uint32_t)__ffsll((long long)mm) - 1;
+            mm &= mm - 1;
+            const uint32_t e = e0 + bb;
+            const uint32_t q = lane_read(qx, bb);
+            const bool mine = (q - bk.qc < bk.len) & (bk.qc >= lane_read(pq1, bb));
+            const uint64_t mb = __builtin_amdgcn_ballot_w64(mine);
+            if (!mb) continue;
+            n_evals += (uint32_t)__popcll(mb);
+            const uint32_t re = lane_read(pend, bb);
+            while (next < re) {
+                const uint32_t rel = lane_read(frl, next & 63);
+#pragma unroll
+                for (int r = 0; r < R; r++) last[r] = lane + 64 * r == rel ? next + 1 : last[r];
+                frel &= frel - 1;
+                if (frel) {
+                    next = fc + (uint32_t)__builtin_ctzll(frel);
+                } else {
+                    fc += 64;
+                    chunk_of_next();
+                }
+            }
+            uint64_t M[R];
+            uint32_t cnt = 0;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                M[r] = __builtin_amdgcn_ballot_w64(last[r] > e);
+                cnt += (uint32_t)__popc((uint32_t)M[r] & (uint32_t)wm[r]);
+                cnt += (uint32_t)__popc((uint32_t)(M[r] >> 32) & (uint32_t)(wm[r] >> 32));
+            }
+            uint64_t rep = 0;  // (again[] is empty without repeats)
+#pragma unroll
+            for (int r = 0; r < R; r++) rep |= M[r] & again[r];
+            if (rep) {
+                // a marked minimizer that repeats the hash of an earlier marked one
+                // does not count in the windows that hold the nearest such one too
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    uint64_t dm = M[r] & again[r];
+                    while (dm) {
+                        const uint32_t dq = qlo + 64 * r + (uint32_t)__ffsll((long long)dm) - 1;
+                        dm &= dm - 1;
+                        int x = (int)uni((uint32_t)(int)L.qprev[dq]);
+                        for (; x >= (int)qlo; x = (int)uni((uint32_t)(int)L.qprev[x])) {
+                            const uint32_t rx = (uint32_t)x - qlo;
+                            uint64_t m = 0;
+#pragma unroll
+                            for (int v = 0; v < R; v++) m = (rx >> 6) == (uint32_t)v ? M[v] : m;
+                            if ((m >> (rx & 63)) & 1) break;
+                        }
+                        if (x >= (int)qlo && dq < bk.qc + bk.len && (uint32_t)x >= bk.qc) cnt--;
+                    }
+                }
+            }
+            run_step(a, L, sbuf, bk, rs, er, lane, mine, cnt, lane_read(c.j, bb), lane_read(c.lo, bb),
+                     lane_read(c.kx, bb));
+        }
+    }
+}
+
+// A window's shared count changes when a minimizer of it gets its first kept
+// hit in the target window or loses its last one.  With repeated hashes a
+// window holding another marked minimizer of the same hash does not change:
+// nearest marked ones before (a) and after (b).
+struct Marks {
+    uint32_t live, multi;  // lane l, bit r: minimizer qlo + 64 r + l has one kept hit, or several
+};
+static_assert(QCAP <= 64 * 32, "mark bits of a lane");
+__device__ __forceinline__ bool mark_counts(const TileLds &L, const Marks &m, const Block &bk,
+                                            uint32_t q, bool dup) {
+    bool in = q - bk.qc < bk.len;
+    if (dup) {
+        const int qlo = (int)bk.qlo, qhi = (int)bk.qhi;
+        auto live = [&](int r) {
+            return (lane_read(m.live, (uint32_t)(r - qlo) & 63u) >> ((uint32_t)(r - qlo) >> 6)) & 1u;
+        };
+        int a = (int)uni((uint32_t)(int)L.qprev[q]);
+        while (a >= qlo && !live(a)) a = (int)uni((uint32_t)(int)L.qprev[a]);
+        int b = (int)uni((uint32_t)(int)L.u.post.qnext[q]);
+        while (b >= 0 && b < qhi && !live(b)) b = (int)uni((uint32_t)(int)L.u.post.qnext[b]);
+        if (a >= qlo) in = in && (uint32_t)a < bk.qc;
+        if (b >= 0 && b < qhi) in = in && (uint32_t)b >= bk.qc + bk.len;
+    }
+    return in;
+}
+
+// The same as eval_masks for any number of minimizers.
+__device__ __forceinline__ void eval_events(const SearchArgs &a, TileLds &L, SeedBuf &sbuf,
+                                            const Block &bk, RunState &rs, EndedRuns &er,
+                                           uint32_t ob, uint32_t oe,
+                                            uint32_t lane, bool dup, uint32_t &n_evals,
+                                            uint32_t &n_scan) {
+    const PostLds &F = L.u.post;
+    const uint32_t qlo = bk.qlo, nq = bk.qhi - bk.qlo;
+    Marks mk{0, 0};
+    uint32_t cnt = 0;
+    uint32_t f = ob, fc = NONE32, fq = 0;  // next hit to enter; its chunk
+    uint64_t frel = 0;
+    uint32_t carry_q = EI_Q;  // minimizer of the hit before the chunk
+    for (uint32_t e0 = ob & ~63u; e0 < oe; e0 += 64) {
+        n_scan++;
+        const uint32_t ex = e0 + lane;
+        const bool valid = ex >= ob && ex < oe;
+        const uint32_t info = valid ? F.einfo[ex] : 0u;
+        const uint32_t qx = info & EI_Q;
+        // hits whose minimizer lies in one of the block's windows
+        const bool rel = valid && qx - qlo < nq;
+        uint64_t mm = __ballot(rel);
+        uint32_t pq = (uint32_t)__builtin_amdgcn_update_dpp((int)carry_q, (int)qx, DPP_WAVE_SHR1, 0xf,
+                                                            0xf, false);
+        carry_q = lane_read(qx, 63);
+        if (!mm) continue;
+        const uint32_t pq1 = (info & EI_SAMEP) ? pq + 1 : 0u;
+        Cand c{0, 0, 0};
+        uint32_t pend = 0;
+        if (rel && (info & EI_CAND)) {
+            c = candidate(a, L, ex);
+            pend = F.rng_end[ex];
+        }
+        while (mm) {
+            const uint32_t bb = (uint32_t)__ffsll((long long)mm) - 1;
+            mm &= mm - 1;
+            const uint32_t e = e0 + bb;
+            const uint32_t ie = lane_read(info, bb);
+            const uint32_t q = ie & EI_Q;
+            const bool mine = (ie & EI_CAND) && q - bk.qc < bk.len && bk.qc >= lane_read(pq1, bb);
+            const uint64_t mb = __ballot(mine);
+            if (mb) {
+                n_evals += (uint32_t)__popcll(mb);
+                const uint32_t re = lane_read(pend, bb);
+                if (f < e) f = e;  // hits passed before they entered
+                while (f < re) {
+                    if ((f & ~63u) != fc) {
+                        fc = f & ~63u;
+                        const uint32_t fx = fc + lane;
+                        fq = fx < oe ? (F.einfo[fx] & EI_Q) : 0u;
+                        frel = __ballot(fx < oe && fq - qlo < nq);
+                    }
+                    const uint32_t end = min(re, fc + 64);
+                    uint64_t m2 = frel & (~0ull << (f & 63));
+                    if (end < fc + 64) m2 &= (1ull << (end & 63)) - 1;
+                    while (m2) {
+                        const uint32_t b2 = (uint32_t)__ffsll((long long)m2) - 1;
+                        m2 &= m2 - 1;
+                        const uint32_t eq = lane_read(fq, b2);
+                        const uint32_t ln = (eq - qlo) & 63u, bit = 1u << ((eq - qlo) >> 6);
+                        const uint32_t cur = lane_read(mk.live, ln), mul = lane_read(mk.multi, ln);
+                        if (cur & bit) {
+                            mk.multi = lane == ln ? mul | bit : mk.multi;
+                        } else {
+                            cnt += mark_counts(L, mk, bk, eq, dup) ? 1u : 0u;
+                            mk.live = lane == ln ? cur | bit : mk.live;
+                        }
+                    }
+                    f = end;
+                }
+                run_step(a, L, sbuf, bk, rs, er, lane, mine, cnt, lane_read(c.j, bb), lane_read(c.lo, bb),
+                         lane_read(c.kx, bb));
+            }
+            if (e < f) {  // hit e leaves
+                const uint32_t ln = (q - qlo) & 63u, bit = 1u << ((q - qlo) >> 6);
+                const uint32_t cur = lane_read(mk.live, ln), mul = lane_read(mk.multi, ln);
+                uint32_t others = 0;
+                if (mul & bit) {  // others of its minimizer among the entered
+                    for (uint32_t g = e + 1; g < f; g += 64) {
+                        const uint32_t gx = g + lane;
+                        others += (uint32_t)__popcll(__ballot(gx < f && (F.einfo[gx] & EI_Q) == q));
+                    }
+                    if (others < 2) mk.multi = lane == ln ? mul & ~bit : mk.multi;
+                }
+                if (!others) {
+                    mk.live = lane == ln ? cur & ~bit : mk.live;
+                    cnt -= mark_counts(L, mk, bk, q, dup) ? 1u : 0u;
+                }
+            }
+        }
+    }
+}
+
+// Tile t of the queue and its span, into the next_* fields (by one wave, t the
+// same in all lanes).  Consecutive tiles mostly stay in the span kept in LDS;
+// otherwise the lanes probe 64 spans per round for the last one that starts
+// at or before t.
+__device__ __forceinline__ void next_tile(const SearchArgs &a, TileLds &L, uint32_t t, uint32_t lane) {
+    if (t < L.ntiles && (t < L.span.tile0 || t >= L.span_end)) {
+        uint32_t lo = 0, hi = a.nspans;
+        while (hi - lo > 1) {
+            const uint32_t step = (hi - lo + 63) / 64, p = lo + lane * step;
+            const bool le = p < hi && a.spans[p].tile0 <= t;  // a prefix of the lanes
+            const uint32_t c = max((uint32_t)__popcll(__ballot(le)), 1u);
+            const uint32_t nhi = min(hi, lo + c * step);
+            lo += (c - 1) * step;
+            hi = nhi;
+        }
+        const uint32_t end = lo + 1 < a.nspans ? a.spans[lo + 1].tile0 : L.ntiles;
+        const SpanDesc sd = a.spans[lo];
+        if (lane == 0) {
+            L.span = sd;
+            L.span_end = end;
+            L.span_tb = (uint32_t)a.ix.off[sd.qseq];
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (lane == 0) {
+        L.next_tile = t;
+        if (t < L.ntiles) {
+            L.next_c0 = L.span.m_lo + (t - L.span.tile0) * a.core;
+            L.next_c1 = min(L.next_c0 + a.core, L.span.m_hi);
+            L.next_ge = L.span.ge;
+            L.next_qid = L.span.qid;
+            L.next_qtb = L.span_tb;
+        }
+    }
+}
+
 __global__ void __launch_bounds__(TB) __attribute__((amdgpu_waves_per_eu(SDF_TILE_WAVES_PER_EU)))
-k_tile_search(SearchArgs a) {
+k_tile_search(SearchArgs) {
     __shared__ TileLds L;
-    const IndexView &ix = a.ix;
-    const uint32_t n = a.n, k = ix.k;
-    const int lane = lane_id(), wave = wave_id();
-    const bool prof = a.phase != nullptr && threadIdx.x == 0;
+    const uint32_t n = kernel_args().n, k = kernel_args().ix.k;
+    const uint32_t wave = uni(wave_id());
+    const bool prof = kernel_args().phase != nullptr && threadIdx.x == 0;
     if (threadIdx.x < PH_N) L.ph[threadIdx.x] = 0;
     if (threadIdx.x < CNT_N) L.cnt[threadIdx.x] = 0;
     uint64_t ph_t = prof ? wall_clock64() : 0;
-    // per-wave bitmasks start empty; each use clears the words it counted
-    uint32_t span_cache = 0;  // thread 0: span of the previous tile
-    if (threadIdx.x == 0) L.ntiles = *a.total_tiles;
-    __syncthreads();
+    if (wave == NWAVES - 1) {
+        const uint32_t lane = threadIdx.x & 63;
+        if (lane == 0) {
+            L.ntiles = *kernel_args().total_tiles;
+            L.span.tile0 = 0;
+            L.span_end = 0;  // no span kept yet
+        }
+        __builtin_amdgcn_wave_barrier();
+        uint32_t t = 0;
+        if (lane == 0) t = atomicAdd(kernel_args().work, 1u);
+        next_tile(kernel_args(), L, uni(t), lane);
+    }
+    constexpr int QR = (QCAP + TB) / TB;  // minimizers per thread, the sentinel included
 
     for (;;) {
-        if (threadIdx.x == 0) {
-            const uint32_t t = atomicAdd(a.work, 1u);
-            L.tile = t;
-            if (t < L.ntiles) {
-                // span of this tile: largest s with tile0[s] <= t (consecutive
-                // tiles mostly stay in one span)
-                uint32_t s = span_cache;
-                const bool hit = a.spans[s].tile0 <= t &&
-                                 (s + 1 == a.nspans || a.spans[s + 1].tile0 > t);
-                if (!hit) {
-                    uint32_t lo = 0, hi = a.nspans;
-                    while (hi - lo > 1) {
-                        uint32_t m = (lo + hi) >> 1;
-                        if (a.spans[m].tile0 <= t) lo = m; else hi = m;
-                    }
-                    s = lo;
-                }
-                span_cache = s;
-                const SpanDesc sd = a.spans[s];
-                L.c0 = sd.m_lo + (t - sd.tile0) * a.core;
-                L.c1 = min(L.c0 + a.core, sd.m_hi);
-                L.gb = sd.gb;
-                L.ge = sd.ge;
-                L.qid = sd.qid;
-                L.qseq = sd.qseq;
-            }
-        }
-        __syncthreads();
-        if (L.tile >= L.ntiles) break;
-
+        __syncthreads();  // next_* written, everything of the previous tile read
+        if (L.next_tile >= L.ntiles) break;
         // A tile core may be processed in several pieces when its windows
         // reach more minimizers than fit on chip.
-        const uint32_t piece_end = L.c1;
-        uint32_t c_begin = L.c0;
-        __syncthreads();  // everyone has read the core bounds before they change
+        uint32_t c_begin = L.next_c0;
+        const uint32_t piece_end = L.next_c1;
+        const uint64_t ge = L.next_ge;
+        const uint32_t qid = L.next_qid, qtb = L.next_qtb;
+        // the next tile's number, asked for here and used by the last wave in the
+        // window phase, where it has the least to do
+        uint32_t ticket = NONE32;
+        if (threadIdx.x == TB - 64) ticket = atomicAdd(kernel_args().work, 1u);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            L.qid = qid;
+            L.qtb = qtb;
+        }
+        bool first_piece = true;
         while (c_begin < piece_end) {
-            // positions of the next QCAP + 1 minimizers (coalesced)
-            for (uint32_t q = threadIdx.x; q <= QCAP; q += TB) {
-                const uint64_t m = (uint64_t)c_begin + q;
-                L.qpos[q] = m < ix.nm ? ix.mpos[m] : 0xFFFFFFFFu;
+            const uint32_t tid = opaque(threadIdx.x), lane = tid & 63;
+            const SearchArgs &a = kernel_args();
+            const IndexView &ix = a.ix;
+            // ---- query minimizers of the tile: all loads at once, the
+            // directory entries of the eligible ones behind their hashes ----
+            uint32_t C = piece_end - c_begin;
+            uint32_t qn = min(C + a.halo, (uint32_t)QCAP + 1);  // loaded, at least core + 1
+            uint32_t hash[QR];
+            uint32_t mext = 0;
+            if (tid == 0) {
+                L.ndup = 0;
+                L.dup = 0;
+                L.nwin = 0;
+                L.err = 0;
+                L.skip = 0;
+                L.c0 = c_begin;
             }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                uint32_t c1 = piece_end;
-                uint32_t qe = 0;
-                for (;;) {
-                    // query range: up to the last minimizer inside the last window
-                    const uint64_t lim = (uint64_t)L.qpos[c1 - 1 - c_begin] + n - k;
-                    uint32_t lo = c1 - c_begin, hi = QCAP + 1;
+            if (tid < C) mext = ix.mext[c_begin + tid];
+            uint16_t *dups = reinterpret_cast<uint16_t *>(L.coll);
+            static_assert(sizeof(uint16_t) * QCAP <= sizeof(uint64_t) * CB, "dups in coll");
+            for (;;) {
+                __syncthreads();  // ndup and dup cleared
+#pragma unroll
+                for (int r = 0; r < QR; r++) {
+                    const uint32_t q = tid + (uint32_t)r * TB;
+                    const uint64_t m = (uint64_t)c_begin + q;
+                    hash[r] = 0;
+                    if (q >= qn) continue;
+                    if (m >= ix.nm) {
+                        L.qpos[q] = 0xFFFFFFFFu;
+                        if (q < QCAP) {
+                            L.qfl[q] = 0;
+                            L.qprev[q] = -1;
+                        }
+                        continue;
+                    }
+                    L.qpos[q] = ix.mpos[m];
+                    if (q == QCAP) continue;
+                    hash[r] = ix.mhash[m];
+                    const uint32_t fl = ix.mflags[m] & 3u, pg = ix.mprev[m];
+                    L.qfl[q] = (uint8_t)fl;
+                    const bool rep = pg != NONE32 && pg >= c_begin;
+                    L.qprev[q] = rep ? (int16_t)(pg - c_begin) : (int16_t)-1;
+                    if (rep) {  // the hash repeats inside the tile (usually few)
+                        if (fl & QF_ELIG) L.dup = 1;
+                        dups[atomicAdd(&L.ndup, 1u)] = (uint16_t)q;
+                    }
+                }
+                __syncthreads();
+                const uint64_t lim = (uint64_t)L.qpos[C - 1] + n - k;
+                if (qn > QCAP || (uint64_t)L.qpos[qn - 1] > lim) break;
+                // the windows reach past what was loaded: all that the tile holds
+                __syncthreads();
+                qn = QCAP + 1;
+                if (tid == 0) {
+                    L.ndup = 0;
+                    L.dup = 0;
+                }
+            }
+            // directory entries behind the hashes (in flight until the lists are made)
+            uint32_t d0[QR], d1[QR], d2[QR];
+#pragma unroll
+            for (int r = 0; r < QR; r++) {
+                const uint32_t q = tid + (uint32_t)r * TB;
+                d0[r] = d1[r] = d2[r] = 0;
+                if (ix.dir_shift == 0 && q < min(qn, (uint32_t)QCAP) && (L.qfl[q] & QF_ELIG)) {
+                    const uint64_t h = (uint64_t)hash[r] * 2;
+                    d0[r] = ix.dir[h];
+                    d1[r] = ix.dir[h + 1];
+                    d2[r] = ix.dir[h + 2];
+                }
+            }
+            if ((uint64_t)L.qpos[min(qn, (uint32_t)QCAP + 1) - 1] <= (uint64_t)L.qpos[C - 1] + n - k) {
+                // more minimizers than a tile holds: fewer window starts
+                if (tid == 0) {
+                    uint32_t c = C;
+                    while (c > 1 && (uint64_t)L.qpos[QCAP] <= (uint64_t)L.qpos[c - 1] + n - k) c /= 2;
+                    if ((uint64_t)L.qpos[QCAP] <= (uint64_t)L.qpos[c - 1] + n - k) {
+                        L.skip = 1;  // one window alone reaches too many
+                        list_dense(a, L, c_begin);
+                        if (L.err) atomicOr(a.err, L.err);
+                    }
+                    L.C = c;
+                }
+                __syncthreads();
+                C = L.C;
+                if (L.skip) {
+                    c_begin += C;
+                    __syncthreads();
+                    continue;
+                }
+            }
+            const uint32_t c0 = c_begin;
+            PHASE(PH_SETUP);
+
+            // ---- windows of the core: eligible, inside the span, gap-free;
+            // their minimizers, sketch sizes and thresholds ----
+            {
+                const uint32_t ndup = L.ndup;
+                const uint32_t qc = tid;
+                uint32_t T = 0xFFFFu;
+                bool win = false;
+                if (qc < C) {
+                    const uint32_t i = L.qpos[qc];
+                    const uint64_t wl = (uint64_t)i + n - k;  // last minimizer inside [i, i + n)
+                    uint32_t lo = qc, hi = min(qn, (uint32_t)QCAP);
                     while (lo < hi) {
                         uint32_t m = (lo + hi) >> 1;
-                        if ((uint64_t)L.qpos[m] <= lim) lo = m + 1; else hi = m;
+                        if ((uint64_t)L.qpos[m] <= wl) lo = m + 1; else hi = m;
                     }
-                    qe = lo;
-                    if (qe <= QCAP || c1 - c_begin == 1) break;
-                    c1 = c_begin + (c1 - c_begin) / 2;
+                    win = (L.qfl[qc] & QF_ELIG) && (uint64_t)i + n <= ge && mext >= n;
+                    uint32_t s = 0;
+                    if (win) {
+                        // s_i: distinct hashes among all minimizers of the window =
+                        // all of them minus those repeating a hash already inside
+                        s = lo - qc;
+                        if (ndup <= 256) {
+                            for (uint32_t d = 0; d < ndup; d++) {
+                                const uint32_t q = dups[d];
+                                if (q >= qc && q < lo && L.qprev[q] >= (int)qc) s--;
+                            }
+                        } else {
+                            s = 0;
+                            for (uint32_t q = qc; q < lo; q++) s += (L.qprev[q] < (int)qc) ? 1u : 0u;
+                        }
+                        T = a.T[s];
+                    }
+                    L.win_qend[qc] = (uint16_t)lo;
+                    L.win_s[qc] = (uint16_t)s;
                 }
-                L.c0 = c_begin;
-                L.c1 = c1;
-                L.err = 0;
-                L.skip = qe > QCAP;  // one window alone reaches more minimizers than a tile holds
-                if (L.skip) {
-                    list_dense(a, L, c_begin);
-                    if (L.err) atomicOr(a.err, L.err);
+                // minima over 32 window starts and over the wave
+                uint32_t t = T;
+#pragma unroll
+                for (int d = 1; d < 32; d <<= 1) t = min(t, (uint32_t)__shfl_xor((int)t, d, 64));
+                if (qc < CMAX && (lane & 31) == 0) L.Tblk[qc >> 5] = (uint16_t)t;
+                t = min(t, (uint32_t)__shfl_xor((int)t, 32, 64));
+                const uint32_t nw = (uint32_t)__popcll(__ballot(win));
+                if (lane == 0) {
+                    L.wmin[wave] = t;
+                    if (nw) atomicAdd(&L.nwin, nw);
                 }
-                L.Q = min<uint32_t>(qe, QCAP);
-                L.C = c1 - c_begin;
-                L.nwin = 0;
-                L.Tmin = 0xFFFFu;
-                L.dup = 0;
+                if (wave == NWAVES - 1 && first_piece) next_tile(a, L, uni(ticket), lane);
+                first_piece = false;
+                for (uint32_t t2 = tid; t2 < NCHUNK; t2 += TB) L.marks[t2] = 0;
+                for (uint32_t t2 = tid; t2 < TBYTES / 16; t2 += TB)
+                    L.u.vec[t2] = uint4{0, 0, 0, 0};
             }
             __syncthreads();
-            PHASE(PH_SETUP);
-            const uint32_t c0 = L.c0, Q = L.Q, C = L.C;
-            if (L.skip) {
-                c_begin = L.c1;
+            PHASE(PH_QUERY);
+            const uint32_t Q = L.win_qend[C - 1];
+            if (L.nwin == 0) {
+                c_begin += C;
                 __syncthreads();
                 continue;
             }
+            if (tid == 0) {
+                L.cnt[CNT_WINDOWS] += L.nwin;
+                if (L.dup) L.cnt[CNT_DUP_TILES] += 1;
+            }
+            uint32_t Tmin = 0xFFFFu;
+#pragma unroll
+            for (int w = 0; w < NWAVES; w++) Tmin = min(Tmin, L.wmin[w]);
+            Tmin = uni(Tmin);
+            const bool dup = uni(L.dup) != 0;
 
-            // ---- query minimizers of the tile ----
-            for (uint32_t q = threadIdx.x; q < Q; q += TB) {
-                const uint32_t m = c0 + q;
-                L.qhash[q] = ix.mhash[m];
-                L.qfl[q] = ix.mflags[m];
-                L.qmode[q] = QM_NORMAL;
-                const uint32_t pg = ix.mprev[m];
-                L.qprev[q] = (pg != NONE32 && pg >= c0) ? (int16_t)(pg - c0) : (int16_t)-1;
-            }
-            // ---- windows of the core: eligible, inside the span, gap-free ----
-            for (uint32_t qc = threadIdx.x; qc < C; qc += TB) {
-                const uint32_t i = L.qpos[qc];
-                const bool w = (ix.mflags[c0 + qc] & 2) && (uint64_t)i + n <= L.ge &&
-                               ix.mext[c0 + qc] >= n;
-                L.win_T[qc] = w ? 1 : 0;  // finished below
-            }
-            __syncthreads();
-            // minimizers whose hash repeats earlier in the tile (usually few)
-            uint16_t *dups = reinterpret_cast<uint16_t *>(L.u.table);
-            if (threadIdx.x == 0) L.ndup = 0;
-            if (threadIdx.x < CMAX / 32) L.Tblk[threadIdx.x] = 0xFFFFu;
-            __syncthreads();
-            for (uint32_t q = threadIdx.x; q < Q; q += TB) {
-                if (L.qprev[q] >= 0) {
-                    if (L.qfl[q] & 2) L.dup = 1;
-                    dups[atomicAdd(&L.ndup, 1u)] = (uint16_t)q;
+            // Lists of the partition, in the order of their minimizers' threads:
+            // records, the marks that let a hit find its list, and the counters
+            // of the minimizers' own positions taken out (an occurrence is
+            // never paired with itself).  Returns the hits; more than HCAP:
+            // only their number (saturated) is right.
+            auto make_lists = [&](const uint32_t (&lo0)[QR], const uint32_t (&n0)[QR],
+                                  const uint32_t (&lo1)[QR], const uint32_t (&n1)[QR]) -> uint32_t {
+                uint32_t hits = 0, cnt = 0;
+#pragma unroll
+                for (int r = 0; r < QR; r++) {
+                    const uint32_t len = min(n0[r], 1u << 19) + min(n1[r], 1u << 19);
+                    hits += len;  // at most 2^20 each: no overflow over QCAP lists
+                    cnt += len ? 1u : 0u;
                 }
-            }
-            __syncthreads();
-            const uint32_t ndup = L.ndup;
-            for (uint32_t qc = threadIdx.x; qc < C; qc += TB) {
-                uint16_t T = 0, s = 0;
-                // last minimizer inside [pos, pos + n): for every core entry
-                const uint64_t lim = (uint64_t)L.qpos[qc] + n - k;
-                uint32_t lo = qc, hi = Q;
-                while (lo < hi) {
-                    uint32_t m = (lo + hi) >> 1;
-                    if ((uint64_t)L.qpos[m] <= lim) lo = m + 1; else hi = m;
-                }
-                if (L.win_T[qc]) {
-                    // s_i: distinct hashes among all minimizers of the window =
-                    // all of them minus those repeating a hash already inside
-                    uint32_t cnt = lo - qc;
-                    if (ndup <= 256) {
-                        for (uint32_t d = 0; d < ndup; d++) {
-                            const uint32_t q = dups[d];
-                            if (q >= qc && q < lo && L.qprev[q] >= (int)qc) cnt--;
-                        }
-                    } else {
-                        cnt = 0;
-                        for (uint32_t q = qc; q < lo; q++) cnt += (L.qprev[q] < (int)qc) ? 1u : 0u;
+                const uint32_t hx = wave_sum_scan(hits), cx = wave_sum_scan(cnt);
+                if (lane == 63) L.wtmp[wave] = ((uint64_t)cx << 32) | hx;
+                __syncthreads();
+                uint32_t hb = hx - hits, cb = cx - cnt, H = 0;
+#pragma unroll
+                for (int w = 0; w < NWAVES; w++) {
+                    const uint64_t t = L.wtmp[w];
+                    if (w < wave) {
+                        hb += (uint32_t)t;
+                        cb += (uint32_t)(t >> 32);
                     }
-                    s = (uint16_t)cnt;
-                    T = a.T[cnt];
-                    atomicMin(&L.Tmin, (uint32_t)T);
-                    atomicAdd(&L.nwin, 1u);
-                    atomicMin(&L.Tblk[qc >> 5], (uint32_t)T);
+                    H += (uint32_t)t;
                 }
-                L.win_T[qc] = T;
-                L.win_qend[qc] = (uint16_t)lo;
-                L.win_s[qc] = s;
-                L.run[qc][0] = RunState{NONE32, 0, 0, 0, 0};
-                L.run[qc][1] = RunState{NONE32, 0, 0, 0, 0};
-            }
-            __syncthreads();
-            // per query minimizer: the smallest threshold of the windows that
-            // hold it, bounded by the minima of the 32-entry blocks covering
-            // those windows (lossless: never above the true minimum)
-            for (uint32_t q = threadIdx.x; q < Q; q += TB) {
+                H = uni(H);
+                if (H > HCAP) return H;
+#pragma unroll
+                for (int r = 0; r < QR; r++) {
+                    const uint32_t len = n0[r] + n1[r];
+                    if (!len) continue;
+                    const uint32_t q = tid + (uint32_t)r * TB;
+                    L.rec[cb] = uint2{lo0[r] - hb, q | ((L.qfl[q] & QF_STRAND) << 11) |
+                                                       ((hb + n0[r]) << 12)};
+                    L.rec1[cb] = lo1[r] - (hb + n0[r]);
+                    if (hb) atomicOr(&L.marks[(hb - 1) >> 6], 1ull << ((hb - 1) & 63));
+                    for (uint32_t c = (hb + 63) >> 6; c * 64 < hb + len; c++) L.pre[c] = (uint16_t)cb;
+                    hb += len;
+                    cb++;
+                }
+                return H;
+            };
+            static_assert((uint64_t)QCAP << 20 <= 1ull << 31, "sums of clamped list lengths");
+
+            // ---- full-range lists and partition count ----
+            uint32_t lo0[QR], n0[QR], lo1[QR], n1[QR];
+#pragma unroll
+            for (int r = 0; r < QR; r++) {
+                const uint32_t q = tid + (uint32_t)r * TB;
+                lo0[r] = n0[r] = lo1[r] = n1[r] = 0;
+                if (q >= Q) continue;
+                // the smallest threshold of the windows that hold q, bounded by
+                // the minima of the 32-entry blocks covering those windows
+                // (lossless: never above the true minimum)
                 uint32_t lo = 0, hi = C;  // first core entry whose window reaches past q
                 while (lo < hi) {
                     uint32_t m = (lo + hi) >> 1;
@@ -752,39 +1230,29 @@ k_tile_search(SearchArgs a) {
                 const uint32_t last = q < C ? q : C - 1;
                 uint32_t t = 0xFFFFu;
                 if (lo <= last)
-                    for (uint32_t b = lo >> 5; b <= (last >> 5); b++) t = min(t, L.Tblk[b]);
+                    for (uint32_t b = lo >> 5; b <= (last >> 5); b++) t = min(t, (uint32_t)L.Tblk[b]);
                 L.qT[q] = (uint16_t)t;
+                const uint32_t fl = L.qfl[q];
+                if ((fl & QF_ELIG) && t != 0xFFFFu) {
+                    if (ix.dir_shift) lookup(ix, hash[r], d0[r], d1[r], d2[r]);
+                    lo0[r] = d0[r];
+                    n0[r] = d1[r] - d0[r];
+                    lo1[r] = d1[r];
+                    n1[r] = d2[r] - d1[r];
+                    L.qfl[q] = (uint8_t)(fl | QF_LISTED);
+                }
             }
-            __syncthreads();
-            PHASE(PH_QUERY);
-            if (L.nwin == 0) {
-                c_begin = L.c1;
-                __syncthreads();
-                continue;
-            }
-            if (threadIdx.x == 0) {
-                L.cnt[CNT_WINDOWS] += L.nwin;
-                if (L.dup) L.cnt[CNT_DUP_TILES] += 1;
-            }
-            const uint32_t Tmin = L.Tmin;
-            const bool dup = L.dup != 0;
-
-            // ---- full-range lists and partition count ----
-            const uint32_t nl = 2 * Q;
-            for (uint32_t l = threadIdx.x; l < nl; l += TB) {
-                const uint32_t q = l >> 1, b = l & 1;
-                uint32_t lo = 0, hi = 0;
-                if ((L.qfl[q] & 2) && L.qT[q] != 0xFFFFu) lookup(ix, L.qhash[q], b, lo, hi);
-                L.lst_lo[l] = lo;
-                L.hoff[l] = hi - lo;
-            }
-            __syncthreads();
-            const uint32_t Hfull = block_scan_u32(L.hoff, (int)nl, L.wtmp);
-            PHASE(PH_LISTS);
+            const uint32_t Hfull = make_lists(lo0, n0, lo1, n1);
             uint32_t P = (Hfull + a.hpart - 1) / a.hpart;
             if (P < 1) P = 1;
-            bool lists_full = true;  // lst_lo/hoff hold the full lists
-            bool modes_set = false;  // some qmode differs from QM_NORMAL
+            bool lists_full = Hfull <= HCAP;  // the lists hold every hit of every window
+            bool clean = true;                // table and marks as the window phase left them
+            bool modes_set = false;           // some minimizer has a mode
+            bool multi = P > 1;               // run state crosses partitions
+            if (tid == 0) L.sp = 0;
+            if (multi)
+                for (uint32_t t = tid; t < 2 * C; t += TB) L.run_c[t] = 0;
+            PHASE(PH_LISTS);
             // Target partitions in increasing order; a partition with too many
             // hits or kept hits is split in halves on a small stack (LIFO,
             // left half first, so candidates still arrive in target order).
@@ -792,195 +1260,353 @@ k_tile_search(SearchArgs a) {
             // starts instead: each window keeps its own run state, so any
             // grouping of windows sees its candidates in target order.
             for (uint32_t pt = 0; pt < P; pt++) {
-            if (threadIdx.x == 0) {
+            if (tid == 0) {
                 L.sp = 1;
                 L.stackA[0] = (uint32_t)((ix.total * (uint64_t)pt) / P);
                 L.stackB[0] = (uint32_t)((ix.total * (uint64_t)(pt + 1)) / P);
                 L.stackW[0] = C << 16;
             }
             for (;;) {
+                const uint32_t tid = opaque(threadIdx.x), lane = tid & 63;
+                const SearchArgs &a = kernel_args();
+                const IndexView &ix = a.ix;
                 __syncthreads();
                 if (L.sp == 0) break;
-                const uint32_t A = L.stackA[L.sp - 1], B = L.stackB[L.sp - 1];
-                const uint32_t WA = L.stackW[L.sp - 1] & 0xFFFFu, WB = L.stackW[L.sp - 1] >> 16;
+                const uint32_t A = uni(L.stackA[L.sp - 1]), B = uni(L.stackB[L.sp - 1]);
+                const uint32_t WA = uni(L.stackW[L.sp - 1] & 0xFFFFu), WB = uni(L.stackW[L.sp - 1] >> 16);
                 __syncthreads();
-                if (threadIdx.x == 0) L.sp--;
+                if (tid == 0) {
+                    L.sp--;
+                    L.ncoll = 0;
+                    L.nraw = 0;
+                    L.csum = 0;
+                    L.nself = 0;
+                }
                 const bool full = (A == 0 && (uint64_t)B >= ix.total);
                 const bool allw = (WA == 0 && WB == C);
-                const bool single_dup = dup && WB - WA == 1;
+                const bool single = WB - WA == 1;
+                const bool single_dup = dup && single;
                 const uint32_t QE = L.win_qend[WB - 1];  // minimizers [WA, QE) of the windows
                 const uint64_t lo_pos = (A > n) ? (uint64_t)A - n : 0;
                 const uint64_t hi_pos = (uint64_t)B + 2ull * n;  // exclusive
-                // ---- lists restricted to [A - n, B + 2n) and the windows' minimizers ----
-                if (single_dup) {
-                    for (uint32_t q = threadIdx.x; q < Q; q += TB) {
-                        uint8_t m = QM_NORMAL;
-                        if (q >= WA && q < QE && (L.qfl[q] & 2))
-                            for (int r = L.qprev[q]; r >= (int)WA; r = L.qprev[r])
-                                if ((L.qfl[r] & 2) && ((L.qfl[r] ^ L.qfl[q]) & 1) == 0) {
-                                    m = QM_SKIP;
-                                    break;
-                                }
-                        L.qmode[q] = m;
-                    }
-                    __syncthreads();
-                    for (uint32_t q = threadIdx.x; q < Q; q += TB) {
-                        if (L.qmode[q] != QM_SKIP) continue;
-                        int first = -1;  // earliest member in the window
-                        for (int r = L.qprev[q]; r >= (int)WA; r = L.qprev[r])
-                            if ((L.qfl[r] & 2) && ((L.qfl[r] ^ L.qfl[q]) & 1) == 0) first = r;
-                        L.qmode[first] = QM_UNION;
-                    }
-                    __syncthreads();
-                    modes_set = true;
-                } else if (modes_set) {
-                    for (uint32_t q = threadIdx.x; q < Q; q += TB) L.qmode[q] = QM_NORMAL;
-                    __syncthreads();
-                    modes_set = false;
-                }
+                uint32_t H = Hfull;
+                bool pieces = false;  // a list's strands are not adjacent
                 if (!(full && allw && lists_full && !single_dup)) {
-                    for (uint32_t l = threadIdx.x; l < nl; l += TB) {
-                        const uint32_t q = l >> 1, b = l & 1;
-                        uint32_t lo = 0, hi = 0;
-                        if ((L.qfl[q] & 2) && L.qT[q] != 0xFFFFu && q >= WA && q < QE &&
-                            L.qmode[q] != QM_SKIP) {
-                            lookup(ix, L.qhash[q], b, lo, hi);
-                            if (!full) {
-                                uint32_t a0, b0;
-                                lower_pos2(ix, lo, hi, lo_pos, hi_pos, a0, b0);
-                                lo = a0;
-                                hi = b0;
-                            }
+                    // ---- lists restricted to [A - n, B + 2n) and the windows' minimizers ----
+                    if (!clean) {
+                        for (uint32_t t = tid; t < NCHUNK; t += TB) L.marks[t] = 0;
+                        for (uint32_t t = tid; t < TBYTES / 16; t += TB)
+                            L.u.vec[t] = uint4{0, 0, 0, 0};
+                    } else if (lists_full) {
+                        for (uint32_t t = tid; t < NCHUNK; t += TB) L.marks[t] = 0;
+                    }
+                    if (single_dup) {
+                        for (uint32_t q = tid; q < Q; q += TB) {
+                            uint32_t m = L.qfl[q] & ~(uint32_t)(QF_SKIP | QF_UNION);
+                            if (q >= WA && q < QE && (m & QF_ELIG))
+                                for (int r = L.qprev[q]; r >= (int)WA; r = L.qprev[r])
+                                    if ((L.qfl[r] & QF_ELIG) && ((L.qfl[r] ^ m) & QF_STRAND) == 0) {
+                                        m |= QF_SKIP;
+                                        break;
+                                    }
+                            L.qfl[q] = (uint8_t)m;
                         }
-                        L.lst_lo[l] = lo;
-                        L.hoff[l] = hi - lo;
+                        __syncthreads();
+                        // the earliest member in the window stands for the skipped
+                        // (several may write it: the same value)
+                        for (uint32_t q = tid; q < Q; q += TB) {
+                            if (!(L.qfl[q] & QF_SKIP)) continue;
+                            int first = -1;
+                            for (int r = L.qprev[q]; r >= (int)WA; r = L.qprev[r])
+                                if ((L.qfl[r] & QF_ELIG) && ((L.qfl[r] ^ L.qfl[q]) & QF_STRAND) == 0)
+                                    first = r;
+                            if (first >= 0) L.qfl[first] = (uint8_t)(L.qfl[first] | QF_UNION);
+                        }
+                        modes_set = true;
+                    } else if (modes_set) {
+                        for (uint32_t q = tid; q < Q; q += TB)
+                            L.qfl[q] = (uint8_t)(L.qfl[q] & ~(QF_SKIP | QF_UNION));
+                        modes_set = false;
                     }
                     __syncthreads();
-                    block_scan_u32(L.hoff, (int)nl, L.wtmp);
-                    lists_full = full && allw && !single_dup;
+#pragma unroll
+                    for (int r = 0; r < QR; r++) {
+                        const uint32_t q = tid + (uint32_t)r * TB;
+                        lo0[r] = n0[r] = lo1[r] = n1[r] = 0;
+                        if (q >= Q) continue;
+                        uint32_t fl = L.qfl[q] & ~(uint32_t)QF_LISTED;
+                        if ((fl & QF_ELIG) && L.qT[q] != 0xFFFFu && q >= WA && q < QE &&
+                            !(fl & QF_SKIP)) {
+                            uint32_t x0, x1, x2;
+                            lookup(ix, ix.mhash[c0 + q], x0, x1, x2);
+                            uint32_t b0 = x1, b1 = x2;
+                            lo0[r] = x0;
+                            lo1[r] = x1;
+                            if (!full) {
+                                lower_pos2(ix, x0, x1, lo_pos, hi_pos, lo0[r], b0);
+                                lower_pos2(ix, x1, x2, lo_pos, hi_pos, lo1[r], b1);
+                            }
+                            n0[r] = b0 - lo0[r];
+                            n1[r] = b1 - lo1[r];
+                            const uint64_t p = L.qpos[q];
+                            if (p >= lo_pos && p < hi_pos) fl |= QF_LISTED;
+                        }
+                        L.qfl[q] = (uint8_t)fl;
+                    }
+                    H = make_lists(lo0, n0, lo1, n1);
+                    lists_full = full && allw && !single_dup && H <= HCAP;
+                    pieces = !full;
+                    clean = true;
                 }
                 PHASE(PH_PLISTS);
-                const uint32_t H = L.hoff[nl];
                 if (H == 0) continue;
-                if (H > HMAX) {
-                    if (threadIdx.x == 0) split_partition(a, L, A, B, WA, WB, n);
+                if (H > HCAP) {
+                    __syncthreads();
+                    if (tid == 0) split_partition(a, L, A, B, WA, WB, n);
+                    if (!multi)
+                        for (uint32_t t = tid; t < 2 * C; t += TB) L.run_c[t] = 0;
+                    multi = true;
                     __syncthreads();
                     if (L.err) break;
                     continue;
                 }
-                if (threadIdx.x == 0) {
+                __syncthreads();  // lists made, scalars cleared
+                clean = false;
+                if (tid == 0) {
                     L.cnt[CNT_HITS] += H;
                     L.cnt[CNT_PARTS] += 1;
-                    L.ncoll = 0;
                 }
-                // ---- pass 1: bin counts ----
-                for (uint32_t t = threadIdx.x; t < TWORDS; t += TB) L.u.table[t] = 0;
-                __syncthreads();
                 const uint32_t SB = a.bin_shift;
-                uint32_t *stash_p = L.eseq;                                        // STASH x u32
-                uint16_t *stash_l = reinterpret_cast<uint16_t *>(L.eseq + STASH);  // STASH x u16
-                static_assert(offsetof(TileLds, einfo) + sizeof(uint32_t) * CB -
-                                  offsetof(TileLds, eseq) >= STASH * 6,
-                              "the stash exceeds the kept-hit arrays");
-                // Each wave takes HU * 64 consecutive hits per round and issues
-                // all their position loads before using any, so a thread waits
-                // for memory once per round instead of once per hit.
-                for (uint32_t r0 = 0; r0 < H; r0 += TB * HU) {
-                    const uint32_t cb = r0 + (uint32_t)wave * 64 * HU;
-                    uint32_t pv[HU], lv[HU];
-                    gather_hits(L, ix, nl, H, cb, lane, pv, lv);
-                    if (cb < STASH) {
+                const uint32_t nch = (H + 63) / 64;
+                // counter bits: 2^lb.  Four while the hits would crowd byte
+                // counters (more than 0.42 a slot: at thresholds around 6 a
+                // slot then gets hot by chance too often), 16 for a single
+                // window, where what is kept has to be exactly what its own
+                // threshold keeps (a window that cannot be split is listed as
+                // dense when too many are kept), or past the smaller ones' range.
+                uint32_t lb = (H * 19 > TBYTES * 8 && Tmin <= 15) ? 2u : 3u;
+                if (Tmin > 255 || single) lb = 4;
+                uint32_t st[SG][HU] = {};  // (set here, so that nothing lives on from the last partition)
+                uint32_t om[SG] = {};
+                bool fresh = true;
+                for (;;) {
+                    if (lb == 4) break;
+                    // ---- gather: bin counts, hits into registers ----
+                    const uint32_t tid = opaque(threadIdx.x), lane = tid & 63;
+                    const uint32_t *const epos = kernel_args().ix.epos;
+                    const uint32_t hl = TLOG + 2 - lb;  // log2 of half the slots
+                    const uint32_t lw = 5 - lb;         // log2 of the slots per word
+                    const uint32_t fm = (1u << lw) - 1;
+                    auto count = [&](uint32_t p, uint32_t o) {
+                        const uint32_t slot = slot_of(p, o, SB, hl);
+                        atomicAdd(&L.u.table[slot >> lw], 1u << ((slot & fm) << lb));
+                    };
 #pragma unroll
-                        for (int u = 0; u < HU; u++) {
-                            const uint32_t e = cb + (uint32_t)u * 64 + lane;
-                            stash_p[e] = pv[u];
-                            stash_l[e] = (uint16_t)lv[u];  // NONE32 -> 0xFFFF
+                    for (int g = 0; g < SG; g++) {
+                        const uint32_t c = (uint32_t)(g * NWAVES + wave) * HU;
+                        if (c < nch) {
+                            if (fresh) om[g] = gather_hits(L, epos, H, nch, pieces, c, lane, st[g]);
+#pragma unroll
+                            for (int u = 0; u < HU; u++)
+                                if ((c + (uint32_t)u) * 64 + lane < H)
+                                    count(st[g][u], (om[g] >> u) & 1u);
                         }
                     }
+                    for (uint32_t c = (uint32_t)(SG * NWAVES + wave) * HU; c < nch; c += NWAVES * HU) {
+                        uint32_t pv[HU];
+                        const uint32_t ob = gather_hits(L, epos, H, nch, pieces, c, lane, pv);
 #pragma unroll
-                    for (int u = 0; u < HU; u++) {
-                        if (lv[u] == NONE32) continue;
-                        const uint32_t q = lv[u] >> 1, b = lv[u] & 1;
-                        if (pv[u] == L.qpos[q] && L.qmode[q] != QM_UNION) {  // never with itself
-                            lv[u] = NONE32;
-                            continue;
-                        }
-                        const uint32_t o = b ^ (L.qfl[q] & 1);
-                        const uint32_t slot = slot_of(pv[u] >> SB, o);
-                        atomicAdd(&L.u.table[slot >> 1], 1u << ((slot & 1) * 16));
+                        for (int u = 0; u < HU; u++)
+                            if ((c + (uint32_t)u) * 64 + lane < H) count(pv[u], (ob >> u) & 1u);
                     }
+                    // the minimizers' own positions, each once in their lists
+                    uint32_t self = 0;
+                    for (uint32_t q = tid; q < Q; q += TB)
+                        if (L.qfl[q] & QF_LISTED) {
+                            const uint32_t slot = slot_of(L.qpos[q], 0, SB, hl);
+                            atomicSub(&L.u.table[slot >> lw], 1u << ((slot & fm) << lb));
+                            self++;
+                        }
+                    self = wave_sum_scan(self);
+                    if (lane == 63 && self) atomicAdd(&L.nself, self);
+                    __syncthreads();
+                    PHASE(PH_PASS1);
+                    // ---- counters into hot flags ----
+                    uint4 hv[TBYTES / 16 / TB];
+                    uint32_t sum = 0;
+#pragma unroll
+                    for (uint32_t v = 0; v < TBYTES / 16 / TB; v++) {
+                        const uint32_t x = tid + v * TB;
+                        const uint4 w = L.u.vec[x];
+                        const uint32_t hb = (x * 4) & (TWORDS / 2), hm = TWORDS / 2 - 1;
+                        const uint32_t pw = L.u.table[hb | ((x * 4 - 1) & hm)];
+                        const uint32_t nw = L.u.table[hb | ((x * 4 + 4) & hm)];
+                        if (lb == 2) {
+                            hv[v].x = hot_nibbles(pw, w.x, w.y, Tmin, sum);
+                            hv[v].y = hot_nibbles(w.x, w.y, w.z, Tmin, sum);
+                            hv[v].z = hot_nibbles(w.y, w.z, w.w, Tmin, sum);
+                            hv[v].w = hot_nibbles(w.z, w.w, nw, Tmin, sum);
+                        } else {
+                            hv[v].x = hot_bytes(pw, w.x, w.y, Tmin, sum);
+                            hv[v].y = hot_bytes(w.x, w.y, w.z, Tmin, sum);
+                            hv[v].z = hot_bytes(w.y, w.z, w.w, Tmin, sum);
+                            hv[v].w = hot_bytes(w.z, w.w, nw, Tmin, sum);
+                        }
+                    }
+                    sum = wave_sum_scan(sum);
+                    if (lane == 63) atomicAdd(&L.csum, sum);
+                    __syncthreads();
+                    const bool exact = L.csum == H - L.nself;
+                    if (exact) {
+#pragma unroll
+                        for (uint32_t v = 0; v < TBYTES / 16 / TB; v++) L.u.vec[tid + v * TB] = hv[v];
+                        __syncthreads();
+                        break;
+                    }
+                    // a counter overflowed: once more with wider ones
+                    for (uint32_t t = tid; t < TBYTES / 16; t += TB) L.u.vec[t] = uint4{0, 0, 0, 0};
+                    __syncthreads();
+                    if (tid == 0) {
+                        L.csum = 0;
+                        L.nself = 0;
+                    }
+                    __syncthreads();
+                    fresh = false;
+                    lb++;
                 }
-                __syncthreads();
-                PHASE(PH_PASS1);
-                // ---- pass 2: keep hits near bins that may be hot ----
-                for (uint32_t r0 = 0; r0 < H; r0 += TB * HU) {
-                    const uint32_t cb = r0 + (uint32_t)wave * 64 * HU;
-                    uint32_t pv[HU], lv[HU];
-                    if (cb < STASH) {
+                if (lb < 4) {
+                    // ---- keep the hits of hot slots: position, orientation, hit number ----
+                    const uint32_t tid = opaque(threadIdx.x), lane = tid & 63;
+                    const uint32_t *const epos = kernel_args().ix.epos;
+                    const uint32_t hl = TLOG + 2 - lb;
+                    auto keep = [&](const uint32_t (&pv)[HU], uint32_t ob, uint32_t c) {
+                        uint32_t kp = 0;
 #pragma unroll
                         for (int u = 0; u < HU; u++) {
-                            const uint32_t e = cb + (uint32_t)u * 64 + lane;
-                            const uint32_t l = stash_l[e];
-                            pv[u] = stash_p[e];
-                            lv[u] = (e < H && l != 0xFFFFu) ? l : NONE32;
+                            const uint32_t slot = slot_of(pv[u], (ob >> u) & 1u, SB, hl);
+                            const uint32_t by = reinterpret_cast<const uint8_t *>(L.u.table)[slot >> (3 - lb)];
+                            const uint32_t hot = (by >> ((slot << lb) & 7u)) & 1u;
+                            kp |= ((c + (uint32_t)u) * 64 + lane < H ? hot : 0u) << u;
                         }
-                    } else {
-                        gather_hits(L, ix, nl, H, cb, lane, pv, lv);
+                        // one LDS atomic per wave and round for the kept hits' slots
+                        const uint32_t nk = (uint32_t)__popc(kp);
+                        if (!__ballot(nk != 0)) return;
+                        const uint32_t ex = wave_sum_scan(nk) - nk;
+                        uint32_t base = 0;
+                        if (lane == 63) base = atomicAdd(&L.nraw, ex + nk);
+                        base = lane_read(base, 63) + ex;
+#pragma unroll
+                        for (int u = 0; u < HU; u++) {
+                            if (!((kp >> u) & 1u)) continue;
+                            if (base < CB)
+                                L.coll[base] = ((uint64_t)pv[u] << 17) | (((ob >> u) & 1u) << 16) |
+                                               ((c + (uint32_t)u) * 64 + lane);
+                            base++;
+                        }
+                    };
+#pragma unroll
+                    for (int g = 0; g < SG; g++) {
+                        const uint32_t c = (uint32_t)(g * NWAVES + wave) * HU;
+                        if (c < nch) keep(st[g], om[g], c);
                     }
-                    bool kp[HU];
-#pragma unroll
-                    for (int u = 0; u < HU; u++) {
-                        kp[u] = false;
-                        if (lv[u] == NONE32) continue;
-                        const uint32_t q = lv[u] >> 1, b = lv[u] & 1;
-                        const uint32_t p = pv[u];
-                        if (p == L.qpos[q] && L.qmode[q] != QM_UNION) continue;
-                        const uint32_t Tq = L.qT[q];
-                        const uint32_t o = b ^ (L.qfl[q] & 1);
-                        const uint32_t c = p >> SB;
-                        const uint32_t m2 = slot_count(L.u.table, slot_of(c - 2, o));
-                        const uint32_t m1 = slot_count(L.u.table, slot_of(c - 1, o));
-                        const uint32_t z0 = slot_count(L.u.table, slot_of(c, o));
-                        const uint32_t p1 = slot_count(L.u.table, slot_of(c + 1, o));
-                        kp[u] = (m2 + m1 >= Tq || m1 + z0 >= Tq || z0 + p1 >= Tq);
+                    for (uint32_t c = (uint32_t)(SG * NWAVES + wave) * HU; c < nch; c += NWAVES * HU) {
+                        uint32_t pv[HU];
+                        const uint32_t ob = gather_hits(L, epos, H, nch, pieces, c, lane, pv);
+                        keep(pv, ob, c);
                     }
-                    // one LDS atomic per wave and round for the kept hits' slots
-                    uint32_t nk = 0;
+                    __syncthreads();
+                    // ---- their minimizers; self-hits leave ----
+                    const uint32_t nraw = L.nraw;
+                    if (nraw <= CB) {
+                        uint64_t key[CB / TB];
 #pragma unroll
-                    for (int u = 0; u < HU; u++) nk += kp[u] ? 1u : 0u;
-                    const uint32_t ex = wave_sum_scan(nk) - nk;
-                    const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)(ex + nk), 63);
-                    uint32_t base = 0;
-                    if (lane == 63 && wt) base = atomicAdd(&L.ncoll, wt);
-                    base = (uint32_t)__builtin_amdgcn_readlane((int)base, 63) + ex;
+                        for (int r = 0; r < CB / TB; r++) {
+                            const uint32_t x = tid + (uint32_t)r * TB;
+                            key[r] = SENT64;
+                            if (x >= nraw) continue;
+                            const uint64_t v = L.coll[x];
+                            const uint32_t p = (uint32_t)(v >> 17), o = (uint32_t)(v >> 16) & 1u;
+                            const uint32_t q = L.rec[list_of(L, (uint32_t)v & 0xFFFFu)].y & 2047u;
+                            if (p != L.qpos[q]) key[r] = ckey(o, p, q);
+                        }
+                        __syncthreads();
 #pragma unroll
-                    for (int u = 0; u < HU; u++) {
-                        if (!kp[u]) continue;
-                        const uint32_t q = lv[u] >> 1, b = lv[u] & 1;
-                        if (base < CB) L.coll[base] = ckey(b ^ (L.qfl[q] & 1), pv[u], q);
-                        base++;
+                        for (int r = 0; r < CB / TB; r++) {
+                            const uint64_t m = __ballot(key[r] != SENT64);
+                            if (!m) continue;
+                            uint32_t base = 0;
+                            if (lane == 0) base = atomicAdd(&L.ncoll, (uint32_t)__popcll(m));
+                            base = lanes_below(m, uni(base));
+                            if (key[r] != SENT64) L.coll[base] = key[r];
+                        }
+                    } else if (tid == 0) {
+                        L.ncoll = NONE32;
+                    }
+                } else {
+                    // ---- 16-bit counters, in two passes over the lists: counts
+                    // without self-hits, then each hit against its minimizer's
+                    // own threshold ----
+                    constexpr uint32_t hl = TLOG - 2;
+                    const uint32_t *const epos = kernel_args().ix.epos;
+                    const uint16_t *t16 = reinterpret_cast<const uint16_t *>(L.u.table);
+                    for (int pass = 0; pass < 2; pass++) {
+                        for (uint32_t c = wave; c < nch; c += NWAVES) {
+                            const uint32_t e = c * 64 + lane;
+                            bool kp = false;
+                            uint32_t p = 0, q = 0, o = 0;
+                            if (e < H) {
+                                const uint32_t l = list_of(L, e);
+                                const uint2 r = L.rec[l];
+                                const uint32_t b = e >= (r.y >> 12) ? 1u : 0u;
+                                q = r.y & 2047u;
+                                p = epos[(pieces && b ? L.rec1[l] : r.x) + e];
+                                o = b ^ ((r.y >> 11) & 1u);
+                                kp = p != L.qpos[q] || (L.qfl[q] & QF_UNION);
+                            }
+                            const uint32_t slot = slot_of(p, o, SB, hl);
+                            if (pass == 0) {
+                                if (kp) atomicAdd(&L.u.table[slot >> 1], 1u << ((slot & 1) * 16));
+                                continue;
+                            }
+                            if (kp) {
+                                const uint32_t hm = (1u << hl) - 1, hb = o << hl, Tq = L.qT[q];
+                                const uint32_t m2 = t16[hb | ((slot - 2) & hm)];
+                                const uint32_t m1 = t16[hb | ((slot - 1) & hm)];
+                                const uint32_t z0 = t16[slot];
+                                const uint32_t p1 = t16[hb | ((slot + 1) & hm)];
+                                kp = m2 + m1 >= Tq || m1 + z0 >= Tq || z0 + p1 >= Tq;
+                            }
+                            const uint64_t m = __ballot(kp);
+                            if (!m) continue;
+                            uint32_t base = 0;
+                            if (lane == 0) base = atomicAdd(&L.ncoll, (uint32_t)__popcll(m));
+                            base = lanes_below(m, uni(base));
+                            if (kp && base < CB) L.coll[base] = ckey(o, p, q);
+                        }
+                        __syncthreads();
                     }
                 }
                 __syncthreads();
                 PHASE(PH_PASS2);
-                const uint32_t ncoll = L.ncoll;
+                const uint32_t ncoll = uni(L.ncoll);
                 if (ncoll == 0) continue;
                 if (ncoll > min(a.kept_cap, (uint32_t)CB)) {
-                    if (threadIdx.x == 0) split_partition(a, L, A, B, WA, WB, n);
+                    if (tid == 0) split_partition(a, L, A, B, WA, WB, n);
+                    if (!multi)
+                        for (uint32_t t = tid; t < 2 * C; t += TB) L.run_c[t] = 0;
+                    multi = true;
                     __syncthreads();
                     if (L.err) break;
                     continue;
                 }
-                if (threadIdx.x == 0) L.cnt[CNT_KEPT] += ncoll;
+                if (tid == 0) L.cnt[CNT_KEPT] += ncoll;
                 // ---- sort kept hits by (o, p', q) ----
                 static_assert(CB % 64 == 0, "runs of 64 kept hits");
                 block_sort_runs(L.coll, ncoll);
                 PHASE(PH_SORT);
                 // ---- exact hot starts: >= Tmin hits in [x, x + n - k] ----
-                uint32_t *hot = reinterpret_cast<uint32_t *>(L.u.scratch);  // entry index + 1
-                uint8_t *relf = reinterpret_cast<uint8_t *>(hot + CB);
-                uint32_t *pref = hot + CB + CB / 4;
-                for (uint32_t e = threadIdx.x; e < ncoll; e += TB) {
+                PostLds &F = L.u.post;
+                for (uint32_t e = tid; e < ncoll; e += TB) {
                     const uint64_t key = L.coll[e];
                     uint32_t hv = 0;
                     const bool first = (e == 0) || ck_op(L.coll[e - 1]) != ck_op(key);
@@ -989,14 +1615,14 @@ k_tile_search(SearchArgs a) {
                         if (ck_o(k2) == ck_o(key) && (uint64_t)ck_p(k2) <= (uint64_t)ck_p(key) + n - k)
                             hv = e + 1;
                     }
-                    hot[e] = hv;
+                    F.hot[e] = hv;
                 }
                 __syncthreads();
-                block_maxscan_u32(hot, (int)ncoll, L.wtmp);
+                block_maxscan_u32(F.hot, (int)ncoll, L.wtmp);
                 // ---- relevant: within [x, x + 2n - k) of the last hot x ----
-                for (uint32_t e = threadIdx.x; e < ncoll; e += TB) {
+                for (uint32_t e = tid; e < ncoll; e += TB) {
                     const uint64_t key = L.coll[e];
-                    const uint32_t lh = hot[e];
+                    const uint32_t lh = F.hot[e];
                     uint32_t f = 0;
                     if (lh && ck_o(L.coll[lh - 1]) == ck_o(key)) {
                         const uint64_t x = ck_p(L.coll[lh - 1]);
@@ -1004,23 +1630,23 @@ k_tile_search(SearchArgs a) {
                         if (d < 2ull * n - k) f |= 4;   // relevant
                         if (d < n) f |= EF_CAND;
                     }
-                    relf[e] = (uint8_t)f;
-                    pref[e] = (f & 4) ? 1u : 0u;
+                    F.relf[e] = (uint8_t)f;
+                    F.pref[e] = (f & 4) ? 1u : 0u;
                 }
                 __syncthreads();
-                const uint32_t nrel = block_scan_u32(pref, (int)ncoll, L.wtmp);
+                const uint32_t nrel = uni(block_scan_u32(F.pref, (int)ncoll, L.wtmp));
                 // stable compaction in place: read everything first, then write
-                uint64_t keep_k[CB / TB];
+                uint64_t keep_k[CB / TB] = {};
                 uint32_t keep_at[CB / TB];
-                uint8_t keep_f[CB / TB];
+                uint8_t keep_f[CB / TB] = {};
 #pragma unroll
                 for (int r = 0; r < CB / TB; r++) {
-                    const uint32_t e = threadIdx.x + r * TB;
+                    const uint32_t e = tid + r * TB;
                     keep_at[r] = NONE32;
-                    if (e < ncoll && (relf[e] & 4)) {
+                    if (e < ncoll && (F.relf[e] & 4)) {
                         keep_k[r] = L.coll[e];
-                        keep_f[r] = relf[e] & EF_CAND;
-                        keep_at[r] = pref[e];
+                        keep_f[r] = F.relf[e] & EF_CAND;
+                        keep_at[r] = F.pref[e];
                     }
                 }
                 __syncthreads();
@@ -1030,11 +1656,16 @@ k_tile_search(SearchArgs a) {
                 for (int r = 0; r < CB / TB; r++) {
                     if (keep_at[r] != NONE32) {
                         L.coll[keep_at[r]] = keep_k[r];
-                        L.einfo[keep_at[r]] = keep_f[r] ? EI_CAND : 0u;
+                        F.einfo[keep_at[r]] = keep_f[r] ? EI_CAND : 0u;
                     }
                 }
+                if (dup)  // the repeats' chains forwards
+                    for (uint32_t q = tid; q < Q; q += TB) F.qnext[q] = -1;
                 __syncthreads();
-                if (threadIdx.x == 0) {
+                if (dup)
+                    for (uint32_t q = tid; q < Q; q += TB)
+                        if (L.qprev[q] >= 0) F.qnext[L.qprev[q]] = (int16_t)q;
+                if (tid == 0) {
                     // orientation 1 starts at the first entry with o = 1
                     uint32_t lo = 0, hi = nrel;
                     while (lo < hi) {
@@ -1047,7 +1678,7 @@ k_tile_search(SearchArgs a) {
                     L.oend[1] = nrel;
                 }
                 __syncthreads();
-                for (uint32_t e = threadIdx.x; e < nrel; e += TB) {
+                for (uint32_t e = tid; e < nrel; e += TB) {
                     const uint64_t key = L.coll[e];
                     const uint32_t o = ck_o(key), p = ck_p(key), q = ck_q(key);
                     // end of the counting range [p, p + n - k]
@@ -1057,172 +1688,79 @@ k_tile_search(SearchArgs a) {
                         uint32_t m = (lo + hi) >> 1;
                         if ((uint64_t)ck_p(L.coll[m]) <= lim) lo = m + 1; else hi = m;
                     }
-                    L.rng_end[e] = (uint16_t)lo;
+                    F.rng_end[e] = (uint16_t)lo;
                     uint32_t info = q;
                     if (e > L.obeg[o] && ck_p(L.coll[e - 1]) == p) info |= EI_SAMEP;
-                    if ((L.einfo[e] & EI_CAND) && p >= A && p < B) {  // owned by this partition
+                    if ((F.einfo[e] & EI_CAND) && p >= A && p < B) {  // owned by this partition
                         uint32_t sq = 0;
                         if (window_ok(ix, p, n, &sq)) info |= EI_CAND;
-                        L.eseq[e] = sq;
+                        F.etb[e] = (uint32_t)ix.off[sq];
                     }
-                    L.einfo[e] = info;
+                    F.einfo[e] = info;
                 }
                 __syncthreads();
                 PHASE(PH_SEGINFO);
 
                 // ---- exact counts, runs and seeds: one lane per window ----
-                // A wave takes 64 consecutive windows, one per lane, and walks
-                // the kept hits of each orientation in target order.  At a kept
-                // hit that is a candidate j of some of its windows it marks, in
-                // a bitmask over the tile's query minimizers, those with a kept
-                // hit in [j, j+n-k]; a window's shared count is the popcount of
-                // the mask over its own minimizers (less the repeats of a hash
-                // when the tile has any), and every lane applies its window's
-                // run logic to its candidates in target order.
-                SeedBuf sbuf{reinterpret_cast<uint32_t *>(L.u.scratch) + wave * SBUF * 6, 0};
-                uint64_t *sbits = L.u.scratch + (NWAVES * SBUF * 6) / 2 + wave * QW;
-                uint64_t *dbits = L.u.scratch + (NWAVES * SBUF * 6) / 2 + NWAVES * QW + wave * QW;
-                static_assert((NWAVES * SBUF * 6) / 2 + 2 * NWAVES * QW <= TWORDS / 2,
-                              "per-wave eval buffers exceed the scratch area");
-                if (lane < QW) {
-                    sbits[lane] = 0;
-                    dbits[lane] = 0;
-                }
-                __builtin_amdgcn_wave_barrier();
+                // A wave takes 64 consecutive windows and one orientation, and
+                // walks the kept hits that are candidates j of its windows in
+                // target order; a window's count is the number of its
+                // minimizers with a kept hit in [j, j + n - k] (repeats of a
+                // hash once).  A step of a candidate is a few compares, ballots
+                // and popcounts and the run logic, without memory accesses
+                // (eval_masks); blocks whose windows reach more than 256
+                // minimizers follow the hits that enter and leave instead.
+                SeedBuf sbuf{F.seeds + wave * SBUF * 6, 0};
                 uint32_t n_evals = 0, n_scan = 0;
-                for (uint32_t b0 = WA + (uint32_t)wave * 64; b0 < WB; b0 += TB) {
+                // all windows of orientation 0, then of 1: a tile's hits are mostly
+                // of one orientation, and every wave gets a share of them
+                const uint32_t nblock = (WB - WA + 63) / 64, ntask = 2 * nblock;
+                for (uint32_t task = wave; task < ntask; task += NWAVES) {
+                    const SearchArgs &a = kernel_args();
+                    const uint32_t o = task >= nblock ? 1u : 0u, b0 = WA + (task - o * nblock) * 64;
+                    const uint32_t ob = uni(L.obeg[o]), oe = uni(L.oend[o]);
+                    if (ob >= oe) continue;  // nothing ends a run but a candidate
                     const uint32_t qc = b0 + lane;
-                    const uint32_t qlo = b0, qhi = L.win_qend[min(b0 + 63, WB - 1)];
-                    const uint32_t wlo = qlo >> 6, nwb = ((qhi - 1) >> 6) - wlo + 1;
-                    const uint32_t Ti = qc < WB ? L.win_T[qc] : 0u;
-                    const bool win = Ti != 0;
-                    const uint32_t qe = win ? L.win_qend[qc] : 0u;
-                    const uint32_t i = win ? L.qpos[qc] : 0u;
-                    const uint32_t si = win ? L.win_s[qc] : 0u;
-                    for (uint32_t o = 0; o < 2; o++) {
-                        const uint32_t ob = L.obeg[o], oe = L.oend[o];
-                        if (ob >= oe) continue;
-                        RunState rs{0, 0, 0, 0, 0};
-                        if (win) rs = L.run[qc][o];
-                        uint32_t carry_q = EI_Q;  // minimizer of the hit before the chunk
-                        for (uint32_t e0 = ob & ~63u; e0 < oe; e0 += 64) {
-                            n_scan++;
-                            const uint32_t ex = e0 + lane;
-                            const bool valid = ex >= ob && ex < oe;
-                            const uint32_t info = valid ? L.einfo[ex] : 0u;
-                            const uint32_t qx = info & EI_Q;
-                            // candidates whose minimizer lies in one of the block's windows
-                            uint64_t mm = __ballot(valid && (info & EI_CAND) && qx >= qlo && qx < qhi);
-                            const uint32_t chunk_last_q = (uint32_t)__builtin_amdgcn_readlane((int)qx, 63);
-                            while (mm) {
-                                const uint32_t bb = (uint32_t)__ffsll((long long)mm) - 1;
-                                mm &= mm - 1;
-                                const uint32_t e = e0 + bb;
-                                const uint32_t ie = (uint32_t)__builtin_amdgcn_readlane((int)info, (int)bb);
-                                const uint32_t q = ie & EI_Q;
-                                const uint32_t pq = bb ? ((uint32_t)__builtin_amdgcn_readlane((int)info, (int)bb - 1) & EI_Q)
-                                                       : carry_q;
-                                // the window's first hit at this position
-                                const bool mine = win && q >= qc && q < qe && !((ie & EI_SAMEP) && pq >= qc);
-                                const uint64_t mb = __ballot(mine);
-                                if (!mb) continue;
-                                n_evals += (uint32_t)__popcll(mb);
-                                const uint32_t j = ck_p(L.coll[e]);
-                                const uint32_t tseq = L.eseq[e];
-                                const uint32_t re = L.rng_end[e];  // > e
-                                // minimizers of the block with a kept hit in [j, j+n-k]
-                                for (uint32_t f0 = e; f0 < re; f0 += 64) {
-                                    const uint32_t f = f0 + lane;
-                                    if (f < re) {
-                                        const uint32_t qf = L.einfo[f] & EI_Q;
-                                        if (qf >= qlo && qf < qhi) atomicOr(&sbits[qf >> 6], 1ull << (qf & 63));
-                                    }
-                                }
-                                __builtin_amdgcn_wave_barrier();
-                                uint32_t cnt = 0;
-                                if (mine) {
-                                    const uint32_t w0 = qc >> 6, w1 = (qe - 1) >> 6;
-                                    for (uint32_t x = w0; x <= w1; x++) {
-                                        uint64_t m = sbits[x];
-                                        if (x == w0) m &= ~0ull << (qc & 63);
-                                        if (x == w1 && (qe & 63)) m &= (1ull << (qe & 63)) - 1;
-                                        cnt += (uint32_t)__popcll(m);
-                                    }
-                                }
-                                if (dup) {
-                                    // a marked minimizer repeats a hash when an earlier
-                                    // marked one has the same hash; it does not count
-                                    // in the windows holding that earlier one too
-                                    for (uint32_t f0 = e; f0 < re; f0 += 64) {
-                                        const uint32_t f = f0 + lane;
-                                        uint32_t qf = 0;
-                                        int ps = -1;
-                                        if (f < re) {
-                                            qf = L.einfo[f] & EI_Q;
-                                            if (qf >= qlo && qf < qhi)
-                                                for (int r = L.qprev[qf]; r >= (int)qlo; r = L.qprev[r])
-                                                    if ((sbits[r >> 6] >> (r & 63)) & 1) {
-                                                        ps = r;
-                                                        break;
-                                                    }
-                                        }
-                                        bool own = false;
-                                        if (ps >= 0) {  // once per minimizer
-                                            const uint64_t old = atomicOr(&dbits[qf >> 6], 1ull << (qf & 63));
-                                            own = ((old >> (qf & 63)) & 1) == 0;
-                                        }
-                                        uint64_t om = __ballot(own);
-                                        while (om) {
-                                            const uint32_t t = (uint32_t)__ffsll((long long)om) - 1;
-                                            om &= om - 1;
-                                            const uint32_t dq = (uint32_t)__builtin_amdgcn_readlane((int)qf, (int)t);
-                                            const uint32_t dp = (uint32_t)__builtin_amdgcn_readlane(ps, (int)t);
-                                            if (mine && dq >= qc && dq < qe && dp >= qc) cnt--;
-                                        }
-                                    }
-                                }
-                                __builtin_amdgcn_wave_barrier();
-                                if ((uint32_t)lane < nwb) {
-                                    sbits[wlo + lane] = 0;
-                                    dbits[wlo + lane] = 0;
-                                }
-                                __builtin_amdgcn_wave_barrier();
-                                // run logic: a passing candidate continues the open run
-                                // when it lies in its sequence less than n after the
-                                // previous candidate; a run's seed is its largest count,
-                                // earliest j on ties
-                                bool excl = false;
-                                if (tseq == L.qseq) {
-                                    const uint32_t dd = j > i ? j - i : i - j;
-                                    excl = dd < n && (n - dd) > a.max_overlap;
-                                }
-                                const bool pass = mine && cnt >= Ti && !excl;
-                                const bool link = pass && rs.active && tseq == rs.prev_seq && j - rs.prev_j < n;
-                                // a run ends: its seed, or with runs_out its first and
-                                // last candidate (the previous one) for the estimate
-                                seeds_push_lanes(a, sbuf, lane, mine && rs.active && !link, L.qid, i,
-                                                 rs.best_j, o, a.runs_out ? rs.prev_j : rs.best_c, si);
-                                if (mine) {
-                                    if (link) {
-                                        if (!a.runs_out && cnt > rs.best_c) {
-                                            rs.best_c = (uint16_t)cnt;
-                                            rs.best_j = j;
-                                        }
-                                    } else if (pass) {
-                                        rs.active = 1;
-                                        rs.best_c = (uint16_t)cnt;
-                                        rs.best_j = j;
-                                    } else {
-                                        rs.active = 0;
-                                    }
-                                    rs.prev_j = j;
-                                    rs.prev_seq = tseq;
-                                }
-                            }
-                            carry_q = chunk_last_q;
-                        }
-                        if (win) L.run[qc][o] = rs;
+                    Block bk;
+                    bk.qlo = b0;
+                    bk.qhi = uni(L.win_qend[min(b0 + 63, WB - 1)]);
+                    bk.si = qc < WB ? L.win_s[qc] : 0u;
+                    const bool win = bk.si != 0;
+                    bk.Ti = opaque(win ? a.T[bk.si] : 0u);  // (waited for here, not in the steps)
+                    bk.qc = qc;
+                    bk.len = win ? L.win_qend[qc] - qc : 0u;
+                    bk.i = win ? L.qpos[qc] : 0u;
+                    bk.o = o;
+                    bk.near = a.n - a.max_overlap - 1;
+                    bk.runs_out = a.runs_out != 0;
+                    RunState rs{0, 0, 0};
+                    if (win && multi) {
+                        rs.prev_j = L.run_prev[2 * qc + o];
+                        rs.best_j = L.run_best[2 * qc + o];
+                        rs.best_c = L.run_c[2 * qc + o];
                     }
+                    EndedRuns er{0, 0, 0};
+                    const uint32_t nq = bk.qhi - bk.qlo;
+                    if (nq <= 192)
+                        eval_masks<3>(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
+                    else if (nq <= 256)
+                        eval_masks<4>(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
+                    else
+                        eval_events(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
+                    if (multi) {
+                        if (win) {
+                            L.run_prev[2 * qc + o] = rs.prev_j;
+                            L.run_best[2 * qc + o] = rs.best_j;
+                            L.run_c[2 * qc + o] = (uint16_t)rs.best_c;
+                        }
+                    } else {  // the only partition: the open runs end
+                        const uint64_t em = __ballot(rs.best_c != 0);
+                        if (em & er.m) push_ended(a, L, sbuf, bk, er, lane);
+                        er.m |= em;
+                        er.j = rs.best_c ? rs.best_j : er.j;
+                        er.v = rs.best_c ? (bk.runs_out ? rs.prev_j : rs.best_c) : er.v;
+                    }
+                    if (er.m) push_ended(a, L, sbuf, bk, er, lane);
                 }
                 if (lane == 0) {
                     atomicAdd(&L.cnt[CNT_EVALS], (unsigned long long)n_evals);
@@ -1236,31 +1774,31 @@ k_tile_search(SearchArgs a) {
             if (L.err) break;
             }  // partitions
             if (L.err) {
-                if (threadIdx.x == 0) atomicOr(a.err, L.err);
-            } else {
+                if (tid == 0) atomicOr(a.err, L.err);
+            } else if (multi) {
                 // close the runs still open after the last partition: one
                 // (window, orientation) per lane
-                SeedBuf sbuf{reinterpret_cast<uint32_t *>(L.u.scratch) + wave * SBUF * 6, 0};
-                for (uint32_t b0 = (uint32_t)wave * 64; b0 < 2 * C; b0 += TB) {
-                    const uint32_t x = b0 + lane, qc = x >> 1, o = x & 1;
-                    bool mine = false;
-                    RunState rs{0, 0, 0, 0, 0};
-                    if (x < 2 * C && L.win_T[qc]) {
-                        rs = L.run[qc][o];
-                        mine = rs.active != 0;
-                    }
-                    seeds_push_lanes(a, sbuf, lane, mine, L.qid, mine ? L.qpos[qc] : 0, rs.best_j,
-                                     o, a.runs_out ? rs.prev_j : rs.best_c, mine ? L.win_s[qc] : 0);
+                SeedBuf sbuf{L.u.post.seeds + wave * SBUF * 6, 0};
+                for (uint32_t b0 = wave * 64; b0 < 2 * C; b0 += TB) {
+                    const uint32_t x = b0 + lane, qc = x >> 1;
+                    const bool mine = x < 2 * C && L.win_s[qc] && L.run_c[x];
+                    seeds_push_lanes(a, sbuf, lane, mine, L.qid, mine ? L.qpos[qc] : 0,
+                                     mine ? L.run_best[x] : 0, x & 1,
+                                     mine ? (a.runs_out ? L.run_prev[x] : L.run_c[x]) : 0,
+                                     mine ? L.win_s[qc] : 0);
                 }
                 seeds_flush_block(a, L, sbuf, lane, wave);
             }
-            c_begin = L.c1;
+            c_begin += C;
             __syncthreads();
             PHASE(PH_FLUSH);
         }
-        __syncthreads();
+        // (every piece left out: no window phase ran)
+        if (wave == NWAVES - 1 && first_piece)
+            next_tile(kernel_args(), L, uni(ticket), threadIdx.x & 63);
     }
     __syncthreads();
+    const SearchArgs &a = kernel_args();
     if (threadIdx.x < CNT_N && threadIdx.x != CNT_SEEDS && L.cnt[threadIdx.x])
         atomicAdd(&a.counters[threadIdx.x], L.cnt[threadIdx.x]);
     if (prof)
@@ -1273,6 +1811,7 @@ void launch_tile_search(const SearchArgs &a, uint32_t grid, hipStream_t st) {
 }
 
 uint32_t tile_core_max() { return CMAX; }
+TileLimits tile_limits() { return TileLimits{CMAX, QCAP, HCAP, CB, 2 * TBYTES}; }
 
 }  // namespace tile1024 / tile512
 

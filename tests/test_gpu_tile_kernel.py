@@ -1,0 +1,49 @@
+"""The tile kernel's branches against the oracle, where they can go wrong:
+blocks of windows at the edges of the mask words and past them, counters that
+overflow, tiles in partitions.  All outputs are whole numbers: equality."""
+import numpy as np
+import pytest
+
+from paper_1807_00205_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SEED_F = ["query_id", "i", "j", "strand", "shared", "sketch"]
+CAND_F = ["query_id", "strand", "q_seq", "t_seq", "q_begin", "q_end", "t_begin", "t_end",
+          "n_seeds", "max_shared"]
+
+
+def _same(a, b, fields, what):
+    assert len(a) == len(b), "%s: %d vs %d records" % (what, len(a), len(b))
+    for f in fields:
+        assert np.array_equal(np.asarray(a[f]).astype(np.uint64),
+                              np.asarray(b[f]).astype(np.uint64)), (what, f)
+
+
+# 64 windows reach 64 + 2 n / (w + 1) minimizers: three words of masks, four,
+# and more (hits followed one by one); with k = 5 and 6 a tile has so many hits
+# per target bin that counters of 4 and 8 bits overflow
+@pytest.mark.parametrize("k,w,min_len,hits_per_part,threads", [
+    (12, 16, 300, None, 512), (12, 16, 1400, None, 512), (12, 16, 1500, None, 1024),
+    (12, 16, 3000, None, 1024), (12, 3, 1000, None, 512), (12, 1, 400, None, 1024),
+    (12, 16, 1000, 1024, 1024), (12, 3, 1000, 1024, 512),
+    (6, 8, 600, None, 512), (6, 8, 600, None, 1024), (6, 5, 500, 4000, 512),
+    (5, 8, 600, None, 512), (5, 6, 600, None, 1024)])
+def test_tile_kernel_branches(oracle_lib, k, w, min_len, hits_per_part, threads):
+    from paper_1807_00205_amd import sdf
+    g = synth.tandem_case(1000 + 31 * k + w + min_len, length=24_000, n_arrays=24, copies_hi=50,
+                          n_seqs=2, n_sd=4)
+    src = g.seqs[0][2_000:2_000 + 2 * min_len]
+    g.seqs[1][9_000:9_000 + len(src)] = src          # an exact copy longer than the windows,
+    g.seqs[0][15_000:15_000 + len(src)] = synth.revcomp(src)  # and one in reverse
+    b, off = g.concat()
+    spans = list(g.spans) + [(0, 1_111, 1_111 + min_len + 3), (1, 5, len(g.seqs[1]) - 7)]
+    ix = sdf.Index(g.seqs, k, w)
+    orc = oracle_lib.OracleIndex(b, off, k, w)
+    os_, oc = orc.search(spans, 0.25, min_len)
+    with sdf.tuning(tile_threads=threads, hits_per_part=hits_per_part):
+        r = ix.search_batch(spans, 0.25, min_len)
+    _same(r.seeds(), os_, SEED_F, "seeds")
+    _same(r.candidates(), oc, CAND_F, "candidates")
+    assert len(oc) > 0
+    ix.close()
