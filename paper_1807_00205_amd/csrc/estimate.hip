@@ -13,11 +13,20 @@
 //
 // A run (consecutive passing candidates of one window and orientation) is
 // given by its first and last candidate; every candidate between them
-// belongs to it.  One wave takes one run: it sorts the query window's
-// hashes once, enumerates the run's candidates from the minimizer array,
-// computes m for each whose shared count could beat the best so far, and
-// emits the seed of the largest m (earliest j on ties) when m reaches the
-// threshold T[s].
+// belongs to it.  One wave takes one run and emits the seed of its largest m
+// (earliest j on ties) when m reaches the threshold T[s].
+//
+// First launch (windows and runs of up to 256 minimizers): the run's target
+// minimizers are classified against the sorted query hashes and sorted by
+// hash once, in registers.  In that order a candidate needs no sort of its
+// own: the distinct outside hashes of its window are the lanes whose
+// occurrence lies in it and whose previous occurrence does not (a compare and
+// a ballot), the number of them below a lane is the popcount of the ballot
+// below it, and y, the shared count and m are popcounts too.  Bound by the
+// instructions of the two sorts and of the steps: 5.9 ms for the 1.5 million
+// runs of the 50 Mbp workload, where a sort per candidate, shared ranks marked
+// in LDS and a global atomic per seed took 14.2.  A second launch takes the
+// runs that do not fit, with the window of each candidate sorted by itself.
 #include <algorithm>
 #include <cstdlib>
 
@@ -26,11 +35,12 @@
 namespace sdf {
 
 constexpr int EW = 3;         // runs (waves) per workgroup
-// A first launch holds windows of up to 256 minimizers and runs of up to 256
-// target minimizers in LDS (5.8 KB per wave, 27 waves per CU); a run that
-// does not fit is handed to a second launch with room for 1,024 and 512.
-constexpr int AMAX_S = 256, TCAP_S = 256;
-constexpr int AMAX_L = 1024, TCAP_L = 512;
+constexpr int FMAX = 256;     // minimizers of a window and of a run, first launch
+// Runs per wave of the first launch: their seeds leave with one atomic, since
+// the seed counter takes one about every 12 ns from all CUs together (one per
+// run: 14.2 ms for 1.2 million seeds, whatever the kernel did besides).
+constexpr uint32_t ERUNS = 32;
+constexpr int AMAX_L = 1024, TCAP_L = 512;  // second launch
 constexpr uint16_t TR_IN = 0x8000, TR_SHARED = 0x4000, TR_RANK = 0x3FF;
 
 template <int AMAX, int TC>
@@ -292,27 +302,23 @@ __device__ uint32_t estimate_lds(W &L, uint32_t s, uint32_t xs, uint32_t xe, boo
     return estimate_finish(L, out, L.u.run.first, s, nb, have, beat, reg_cap);  // nb <= W::tcap
 }
 
-// FIRST: run r = the wave's index; a run that does not fit (window above
-// amax_rt minimizers, or a target window with more outside hashes than the
-// wave holds) is appended to `over` instead.  Otherwise the runs are those
-// listed in `list`, and not fitting is an error.
-template <int AMAX, int TC, bool FIRST>
-__global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const uint32_t *runs,
+// The runs listed in `list`, with windows of up to 1,024 minimizers.
+__global__ void __launch_bounds__(EW * 64) k_estimate_long(IndexView ix, const uint32_t *runs,
                                                             uint64_t nruns, const uint32_t *list,
                                                             uint32_t n, const uint16_t *T,
                                                             uint32_t *seeds, uint64_t cap,
                                                             unsigned long long *nseeds,
                                                             uint32_t *err, uint32_t lds_cap,
-                                                            uint32_t reg_cap, uint32_t amax_rt,
-                                                            uint32_t *over,
-                                                            unsigned long long *nover) {
+                                                            uint32_t reg_cap) {
+    constexpr int AMAX = AMAX_L, TC = TCAP_L;
+    constexpr uint32_t amax_rt = AMAX_L;
     using Wave = EstWave<AMAX, TC>;
     __shared__ Wave W[EW];
     const uint32_t lane = e_lane(), wv = threadIdx.x >> 6;
     Wave &L = W[wv];
     const uint64_t slot = (uint64_t)blockIdx.x * EW + wv;
     if (slot >= nruns) return;  // whole wave; no workgroup barrier below
-    const uint64_t r = FIRST ? slot : list[slot];
+    const uint64_t r = list[slot];
     const uint64_t ltmask = lane ? (~0ull >> (64 - lane)) : 0ull;
     const uint32_t *rec = runs + r * 6;
     const uint32_t qid = rec[0], i = rec[1], jf = rec[2], o = rec[3], jl = rec[4], s = rec[5];
@@ -329,10 +335,6 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
         if (v && na + lane < AMAX) L.u.key[na + lane] = ((uint64_t)ix.mhash[m] << 32) | (na + lane);
         na += (uint32_t)__popcll(bv);
         if (bv != ~0ull || na > amax_rt) break;
-    }
-    if (FIRST && na > amax_rt) {  // the second launch takes it
-        if (lane == 0) over[atomicAdd(nover, 1ull)] = (uint32_t)r;
-        return;
     }
     if (na > amax_rt || s == 0 || s > na) {
         if (lane == 0) atomicOr(err, na > amax_rt ? 1u : 2u);
@@ -454,10 +456,7 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
             const uint32_t m =
                 estimate_at(ix, L, s, o, base + l, (uint64_t)j + n - k, have, best_m, reg_cap, q0, na);
             if (m == NONE32) {
-                if (lane == 0) {
-                    if (FIRST) over[atomicAdd(nover, 1ull)] = (uint32_t)r;
-                    else atomicOr(err, 1u);
-                }
+                if (lane == 0) atomicOr(err, 1u);
                 return;
             }
             if (!have || m > best_m) {
@@ -477,6 +476,274 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
     }
 }
 
+// ------------------------------------------------------- first launch --
+// Ascending bitonic sort of 64 E keys in registers, element e * 64 + lane.
+template <class K, int E>
+__device__ __forceinline__ void wave_sort_keys(K (&x)[E], uint32_t lane) {
+#pragma unroll
+    for (uint32_t k = 2; k <= 64u * E; k <<= 1) {
+#pragma unroll
+        for (uint32_t j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                if (j >= 64) {  // between registers: each pair once
+                    const int f = e ^ (int)(j >> 6);
+                    if (f < e) continue;
+                    const bool up = ((uint32_t)(e * 64) & k) == 0;
+                    const K lo = x[e] < x[f] ? x[e] : x[f], hi = x[e] < x[f] ? x[f] : x[e];
+                    x[e] = up ? lo : hi;
+                    x[f] = up ? hi : lo;
+                } else {
+                    K y;
+                    if constexpr (sizeof(K) == 8)
+                        y = ((K)lane_xor((uint32_t)(x[e] >> 32), j) << 32) | lane_xor((uint32_t)x[e], j);
+                    else
+                        y = lane_xor(x[e], j);
+                    const bool up = (((uint32_t)(e * 64) | (lane & 63)) & k) == 0;
+                    const bool lower = (lane & j) == 0;
+                    const K lo = x[e] < y ? x[e] : y, hi = x[e] < y ? y : x[e];
+                    x[e] = lower == up ? lo : hi;
+                }
+            }
+        }
+    }
+}
+
+struct EstFirst {
+    uint32_t ahash[FMAX];  // distinct query hashes, ascending (W_i)
+    uint32_t acnt[FMAX];   // eligible occurrences per hash: strand 0 low 16 bits, strand 1 high
+    uint32_t tp[FMAX];     // the run's target minimizers: position,
+    uint16_t tr[FMAX];     // TR_* and rank, or the hashes of W_i below it when outside
+    uint64_t sorted[FMAX]; // their keys in order
+    uint32_t seeds[ERUNS * 6];
+};
+
+// Query hashes of a window in order: distinct ones and their eligible
+// occurrences; the number of distinct ones.  Keys are hash << 8 | index of
+// the minimizer in the window.
+template <class K, int E>
+__device__ __forceinline__ uint32_t sort_query(const IndexView &ix, EstFirst &L, uint64_t q0,
+                                               uint32_t na, uint32_t lane) {
+    K x[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint32_t t = e * 64 + lane;
+        x[e] = t < na ? ((K)ix.mhash[q0 + t] << 8) | t : (K)~(K)0;
+    }
+    wave_sort_keys<K, E>(x, lane);
+    for (uint32_t t = lane; t < na; t += 64) L.acnt[t] = 0;
+    __builtin_amdgcn_wave_barrier();
+    const uint64_t le = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1;
+    uint32_t nd = 0;
+    K before = 0;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        K p = x[e];
+        if constexpr (sizeof(K) == 8)
+            p = ((K)(uint32_t)__shfl_up((int)(uint32_t)(x[e] >> 32), 1, 64) << 32) |
+                (uint32_t)__shfl_up((int)(uint32_t)x[e], 1, 64);
+        else
+            p = (K)__shfl_up((int)x[e], 1, 64);
+        if (lane == 0) p = before;
+        const uint32_t t = e * 64 + lane;
+        const bool first = t < na && (t == 0 || (p >> 8) != (x[e] >> 8));
+        const uint64_t fm = __ballot(first);
+        const uint32_t rk = nd + (uint32_t)__popcll(fm & le) - 1;
+        if (t < na) {
+            if (first) L.ahash[rk] = (uint32_t)(x[e] >> 8);
+            const uint8_t fl = ix.mflags[q0 + (uint32_t)(x[e] & 255)];
+            if (fl & 2) atomicAdd(&L.acnt[rk], (fl & 1) ? 0x10000u : 1u);
+        }
+        nd += (uint32_t)__popcll(fm);
+        if constexpr (sizeof(K) == 8)
+            before = ((K)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x[e] >> 32), 63) << 32) |
+                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x[e], 63);
+        else
+            before = (K)__builtin_amdgcn_readlane((int)x[e], 63);
+    }
+    __builtin_amdgcn_wave_barrier();
+    return nd;
+}
+
+// The candidate of the largest m among the run's nt <= 64 E target minimizers
+// [t0, t0 + nt), whose positions are in tp: best_m, best_j; false: none.
+template <class K, int E>
+__device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L, uint64_t t0,
+                                               uint32_t nt, uint64_t q0, uint32_t na, uint32_t s,
+                                               uint32_t o, uint32_t n, uint32_t jl, uint32_t lane,
+                                               uint32_t &best_m, uint32_t &best_j) {
+    const uint32_t k = ix.k;
+    K x[E];
+    uint64_t cand[E];
+    uint32_t wend[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint32_t t = e * 64 + lane;
+        x[e] = (K)~(K)0;
+        wend[e] = 0;
+        bool c = false;
+        if (t < nt) {
+            const uint32_t h = ix.mhash[t0 + t], pos = L.tp[t];
+            const uint8_t fl = ix.mflags[t0 + t];
+            const uint32_t rk = rank_below(L.ahash, s, h);
+            uint32_t tr = rk;
+            if (rk < s && L.ahash[rk] == h) {
+                tr |= TR_IN;
+                if ((fl & 2) && pairs(L, rk, fl & 1, o, t0 + t, q0, na)) tr |= TR_SHARED;
+            }
+            L.tr[t] = (uint16_t)tr;
+            x[e] = ((K)h << 8) | t;
+            c = pos <= jl && (tr & TR_SHARED) && window_ok(ix, pos, n, nullptr);
+            if (c) {  // the end of its window's minimizers
+                uint32_t lo = t, hi = nt;
+                const uint64_t lim = (uint64_t)pos + n - k;
+                while (lo < hi) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if ((uint64_t)L.tp[mid] <= lim) lo = mid + 1; else hi = mid;
+                }
+                wend[e] = lo;
+            }
+        }
+        cand[e] = __ballot(c);
+    }
+    wave_sort_keys<K, E>(x, lane);
+#pragma unroll
+    for (int e = 0; e < E; e++) L.sorted[e * 64 + lane] = x[e];
+    __builtin_amdgcn_wave_barrier();
+    // each occurrence, in hash order: its place t in the run, the place of the
+    // occurrence before it + 1 (of the shared one before it, if it is shared;
+    // FMAX: it never counts), and its rank among the query hashes
+    uint32_t at[E], prev[E], rank[E];
+    uint64_t outside[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint32_t y = e * 64 + lane;
+        const bool v = y < nt;
+        const uint32_t t = v ? (uint32_t)(x[e] & 255) : 0u;
+        const uint32_t tr = v ? L.tr[t] : (uint32_t)TR_IN;
+        uint32_t pv = 0;
+        if (v) {
+            for (uint32_t z = y; z > 0; z--) {
+                const K b = (K)L.sorted[z - 1];
+                if ((b >> 8) != (x[e] >> 8)) break;
+                const uint32_t tb = (uint32_t)(b & 255);
+                if (!(tr & TR_SHARED) || (L.tr[tb] & TR_SHARED)) {
+                    pv = tb + 1;
+                    break;
+                }
+            }
+        }
+        at[e] = t;
+        prev[e] = (tr & TR_IN) && !(tr & TR_SHARED) ? (uint32_t)FMAX : pv;
+        rank[e] = tr & TR_RANK;
+        outside[e] = __ballot(!(tr & TR_IN));
+    }
+    bool have = false;
+#pragma unroll
+    for (int ec = 0; ec < E; ec++) {
+        uint64_t cm = cand[ec];
+        while (cm) {
+            const uint32_t l = (uint32_t)__ffsll((long long)cm) - 1;
+            cm &= cm - 1;
+            const uint32_t xs = ec * 64 + l, len = (uint32_t)__builtin_amdgcn_readlane((int)wend[ec], (int)l) - xs;
+            uint64_t live[E];
+            uint32_t c = 0;
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                live[e] = __builtin_amdgcn_ballot_w64((at[e] - xs < len) & (prev[e] <= xs));
+                c += (uint32_t)__popcll(live[e] & ~outside[e]);
+            }
+            // (m <= c, and ties go to the earlier candidate)
+            if (have && c <= best_m) continue;
+            uint32_t y = 0, below = 0;
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                const uint64_t ob = live[e] & outside[e];
+                const uint32_t d = __builtin_amdgcn_mbcnt_hi(
+                    (uint32_t)(ob >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)ob, below));
+                y += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(d + rank[e] < s) & ob);
+                below += (uint32_t)__popcll(ob);
+            }
+            uint32_t m = 0;
+#pragma unroll
+            for (int e = 0; e < E; e++)
+                m += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(rank[e] < s - y) & live[e] & ~outside[e]);
+            if (!have || m > best_m) {
+                best_m = m;
+                best_j = L.tp[xs];
+                have = true;
+            }
+        }
+    }
+    return have;
+}
+
+template <class K>
+__global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const uint32_t *runs,
+                                                            uint64_t nruns, uint32_t n,
+                                                            const uint16_t *T, uint32_t *seeds,
+                                                            uint64_t cap, unsigned long long *nseeds,
+                                                            uint32_t *err, uint32_t amax,
+                                                            uint32_t tmax, uint32_t *over,
+                                                            unsigned long long *nover) {
+    __shared__ EstFirst W[EW];
+    const uint32_t lane = e_lane(), wv = threadIdx.x >> 6;
+    EstFirst &L = W[wv];
+    const uint32_t k = ix.k;
+    const uint64_t r0 = ((uint64_t)blockIdx.x * EW + wv) * ERUNS;  // (no workgroup barrier below)
+    const uint64_t r1 = min(r0 + ERUNS, nruns);
+    uint32_t nbuf = 0;
+    // minimizers [first, first + count) at positions [from, to]; above `most`: most + 1
+    auto count = [&](uint64_t first, uint64_t to, uint32_t most, uint32_t *pos) {
+        uint32_t c = 0;
+        while (c <= most) {
+            const uint64_t m = first + c + lane;
+            const uint32_t p = m < ix.nm ? ix.mpos[m] : 0xFFFFFFFFu;
+            const bool v = m < ix.nm && (uint64_t)p <= to;
+            if (pos && v && c + lane < FMAX) pos[c + lane] = p;
+            const uint64_t bv = __ballot(v);  // a prefix of the lanes
+            c += (uint32_t)__popcll(bv);
+            if (bv != ~0ull) return c;
+        }
+        return most + 1;
+    };
+    for (uint64_t r = r0; r < r1; r++) {
+        const uint32_t *rec = runs + r * 6;
+        const uint32_t qid = rec[0], i = rec[1], jf = rec[2], o = rec[3], jl = rec[4], s = rec[5];
+        const uint64_t q0 = wave_lower_bound(ix.mpos, ix.nm, i);
+        const uint32_t na = count(q0, (uint64_t)i + n - k, amax, nullptr);
+        const uint64_t t0 = wave_lower_bound(ix.mpos, ix.nm, jf);
+        const uint32_t nt = na > amax ? 0u : count(t0, (uint64_t)jl + n - k, tmax, L.tp);
+        if (na > amax || nt > tmax) {  // the second launch takes it
+            if (lane == 0) over[atomicAdd(nover, 1ull)] = (uint32_t)r;
+            continue;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t nd = na <= 128 ? sort_query<K, 2>(ix, L, q0, na, lane)
+                                      : sort_query<K, 4>(ix, L, q0, na, lane);
+        if (nd != s || s == 0) {
+            if (lane == 0) atomicOr(err, 2u);
+            continue;
+        }
+        uint32_t best_m = 0, best_j = 0;
+        const bool have = nt <= 128 ? best_candidate<K, 2>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_j)
+                                    : best_candidate<K, 4>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_j);
+        if (have && best_m >= T[s]) {
+            if (lane < 6)
+                L.seeds[nbuf * 6 + lane] =
+                    lane == 0 ? qid : lane == 1 ? i : lane == 2 ? best_j : lane == 3 ? o : lane == 4 ? best_m : s;
+            nbuf++;
+        }
+    }
+    if (nbuf == 0) return;
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(nseeds, (unsigned long long)nbuf);
+    at = __shfl(at, 0, 64);
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t t = lane; t < nbuf * 6; t += 64)
+        if (at + t / 6 < cap) seeds[at * 6 + t] = L.seeds[t];
+}
+
 void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nruns, uint32_t n,
                           const uint16_t *T, uint32_t *seeds, uint64_t cap,
                           unsigned long long *nseeds, uint32_t *err, hipStream_t st) {
@@ -487,13 +754,16 @@ void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nr
     const sdf_tuning &tu = tuning();
     const uint32_t lds_cap = std::min<uint32_t>(TCAP_L, knob(tu.est_lds_cap, TCAP_L));
     const uint32_t reg_cap = std::min<uint32_t>(128, knob(tu.est_reg_cap, 128));
-    const uint32_t amax_s = std::min<uint32_t>(AMAX_S, knob(tu.est_first_amax, AMAX_S));
+    const uint32_t amax = std::min<uint32_t>(FMAX, knob(tu.est_first_amax, FMAX));
+    const uint32_t tmax = std::min<uint32_t>(FMAX, lds_cap);
     DevBuf<uint32_t> over(nruns);
     DevBuf<unsigned long long> nover(1);
     SDF_HIP(hipMemsetAsync(nover.p, 0, 8, st));
-    k_estimate_runs<AMAX_S, TCAP_S, true><<<(unsigned)((nruns + EW - 1) / EW), EW * 64, 0, st>>>(
-        ix, runs, nruns, nullptr, n, T, seeds, cap, nseeds, err, std::min<uint32_t>(lds_cap, TCAP_S),
-        reg_cap, amax_s, over.p, nover.p);
+    // hash and index in 32 bits while the hash has at most 24 (k <= 12): half the
+    // instructions per exchange of a sort
+    const auto first = 2 * ix.k <= 24 ? k_estimate_runs<uint32_t> : k_estimate_runs<uint64_t>;
+    first<<<(unsigned)((nruns + EW * ERUNS - 1) / (EW * ERUNS)), EW * 64, 0, st>>>(
+        ix, runs, nruns, n, T, seeds, cap, nseeds, err, amax, tmax, over.p, nover.p);
     SDF_HIP(hipGetLastError());
     unsigned long long no = 0;
     {
@@ -502,9 +772,8 @@ void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nr
         rb.wait();
     }
     if (no == 0) return;
-    k_estimate_runs<AMAX_L, TCAP_L, false><<<(unsigned)((no + EW - 1) / EW), EW * 64, 0, st>>>(
-        ix, runs, no, over.p, n, T, seeds, cap, nseeds, err, lds_cap, reg_cap, AMAX_L, nullptr,
-        nullptr);
+    k_estimate_long<<<(unsigned)((no + EW - 1) / EW), EW * 64, 0, st>>>(
+        ix, runs, no, over.p, n, T, seeds, cap, nseeds, err, lds_cap, reg_cap);
     SDF_HIP(hipGetLastError());
     SDF_HIP(hipStreamSynchronize(st));  // `over` is released on return
 }
