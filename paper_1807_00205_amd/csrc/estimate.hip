@@ -183,8 +183,10 @@ __device__ uint32_t estimate_finish(W &L, const uint32_t *out, uint8_t *first, u
         }
         // padding (all ones) sorts last, so elements [0, nb) are the values
         const uint32_t p0 = (uint32_t)__shfl_up((int)x0, 1, 64);
-        const uint32_t p1 = lane ? (uint32_t)__shfl_up((int)x1, 1, 64)
-                                 : (uint32_t)__builtin_amdgcn_readlane((int)x0, 63);
+        // (shifted by all lanes: a shift by the lanes past the first alone finds
+        // nothing in the first)
+        const uint32_t s1 = (uint32_t)__shfl_up((int)x1, 1, 64);
+        const uint32_t p1 = lane ? s1 : (uint32_t)__builtin_amdgcn_readlane((int)x0, 63);
         const bool f0 = lane < nb && (lane == 0 || p0 != x0);
         const bool f1 = lane + 64 < nb && p1 != x1;
         const uint64_t fm0 = __ballot(f0), fm1 = __ballot(f1);

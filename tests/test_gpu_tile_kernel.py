@@ -47,3 +47,27 @@ def test_tile_kernel_branches(oracle_lib, k, w, min_len, hits_per_part, threads)
     _same(r.candidates(), oc, CAND_F, "candidates")
     assert len(oc) > 0
     ix.close()
+
+
+# windows of up to 128, 256 and more minimizers (sorts of two and four keys per
+# lane, the second launch), keys of 32 and 64 bits (k <= 12, above), and runs
+# that repeat hashes
+@pytest.mark.parametrize("k,w,min_len", [(12, 16, 900), (12, 16, 1400), (12, 16, 2000),
+                                         (12, 10, 1400), (13, 16, 900), (14, 9, 1200),
+                                         (12, 16, 3100), (11, 4, 700)])
+def test_estimate_windows(oracle_lib, k, w, min_len):
+    from paper_1807_00205_amd import sdf
+    g = synth.tandem_case(2000 + 31 * k + w + min_len, length=26_000, n_arrays=10, copies_hi=12,
+                          n_seqs=2, n_sd=4)
+    src = g.seqs[0][2_000:2_000 + 2 * min_len]
+    g.seqs[1][9_000:9_000 + len(src)] = src
+    g.seqs[0][15_000:15_000 + len(src)] = synth.revcomp(src)
+    b, off = g.concat()
+    ix = sdf.Index(g.seqs, k, w)
+    orc = oracle_lib.OracleIndex(b, off, k, w)
+    os_, oc = orc.search(g.spans, 0.25, min_len, estimate=True)
+    r = ix.search_batch(g.spans, 0.25, min_len, estimate=True)
+    _same(r.seeds(), os_, SEED_F, "seeds")
+    _same(r.candidates(), oc, CAND_F, "candidates")
+    assert len(oc) > 0
+    ix.close()
