@@ -18,23 +18,31 @@
 //  1. the minimizers of both start windows and of every position a phase can
 //     reach within a horizon H are gathered (six contiguous ranges of the
 //     position-sorted minimizer array) and ranked by hash: bucketed on the
-//     top 11 hash bits, each run of buckets sorted in LDS (bitonic), equal
-//     hashes sharing a rank, so L becomes an array of 4-bit cells by rank;
+//     top 11 hash bits, each run of buckets sorted by one wave in registers,
+//     equal hashes sharing a rank, so L becomes an array of 4-bit cells by rank;
 //  2. the start windows' minimizers are set, and s, the rank v of the s-th
 //     smallest element of L, and m are counted in parallel;
-//  3. one wave walks the minimizers that enter, in step order, keeping s, v
-//     and m up to date per insertion (v moves at most one element of L, to
-//     its successor or predecessor), and checks m >= ceil(tau s) after each
-//     step; a refused step is undone.  Steps at which no minimizer enters
-//     keep the previous state and its outcome.  While the slack m - ceil(tau
-//     s) is at least three per insertion, a run of insertions cannot contain
-//     a refused step and is applied as one batch (cells set in parallel, v
-//     moved by the count of new elements below and above it).
+//  3. the minimizers that enter are taken in step order, s, v and m kept up to
+//     date (an insertion moves v at most one element of L, to its successor or
+//     predecessor) and m >= ceil(tau s) checked after each step; steps at which
+//     no minimizer enters keep the previous state and its outcome.  Up to 256
+//     minimizers per side are tried at once: the state after each step follows
+//     from prefix sums over them and from the elements of L next to v, so all
+//     their steps are checked together, and they are inserted up to the first
+//     step refused.
 // The horizon of one attempt is max(h0, longer side) steps per phase.  A
 // phase that runs through it stops at its last step; the next attempt
 // gathers and ranks again around the region reached and continues the same
 // phase from there (the state is a function of the region, so nothing is
 // repeated).
+//
+// Bound by the slowest region, whose entering minimizers form one chain
+// (430 kbp a side on the 50 Mbp workload, about 200,000 of them: chance
+// matches hold a large region's estimate just above the threshold, so nearly
+// every step has to be checked) and whose ranks are sorted again by every
+// attempt.  9,157 regions of that workload: 30 ms with one wave trying 128
+// events under a slack bound and the ranks sorted in LDS by the workgroup (its
+// slowest region 29 ms), 12.3 ms now (8 ms).
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -57,12 +65,19 @@ static_assert(XT == 256, "k_extend is only validated with 256-thread workgroups"
 constexpr uint32_t NB_BITS = 11;
 constexpr uint32_t NB = 1u << NB_BITS;  // buckets over the top hash bits
 constexpr uint32_t CH = 2048;           // keys sorted at once in LDS
-constexpr uint32_t HALF = CH / 2;
+// A chunk of several buckets holds at most 512 keys; buckets at the low end of
+// the hashes (minimizers crowd there) up to 1,024 are a wave's too.
+constexpr uint32_t HALF = 256;
+constexpr int XW = XT / 64;
+constexpr int UN = 8;                   // elements per thread and round while gathering
+constexpr uint64_t HB_DIV = 4;          // backward horizon: at least a quarter of the longer side
+constexpr uint32_t TAGS = 2048;         // tags of a batch's events
 constexpr uint32_t LDS_WORDS = NB + 1 + (NB + 2) / 2 + 2 * CH + 1;  // the sort area, as words
 constexpr uint64_t INF = 1ull << 62;
 
 enum { C_Q0 = 1, C_Q1 = 2, C_T0 = 4, C_T1 = 8 };
 enum { STOP_BOUND = 1, STOP_CAP = 2, STOP_OVERLAP = 3, STOP_ESTIMATE = 4 };
+constexpr uint32_t RANK_REP = 1u << 31;
 enum { XE_CAP = 1, XE_HASH = 2, XE_STATE = 4 };
 
 struct ExtArgs {
@@ -93,27 +108,45 @@ struct Shared {
         struct {
             uint32_t bs[NB + 1];    // bucket starts
             uint16_t cl[NB + 2];    // first bucket of each chunk
-            uint64_t ck[CH];        // one chunk of keys being sorted
+            uint64_t ck[CH];        // cursors; the hash set of a large bucket
         };
         uint32_t w[LDS_WORDS];      // afterwards: the cells of L
     };
-    uint32_t red[XT];
+    uint32_t red[2 * XW];
+    uint32_t estep[2][XT];      // held events of both sides: step (NONE32 past the last),
+    uint32_t ecell[2][XT];      // rank << 4 | cell bit,
+    uint32_t epre[2][XT];       // inclusive prefix sums of what they change
+    uint32_t wsum[2][XW];
+    uint16_t tag[TAGS];         // event named for each slot of ranks
+    uint32_t near[2][64];       // elements of L above v, and from v down: rank << 1 | shared
+    uint32_t nn[2];
+    int32_t nr[2];              // ranks that near[] describes completely: nr[1] .. nr[0]
+    uint64_t nsh[2];            // bit i: near[][i] is shared
+    uint32_t dark, refused;     // first step of a batch not told, refused
+    uint64_t uq, ut, last;      // events consumed per side, steps taken
+    uint32_t ok, code, nq, nt;
     uint64_t mlo[6], mhi[6];
     uint32_t base[7];
     uint32_t region;
-    uint32_t nrank, nchunk, cnt;
-    uint64_t rr[4];
-    uint32_t codes[2];
+    uint32_t nchunk, cnt;
     int32_t v;
     uint32_t s, m;
     uint32_t flag;
 };
 
-__device__ __forceinline__ uint64_t lower_pos(const IndexView &ix, uint64_t x) {
-    uint64_t lo = 0, hi = ix.nm;  // first minimizer with pos >= x
-    while (lo < hi) {
-        const uint64_t mid = (lo + hi) >> 1;
-        if ((uint64_t)ix.mpos[mid] < x) lo = mid + 1; else hi = mid;
+// First minimizer with pos >= x, searched by 16 neighbouring lanes with the
+// same x: 16 probes per round.  Every lane of the wave takes part.
+__device__ __forceinline__ uint64_t lower_pos16(const IndexView &ix, uint64_t x) {
+    const uint32_t lane = threadIdx.x & 63, sub = lane & 15, sh = lane & 48;
+    uint64_t lo = 0, hi = ix.nm;  // the answer lies in [lo, hi]
+    while (__ballot(hi > lo)) {
+        const uint64_t step = (hi - lo + 15) / 16;
+        const uint64_t pr = lo + sub * step;
+        const bool below = pr < hi && (uint64_t)ix.mpos[pr] < x;  // a prefix of the 16
+        const uint32_t c = (uint32_t)__popcll((__ballot(below) >> sh) & 0xFFFFull);
+        const uint64_t nhi = min(hi, lo + (uint64_t)c * step);
+        lo = c ? lo + (uint64_t)(c - 1) * step + 1 : lo;
+        hi = c ? nhi : lo;
     }
     return lo;
 }
@@ -136,26 +169,29 @@ __device__ __forceinline__ bool cell_shared(uint32_t c, uint32_t o) {
     return shared_mask(c, o) != 0;
 }
 
-// Exclusive block scan of one value per thread; returns the total.
-__device__ uint32_t block_scan(Shared &L, uint32_t v, uint32_t &excl) {
-    const int t = threadIdx.x;
-    L.red[t] = v;
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v);
+
+// Exclusive block scan of one value per thread; returns the total.  One
+// barrier: two sets of wave totals take turns.
+__device__ __forceinline__ uint32_t block_scan(Shared &L, uint32_t v, uint32_t &excl, uint32_t &turn) {
+    const uint32_t incl = wave_incl_sum(v), w = threadIdx.x >> 6;
+    uint32_t *red = L.red + turn * XW;
+    turn ^= 1;
+    if ((threadIdx.x & 63) == 63) red[w] = incl;
     __syncthreads();
-    for (int d = 1; d < XT; d <<= 1) {
-        const uint32_t a = t >= d ? L.red[t - d] : 0;
-        __syncthreads();
-        L.red[t] += a;
-        __syncthreads();
+    uint32_t before = 0, tot = 0;
+#pragma unroll
+    for (uint32_t t = 0; t < (uint32_t)XW; t++) {
+        if (t < w) before += red[t];
+        tot += red[t];
     }
-    excl = L.red[t] - v;
-    const uint32_t tot = L.red[XT - 1];
-    __syncthreads();
+    excl = before + incl - v;
     return tot;
 }
 
-__device__ uint32_t block_sum(Shared &L, uint32_t v) {
+__device__ __forceinline__ uint32_t block_sum(Shared &L, uint32_t v, uint32_t &turn) {
     uint32_t e;
-    return block_scan(L, v, e);
+    return block_scan(L, v, e, turn);
 }
 
 // Region geometry of one phase: which ends grow.
@@ -340,284 +376,85 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return __builtin_amdgcn_readlane(wave_incl_sum(v), 63);
 }
 
-// The k-th element of L above rank v (k >= 1), and in `sh` the number of
-// shared elements in (v, that rank].  64 cell words per step.
-__device__ __forceinline__ int32_t kth_succ(const uint32_t *nib, uint32_t nw, int32_t v, uint32_t k,
-                                            uint32_t o, uint32_t &sh) {
+// The value of lane ^ j (a constant power of two).
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v, uint32_t j) {
+    switch (j) {
+    case 1: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false);
+    case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false);
+    case 4: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (4 << 10) | 0x1F);
+    case 8: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (8 << 10) | 0x1F);
+    case 16: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (16 << 10) | 0x1F);
+    default: return (uint32_t)__shfl_xor((int)v, (int)j, 64);
+    }
+}
+
+// Keys [b, e) of src (whole buckets, so no hash continues outside, and at most
+// 64 N): one wave sorts them in registers (bitonic, key t * 64 + lane in x[t])
+// and gives every element its rank, equal hashes sharing one.  Ranks of the
+// chunk start at b: they have gaps where hashes repeat, but keep the order.
+// RANK_REP marks the elements of a hash that occurs more than once.  Sorted
+// are the hash, less the chunk's first (hbase), over ten bits of index: in 32
+// bits where the chunk's hashes allow, half the instructions per exchange.
+template <int N, class K>
+__device__ __forceinline__ void rank_chunk(const uint64_t *src, uint32_t b, uint32_t e, uint32_t hbase,
+                                           uint32_t *rank) {
     const uint32_t lane = threadIdx.x & 63;
-    const int32_t r = v + 1;
-    sh = 0;
-    if ((uint32_t)r >= nw * 8) return -2;
-    const uint32_t w0 = (uint32_t)r >> 3;
-    const uint32_t first_mask = 0xFFFFFFFFu << ((r & 7) * 4);
-    for (uint32_t base = w0; base < nw; base += 64) {
-        const uint32_t w = base + lane;
-        uint32_t word = w < nw ? nib[w] : 0u;
-        if (w == w0) word &= first_mask;
-        const uint32_t u = nz_mask(word);
-        const uint32_t c = __popc(u);
-        const uint32_t incl = wave_incl_sum(c);
-        const uint32_t tot = __builtin_amdgcn_readlane(incl, 63);
-        const uint32_t sm = shared_mask(word, o);
-        if (tot >= k) {
-            const uint32_t l = (uint32_t)__builtin_ctzll(__ballot(incl >= k));
-            const uint32_t before = __builtin_amdgcn_readlane(incl - c, l);
-            uint32_t ul = __builtin_amdgcn_readlane(u, l);
-            for (uint32_t need = k - before; need > 1; need--) ul &= ul - 1;
-            const uint32_t ni = (uint32_t)__builtin_ctz(ul) >> 2;
-            const uint32_t keep = ni == 7 ? 0xFFFFFFFFu : ((1u << ((ni + 1) * 4)) - 1u);
-            const uint32_t mine = lane < l ? sm : (lane == l ? (sm & keep) : 0u);
-            sh += wave_sum(__popc(mine));
-            return (int32_t)((base + l) * 8 + ni);
-        }
-        k -= tot;
-        sh += wave_sum(__popc(sm));
+    K x[N];
+#pragma unroll
+    for (int t = 0; t < N; t++) {
+        const uint32_t i = t * 64 + lane;
+        x[t] = b + i < e ? ((K)((uint32_t)(src[b + i] >> 32) - hbase) << 10) | i : (K)~(K)0;
     }
-    return -2;
-}
-
-// The k-th element of L below rank v (k >= 1), and in `sh` the number of
-// shared elements strictly between it and v.  64 cell words per step.
-__device__ __forceinline__ int32_t kth_pred(const uint32_t *nib, int32_t v, uint32_t k, uint32_t o,
-                                            uint32_t &sh) {
-    const uint32_t lane = threadIdx.x & 63;
-    const int32_t r = v - 1;
-    sh = 0;
-    if (r < 0) return -2;
-    const int32_t w0 = r >> 3;
-    const uint32_t first_mask = (r & 7) == 7 ? 0xFFFFFFFFu : ((1u << (((r & 7) + 1) * 4)) - 1u);
-    for (int32_t top = w0; top >= 0; top -= 64) {
-        const int32_t w = top - (int32_t)lane;
-        uint32_t word = w >= 0 ? nib[w] : 0u;
-        if (w == w0) word &= first_mask;
-        const uint32_t u = nz_mask(word);
-        const uint32_t c = __popc(u);
-        const uint32_t incl = wave_incl_sum(c);
-        const uint32_t tot = __builtin_amdgcn_readlane(incl, 63);
-        const uint32_t sm = shared_mask(word, o);
-        if (tot >= k) {
-            const uint32_t l = (uint32_t)__builtin_ctzll(__ballot(incl >= k));
-            const uint32_t before = __builtin_amdgcn_readlane(incl - c, l);
-            uint32_t ul = __builtin_amdgcn_readlane(u, l);
-            for (uint32_t need = k - before; need > 1; need--)
-                ul &= ~(1u << (31 - __builtin_clz(ul)));
-            const uint32_t ni = (31u - (uint32_t)__builtin_clz(ul)) >> 2;
-            const uint32_t above = ni == 7 ? 0u : ~((1u << ((ni + 1) * 4)) - 1u);
-            const uint32_t mine = lane < l ? sm : (lane == l ? (sm & above) : 0u);
-            sh += wave_sum(__popc(mine));
-            return (top - (int32_t)l) * 8 + (int32_t)ni;
-        }
-        k -= tot;
-        sh += wave_sum(__popc(sm));
-    }
-    return -2;
-}
-
-struct EvCursor {
-    uint64_t next;     // events consumed
-    uint64_t count;
-    uint32_t fill;     // events held in registers (lane-indexed)
-    uint32_t at;       // next held event
-    uint32_t vstep;    // this lane's held event: its step (at most max_len), rank, cell bit
-    uint32_t vrank, vbit;
-};
-
-__device__ __forceinline__ void ev_refill(const ExtArgs &a, const uint32_t *rank, const EvList &l,
-                                          EvCursor &c) {
-    const uint32_t lane = threadIdx.x & 63;
-    const uint64_t e = c.next + lane;
-    c.fill = (uint32_t)std::min<uint64_t>(64, c.count - c.next);
-    c.at = 0;
-    c.vstep = 0xFFFFFFFFu;
-    if (e < c.count) {
-        const uint64_t mi = l.up ? l.lo + e : l.hi - 1 - e;
-        const uint64_t pos = a.ix.mpos[mi];
-        c.vstep = (uint32_t)(l.up ? pos + a.ix.k - l.ref : l.ref - pos);
-        c.vrank = rank[l.base + (uint32_t)(mi - l.lo)];
-        c.vbit = l.side << (a.ix.mflags[mi] & 1);
-    }
-}
-
-__device__ __forceinline__ uint64_t ev_head(const EvCursor &c) {
-    if (c.at >= c.fill) return INF;
-    return __builtin_amdgcn_readlane(c.vstep, c.at);
-}
-
-// Several steps at once: the held events [at, at + nq) of the query list
-// and [at, at + nt) of the target list are inserted together.  The caller
-// has checked that no step among them can fail (each insertion lowers m by
-// at most 1 and raises ceil(tau s) by at most 1, and the slack m -
-// ceil(tau s) is at least three per insertion), so only the state after
-// the last one matters, and it does not depend on their order: s grows by
-// the hashes new to the query side, v moves to the s-th element of the new
-// L (k elements up or down), and m follows the shared elements passed and
-// those that became shared at or below the old v.
-__device__ __forceinline__ bool apply_batch(uint32_t *nib, uint32_t nw, const EvCursor &cq,
-                                            uint32_t nq, const EvCursor &ct, uint32_t nt,
-                                            uint32_t o, Est &e) {
-    const uint32_t lane = threadIdx.x & 63;
-    const bool hq = lane >= cq.at && lane < cq.at + nq;
-    const bool ht = lane >= ct.at && lane < ct.at + nt;
-    const uint32_t rq = cq.vrank, rt = ct.vrank;
-    const uint32_t oq = hq ? cell_at(nib, (int32_t)rq) : 0u;
-    const uint32_t ot = ht ? cell_at(nib, (int32_t)rt) : 0u;
-    __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // reads before writes
-    if (hq) atomicOr(&nib[rq >> 3], cq.vbit << ((rq & 7) * 4));
-    if (ht) atomicOr(&nib[rt >> 3], ct.vbit << ((rt & 7) * 4));
-    __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // writes before reads
-    const uint32_t cq1 = hq ? cell_at(nib, (int32_t)rq) : 0u;
-    const uint32_t ct1 = ht ? cell_at(nib, (int32_t)rt) : 0u;
-    // count each rank once: query events by lane, then target events by lane
-    bool fq = hq, ft = ht;
-    for (uint32_t j = cq.at; j < cq.at + nq; j++) {
-        const uint32_t rj = __builtin_amdgcn_readlane(rq, j);
-        if (j < lane && rj == rq) fq = false;
-        if (rj == rt) ft = false;
-    }
-    for (uint32_t j = ct.at; j < ct.at + nt; j++) {
-        const uint32_t rj = __builtin_amdgcn_readlane(rt, j);
-        if (j < lane && rj == rt) ft = false;
-    }
-    const int32_t v = e.v;
-    auto tally = [&](bool f, uint32_t r, uint32_t c0, uint32_t c1, bool &ds, bool &nb, bool &gb) {
-        ds = f && !(c0 & 3u) && (c1 & 3u);
-        nb = f && c0 == 0 && (int32_t)r < v;
-        gb = f && (int32_t)r <= v && !cell_shared(c0, o) && cell_shared(c1, o);
-    };
-    bool dsq, nbq, gbq, dst, nbt, gbt;
-    tally(fq, rq, oq, cq1, dsq, nbq, gbq);
-    tally(ft, rt, ot, ct1, dst, nbt, gbt);
-    const uint32_t dS = (uint32_t)(__popcll(__ballot(dsq)) + __popcll(__ballot(dst)));
-    const uint32_t nB = (uint32_t)(__popcll(__ballot(nbq)) + __popcll(__ballot(nbt)));
-    const uint32_t gB = (uint32_t)(__popcll(__ballot(gbq)) + __popcll(__ballot(gbt)));
-    const int32_t diff = (int32_t)dS - (int32_t)nB;
-    int32_t vn = v;
-    int64_t m = (int64_t)e.m + gB;
-    if (diff > 0) {
-        uint32_t sh;
-        vn = kth_succ(nib, nw, v, (uint32_t)diff, o, sh);
-        m += sh;
-    } else if (diff < 0) {
-        uint32_t sh;
-        vn = kth_pred(nib, v, (uint32_t)(-diff), o, sh);
-        m -= (int64_t)sh + (cell_shared(cell_at(nib, v), o) ? 1 : 0);
-    }
-    if (vn < 0 || m < 0) return false;
-    e.v = vn;
-    e.s += dS;
-    e.m = (uint32_t)m;
-    return true;
-}
-
-// One phase on wave 0.  Returns the steps taken; `code` is the stop code,
-// or 0 when the events ran out before the phase could stop (larger horizon
-// needed).
-__device__ __forceinline__ uint64_t run_phase(const ExtArgs &a, uint32_t *nib, uint32_t nw, const uint32_t *rank,
-                              const EvList &lq, const EvList &lt, uint64_t known, uint64_t lim,
-                              uint32_t lim_code, uint32_t o, Est &e, bool &ok, uint32_t &code,
-                              unsigned long long &applied, bool &bad) {
-    EvCursor cq, ct;
-    cq.next = ct.next = 0;
-    cq.count = lq.hi - lq.lo;
-    ct.count = lt.hi - lt.lo;
-    ev_refill(a, rank, lq, cq);
-    ev_refill(a, rank, lt, ct);
-    uint64_t last = 0;
-    for (;;) {
-        if (cq.at >= cq.fill && cq.next + cq.fill < cq.count) {
-            cq.next += cq.fill;
-            ev_refill(a, rank, lq, cq);
-        }
-        if (ct.at >= ct.fill && ct.next + ct.fill < ct.count) {
-            ct.next += ct.fill;
-            ev_refill(a, rank, lt, ct);
-        }
-        if (ok && e.s > 0 && a.batch_min) {
-            // all held events up to a step S known to hold every event <= S
-            const uint64_t bq = cq.next + cq.fill < cq.count
-                                    ? __builtin_amdgcn_readlane(cq.vstep, cq.fill - 1) : INF;
-            const uint64_t bt = ct.next + ct.fill < ct.count
-                                    ? __builtin_amdgcn_readlane(ct.vstep, ct.fill - 1) : INF;
-            uint64_t S = std::min(std::min(bq, bt), known);
-            const uint32_t lane = threadIdx.x & 63;
-            auto held = [&](const EvCursor &c) {
-                return (uint32_t)__popcll(
-                    __ballot(lane >= c.at && lane < c.fill && (uint64_t)c.vstep <= S));
-            };
-            uint32_t nq = held(cq), nt = held(ct);
-            const int64_t slack = (int64_t)e.m - (int64_t)(uint32_t)ceil(a.tau * (double)e.s);
-            // as many insertions as the slack covers: cut S back to the step of
-            // the middle held event of the longer list until they fit
-            for (int it = 0; it < 12 && 3 * (int64_t)(nq + nt) > slack; it++) {
-                if (nq >= nt && nq > 1)
-                    S = __builtin_amdgcn_readlane(cq.vstep, cq.at + nq / 2 - 1);
-                else if (nt > 1)
-                    S = __builtin_amdgcn_readlane(ct.vstep, ct.at + nt / 2 - 1);
-                else
-                    break;
-                nq = held(cq);
-                nt = held(ct);
-            }
-            if (nq + nt >= a.batch_min && slack >= 3 * (int64_t)(nq + nt)) {
-                if (!apply_batch(nib, nw, cq, nq, ct, nt, o, e)) { bad = true; code = STOP_ESTIMATE; return last; }
-                cq.at += nq;
-                ct.at += nt;
-                applied += nq + nt;
-                ok = passes(e, a.tau);
-                if (!ok) { bad = true; code = STOP_ESTIMATE; return last; }
-                last = std::max(last, S);
-                continue;
+#pragma unroll
+    for (uint32_t size = 2; size <= 64u * N; size <<= 1) {
+#pragma unroll
+        for (uint32_t j = size >> 1; j > 0; j >>= 1) {
+#pragma unroll
+            for (int t = 0; t < N; t++) {
+                if (j >= 64) {  // between registers: each pair once
+                    const int f = t ^ (int)(j >> 6);
+                    if (f < t) continue;
+                    const bool up = ((uint32_t)(t * 64) & size) == 0;
+                    const K lo = std::min(x[t], x[f]), hi = std::max(x[t], x[f]);
+                    x[t] = up ? lo : hi;
+                    x[f] = up ? hi : lo;
+                } else {
+                    K y = (K)lane_xor((uint32_t)x[t], j);
+                    if constexpr (sizeof(K) == 8) y |= (K)lane_xor((uint32_t)(x[t] >> 32), j) << 32;
+                    const bool up = (((uint32_t)(t * 64) | lane) & size) == 0, lower = (lane & j) == 0;
+                    x[t] = lower == up ? std::min(x[t], y) : std::max(x[t], y);
+                }
             }
         }
-        const uint64_t sq = ev_head(cq), st = ev_head(ct);
-        const uint64_t te = std::min(sq, st);
-        if (te > known) break;
-        if (te > last + 1) {  // steps without an entering minimizer keep the state
-            if (!ok) { code = STOP_ESTIMATE; return last; }
-            last = te - 1;
-        }
-        const Est prev = e;
-        const bool prev_ok = ok;
-        Undo u;
-        u.n = 0;
-        if (sq == te) {
-            const uint32_t r = __builtin_amdgcn_readlane(cq.vrank, cq.at);
-            const uint32_t b = __builtin_amdgcn_readlane(cq.vbit, cq.at);
-            bad |= !insert(nib, nw, r, b, o, e, u);
-            cq.at++;
-            applied++;
-        }
-        if (st == te) {
-            const uint32_t r = __builtin_amdgcn_readlane(ct.vrank, ct.at);
-            const uint32_t b = __builtin_amdgcn_readlane(ct.vbit, ct.at);
-            bad |= !insert(nib, nw, r, b, o, e, u);
-            ct.at++;
-            applied++;
-        }
-        ok = passes(e, a.tau);
-        if (!ok) {
-            undo(nib, u);
-            e = prev;
-            ok = prev_ok;
-            code = STOP_ESTIMATE;
-            return te - 1;
-        }
-        last = te;
     }
-    if (last < known) {
-        if (!ok) { code = STOP_ESTIMATE; return last; }
-        last = known;
+    uint32_t eid[N];
+#pragma unroll
+    for (int t = 0; t < N; t++)
+        eid[t] = b + t * 64 + lane < e ? (uint32_t)src[b + (uint32_t)(x[t] & 1023)] : 0u;
+    uint32_t heads = 0;  // distinct hashes before register t
+    uint32_t before = 0;
+    const uint64_t le = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1;
+#pragma unroll
+    for (int t = 0; t < N; t++) {
+        const uint32_t h = (uint32_t)(x[t] >> 10);
+        const uint32_t up = (uint32_t)__shfl_up((int)h, 1, 64), dn = (uint32_t)__shfl_down((int)h, 1, 64);
+        const uint32_t p = lane ? up : before;
+        before = (uint32_t)__builtin_amdgcn_readlane((int)h, 63);
+        const uint32_t next = t + 1 < N ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x[t + 1 < N ? t + 1 : t] >> 10)) : 0u;
+        const bool head = (t == 0 && lane == 0) || p != h;
+        const uint64_t hm = __ballot(head);
+        const bool tail = b + t * 64 + lane + 1 >= e || (lane == 63 ? next : dn) != h;
+        if (b + t * 64 + lane < e)
+            rank[eid[t]] = (b + heads + (uint32_t)__popcll(hm & le) - 1) | (head && tail ? 0u : RANK_REP);
+        heads += (uint32_t)__popcll(hm);
     }
-    if (known >= lim) { code = lim_code; return lim; }
-    code = 0;  // the horizon ended first
-    return last;
 }
 
-// Keys [b, e) of src (whole buckets, so no hash continues outside): sort
-// in LDS and give every element its rank, equal hashes sharing one.
-__device__ void rank_chunk(Shared &L, const uint64_t *src, uint64_t b, uint64_t e, uint32_t *rank) {
+// The same for a bucket of 64 * 16 to CH keys, by the whole workgroup in LDS.
+__device__ void rank_block(Shared &L, const uint64_t *src, uint32_t b, uint32_t e, uint32_t *rank,
+                           uint32_t &turn) {
     uint64_t *ck = L.ck;
-    const uint32_t cnt = (uint32_t)(e - b);
+    const uint32_t cnt = e - b;
     uint32_t P = 1;
     while (P < cnt) P <<= 1;
     for (uint32_t i = threadIdx.x; i < P; i += XT) ck[i] = i < cnt ? src[b + i] : ~0ull;
@@ -640,14 +477,14 @@ __device__ void rank_chunk(Shared &L, const uint64_t *src, uint64_t b, uint64_t 
     for (uint32_t i = s0; i < s1; i++)
         heads += (i == 0 || (ck[i] >> 32) != (ck[i - 1] >> 32)) ? 1u : 0u;
     uint32_t excl;
-    const uint32_t tot = block_scan(L, heads, excl);
-    uint32_t r = L.nrank + excl;
+    block_scan(L, heads, excl, turn);
+    uint32_t r = b + excl;
     for (uint32_t i = s0; i < s1; i++) {
-        if (i == 0 || (ck[i] >> 32) != (ck[i - 1] >> 32)) r++;
-        rank[(uint32_t)ck[i]] = r - 1;
+        const bool head = i == 0 || (ck[i] >> 32) != (ck[i - 1] >> 32);
+        const bool tail = i + 1 == cnt || (ck[i] >> 32) != (ck[i + 1] >> 32);
+        if (head) r++;
+        rank[(uint32_t)ck[i]] = (r - 1) | (head && tail ? 0u : RANK_REP);
     }
-    __syncthreads();
-    if (threadIdx.x == 0) L.nrank += tot;
     __syncthreads();
 }
 
@@ -711,12 +548,45 @@ __device__ bool rank_big(Shared &L, const uint64_t *src, uint64_t b, uint64_t e,
             const uint32_t mid = (lo + hi) >> 1;
             if (list[mid] < h) lo = mid + 1; else hi = mid;
         }
-        rank[(uint32_t)key] = L.nrank + lo;
+        rank[(uint32_t)key] = ((uint32_t)b + lo) | RANK_REP;
     }
     __syncthreads();
-    if (threadIdx.x == 0) L.nrank += D;
-    __syncthreads();
     return true;
+}
+
+// The elements of L next to v into near[]: those above it by one wave (dir 0),
+// from v itself down by another (dir 1), at most `most`.
+__device__ __forceinline__ void near_v(Shared &L, const uint32_t *nib, uint32_t nw, int32_t v,
+                                       uint32_t most, uint32_t o, int dir) {
+    const uint32_t lane = threadIdx.x & 63;
+    const int32_t w0 = (dir == 0 ? v + 1 : v) >> 3;
+    const int32_t w = dir == 0 ? w0 + (int32_t)lane : w0 - (int32_t)lane;
+    uint32_t c = w >= 0 && w < (int32_t)nw ? nib[w] : 0u;
+    if (lane == 0) {
+        if (dir == 0) c &= 0xFFFFFFFFu << (((v + 1) & 7) * 4);
+        else c &= (v & 7) == 7 ? 0xFFFFFFFFu : (1u << (((v & 7) + 1) * 4)) - 1u;
+    }
+    uint32_t nz = nz_mask(c);
+    const uint32_t sh = shared_mask(c, o);
+    const uint32_t incl = wave_incl_sum(__popc(nz)), tot = __builtin_amdgcn_readlane(incl, 63);
+    const uint32_t n = std::min(most, tot);
+    for (uint32_t i = incl - __popc(nz); nz && i < n; i++) {
+        const uint32_t b = dir == 0 ? (uint32_t)__builtin_ctz(nz) : 31u - (uint32_t)__builtin_clz(nz);
+        nz &= ~(1u << b);
+        L.near[dir][i] = (((uint32_t)w * 8 + (b >> 2)) << 1) | ((sh >> b) & 1u);
+    }
+    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // writes of other lanes before reads
+    const uint32_t e = lane < n ? L.near[dir][lane] : 0u;
+    const uint64_t shared = __ballot(e & 1u);
+    // a list cut short describes the ranks up to its last element, any other
+    // all that was read
+    const int32_t end = dir == 0 ? (w0 + 64) * 8 - 1 : max(0, (w0 - 63) * 8);
+    const int32_t far = tot > n ? (int32_t)(__builtin_amdgcn_readlane(e, n - 1) >> 1) : end;
+    if (lane == 0) {
+        L.nn[dir] = n;
+        L.nr[dir] = far;
+        L.nsh[dir] = shared;
+    }
 }
 
 struct PhaseIn {
@@ -727,17 +597,269 @@ struct PhaseIn {
     uint64_t start[4];  // the region the lists were gathered for
 };
 
-// The phases from `dir0` on, on one wave, from the state e of region r.
-// Returns 0 when both phases stopped (r, e, codes final), or 2 (forward) /
-// 8 (backward) when a phase ran through its horizon: r and e are then the
-// state it reached, which the next attempt continues from.  Inlined once
-// with L in LDS and once in global memory.
-__device__ __forceinline__ uint32_t phases(const ExtArgs &a, const Shared &L, uint32_t *nib,
+// The first step of the held events from (iq, it) on by itself, on wave 0:
+// inserts, checks, and undoes a refused step.
+__device__ __forceinline__ void one_step(const ExtArgs &a, Shared &L, uint32_t *nib, uint32_t nw,
+                                         uint32_t iq, uint32_t it, uint32_t o,
+                                         unsigned long long &applied) {
+    Est e{L.v, L.s, L.m};
+    const Est prev = e;
+    const uint32_t sq = iq < XT ? L.estep[0][iq] : NONE32, st = it < XT ? L.estep[1][it] : NONE32;
+    const uint32_t te = std::min(sq, st);
+    bool ok = L.ok != 0, bad = false;
+    uint64_t last = L.last;
+    uint32_t code = 0, nq = 0, nt = 0;
+    if (te > last + 1 && !ok) {  // steps without an entering minimizer keep the state
+        code = STOP_ESTIMATE;
+    } else {
+        Undo u;
+        u.n = 0;
+        if (sq == te) {
+            const uint32_t c = L.ecell[0][iq];
+            bad |= !insert(nib, nw, c >> 4, c & 15u, o, e, u);
+            nq = 1;
+        }
+        if (st == te) {
+            const uint32_t c = L.ecell[1][it];
+            bad |= !insert(nib, nw, c >> 4, c & 15u, o, e, u);
+            nt = 1;
+        }
+        applied += nq + nt;
+        if (passes(e, a.tau)) {
+            ok = true;
+            last = te;
+        } else {
+            undo(nib, u);
+            e = prev;
+            code = STOP_ESTIMATE;
+            last = te - 1;
+        }
+    }
+    if (threadIdx.x == 0) {
+        L.v = e.v; L.s = e.s; L.m = e.m;
+        L.uq += nq;
+        L.ut += nt;
+        L.last = last;
+        L.ok = ok;
+        L.code = code;
+        if (bad) L.flag |= 4u;
+    }
+}
+
+// Number of the sorted steps [0, XT) up to `step`.
+__device__ __forceinline__ uint32_t upto(const uint32_t *steps, uint32_t step) {
+    uint32_t lo = 0, hi = XT;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (steps[mid] <= step) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+// One phase, by the workgroup.  Up to XT entering minimizers per side are held,
+// in step order, and the steps up to S (every event of which is held) are
+// tried together while the state passes: after an event's step, with all events
+// up to it, s has grown by the hashes new to the query side (dS), the elements
+// new below v (nB) have moved v by d = dS - nB elements up or down, and m
+// follows the elements that became shared at or below v (gB) and the shared
+// ones among those d elements: prefix sums over the two lists and the elements
+// next to v.  Events that change elements next to v, and a v that leaves them,
+// end what can be told; the batch is applied up to the first step refused or
+// not told, which is then done by itself.  Leaves the steps taken in L.last and
+// the stop code in L.code (0: the events ran out before the phase could stop,
+// a larger horizon is needed).
+__device__ __forceinline__ void run_phase(const ExtArgs &a, Shared &L, uint32_t *nib, uint32_t nw,
+                                          const uint32_t *rank, const EvList &lq, const EvList &lt,
+                                          uint64_t known, uint64_t lim, uint32_t lim_code, uint32_t o,
+                                          unsigned long long &applied) {
+    const uint32_t tid = threadIdx.x, wave = tid >> 6;
+    const uint64_t count[2] = {lq.hi - lq.lo, lt.hi - lt.lo};
+    if (tid == 0) {
+        L.uq = L.ut = L.last = 0;
+        L.code = 0;
+        L.ok = passes(Est{L.v, L.s, L.m}, a.tau);
+    }
+    for (;;) {
+        __syncthreads();  // the state of the last round
+        if (L.code || (L.flag & 4u)) return;
+        const uint64_t used[2] = {L.uq, L.ut};
+        uint32_t step[2], cell[2];
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            const EvList &l = d ? lt : lq;
+            const uint64_t u = used[d] + tid;
+            step[d] = NONE32;
+            cell[d] = 0;
+            if (u < count[d]) {
+                const uint64_t mi = l.up ? l.lo + u : l.hi - 1 - u;
+                const uint64_t pos = a.ix.mpos[mi];
+                step[d] = (uint32_t)(l.up ? pos + a.ix.k - l.ref : l.ref - pos);
+                const uint32_t r = rank[l.base + (uint32_t)(mi - l.lo)];
+                cell[d] = (r & RANK_REP) | ((r & ~RANK_REP) << 4) | (l.side << (a.ix.mflags[mi] & 1));
+            }
+            L.estep[d][tid] = step[d];
+            L.ecell[d][tid] = cell[d] & ~RANK_REP;
+        }
+        const int32_t v = L.v;
+        const uint32_t s0 = L.s, m0 = L.m;
+        const bool batch = L.ok && s0 > 0 && a.batch_min;
+        if (tid == 0) L.dark = L.refused = NONE32;
+        if (batch && wave < 2)
+            near_v(L, nib, nw, v, s0 < 512 ? 8u : s0 < 8192 ? 16u : s0 < 32768 ? 32u : 63u, o, (int)wave);
+        __syncthreads();
+        const uint64_t te = std::min(L.estep[0][0], L.estep[1][0]);
+        if (te > known) break;  // (no event: NONE32, which no step reaches)
+        uint64_t S = known;
+        if (used[0] + XT < count[0]) S = std::min<uint64_t>(S, L.estep[0][XT - 1]);
+        if (used[1] + XT < count[1]) S = std::min<uint64_t>(S, L.estep[1][XT - 1]);
+        if (!batch) {
+            if (wave == 0) one_step(a, L, nib, nw, 0, 0, o, applied);
+            continue;
+        }
+        // ---- what each event changes, given those before it ----
+        bool held[2];
+        uint32_t r[2], bit[2], c0[2];
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            held[d] = (uint64_t)step[d] <= S;
+            r[d] = (cell[d] & ~RANK_REP) >> 4;
+            bit[d] = cell[d] & 15u;
+            c0[d] = held[d] ? cell_at(nib, (int32_t)r[d]) : 0u;
+        }
+        // events of one rank see the bits of those before them (by step, query side
+        // first): round by round one event of each slot of ranks is named, and all
+        // events of the slot look at it (rounds: the most events in a slot)
+        bool todo[2];
+#pragma unroll
+        for (int d = 0; d < 2; d++) todo[d] = held[d] && (cell[d] & RANK_REP);
+        const bool rep[2] = {todo[0], todo[1]};
+        while (__syncthreads_or(todo[0] || todo[1])) {
+#pragma unroll
+            for (int d = 0; d < 2; d++)
+                if (todo[d]) L.tag[r[d] % TAGS] = (uint16_t)(d * XT + tid);
+            __syncthreads();
+#pragma unroll
+            for (int d = 0; d < 2; d++) {
+                if (!rep[d]) continue;
+                const uint32_t id = L.tag[r[d] % TAGS];
+                const uint32_t od = id / XT, oc = L.ecell[od][id % XT], os = L.estep[od][id % XT];
+                if ((oc >> 4) == r[d] && (os < step[d] || (os == step[d] && od < (uint32_t)d)))
+                    c0[d] |= oc & 15u;
+                if (id == d * XT + tid) todo[d] = false;
+            }
+        }
+        // dS, nB, gB of an event in ten bits each, and whether it is next to v
+        const int32_t ra = L.nr[1], rb = L.nr[0];
+        uint32_t f[2];
+        bool close[2];
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            const uint32_t c1 = c0[d] | bit[d];
+            const bool ch = held[d] && c1 != c0[d];
+            close[d] = ch && (int32_t)r[d] >= ra && (int32_t)r[d] <= rb;
+            f[d] = !ch ? 0u
+                       : (uint32_t)(!(c0[d] & 3u) && (c1 & 3u)) |
+                             ((c0[d] == 0 && (int32_t)r[d] < v) ? 1u << 10 : 0u) |
+                             (((int32_t)r[d] <= v && !cell_shared(c0[d], o) && cell_shared(c1, o)) ? 1u << 20 : 0u);
+        }
+        const uint32_t i0 = wave_incl_sum(f[0]), i1 = wave_incl_sum(f[1]);
+        if ((tid & 63) == 63) {
+            L.wsum[0][wave] = i0;
+            L.wsum[1][wave] = i1;
+        }
+        __syncthreads();
+        uint32_t pre[2] = {i0, i1};
+#pragma unroll
+        for (uint32_t w = 0; w < (uint32_t)XW; w++)
+            if (w < wave) {
+                pre[0] += L.wsum[0][w];
+                pre[1] += L.wsum[1][w];
+            }
+        L.epre[0][tid] = pre[0];
+        L.epre[1][tid] = pre[1];
+        __syncthreads();
+        // ---- the state after each event's step ----
+        const uint64_t su = L.nsh[0], sd = L.nsh[1];
+        const int32_t nu = (int32_t)L.nn[0], nd = (int32_t)L.nn[1];
+        auto m_of = [&](uint32_t p, int32_t &d) {  // m after the events counted in p
+            d = (int32_t)(p & 1023u) - (int32_t)((p >> 10) & 1023u);
+            const uint32_t x = (uint32_t)std::min(d < 0 ? -d : d, 63);
+            const uint32_t c = (uint32_t)__popcll((d < 0 ? sd : su) & ((1ull << x) - 1));
+            return (int32_t)m0 + (int32_t)(p >> 20) + (d < 0 ? -(int32_t)c : (int32_t)c);
+        };
+#pragma unroll
+        for (int d = 0; d < 2; d++) {
+            bool dark = false, refused = false;
+            if (held[d]) {
+                const uint32_t n = upto(L.estep[1 - d], step[d]);
+                const uint32_t p = pre[d] + (n ? L.epre[1 - d][n - 1] : 0u);
+                int32_t dv;
+                const int32_t m = m_of(p, dv);
+                dark = close[d] || dv > nu || -dv >= nd;
+                refused = m < (int32_t)(uint32_t)ceil(a.tau * (double)(s0 + (p & 1023u)));
+            }
+            // (steps ascend with the lanes: the first is the least)
+            const uint64_t md = __ballot(dark), mr = __ballot(refused);
+            if ((tid & 63) == 0) {
+                if (md) atomicMin(&L.dark, L.estep[d][(tid & ~63u) + (uint32_t)__builtin_ctzll(md)]);
+                if (mr) atomicMin(&L.refused, L.estep[d][(tid & ~63u) + (uint32_t)__builtin_ctzll(mr)]);
+            }
+        }
+        __syncthreads();
+        const uint32_t dark = L.dark, refused = L.refused, cut = std::min(dark, refused);
+#pragma unroll
+        for (int d = 0; d < 2; d++)
+            if (held[d] && step[d] < cut) atomicOr(&nib[r[d] >> 3], bit[d] << ((r[d] & 7) * 4));
+        __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // written before the barrier
+        if (tid == 0) {
+            const uint32_t end = (uint32_t)std::min<uint64_t>((uint64_t)cut - 1, S);  // the last step taken
+            const uint32_t tq = upto(L.estep[0], end), tt = upto(L.estep[1], end);
+            const uint32_t p = (tq ? L.epre[0][tq - 1] : 0u) + (tt ? L.epre[1][tt - 1] : 0u);
+            int32_t d;
+            L.m = (uint32_t)m_of(p, d);
+            L.s = s0 + (p & 1023u);
+            if (d > 0) L.v = (int32_t)(L.near[0][d - 1] >> 1);
+            if (d < 0) L.v = (int32_t)(L.near[1][-d] >> 1);
+            L.uq += tq;
+            L.ut += tt;
+            L.last = std::max<uint64_t>(L.last, end);
+            applied += tq + tt;
+            if (refused < dark) L.code = STOP_ESTIMATE;
+            L.nq = tq;
+            L.nt = tt;
+        }
+        if (dark <= refused && dark != NONE32) {  // the next step, which is held, by itself
+            __syncthreads();
+            if (wave == 0) one_step(a, L, nib, nw, L.nq, L.nt, o, applied);
+        }
+    }
+    // no event up to `known` is left
+    __syncthreads();
+    if (tid == 0) {
+        if (L.last < known && !L.ok) {
+            L.code = STOP_ESTIMATE;
+        } else {
+            L.last = std::max<uint64_t>(L.last, known);
+            if (known >= lim) {
+                L.code = lim_code;
+                L.last = lim;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// The phases from `dir0` on, from the state L.v, L.s, L.m of region r.
+// Returns 0 when both phases stopped (r, codes final), 2 (forward) / 8
+// (backward) when a phase ran through its horizon: r and the state are then
+// what it reached, which the next attempt continues from; 4 for an
+// inconsistent set.  Inlined once with L in LDS and once in global memory.
+__device__ __forceinline__ uint32_t phases(const ExtArgs &a, Shared &L, uint32_t *nib,
                                            uint32_t nw, const uint32_t *rank, const PhaseIn &pi,
-                                           int dir0, uint64_t r[4], Est &e, uint32_t codes[2],
-                                           unsigned long long &app, bool &bad) {
+                                           int dir0, uint64_t r[4], uint32_t codes[2],
+                                           unsigned long long &app) {
     const uint32_t o = pi.o;
-    bool ok = passes(e, a.tau);
+    if (threadIdx.x == 0) L.flag = 0;
     for (int dir = dir0; dir < 2; dir++) {
         const Phase p = phase_of(dir, o);
         uint64_t lim;
@@ -755,19 +877,23 @@ __device__ __forceinline__ uint32_t phases(const ExtArgs &a, const Shared &L, ui
             lq.up = false; lq.ref = pi.start[0];
             lt.up = o == 1; lt.ref = o == 0 ? pi.start[2] : pi.start[3];
         }
-        uint32_t code = 0;
-        const uint64_t t = run_phase(a, nib, nw, rank, lq, lt, known, lim, lcode, o, e, ok, code,
-                                     app, bad);
+        run_phase(a, L, nib, nw, rank, lq, lt, known, lim, lcode, o, app);
+        const uint64_t t = L.last;
+        const uint32_t code = L.code;
+        const bool bad = (L.flag & 4u) != 0;
+        __syncthreads();  // read by all before the next phase
         r[0] -= p.ql * t; r[1] += p.qr * t; r[2] -= p.tl * t; r[3] += p.tr * t;
+        if (bad) return 4u;
         if (code == 0) return dir == 0 ? 2u : 8u;
-        if (dir == 0) codes[0] = code; else codes[1] = code;
+        codes[dir] = code;
     }
     return 0;
 }
 
 }  // namespace
 
-__global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
+__global__ void __launch_bounds__(XT) __attribute__((amdgpu_waves_per_eu(3)))
+k_extend(ExtArgs a) {
     __shared__ Shared L;
     const IndexView &ix = a.ix;
     const uint32_t k = ix.k;
@@ -779,6 +905,7 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
     const uint32_t shift = hbits > NB_BITS ? hbits - NB_BITS : 0;
     const uint32_t nbk = 1u << (hbits - shift);
     constexpr uint32_t PER = NB / XT;
+    uint32_t turn = 0;  // set of wave totals that the next block scan uses
 
     for (;;) {
         if (threadIdx.x == 0) L.region = atomicAdd(a.work, 1u);
@@ -822,9 +949,11 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
             ub_b = std::min(ub_b, a.max_len - longer);
             // the backward phase starts from a state the forward phase has driven
             // to the threshold and seldom goes far: while the forward phase is
-            // pending only a short backward horizon is gathered (a backward phase
-            // that runs through it continues in the next attempt)
-            const uint64_t Hb = std::min(dir == 0 && a.hb0 ? std::min(want, a.hb0) : want, ub_b);
+            // pending a shorter backward horizon is gathered (a backward phase that
+            // runs through it continues in the next attempt, which ranks everything
+            // again: a quarter of the longer side spares most large regions that)
+            const uint64_t Hb =
+                std::min(dir == 0 && a.hb0 ? std::min(want, std::max(a.hb0, longer / HB_DIV)) : want, ub_b);
             // position ranges [pa, pe] of the six element lists: both windows,
             // then the forward and the backward minimizers that can enter
             int64_t pa[6], pe[6];  // (indexed by constants only: registers)
@@ -838,16 +967,19 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
             else { pa[5] = (int64_t)r[3] + 1 - k; pe[5] = (int64_t)(r[3] + Hb) - k; }
             if (Hf == 0) { pa[2] = pa[3] = 1; pe[2] = pe[3] = 0; }
             if (Hb == 0) { pa[4] = pa[5] = 1; pe[4] = pe[5] = 0; }
-            if (threadIdx.x < 12) {
-                const uint32_t l = threadIdx.x >> 1;
+            {
+                const uint32_t gp = threadIdx.x >> 4, l = min(gp >> 1, 5u);  // 16 lanes per bound
                 int64_t lo_p = pa[0], hi_p = pe[0];
 #pragma unroll
                 for (uint32_t t = 1; t < 6; t++)
                     if (l == t) { lo_p = pa[t]; hi_p = pe[t]; }
-                const bool hi_end = threadIdx.x & 1;
+                const bool hi_end = gp & 1;
                 const int64_t x = hi_end ? hi_p + 1 : lo_p;
-                const uint64_t v = (hi_p < lo_p) ? 0 : lower_pos(ix, (uint64_t)std::max<int64_t>(x, 0));
-                if (hi_end) L.mhi[l] = v; else L.mlo[l] = v;
+                uint64_t v = lower_pos16(ix, (uint64_t)std::max<int64_t>(x, 0));
+                if (hi_p < lo_p) v = 0;
+                if (gp < 12 && (threadIdx.x & 15) == 0) {
+                    if (hi_end) L.mhi[l] = v; else L.mlo[l] = v;
+                }
             }
             __syncthreads();
             if (threadIdx.x == 0) {
@@ -859,7 +991,6 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
                     acc = (uint32_t)std::min<uint64_t>((uint64_t)acc + c, 0xFFFFFFFFull);
                 }
                 L.base[6] = acc;
-                L.nrank = 0;
                 L.flag = 0;
             }
             __syncthreads();
@@ -878,15 +1009,25 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
             // 1. bucket by the top hash bits into tmp
             for (uint32_t i = threadIdx.x; i < NB + 1; i += XT) L.bs[i] = 0;
             __syncthreads();
-            for (int l = 0; l < 6; l++)
-                for (uint64_t i = L.mlo[l] + threadIdx.x; i < L.mhi[l]; i += XT)
-                    atomicAdd(&L.bs[(ix.mhash[i] >> shift) & (nbk - 1)], 1u);
+            // (UN elements per thread and round, their loads in flight together: a
+            // region's elements are taken by one workgroup alone)
+            for (int l = 0; l < 6; l++) {
+                const uint64_t hi = L.mhi[l];
+                for (uint64_t i = L.mlo[l] + threadIdx.x; i < hi; i += XT * UN) {
+                    uint32_t h[UN];
+#pragma unroll
+                    for (int u = 0; u < UN; u++) h[u] = ix.mhash[std::min(i + (uint64_t)u * XT, hi - 1)];
+#pragma unroll
+                    for (int u = 0; u < UN; u++)
+                        if (i + (uint64_t)u * XT < hi) atomicAdd(&L.bs[(h[u] >> shift) & (nbk - 1)], 1u);
+                }
+            }
             __syncthreads();
             {
                 uint32_t loc = 0;
                 for (uint32_t t = 0; t < PER; t++) loc += L.bs[threadIdx.x * PER + t];
                 uint32_t ex;
-                block_scan(L, loc, ex);
+                block_scan(L, loc, ex, turn);
                 for (uint32_t t = 0; t < PER; t++) {
                     const uint32_t c = L.bs[threadIdx.x * PER + t];
                     L.bs[threadIdx.x * PER + t] = ex;
@@ -899,19 +1040,29 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
                 uint32_t *cur = reinterpret_cast<uint32_t *>(L.ck);  // NB cursors
                 for (uint32_t i = threadIdx.x; i < NB; i += XT) cur[i] = L.bs[i];
                 __syncthreads();
-                for (int l = 0; l < 6; l++)
-                    for (uint64_t i = L.mlo[l] + threadIdx.x; i < L.mhi[l]; i += XT) {
-                        const uint32_t h = ix.mhash[i];
-                        const uint32_t eid = L.base[l] + (uint32_t)(i - L.mlo[l]);
-                        tmp[atomicAdd(&cur[(h >> shift) & (nbk - 1)], 1u)] =
-                            ((uint64_t)h << 32) | eid;
+                for (int l = 0; l < 6; l++) {
+                    const uint64_t hi = L.mhi[l];
+                    const uint32_t eid = L.base[l] - (uint32_t)L.mlo[l];
+                    for (uint64_t i = L.mlo[l] + threadIdx.x; i < hi; i += XT * UN) {
+                        uint32_t h[UN], at[UN];
+#pragma unroll
+                        for (int u = 0; u < UN; u++) h[u] = ix.mhash[std::min(i + (uint64_t)u * XT, hi - 1)];
+#pragma unroll
+                        for (int u = 0; u < UN; u++)
+                            if (i + (uint64_t)u * XT < hi)
+                                at[u] = atomicAdd(&cur[(h[u] >> shift) & (nbk - 1)], 1u);
+#pragma unroll
+                        for (int u = 0; u < UN; u++)
+                            if (i + (uint64_t)u * XT < hi)
+                                tmp[at[u]] = ((uint64_t)h[u] << 32) | (eid + (uint32_t)(i + (uint64_t)u * XT));
                     }
+                }
                 __syncthreads();
             }
             // 2. chunks of whole buckets: a bucket opens a chunk when its start
             // falls in another half-chunk window than the previous bucket's, or
             // when it or the previous bucket holds more than half a chunk; so a
-            // chunk of several buckets holds fewer than CH keys
+            // chunk of several buckets holds at most 2 HALF keys
             {
                 uint32_t flags = 0, nf = 0;
                 for (uint32_t t = 0; t < PER; t++) {
@@ -927,7 +1078,7 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
                     nf += open ? 1u : 0u;
                 }
                 uint32_t ex;
-                const uint32_t nch = block_scan(L, nf, ex);
+                const uint32_t nch = block_scan(L, nf, ex, turn);
                 for (uint32_t t = 0; t < PER; t++)
                     if (flags & (1u << t)) L.cl[ex++] = (uint16_t)(threadIdx.x * PER + t);
                 if (threadIdx.x == 0) L.nchunk = nch;
@@ -935,49 +1086,85 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
             }
             {
                 const uint32_t nch = L.nchunk;
-                for (uint32_t c = 0; c < nch; c++) {
-                    const uint32_t b0 = L.cl[c];
+                auto bounds = [&](uint32_t c, uint32_t &c0, uint32_t &c1) {
                     const uint32_t b1 = c + 1 < nch ? L.cl[c + 1] : nbk;
-                    const uint32_t c0 = L.bs[b0];
-                    const uint32_t c1 = b1 < nbk ? L.bs[b1] : (uint32_t)E;
-                    if (c1 == c0) continue;
-                    if (c1 - c0 <= CH) {
-                        rank_chunk(L, tmp, c0, c1, rank);
-                    } else if (rank_big(L, tmp, c0, c1, rank)) {
-                        if (threadIdx.x == 0) atomicAdd(&a.stats[6], 1ull);
+                    c0 = L.bs[L.cl[c]];
+                    c1 = b1 < nbk ? L.bs[b1] : (uint32_t)E;
+                };
+                bool big = false;
+                for (uint32_t c = threadIdx.x >> 6; c < nch; c += XW) {
+                    uint32_t c0, c1;
+                    bounds(c, c0, c1);
+                    const uint32_t b0 = L.cl[c], b1 = c + 1 < nch ? L.cl[c + 1] : nbk;
+                    const uint32_t hbase = b0 << shift;
+                    if (c1 - c0 > 1024) big = true;
+                    else if (((uint64_t)(b1 - b0) << shift) >= 1ull << 22) {
+                        if (c1 - c0 <= 128) rank_chunk<2, uint64_t>(tmp, c0, c1, hbase, rank);
+                        else if (c1 - c0 <= 512) rank_chunk<8, uint64_t>(tmp, c0, c1, hbase, rank);
+                        else rank_chunk<16, uint64_t>(tmp, c0, c1, hbase, rank);
                     } else {
-                        if (threadIdx.x == 0) { atomicOr(a.err, (uint32_t)XE_HASH); L.flag = 1; }
-                        __syncthreads();
-                        break;
+                        if (c1 - c0 <= 128) rank_chunk<2, uint32_t>(tmp, c0, c1, hbase, rank);
+                        else if (c1 - c0 <= 256) rank_chunk<4, uint32_t>(tmp, c0, c1, hbase, rank);
+                        else if (c1 - c0 <= 512) rank_chunk<8, uint32_t>(tmp, c0, c1, hbase, rank);
+                        else rank_chunk<16, uint32_t>(tmp, c0, c1, hbase, rank);
                     }
                 }
+                if (__syncthreads_or(big))
+                    for (uint32_t c = 0; c < nch; c++) {
+                        uint32_t c0, c1;
+                        bounds(c, c0, c1);
+                        if (c1 - c0 <= 1024) continue;
+                        if (c1 - c0 <= CH) {
+                            rank_block(L, tmp, c0, c1, rank, turn);
+                        } else if (rank_big(L, tmp, c0, c1, rank)) {
+                            if (threadIdx.x == 0) atomicAdd(&a.stats[6], 1ull);
+                        } else {
+                            if (threadIdx.x == 0) { atomicOr(a.err, (uint32_t)XE_HASH); L.flag = 1; }
+                            __syncthreads();
+                            break;
+                        }
+                    }
                 __syncthreads();
             }
             if (L.flag) { failed = true; break; }
-            const uint32_t nr = L.nrank;
+            const uint32_t nr = (uint32_t)E;  // ranks, gaps included
             const uint32_t nw = (nr + 7) / 8;
             uint32_t *nib = (nw <= a.lds_words) ? L.w : gnib;
             // 3. the state of the current region
             for (uint32_t i = threadIdx.x; i < nw; i += XT) nib[i] = 0;
             __syncthreads();
-            for (int l = 0; l < 2; l++)
-                for (uint64_t i = L.mlo[l] + threadIdx.x; i < L.mhi[l]; i += XT) {
-                    const uint32_t rr = rank[L.base[l] + (uint32_t)(i - L.mlo[l])];
-                    const uint32_t bit = (l == 0 ? C_Q0 : C_T0) << (ix.mflags[i] & 1);
-                    atomicOr(&nib[rr >> 3], bit << ((rr & 7) * 4));
+            for (int l = 0; l < 2; l++) {
+                const uint64_t hi = L.mhi[l];
+                const uint32_t eid = L.base[l] - (uint32_t)L.mlo[l];
+                for (uint64_t i = L.mlo[l] + threadIdx.x; i < hi; i += XT * UN) {
+                    uint32_t rr[UN], fl[UN];
+#pragma unroll
+                    for (int u = 0; u < UN; u++) {
+                        const uint64_t x = std::min(i + (uint64_t)u * XT, hi - 1);
+                        rr[u] = rank[eid + (uint32_t)x] & ~RANK_REP;
+                        fl[u] = ix.mflags[x] & 1u;
+                    }
+#pragma unroll
+                    for (int u = 0; u < UN; u++)
+                        if (i + (uint64_t)u * XT < hi)
+                            atomicOr(&nib[rr[u] >> 3], (l == 0 ? C_Q0 : C_T0) << fl[u] << ((rr[u] & 7) * 4));
                 }
+            }
+            __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");  // written before the barrier
             __syncthreads();
             {
                 const uint32_t seg = (nw + XT - 1) / XT;
                 const uint32_t w0 = std::min(nw, threadIdx.x * seg), w1 = std::min(nw, w0 + seg);
                 uint32_t qc = 0, uc = 0;
+#pragma unroll 8
                 for (uint32_t i = w0; i < w1; i++) {
-                    qc += __popc(q_mask(nib[i] & 0x33333333u));
-                    uc += __popc(nz_mask(nib[i]));
+                    const uint32_t c = nib[i];
+                    qc += __popc(q_mask(c & 0x33333333u));
+                    uc += __popc(nz_mask(c));
                 }
-                const uint32_t s = block_sum(L, qc);
+                const uint32_t s = block_sum(L, qc, turn);
                 uint32_t ex;
-                block_scan(L, uc, ex);
+                block_scan(L, uc, ex, turn);
                 if (threadIdx.x == 0) { L.v = -1; L.s = s; }
                 __syncthreads();
                 if (s > 0 && ex < s && s <= ex + uc) {
@@ -994,39 +1181,24 @@ __global__ void __launch_bounds__(XT) k_extend(ExtArgs a) {
                 __syncthreads();
                 const int32_t v = L.v;
                 uint32_t mc = 0;
+#pragma unroll 8
                 for (uint32_t i = w0; i < w1; i++) {
-                    uint32_t sm = shared_mask(nib[i], o);
-                    if ((int32_t)(i * 8) > v) break;
-                    if ((int32_t)(i * 8 + 7) > v) sm &= (v - (int32_t)(i * 8)) == 7 ? 0xFFFFFFFFu
-                                                  : ((1u << (((v - (int32_t)(i * 8)) + 1) * 4)) - 1u);
-                    mc += __popc(sm);
+                    const int32_t left = v - (int32_t)(i * 8);  // cells [0, left] of the word count
+                    const uint32_t keep = left < 0 ? 0u : left >= 7 ? 0xFFFFFFFFu : (1u << ((left + 1) * 4)) - 1u;
+                    mc += __popc(shared_mask(nib[i], o) & keep);
                 }
-                const uint32_t m = block_sum(L, mc);
+                const uint32_t m = block_sum(L, mc, turn);
                 if (threadIdx.x == 0) L.m = m;
                 __syncthreads();
             }
             const uint64_t t_mid = wall_clock64();
-            // 4. the phases, on wave 0 (L in LDS or in global memory)
-            if (threadIdx.x < 64) {
-                e.v = L.v; e.s = L.s; e.m = L.m;
-                PhaseIn pi{qlo, qhi, tlo, thi, same, o, Hf, Hb, {r[0], r[1], r[2], r[3]}};
-                unsigned long long app = 0;
-                bool bad = false;
-                const uint32_t ex = nw <= a.lds_words
-                                        ? phases(a, L, L.w, nw, rank, pi, dir, r, e, codes, app, bad)
-                                        : phases(a, L, gnib, nw, rank, pi, dir, r, e, codes, app, bad);
-                if (threadIdx.x == 0) {
-                    L.flag = ex | (bad ? 4u : 0u);
-                    L.rr[0] = r[0]; L.rr[1] = r[1]; L.rr[2] = r[2]; L.rr[3] = r[3];
-                    L.codes[0] = codes[0]; L.codes[1] = codes[1];
-                    applied += app;
-                }
-            }
-            __syncthreads();
-            const uint32_t fl = L.flag;
-            for (int d = 0; d < 4; d++) r[d] = L.rr[d];
-            codes[0] = L.codes[0];
-            codes[1] = L.codes[1];
+            // 4. the phases (L in LDS or in global memory)
+            const PhaseIn pi{qlo, qhi, tlo, thi, same, o, Hf, Hb, {r[0], r[1], r[2], r[3]}};
+            unsigned long long app = 0;
+            const uint32_t fl = nw <= a.lds_words ? phases(a, L, L.w, nw, rank, pi, dir, r, codes, app)
+                                                  : phases(a, L, gnib, nw, rank, pi, dir, r, codes, app);
+            applied += app;
+            e.v = L.v; e.s = L.s; e.m = L.m;
             __syncthreads();
             const uint64_t t_end = wall_clock64();
             t_rank += t_mid - t_att;
@@ -1076,7 +1248,7 @@ void launch_extend(const IndexView &ix, const sdf_region *in, uint64_t n, double
     // batch (0: one step at a time) and the backward horizon gathered while
     // the forward phase is pending (hb0)
     const sdf_tuning &tu = tuning();
-    const uint64_t h0 = knob(tu.ext_h0, 16384);
+    const uint64_t h0 = knob(tu.ext_h0, 4096);
     const uint64_t ecap = std::max<uint64_t>(64, knob(tu.ext_ecap, 1u << 18));
     const uint32_t ldsw = std::min<uint32_t>(LDS_WORDS, knob(tu.ext_lds_words, LDS_WORDS));
     const uint32_t batch_min = knob(tu.ext_batch_min, 4);
