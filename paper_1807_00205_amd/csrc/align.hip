@@ -262,6 +262,14 @@ __device__ __forceinline__ bool link_trim(uint32_t bex, uint32_t bey, uint32_t a
 
 __device__ __forceinline__ uint32_t absdiff(uint32_t a, uint32_t b) { return a > b ? a - b : b - a; }
 
+// What link_trim and a gap limit G ask of the y coordinates alone: the cut
+// leaves a base of the first anchor (bey - ay < alen) and ay - bey <= G.  Most
+// anchors of a large region are chance matches far off in y, so this settles
+// nearly all pairs.
+__device__ __forceinline__ bool y_in_reach(uint32_t bey, uint32_t ay, uint32_t alen, uint32_t G) {
+    return ay - bey + (alen - 1) < G + alen;
+}
+
 // The best predecessor seen by a lane: largest value, then (for values
 // above 0) the larger start (x, then y).  Starts are unique within a
 // region, so the choice does not depend on the order candidates are met.
@@ -316,18 +324,22 @@ __device__ __forceinline__ void st_score(int64_t *p, int64_t v) {
 // Only positive link values are kept and the choice among equal ones does
 // not depend on the order candidates are met, so this equals scoring the
 // anchors one at a time against every earlier anchor.  Candidates' lengths,
-// scores and anchor ids come from arrays kept in end order.
+// scores and anchor ids come from arrays kept in end order.  Bound by the
+// compares of the largest region's chance anchors: an entry no window of the
+// batch holds is left out by its own lane, and a pair too far apart in y after
+// three instructions (50 Mbp, all regions: 25.6 -> 9.8 ms).
 __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, const uint32_t *byxy,
                                               const uint32_t *alen, const uint64_t *endkey,
                                               const uint32_t *byend, const uint32_t *elen,
                                               const uint32_t *pos_e, const uint32_t *bnd,
                                               uint32_t nr, uint32_t G1, Tier1 t1,
-                                              int64_t *score_e, uint32_t nblk) {
+                                              int64_t *score_e, uint32_t nblk,
+                                              const uint32_t *large_first) {
     extern __shared__ uint32_t t1_lds[];
     uint32_t *const exhi = t1_lds;  // [nblk]
     __shared__ Best2 part[T1_WAVES][64];  // per wave and anchor
-    const uint32_t r = blockIdx.x;
-    if (r >= nr) return;
+    if (blockIdx.x >= nr) return;
+    const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t lo = bnd[r], hi = bnd[r + 1];
     const uint32_t nbr = (hi - lo + 63) / 64;  // blocks of the region's end order
@@ -354,7 +366,6 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
             apos = pos_e[a];
         }
         const uint32_t xend = x + len;  // this anchor's window: ends in [x - G1, xend)
-        const uint64_t khi = rk | ((uint64_t)xend << 21);
         const uint32_t x0 = lane_u32(x, 0), y0 = lane_u32(y, 0);  // the batch's first start
         const uint32_t xend_max = wave_max_u32(mine ? xend : 0u);
         const uint64_t khi_max = rk | ((uint64_t)xend_max << 21);
@@ -368,16 +379,19 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
             if (cb < 64) break;
         }
         const auto scan = [&](uint64_t ek, uint32_t el, int32_t es, uint32_t esl) {
-            for (uint32_t i = 0; i < 64; i++) {
-                const uint64_t key = ((uint64_t)lane_u32((uint32_t)(ek >> 32), i) << 32) |
-                                     lane_u32((uint32_t)ek, i);
-                if (key >= khi_max) break;  // sorted: no later entry is in any window
-                const uint32_t bex = (uint32_t)(key >> 21) & 0x1FFFFFu;
-                const uint32_t bey = (uint32_t)key & 0x1FFFFFu;
-                const bool pass = mine && key < khi && bex + G1 >= x;
+            // entries some window of the batch holds and that are scored already,
+            // told by their own lanes; then one at a time against every lane's anchor
+            const uint32_t lex = (uint32_t)(ek >> 21) & 0x1FFFFFu, lbx = lex - el;
+            const uint32_t lby = ((uint32_t)ek & 0x1FFFFFu) - el;
+            uint64_t todo = __ballot(ek < khi_max && lex + G1 >= x0 && (lbx < x0 || (lbx == x0 && lby < y0)));
+            for (; todo; todo &= todo - 1) {
+                const uint32_t i = (uint32_t)__builtin_ctzll(todo);
+                const uint32_t elo = lane_u32((uint32_t)ek, i), ehi = lane_u32((uint32_t)(ek >> 32), i);
+                const uint32_t bex = (uint32_t)((((uint64_t)ehi << 32) | elo) >> 21) & 0x1FFFFFu;
+                const uint32_t bey = elo & 0x1FFFFFu;
+                const bool pass = mine & (bex < xend) & (bex + G1 >= x) & y_in_reach(bey, y, len, G1);
                 if (!__ballot(pass)) continue;
                 const uint32_t bl = lane_u32(el, i), bx = bex - bl, by = bey - bl;
-                if (!(bx < x0 || (bx == x0 && by < y0))) continue;  // not scored yet
                 uint32_t o, dx, dy;
                 if (pass && link_trim(bex, bey, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1) {
                     const int32_t val =
@@ -433,7 +447,7 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
                 const int32_t sk = (int32_t)lane_u32((uint32_t)((int32_t)len + B.v), k);
                 const uint32_t xk = lane_u32(x, k), yk = lane_u32(y, k), lk = lane_u32(len, k);
                 const uint32_t exk = xk + lk, eyk = yk + lk;
-                if (lane > k && mine && exk < xend && exk + G1 >= x) {
+                if ((lane > k) & mine & (exk < xend) & (exk + G1 >= x) & y_in_reach(eyk, y, len, G1)) {
                     uint32_t o, dx, dy;
                     if (link_trim(exk, eyk, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1) {
                         const int32_t val = sk - (int32_t)(absdiff(dx, dy) + o);
@@ -573,10 +587,10 @@ struct UsedBits {
 __global__ __launch_bounds__(64) void k_extract1(Anchors an, const uint32_t *byscore,
                                                  const uint32_t *bnd, uint32_t nr, const Tier1 t1,
                                                  const uint8_t *has_child, uint8_t *used,
-                                                 uint32_t *tmp, Chains1 c, uint32_t cap) {
+                                                 uint32_t *tmp, Chains1 c, uint32_t cap, const uint32_t *large_first) {
     extern __shared__ uint32_t x1_bits[];
-    const uint32_t r = blockIdx.x;
-    if (r >= nr) return;
+    if (blockIdx.x >= nr) return;
+    const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x;
     const uint32_t lo = bnd[r], hi = bnd[r + 1];
     if (hi - lo > cap) {
@@ -731,17 +745,21 @@ __device__ __forceinline__ int64_t tier2_cost(uint32_t dx, uint32_t dy, uint32_t
 //     lane tests node k as its predecessor.
 // Only positive link values are kept and the choice among equal ones does
 // not depend on the order candidates are met, so this equals scoring the
-// nodes one at a time against every earlier node.
+// nodes one at a time against every earlier node.  Within a block, an entry
+// whose score the batch's first start is too far for is left out by its own
+// lane (most are chance chains of one anchor), and a pair too far apart in y
+// after three instructions (50 Mbp, all regions: 57 -> 26 ms).
 __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
     const uint32_t *nbnd, uint32_t nr, const uint32_t *nodes, const uint64_t *xykey,
     const uint64_t *ekey, const uint32_t *nodes_e, const uint2 *ecxy, const uint32_t *pos_e,
-    const Chains1 c, int64_t *score, int64_t *score_e, uint32_t *pred, uint32_t nblk) {
+    const Chains1 c, int64_t *score, int64_t *score_e, uint32_t *pred, uint32_t nblk,
+    const uint32_t *large_first) {
     extern __shared__ uint32_t t2_lds[];
     uint32_t *const exhi = t2_lds;                                      // [nblk]
     int32_t *const bmax = reinterpret_cast<int32_t *>(t2_lds + nblk);  // [nblk]
     __shared__ Best2 part[T2_WAVES][64];                                 // per wave and node
-    const uint32_t r = blockIdx.x;
-    if (r >= nr) return;
+    if (blockIdx.x >= nr) return;
+    const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t lo = nbnd[r], hi = nbnd[r + 1];
     const uint32_t nbr = (hi - lo + 63) / 64;  // blocks of the region
@@ -769,7 +787,6 @@ __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
             flen = c.flen[a];
         }
         const uint32_t xend = x + flen;  // this node's window: ends in [x - 10000, xend)
-        const uint64_t khi = rk | ((uint64_t)xend << 21);
         const uint32_t x0 = lane_u32(x, 0), y0 = lane_u32(y, 0);  // the batch's first start
         const uint32_t xend_max = wave_max_u32(mine ? xend : 0u);
         const uint64_t khi_max = rk | ((uint64_t)xend_max << 21);
@@ -783,17 +800,23 @@ __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
             if (cb < 64) break;
         }
         const auto scan = [&](uint64_t ek, uint2 exy, int32_t es, uint32_t esl) {
-            for (uint32_t i = 0; i < 64; i++) {
-                const uint64_t key = ((uint64_t)lane_u32((uint32_t)(ek >> 32), i) << 32) |
-                                     lane_u32((uint32_t)ek, i);
-                if (key >= khi_max) break;  // sorted: no later entry is in any window
+            // entries before the windows' end, scored already, whose score exceeds
+            // the least cost of a link to the batch's first start (the others are no
+            // nearer), told by their own lanes; then one at a time against every
+            // lane's node
+            const uint32_t lex = (uint32_t)(ek >> 21) & 0x1FFFFFu;
+            uint64_t todo = __ballot(ek < khi_max && es > tier2_min_cost(x0 > lex ? x0 - lex : 0) &&
+                                     (exy.x < x0 || (exy.x == x0 && exy.y < y0)));
+            for (; todo; todo &= todo - 1) {
+                const uint32_t i = (uint32_t)__builtin_ctzll(todo);
+                const uint32_t elo = lane_u32((uint32_t)ek, i), ehi = lane_u32((uint32_t)(ek >> 32), i);
                 const int32_t sb = (int32_t)lane_u32((uint32_t)es, i);
-                const uint32_t bex = (uint32_t)(key >> 21) & 0x1FFFFFu;
-                const uint32_t bey = (uint32_t)key & 0x1FFFFFu;
-                const bool pass = mine && key < khi && sb > tier2_min_cost(x > bex ? x - bex : 0);
+                const uint32_t bex = (uint32_t)((((uint64_t)ehi << 32) | elo) >> 21) & 0x1FFFFFu;
+                const uint32_t bey = elo & 0x1FFFFFu;
+                const bool pass = mine & (bex < xend) & y_in_reach(bey, y, flen, TIER2_GAP) &
+                                  (sb > tier2_min_cost(x > bex ? x - bex : 0));
                 if (!__ballot(pass)) continue;
                 const uint32_t bx = lane_u32(exy.x, i), by = lane_u32(exy.y, i);
-                if (!(bx < x0 || (bx == x0 && by < y0))) continue;  // not scored yet
                 uint32_t o, dx, dy;
                 if (pass && link_trim(bex, bey, x, y, flen, o, dx, dy) &&
                     (dx > dy ? dx : dy) <= TIER2_GAP) {
@@ -869,8 +892,8 @@ __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
             for (uint32_t k = 0; k + 1 < cnt; k++) {
                 const int32_t sk = (int32_t)lane_u32((uint32_t)(w + B.v), k);
                 const uint32_t exk = lane_u32(ex, k), eyk = lane_u32(ey, k);
-                if (lane > k && mine && exk < xend &&
-                    sk > tier2_min_cost(x > exk ? x - exk : 0)) {
+                if ((lane > k) & mine & (exk < xend) & y_in_reach(eyk, y, flen, TIER2_GAP) &
+                    (sk > tier2_min_cost(x > exk ? x - exk : 0))) {
                     const uint32_t xk = lane_u32(x, k), yk = lane_u32(y, k);
                     uint32_t o, dx, dy;
                     if (link_trim(exk, eyk, x, y, flen, o, dx, dy) &&
@@ -970,10 +993,10 @@ __global__ __launch_bounds__(64) void k_extract2(const uint32_t *nbnd, const uin
                                                  uint32_t nr, const uint32_t *order,
                                                  const uint32_t *pred, const uint8_t *has_child,
                                                  uint8_t *used, uint32_t *tmp, Final fin,
-                                                 uint32_t cap) {
+                                                 uint32_t cap, const uint32_t *large_first) {
     extern __shared__ uint32_t x2_bits[];
-    const uint32_t r = blockIdx.x;
-    if (r >= nr) return;
+    if (blockIdx.x >= nr) return;
+    const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x;
     const uint32_t lo = nbnd[r], hi = nbnd[r + 1], base = bnd[r], ns = bnd[r + 1] - base;
     if (ns > cap) {
@@ -1720,6 +1743,15 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     SDF_HIP(hipMemcpyAsync(dreg.p, hr.data(), n * sizeof(ARegion), hipMemcpyHostToDevice, st));
     SDF_HIP(hipMemcpyAsync(toff.p, hto.data(), (n + 1) * 8, hipMemcpyHostToDevice, st));
     SDF_HIP(hipMemcpyAsync(qoff.p, hqo.data(), (n + 1) * 8, hipMemcpyHostToDevice, st));
+    // the regions by falling size: one workgroup or wave takes a region in the
+    // chaining kernels, and the largest take longest, so they start first
+    std::vector<uint32_t> hl(n);
+    for (uint64_t r = 0; r < n; r++) hl[r] = (uint32_t)r;
+    std::stable_sort(hl.begin(), hl.end(), [&](uint32_t a, uint32_t b) {
+        return (hto[a + 1] - hto[a]) + (hqo[a + 1] - hqo[a]) > (hto[b + 1] - hto[b]) + (hqo[b + 1] - hqo[b]);
+    });
+    DevBuf<uint32_t> large(n);
+    SDF_HIP(hipMemcpyAsync(large.p, hl.data(), n * 4, hipMemcpyHostToDevice, st));
     const uint64_t TT = hto[n], QT = hqo[n];
     // key bits of a region number: every region number stays below 2^rbits - 1, so
     // no key of a region has all of its bits set like the sentinel ~0
@@ -1817,7 +1849,7 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
                                (most_anchors + 63) / 64);
         k_tier1<<<nr, 64 * T1_WAVES, 4 * nblk, st>>>(kxy.p, byxy.p, an.len, kend.p, byend.p,
                                                      elen.p, pos_e.p, bnd.p, nr, G1, t1, s1e.p,
-                                                     nblk);
+                                                     nblk, large.p);
         SDF_HIP(hipGetLastError());
     }
     // score order: y first (stable), then (region, score descending, x)
@@ -1841,7 +1873,7 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     fill_u32(reinterpret_cast<uint32_t *>(child.p), 0u, (A + 3) / 4, st);
     k_child_flags<<<nb(A), 256, 0, st>>>(t1.pred, nullptr, A, nullptr, child.p);
     k_extract1<<<nr, 64, std::max<uint32_t>(4, xcap / 8), st>>>(an, byscore.p, bnd.p, nr, t1,
-                                                                child.p, used.p, tmp.p, c, xcap);
+                                                                child.p, used.p, tmp.p, c, xcap, large.p);
     SDF_HIP(hipGetLastError());
     // nodes ordered by (region, x, y)
     DevBuf<uint32_t> rslot(A), nodes(A), nbnd(n + 1);
@@ -1878,7 +1910,7 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
             (read1(most.p, st) + 63) / 64);
         k_tier2<<<nr, 64 * T2_WAVES, 8 * nblk, st>>>(nbnd.p, nr, nodes.p, kbuf.p, ekey.p,
                                                      nodes_e.p, ecxy.p, pos_e.p, c, s2.p, s2e.p,
-                                                     p2.p, nblk);
+                                                     p2.p, nblk, large.p);
         SDF_HIP(hipGetLastError());
     }
     k_node_keys2<<<nb(A), 256, 0, st>>>(nodes.p, A, nbnd.p + nr, rslot.p, c, s2.p, 1, nullptr,
@@ -1894,7 +1926,7 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     fill_u32(reinterpret_cast<uint32_t *>(child.p), 0u, (A + 3) / 4, st);
     k_child_flags<<<nb(A), 256, 0, st>>>(p2.p, order.p, A, nbnd.p + nr, child.p);
     k_extract2<<<nr, 64, std::max<uint32_t>(4, xcap / 8), st>>>(nbnd.p, bnd.p, nr, order.p, p2.p,
-                                                                child.p, used.p, tmp.p, fin, xcap);
+                                                                child.p, used.p, tmp.p, fin, xcap, large.p);
     SDF_HIP(hipGetLastError());
     DevBuf<uint64_t> foff(n + 1);
     scan_u32_to_u64(fcount.p, foff.p, n, st);
@@ -1930,7 +1962,11 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
                                        roff.p, seg.p, fanchor.p);
     SDF_HIP(hipGetLastError());
     if (NS) {
-        const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 14);
+        // stretches a thread takes: a thread needs about 0.25 us per cell whatever
+        // else runs, so a call of few stretches waits for its longest, while a wave
+        // is as fast overall (50 Mbp, all regions: 247, 237, 237, 241 ms at 16,384,
+        // 4,096, 2,048, 1,024 cells; 3 Mbp: 11.3, 7.6, 7.0, 6.6 ms)
+        const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 11);
         const uint32_t wave_cols = min(knob(tuning().align_wave_lds_cols, WAVE_COLS), WAVE_COLS);
         DevBuf<uint32_t> okey(NS), order(NS);
         DevBuf<unsigned long long> mcount(3);
