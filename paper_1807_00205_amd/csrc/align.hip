@@ -1964,8 +1964,8 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     if (NS) {
         // stretches a thread takes: a thread needs about 0.25 us per cell whatever
         // else runs, so a call of few stretches waits for its longest, while a wave
-        // is as fast overall (50 Mbp, all regions: 247, 237, 237, 241 ms at 16,384,
-        // 4,096, 2,048, 1,024 cells; 3 Mbp: 11.3, 7.6, 7.0, 6.6 ms)
+        // is as fast overall (50 Mbp, all regions: 198.3, 190.8, 190.4, 194.4, 199.7 ms
+        // at 8,192, 4,096, 2,048, 1,024, 512 cells; 3 Mbp: 8.0, 6.5, 5.9, 5.5, 5.3 ms)
         const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 11);
         const uint32_t wave_cols = min(knob(tuning().align_wave_lds_cols, WAVE_COLS), WAVE_COLS);
         DevBuf<uint32_t> okey(NS), order(NS);
