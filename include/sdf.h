@@ -422,8 +422,8 @@ typedef struct {
     uint32_t ext_stats;           /* 1: one line of extension counters on stderr per call */
     uint32_t align_wave_cells;    /* final SDs: stretches of at least this many cells are
                                      aligned by one wave each */
-    uint32_t align_wave_lds_cols; /* final SDs: the most columns whose previous row such a
-                                     wave keeps in LDS (at most 4,096; global memory above) */
+    uint32_t align_wave_lds_cols; /* without effect: such a wave keeps its rows in registers,
+                                     whatever the stretch's size */
     uint32_t align_lds_blocks;    /* final SDs: end-order blocks of 64 anchors or nodes per
                                      region whose bounds the chaining tiers keep in LDS
                                      (at most 4,096; later blocks are read from memory and

@@ -1096,18 +1096,39 @@ __device__ __forceinline__ uint64_t seg_cells(uint32_t dx, uint32_t dy) {
     return c <= DP_CELLS ? c : 0;  // 0: the diagonal stand-in, no table
 }
 
-// Traceback tables hold one byte per cell, row by row, each row padded to a
-// multiple of 8 bytes (tables start at multiples of 8 too), so that the
-// thread aligner writes eight cells of a row with one 8-byte store.
-__device__ __forceinline__ uint32_t tb_pitch(uint32_t dy) { return (dy + 1 + 7) & ~7u; }
+// Traceback tables hold one byte per cell, line by line, each line padded to
+// a multiple of 8 bytes (tables start at multiples of 8 too), so that eight
+// cells of a line are written with one 8-byte store.  A line is a row (query
+// base i), except in the wave aligner's tables of stretches with dx > dy,
+// whose lines are columns (target base j); room for either.
+__device__ __forceinline__ uint32_t tb_pitch(uint32_t d) { return (d + 1 + 7) & ~7u; }
 __device__ __forceinline__ uint64_t seg_tb_bytes(uint32_t dx, uint32_t dy) {
-    return seg_cells(dx, dy) ? (uint64_t)(dx + 1) * tb_pitch(dy) : 0;
+    if (!seg_cells(dx, dy)) return 0;
+    const uint64_t rows = (uint64_t)(dx + 1) * tb_pitch(dy);
+    const uint64_t cols = (uint64_t)(dy + 1) * tb_pitch(dx);
+    return dx > dy && cols > rows ? cols : rows;
+}
+
+// Stretches of at least `wave_cells` cells are aligned by one 64-lane
+// workgroup each (k_align_wave), which holds the shorter side in its
+// registers: at most 1,024 of its DP_CELLS cells' lines, WAVE_S per lane.  The
+// others are aligned by one thread each (k_align_segs).
+constexpr uint32_t WAVE_S = 16;
+static_assert((uint64_t)(64 * WAVE_S) * (64 * WAVE_S) >= DP_CELLS, "the shorter side fits");
+__device__ __forceinline__ bool seg_wave(uint32_t dx, uint32_t dy, uint32_t wave_cells) {
+    const uint64_t c = seg_cells(dx, dy);
+    return c && c >= wave_cells;
+}
+// Rolling score cells a stretch needs in memory: the thread aligner's.
+__device__ __forceinline__ uint64_t seg_rows(uint32_t dx, uint32_t dy, uint32_t wave_cells) {
+    return seg_cells(dx, dy) && !seg_wave(dx, dy, wave_cells) ? 3ull * (dy + 1) : 0;
 }
 
 // 5a. per final chain: stretches, traceback bytes, column operations
 __global__ void k_seg_count(const Anchors an, const Chains1 c, const Final fin,
                             const uint64_t *foff, uint32_t nr, const uint32_t *nbnd, uint64_t nf,
-                            uint32_t *nseg, uint64_t *ncell, uint64_t *nops, uint64_t *nrow) {
+                            uint32_t wave_cells, uint32_t *nseg, uint64_t *ncell, uint64_t *nops,
+                            uint64_t *nrow) {
     const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= nf) return;
     uint32_t r, e;
@@ -1120,10 +1141,9 @@ __global__ void k_seg_count(const Anchors an, const Chains1 c, const Final fin,
             uint32_t o = 0, dx = 0, dy = 0;
             link_trim(px, py, an.x[a], an.y[a], an.len[a], o, dx, dy);
             ns++;
-            const uint64_t cc = seg_cells(dx, dy);
             cells += seg_tb_bytes(dx, dy);
             ops += (uint64_t)dx + dy;
-            rows += cc ? 3ull * (dy + 1) : 0;
+            rows += seg_rows(dx, dy, wave_cells);
         }
         first = false;
         px = an.x[a] + an.len[a];
@@ -1138,7 +1158,8 @@ __global__ void k_seg_count(const Anchors an, const Chains1 c, const Final fin,
 __global__ void k_seg_emit(const Anchors an, const Chains1 c, const Final fin,
                            const uint64_t *foff, uint32_t nr, const uint32_t *nbnd, uint64_t nf,
                            const uint64_t *soff, const uint64_t *coff, const uint64_t *ooff,
-                           const uint64_t *roff, Seg *seg, uint32_t *fanchor) {
+                           const uint64_t *roff, uint32_t wave_cells, Seg *seg,
+                           uint32_t *fanchor) {
     const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= nf) return;
     uint32_t r, e;
@@ -1162,10 +1183,9 @@ __global__ void k_seg_emit(const Anchors an, const Chains1 c, const Final fin,
             x.ops = ops;
             x.rows = rows;
             seg[s++] = x;
-            const uint64_t cc = seg_cells(x.dx, x.dy);
             cells += seg_tb_bytes(x.dx, x.dy);
             ops += (uint64_t)x.dx + x.dy;
-            rows += cc ? 3ull * (x.dy + 1) : 0;
+            rows += seg_rows(x.dx, x.dy, wave_cells);
         } else {  // the chain's first anchor, kept whole
             first3[0] = an.x[a];
             first3[1] = an.y[a];
@@ -1177,22 +1197,9 @@ __global__ void k_seg_emit(const Anchors an, const Chains1 c, const Final fin,
     });
 }
 
-constexpr int NEG = -1000000000;
-
-// Stretches of at least `wave_cells` cells are aligned by one 64-lane
-// workgroup each (k_align_wave), with the previous row in LDS up to
-// WAVE_COLS columns and in the stretch's global rows beyond; the others by
-// one thread each (k_align_segs).
-constexpr uint32_t WAVE_S = 64;              // columns per lane in LDS at most
-constexpr uint32_t WAVE_COLS = 64 * WAVE_S;  // 4,096 columns
-enum : uint32_t { SEG_THREAD = 0, SEG_WAVE_LDS = 1, SEG_WAVE_GLOBAL = 2 };
-// wave_cols: the most columns whose previous row goes in LDS (<= WAVE_COLS)
-__device__ __forceinline__ uint32_t seg_mode(uint32_t dx, uint32_t dy, uint32_t wave_cells,
-                                             uint32_t wave_cols) {
-    const uint64_t c = seg_cells(dx, dy);
-    if (!c || c < wave_cells) return SEG_THREAD;
-    return dy + 1 <= wave_cols ? SEG_WAVE_LDS : SEG_WAVE_GLOBAL;
-}
+// States of the recurrence, the higher preferred among equal scores: in the
+// table (M), in a gap of the target (I), in a gap of the query (D).
+enum : uint32_t { ST_D = 0, ST_I = 1, ST_M = 2 };
 
 // Traceback byte of a cell (i, j): bits 0-1 the best state before a
 // diagonal step, 2-3 the source of the query-gap state, 4-5 of the
@@ -1200,49 +1207,46 @@ __device__ __forceinline__ uint32_t seg_mode(uint32_t dx, uint32_t dy, uint32_t 
 // (neither an N), so that the traceback reads no bases.
 constexpr uint8_t TB_EQ = 64;
 
-// One cell of the three-state recurrence (match 2, mismatch -4, a gap of L
-// bases -(4 + 2 L); ties to M, then I, then D) from its diagonal (p*), upper
-// (u*) and left (l*) neighbours: M, I, D and the traceback byte.  Cells
-// outside the table, and states that cannot be reached, hold values near
-// NEG: they stay far below every reachable score (a step moves a value by 6
+// Scores are held as 4 * score + state, so that one maximum of three picks the
+// best score, settles ties (M, then I, then D) and says which state it was.
+// Cells outside the table, and states that cannot be reached, hold values near
+// NEG: they stay far below every reachable score (a step moves a value by 24
 // at most and a stretch has fewer than 2^21 steps, so they stay within
-// 1.3e7 of NEG = -1e9, and reachable scores above -1.3e7), so they never win
+// 5.1e7 of NEG = -4e8, and reachable values above -5.1e7), so they never win
 // against a reachable state and need no test of their own; the traceback
 // never enters them.
-__device__ __forceinline__ uint8_t cell(int pm, int pi, int pd, int um, int ui, int ud, int lm,
-                                        int li, int ld, bool eq, int &m, int &ii, int &dd) {
-    constexpr int GO = 4, GE = 2, MA = 2, MI = -4;
-    int best = pm;
-    uint32_t sm = 0;
-    if (pi > best) { best = pi; sm = 1; }
-    if (pd > best) { best = pd; sm = 2; }
-    m = best + (eq ? MA : MI);
-    ii = um - GO - GE;
-    uint32_t si = 0;
-    if (ui - GE > ii) { ii = ui - GE; si = 1; }
-    if (ud - GO - GE > ii) { ii = ud - GO - GE; si = 2; }
-    dd = lm - GO - GE;
-    uint32_t sd = 0;
-    if (li - GO - GE > dd) { dd = li - GO - GE; sd = 1; }
-    if (ld - GE > dd) { dd = ld - GE; sd = 2; }
-    return (uint8_t)(sm | (si << 2) | (sd << 4) | (eq ? TB_EQ : 0));
+constexpr int NEG = -400000000;
+__device__ __forceinline__ int max3(int a, int b, int c) { return max(max(a, b), c); }
+
+// One cell of the three-state recurrence (match 2, mismatch -4, a gap of L
+// bases -(4 + 2 L)) from its diagonal (p*), upper (u*) and left (l*)
+// neighbours: M, I, D and the traceback byte.
+__device__ __forceinline__ uint32_t cell(int pm, int pi, int pd, int um, int ui, int ud, int lm,
+                                         int li, int ld, bool eq, int &m, int &ii, int &dd) {
+    constexpr int OPEN = -4 * 6, EXT = -4 * 2, MA = 4 * 2, MI = -4 * 4;
+    const int b = max3(pm, pi, pd);
+    m = (b | 3) + (eq ? MA - 1 : MI - 1);  // 4 * score + ST_M
+    const int x = max3(um + OPEN, ui + EXT, ud + OPEN);
+    ii = (x | 3) - 2;                      // + ST_I
+    const int y = max3(lm + OPEN, li + OPEN, ld + EXT);
+    dd = y & ~3;                           // + ST_D
+    return ((uint32_t)b & 3u) | (((uint32_t)x & 3u) << 2) | (((uint32_t)y & 3u) << 4) |
+           (eq ? TB_EQ : 0);
 }
 
-
 // The traceback of a filled stretch (table rows P bytes apart) from its end
-// state st (0 M, 1 I, 2 D): column operations written to out in order;
-// returns their number.
-__device__ uint32_t trace_back(const Seg &S, const uint8_t *T, uint32_t P, int st,
+// state st: column operations written to out in order; returns their number.
+__device__ uint32_t trace_back(const Seg &S, const uint8_t *T, uint32_t P, uint32_t st,
                                uint8_t *out) {
     uint32_t i = S.dx, j = S.dy, n = 0;
     while (i > 0 || j > 0) {
         const uint8_t code = T[(uint64_t)i * P + j];
-        if (st == 0) {
+        if (st == ST_M) {
             out[n++] = (code & TB_EQ) ? OP_EQ : OP_X;
             st = code & 3;
             i--;
             j--;
-        } else if (st == 1) {
+        } else if (st == ST_I) {
             out[n++] = OP_I;
             st = (code >> 2) & 3;
             i--;
@@ -1261,27 +1265,26 @@ __device__ uint32_t trace_back(const Seg &S, const uint8_t *T, uint32_t P, int s
     return n;
 }
 
-// The stretches by the aligner that takes them (a stable sort on the mode:
+// The stretches by the aligner that takes them (a stable sort on the class:
 // the thread aligner's first, in chain order, whose neighbours share cache
-// lines; then the wave aligner's, LDS rows before global ones), so that
-// each aligner is launched on its own stretches only.  counts[m]: stretches
-// of mode m.  (Ordering the thread aligner's stretches by size, for alike
-// work per wave, was slower: it scatters the lanes' memory.)
-__global__ void k_seg_order(const Seg *seg, uint64_t ns, uint32_t wave_cells, uint32_t wave_cols,
-                            uint32_t *key, uint32_t *val, unsigned long long *counts) {
+// lines; then the wave aligner's, those with the most lines per lane first, as
+// they take longest).  count: the thread aligner's.  (Ordering the thread
+// aligner's stretches by size, for alike work per wave, was slower: it
+// scatters the lanes' memory.)
+__global__ void k_seg_order(const Seg *seg, uint64_t ns, uint32_t wave_cells, uint32_t *key,
+                            uint32_t *val, unsigned long long *count) {
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t mode = 3;
+    bool thread = false;
     if (t < ns) {
         const Seg S = seg[t];
-        mode = seg_mode(S.dx, S.dy, wave_cells, wave_cols);
-        key[t] = mode;
+        thread = !seg_wave(S.dx, S.dy, wave_cells);
+        const uint32_t side = min(S.dx, S.dy);
+        key[t] = thread ? 0u : side >= 512 ? 1u : side >= 256 ? 2u : side >= 64 ? 3u : 4u;
         val[t] = (uint32_t)t;
     }
-    for (uint32_t m = 0; m < 3; m++) {  // one atomic per wave and mode
-        const uint64_t b = __ballot(mode == m);
-        if (b && (threadIdx.x % 64) == (uint32_t)__builtin_ctzll(b))
-            atomicAdd(counts + m, (unsigned long long)__popcll(b));
-    }
+    const uint64_t b = __ballot(thread);  // one atomic per wave
+    if (b && (threadIdx.x % 64) == (uint32_t)__builtin_ctzll(b))
+        atomicAdd(count, (unsigned long long)__popcll(b));
 }
 
 // 5b. one thread per stretch: the three-state affine recurrence (match 2,
@@ -1348,9 +1351,9 @@ __global__ void k_align_segs(const IndexView ix, const ARegion *reg, const Seg *
                 const uint32_t j = j0 + q;
                 if (j > dy) break;
                 int m, ii, dd;
-                const uint8_t code = cell(pm, pi, pd, um[q], ui[q], ud[q], lm, li, ld,
+                const uint32_t code = cell(pm, pi, pd, um[q], ui[q], ud[q], lm, li, ld,
                                           qa < 4 && qa == tbv[q], m, ii, dd);
-                if (i == 0 && j == 0) m = 0;
+                if (i == 0 && j == 0) m = ST_M;
                 pm = um[q];
                 pi = ui[q];
                 pd = ud[q];
@@ -1365,96 +1368,181 @@ __global__ void k_align_segs(const IndexView ix, const ARegion *reg, const Seg *
             *reinterpret_cast<uint64_t *>(T + (uint64_t)i * P + j0) = codes;
         }
     }
-    // end state: ties M, then I, then D
-    int st = 0;
-    {
-        int best = Mr[dy];
-        if (Ir[dy] > best) { best = Ir[dy]; st = 1; }
-        if (Dr[dy] > best) { best = Dr[dy]; st = 2; }
-    }
+    const uint32_t st = (uint32_t)max3(Mr[dy], Ir[dy], Dr[dy]) & 3u;  // end state
     ncol[t] = trace_back(S, T, P, st, out);
 }
 
+// v of the lane before (lane 0: `first`).
+__device__ __forceinline__ int lane_before(int v, int first) {
+    return __builtin_amdgcn_update_dpp(first, v, 0x138 /* wave_shr:1 */, 0xf, 0xf, false);
+}
+
+// The table of one stretch, filled by a wave (k_align_wave): a lane holds SW
+// lines of the shorter side (na + 1 lines in all; rows when ROWS, else
+// columns) and walks the longer one (positions 0..nb), position s - lane at
+// step s.  T: line a's traceback bytes at T + a * P, eight to a store.
+// Returns the end state.
+template <uint32_t SW, bool ROWS>
+__device__ __forceinline__ uint32_t fill_wave(const IndexView &ix, const ARegion &R, const Seg &S,
+                                              uint32_t na, uint32_t nb, uint8_t *T, uint32_t P) {
+    const uint32_t lane = threadIdx.x, a0 = lane * SW;
+    // base d - 1 of the lanes' side and of the walked side
+    const auto line_base = [&](uint32_t d) {
+        return ROWS ? base_at(ix, R.q0 + S.qx + d - 1) : t_base(ix, R, S.ty + d - 1);
+    };
+    const auto walk_base = [&](uint32_t d) {
+        return d == 0 || d > nb ? 4u
+               : ROWS           ? t_base(ix, R, S.ty + d - 1)
+                                : base_at(ix, R.q0 + S.qx + d - 1);
+    };
+    uint32_t lb[SW];                 // 5 where nothing matches: no walked base is 5
+    int M[SW], I[SW], D[SW];         // position b - 1 of each line, then b in place
+    uint32_t lo[SW], hi[SW];         // each line's last eight traceback bytes
+#pragma unroll
+    for (uint32_t k = 0; k < SW; k++) {
+        const uint32_t a = a0 + k;
+        lb[k] = a >= 1 && a <= na ? line_base(a) : 5u;
+        if (lb[k] == 4) lb[k] = 5;
+        M[k] = I[k] = D[k] = NEG;
+        lo[k] = hi[k] = 0;
+    }
+    // the last line of the lane at its last position, and (position b - 1, the
+    // line before the lane's first), which for cell (0, 0) stands for a
+    // mismatch away from score 0
+    int oM = NEG, oI = NEG, oD = NEG;
+    int gM = lane == 0 ? 4 * 4 + (int)ST_M : NEG, gI = NEG, gD = NEG;
+    uint32_t wb = 4, ahead = walk_base(lane);
+    const uint32_t steps = nb + 1 + na / SW;
+    for (uint32_t s0 = 0; s0 < steps; s0 += 64) {
+        const uint32_t now = ahead;  // lane l: walked base of position s0 + l
+        ahead = walk_base(s0 + 64 + lane);
+        const uint32_t su = min(64u, steps - s0);
+        for (uint32_t u = 0; u < su; u++) {
+            const uint32_t b = s0 + u - lane;  // wraps below 0
+            wb = (uint32_t)lane_before((int)wb, __builtin_amdgcn_readlane((int)now, (int)u));
+            const int iM = lane_before(oM, NEG), iI = lane_before(oI, NEG),
+                      iD = lane_before(oD, NEG);
+            if (b <= nb) {
+                int pm = gM, pi = gI, pd = gD;  // position b - 1, the line before
+                int cm = iM, ci = iI, cd = iD;  // position b, the line before
+#pragma unroll
+                for (uint32_t k = 0; k < SW; k++) {
+                    const int vm = M[k], vi = I[k], vd = D[k];
+                    const uint32_t code =
+                        ROWS ? cell(pm, pi, pd, cm, ci, cd, vm, vi, vd, wb == lb[k], M[k], I[k],
+                                    D[k])
+                             : cell(pm, pi, pd, vm, vi, vd, cm, ci, cd, wb == lb[k], M[k], I[k],
+                                    D[k]);
+                    lo[k] = __builtin_amdgcn_alignbyte(hi[k], lo[k], 1);
+                    hi[k] = __builtin_amdgcn_alignbyte(code, hi[k], 1);
+                    pm = vm;
+                    pi = vi;
+                    pd = vd;
+                    cm = M[k];
+                    ci = I[k];
+                    cd = D[k];
+                }
+                oM = cm;
+                oI = ci;
+                oD = cd;
+                if ((b & 7) == 7 || b == nb) {
+                    const uint32_t sh = 8 * (7 - (b & 7));
+                    uint8_t *at = T + (uint64_t)a0 * P + (b & ~7u);
+#pragma unroll
+                    for (uint32_t k = 0; k < SW; k++, at += P)
+                        if (a0 + k <= na)
+                            *reinterpret_cast<uint64_t *>(at) =
+                                (((uint64_t)hi[k] << 32) | lo[k]) >> sh;
+                }
+            }
+            gM = iM;
+            gI = iI;
+            gD = iD;
+        }
+    }
+    int end = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < SW; k++)
+        if (a0 + k == na) end = max3(M[k], I[k], D[k]);
+    return (uint32_t)__builtin_amdgcn_readlane(end, (int)(na / SW)) & 3u;
+}
+
+// The traceback of a table filled by a wave from its end state st: column
+// operations to out (room for dx + dy), in order; returns their number.
+// Cell (i, j) is at T + i * pi + j * pj.  The lanes look at the next 64 cells
+// of a run in one state at once: as the run goes on where the state's source
+// is the state itself, the first lane whose cell came from another one ends it.
+__device__ uint32_t trace_wave(uint32_t dx, uint32_t dy, const uint8_t *T, uint32_t pi,
+                               uint32_t pj, uint32_t st, uint8_t *out) {
+    const uint32_t lane = threadIdx.x, room = dx + dy;
+    uint32_t i = dx, j = dy, n = 0;
+    while (i > 0 || j > 0) {
+        const uint32_t most = st == ST_M ? min(i, j) : st == ST_I ? i : j;
+        if (most == 0) {  // never so in a filled table; the walk ends in any case
+            st = i ? ST_I : ST_D;
+            continue;
+        }
+        const uint32_t ci = i - (st == ST_D ? 0u : lane), cj = j - (st == ST_I ? 0u : lane);
+        uint32_t code = 0, src = 0;
+        if (lane < most) {
+            code = T[(uint64_t)ci * pi + (uint64_t)cj * pj];
+            src = (code >> (2 * (ST_M - st))) & 3u;
+        }
+        const uint64_t stop = __ballot(lane >= most || src != st);
+        uint32_t run = stop ? (uint32_t)__builtin_ctzll(stop) + 1 : 64u;
+        run = min(run, most);
+        if (lane < run)
+            out[room - 1 - n - lane] =
+                st == ST_M ? ((code & TB_EQ) ? OP_EQ : OP_X) : st == ST_I ? OP_I : OP_D;
+        if (st != ST_D) i -= run;
+        if (st != ST_I) j -= run;
+        n += run;
+        st = (uint32_t)__builtin_amdgcn_readlane((int)src, (int)(run - 1));
+    }
+    // to the front of the room
+    __syncthreads();
+    if (n < room)
+        for (uint32_t a = lane; a - lane < n; a += 64) {
+            const uint8_t v = a < n ? out[room - n + a] : (uint8_t)0;
+            if (a < n) out[a] = v;
+        }
+    return n;
+}
+
 // 5c. one 64-lane workgroup per large stretch, the same recurrence and tie
-// rules as k_align_segs.  Lane l owns columns [l * SW, (l + 1) * SW) (SW =
-// ceil((dy + 1) / 64)) and takes row i at step i + l: at each step it gets
-// from lane l - 1 that lane's last column of the row it finished in the
-// step before (the cell to the left) and keeps the value it got one step
-// earlier (the cell up and to the left); its own previous row lives in LDS
-// (GLOBAL false) or in the stretch's rows in global memory (GLOBAL true,
-// wider stretches).  Lane 0 then walks the traceback.
-template <bool GLOBAL>
+// rules as k_align_segs.  A step hands the last line of each lane to the next
+// lane (a move within the registers), so a stretch takes one step per position
+// of its longer side and one per lane in use; bound by the instructions of its
+// cells (about 25 each).  Rows in registers instead of 53 KB of LDS (three
+// waves per CU) or, past 4,096 columns, global memory; codes stored by eights;
+// and the traceback a run at a time by all lanes instead of a base at a time
+// by one: 39.8 -> 4.3 ms for the stretches from 2,048 cells of 50 Mbp's
+// regions.
 __global__ __launch_bounds__(64) void k_align_wave(const IndexView ix, const ARegion *reg,
                                                    const Seg *seg, const uint32_t *order,
-                                                   uint64_t ns, uint8_t *tb, int *rows,
-                                                   uint8_t *cols, uint32_t *ncol) {
-    __shared__ int LM[GLOBAL ? 1 : WAVE_COLS], LI[GLOBAL ? 1 : WAVE_COLS],
-        LD[GLOBAL ? 1 : WAVE_COLS];     // row i - 1, per column
-    __shared__ uint8_t TBc[WAVE_COLS];  // target base j - 1 of the first WAVE_COLS columns
+                                                   uint64_t ns, uint8_t *tb, uint8_t *cols,
+                                                   uint32_t *ncol) {
     if (blockIdx.x >= ns) return;
-    const uint32_t t = order[blockIdx.x];  // the stretch (k_seg_order's part for this mode)
+    const uint32_t t = order[blockIdx.x];  // the stretch (k_seg_order's wave part)
     const Seg S = seg[t];
-    const uint32_t dx = S.dx, dy = S.dy;
     const ARegion R = reg[S.region];
-    const uint32_t W = dy + 1, lane = threadIdx.x;
-    int *PM = GLOBAL ? rows + S.rows : LM;
-    int *PI = GLOBAL ? PM + W : LI;
-    int *PD = GLOBAL ? PI + W : LD;
-    const uint32_t SW = (W + 63) / 64;
-    const uint32_t c0 = min(W, lane * SW), c1 = min(W, c0 + SW);
     uint8_t *T = tb + S.cells;
-    const uint32_t P = tb_pitch(dy);
-    for (uint32_t j = lane; j < W && j < WAVE_COLS; j += 64)
-        TBc[j] = j ? (uint8_t)t_base(ix, R, S.ty + j - 1) : (uint8_t)4;
-    __syncthreads();
-    int oM = NEG, oI = NEG, oD = NEG;  // this lane's last column of its previous row
-    int gM = NEG, gI = NEG, gD = NEG;  // (row i - 1, column c0 - 1), received a step earlier
-    for (uint32_t step = 0; step < dx + 64; step++) {
-        // (row i, column c0 - 1): lane l - 1 finished row i in the step before
-        // (column -1 does not exist: lane 0 takes the unreachable value)
-        int inM = __shfl_up(oM, 1), inI = __shfl_up(oI, 1), inD = __shfl_up(oD, 1);
-        if (lane == 0) inM = inI = inD = NEG;
-        const int64_t irow = (int64_t)step - (int64_t)lane;
-        if (irow >= 0 && irow <= (int64_t)dx && c0 < c1) {
-            const uint32_t i = (uint32_t)irow;
-            const uint32_t qa = i ? base_at(ix, R.q0 + S.qx + i - 1) : 4u;
-            int pm = gM, pi = gI, pd = gD;     // row i - 1, column j - 1
-            int lm = inM, li = inI, ld = inD;  // row i, column j - 1
-            uint8_t *trow = T + (uint64_t)i * P;
-            for (uint32_t j = c0; j < c1; j++) {
-                const int um = i ? PM[j] : NEG, ui = i ? PI[j] : NEG, ud = i ? PD[j] : NEG;
-                int m, ii, dd;
-                const uint32_t tbase =
-                    j < WAVE_COLS ? (uint32_t)TBc[j] : t_base(ix, R, S.ty + j - 1);
-                const uint8_t code = cell(pm, pi, pd, um, ui, ud, lm, li, ld,
-                                          i > 0 && j > 0 && qa < 4 && qa == tbase, m, ii, dd);
-                if (i == 0 && j == 0) m = 0;
-                pm = um;
-                pi = ui;
-                pd = ud;
-                lm = m;
-                li = ii;
-                ld = dd;
-                PM[j] = m;
-                PI[j] = ii;
-                PD[j] = dd;
-                trow[j] = code;
-            }
-            oM = lm;
-            oI = li;
-            oD = ld;
-        }
-        gM = inM;
-        gI = inI;
-        gD = inD;
-    }
-    __syncthreads();  // row dx of every column is written
-    if (lane == 0) {
-        int st = 0, best = PM[dy];
-        if (PI[dy] > best) { best = PI[dy]; st = 1; }
-        if (PD[dy] > best) { best = PD[dy]; st = 2; }
-        ncol[t] = trace_back(S, T, P, st, cols + S.ops);
-    }
+    const uint32_t dx = S.dx, dy = S.dy;
+    const auto fill = [&](auto rows) {
+        constexpr bool ROWS = decltype(rows)::value;
+        const uint32_t na = ROWS ? dx : dy, nb = ROWS ? dy : dx, P = tb_pitch(nb);
+        if (na < 64) return fill_wave<1, ROWS>(ix, R, S, na, nb, T, P);
+        if (na < 128) return fill_wave<2, ROWS>(ix, R, S, na, nb, T, P);
+        if (na < 256) return fill_wave<4, ROWS>(ix, R, S, na, nb, T, P);
+        if (na < 512) return fill_wave<8, ROWS>(ix, R, S, na, nb, T, P);
+        return fill_wave<WAVE_S, ROWS>(ix, R, S, na, nb, T, P);
+    };
+    const bool rows = dx <= dy;
+    const uint32_t st = rows ? fill(std::true_type()) : fill(std::false_type());
+    __syncthreads();  // the table is written
+    const uint32_t n = trace_wave(dx, dy, T, rows ? tb_pitch(dy) : 1u, rows ? 1u : tb_pitch(dx),
+                                  st, cols + S.ops);
+    if (threadIdx.x == 0) ncol[t] = n;
 }
 
 struct SdOut {
@@ -1936,8 +2024,14 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     stage.emplace("sdf final SDs: alignment");
     DevBuf<uint32_t> nseg(NF + 1);
     DevBuf<uint64_t> ncell(NF + 1), nops(NF + 1), nrow(NF + 1);
-    k_seg_count<<<nb(NF), 256, 0, st>>>(an, c, fin, foff.p, nr, nbnd.p, NF, nseg.p, ncell.p,
-                                        nops.p, nrow.p);
+    // Stretches a thread takes: a thread needs about 0.25 us per cell whatever
+    // else runs, so a call of few stretches waits for its longest; a wave is
+    // idle in most lanes on a small one (50 Mbp, all regions: 161, 155.3, 151.2,
+    // 150.2, 149.7, 149.8, 150.1, 151.3 ms from 4,096, 2,048, 1,024, 512, 256,
+    // 128, 64, 1 cells up; 3 Mbp: 6.3, 5.7, 5.3, 5.0, 4.9, 4.8, 4.8, 4.8 ms).
+    const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 8);
+    k_seg_count<<<nb(NF), 256, 0, st>>>(an, c, fin, foff.p, nr, nbnd.p, NF, wave_cells, nseg.p,
+                                        ncell.p, nops.p, nrow.p);
     SDF_HIP(hipGetLastError());
     DevBuf<uint64_t> soff(NF + 1), coff(NF + 1), ooff(NF + 1), roff(NF + 1);
     scan_u32_to_u64(nseg.p, soff.p, NF, st);
@@ -1959,42 +2053,23 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     DevBuf<uint32_t> ncol(NS + 1);
     DevBuf<uint32_t> fanchor(3 * NF);
     k_seg_emit<<<nb(NF), 256, 0, st>>>(an, c, fin, foff.p, nr, nbnd.p, NF, soff.p, coff.p, ooff.p,
-                                       roff.p, seg.p, fanchor.p);
+                                       roff.p, wave_cells, seg.p, fanchor.p);
     SDF_HIP(hipGetLastError());
     if (NS) {
-        // stretches a thread takes: a thread needs about 0.25 us per cell whatever
-        // else runs, so a call of few stretches waits for its longest, while a wave
-        // is as fast overall (50 Mbp, all regions: 198.3, 190.8, 190.4, 194.4, 199.7 ms
-        // at 8,192, 4,096, 2,048, 1,024, 512 cells; 3 Mbp: 8.0, 6.5, 5.9, 5.5, 5.3 ms)
-        const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 11);
-        const uint32_t wave_cols = min(knob(tuning().align_wave_lds_cols, WAVE_COLS), WAVE_COLS);
         DevBuf<uint32_t> okey(NS), order(NS);
-        DevBuf<unsigned long long> mcount(3);
-        fill_u32(reinterpret_cast<uint32_t *>(mcount.p), 0u, 6, st);
-        k_seg_order<<<nb(NS, 256), 256, 0, st>>>(seg.p, NS, wave_cells, wave_cols, okey.p, order.p,
-                                                 mcount.p);
+        DevBuf<unsigned long long> tcount(1);
+        fill_u32(reinterpret_cast<uint32_t *>(tcount.p), 0u, 2, st);
+        k_seg_order<<<nb(NS, 256), 256, 0, st>>>(seg.p, NS, wave_cells, okey.p, order.p, tcount.p);
         SDF_HIP(hipGetLastError());
-        radix_sort_u32(okey.p, order.p, NS, 2, st);
-        unsigned long long mc[3] = {0, 0, 0};
-        {
-            Readback rb(st);
-            rb.add(mc, mcount.p, sizeof(mc));
-            rb.wait();
-        }
-        if (mc[SEG_THREAD])
-            k_align_segs<<<nb(mc[SEG_THREAD], 64), 64, 0, st>>>(ix, dreg.p, seg.p, order.p,
-                                                               mc[SEG_THREAD], tb.p, rows.p,
-                                                               cols.p, ncol.p);
+        radix_sort_u32(okey.p, order.p, NS, 3, st);
+        const uint64_t nthread = read1(tcount.p, st);
+        if (nthread)
+            k_align_segs<<<nb(nthread, 64), 64, 0, st>>>(ix, dreg.p, seg.p, order.p, nthread, tb.p,
+                                                        rows.p, cols.p, ncol.p);
         SDF_HIP(hipGetLastError());
-        if (mc[SEG_WAVE_LDS])
-            k_align_wave<false><<<(unsigned)mc[SEG_WAVE_LDS], 64, 0, st>>>(
-                ix, dreg.p, seg.p, order.p + mc[SEG_THREAD], mc[SEG_WAVE_LDS], tb.p, rows.p, cols.p,
-                ncol.p);
-        SDF_HIP(hipGetLastError());
-        if (mc[SEG_WAVE_GLOBAL])
-            k_align_wave<true><<<(unsigned)mc[SEG_WAVE_GLOBAL], 64, 0, st>>>(
-                ix, dreg.p, seg.p, order.p + mc[SEG_THREAD] + mc[SEG_WAVE_LDS],
-                mc[SEG_WAVE_GLOBAL], tb.p, rows.p, cols.p, ncol.p);
+        if (NS > nthread)
+            k_align_wave<<<(unsigned)(NS - nthread), 64, 0, st>>>(
+                ix, dreg.p, seg.p, order.p + nthread, NS - nthread, tb.p, cols.p, ncol.p);
         SDF_HIP(hipGetLastError());
     }
     // 6. records and CIGAR
