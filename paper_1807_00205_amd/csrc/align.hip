@@ -6,11 +6,10 @@
 // the header of sdf_align_regions (include/sdf.h).
 //
 // Device pipeline, all regions of a call at once:
-//   1. every k-mer of every target side T' (the target read reverse-
-//      complemented on strand 1) as a key (region, k-mer, position), radix
-//      sorted on its region and k-mer bits, every 32nd key sampled; every
-//      query k-mer finds its target occurrences through the samples; seeds
-//      occurring more than 32 times are skipped;
+//   1. one workgroup per 16,384 to 65,536 query positions of a region puts the k-mers of
+//      the target side T' (the target read reverse-complemented on strand 1)
+//      in buckets in LDS, and every query k-mer finds its target occurrences
+//      there; seeds occurring more than 32 times are skipped;
 //   2. matches as keys (region, diagonal, query position), radix sorted;
 //      maximal runs of consecutive positions on a diagonal are the anchors;
 //   3. tier 1: one workgroup per region scores its anchors 64 at a time in
@@ -76,30 +75,6 @@ __device__ __forceinline__ uint32_t region_of(const uint64_t *off, uint32_t nr, 
     return lo;
 }
 
-// 1a. target k-mer keys: region << 42 | k-mer << 20 | position (~0 for none)
-__global__ void k_t_keys(const IndexView ix, const ARegion *reg, uint32_t nr, const uint64_t *toff,
-                         uint64_t total, uint32_t k, uint64_t *key, uint32_t *val) {
-    for (uint64_t f = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; f < total;
-         f += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t r = region_of(toff, nr, f);
-        const ARegion R = reg[r];
-        const uint64_t y = f - toff[r], nt = R.t1 - R.t0;
-        uint64_t out = ~0ull;
-        if (y + k <= nt) {
-            uint64_t code = 0;
-            bool ok = true;
-            for (uint32_t t = 0; t < k && ok; t++) {
-                const uint32_t c = t_base(ix, R, y + t);
-                ok = c < 4;
-                code = code * 4 + c;
-            }
-            if (ok) out = ((uint64_t)r << 42) | (code << 20) | y;
-        }
-        key[f] = out;
-        val[f] = 0;
-    }
-}
-
 __device__ __forceinline__ uint64_t first_at_least(const uint64_t *key, uint64_t n, uint64_t x) {
     uint64_t lo = 0, hi = n;
     while (lo < hi) {
@@ -109,86 +84,173 @@ __device__ __forceinline__ uint64_t first_at_least(const uint64_t *key, uint64_t
     return lo;
 }
 
-// Every TS-th target key (smp[i] = tkey[TS i]): a search first finds its
-// block of TS keys among the samples (a small array that stays in cache)
-// and then its key inside the block, so that it reads few lines of the
-// large key array.
-constexpr uint64_t TS = 32;
+// Seeds: a workgroup joins a part of a region's query positions with its target
+// side, SEED_Y start positions at a time, held in LDS by the buckets of a
+// one-to-one hash of their k-mers (76 KB: two workgroups per CU).
+constexpr uint32_t SEED_THREADS = 1024;
+constexpr uint32_t SEED_XLO = 16384, SEED_XHI = 65536;  // query positions per workgroup
+constexpr uint32_t SEED_Y = 15 * SEED_THREADS;
+constexpr uint32_t SEED_BITS = 13, SEED_TAG = 22 - SEED_BITS, SEED_POS = 14;
+constexpr uint32_t SEED_BUCKETS = 1u << SEED_BITS;
+static_assert(SEED_Y <= 1u << SEED_POS, "an entry holds its position");
+constexpr uint32_t SEED_NOT = 63u << 22;  // no k-mer: as if it occurred too often
+static_assert(MAXOCC + 1 < 63, "counts up to MAXOCC + 1 and SEED_NOT's fit above 22 bits");
+struct SeedWork {
+    uint32_t region, x0, x1;  // query positions [x0, x1) of the region
+};
 
-__global__ void k_key_samples(const uint64_t *key, uint64_t n, uint64_t *smp) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i * TS < n) smp[i] = key[i * TS];
+// The k-mer (k <= 11) at global position p, its first base lowest; false when
+// it holds a gap base.
+__device__ __forceinline__ bool kmer_at(const IndexView &ix, uint64_t p, uint32_t k,
+                                        uint32_t &code) {
+    const uint64_t e = p + k - 1;
+    const uint64_t g = ((uint64_t)ix.gaps[e >> 5] << 32) | ix.gaps[p >> 5];
+    const uint64_t b = ((uint64_t)ix.packed[e >> 4] << 32) | ix.packed[p >> 4];
+    code = (uint32_t)(b >> (2 * (p & 15))) & ((1u << (2 * k)) - 1);
+    return ((uint32_t)(g >> (p & 31)) & ((1u << k) - 1)) == 0;
+}
+__device__ __forceinline__ uint32_t revcomp_kmer(uint32_t c, uint32_t k) {
+    const uint32_t r = __builtin_bitreverse32(~c);  // base order and each base's bits turned
+    return (((r >> 1) & 0x55555555u) | ((r & 0x55555555u) << 1)) >> (32 - 2 * k);
+}
+// One to one on 22 bits: the upper SEED_BITS are the bucket, the rest the tag.
+__device__ __forceinline__ uint32_t kmer_mix(uint32_t code) {
+    return (code * 0x9E3779B1u) & ((1u << 22) - 1);
 }
 
-// first_at_least(key, n, x) through the samples smp[0, (n + TS - 1) / TS).
-__device__ __forceinline__ uint64_t first_at_least_s(const uint64_t *key, uint64_t n,
-                                                     const uint64_t *smp, uint64_t x) {
-    uint64_t lo = 0, hi = (n + TS - 1) / TS;  // first sample >= x
-    while (lo < hi) {
-        const uint64_t m = (lo + hi) >> 1;
-        if (smp[m] < x) lo = m + 1; else hi = m;
+// 1. seed matches per query position (EMIT false: cnt[f], 0 for seeds that
+// occur more than MAXOCC times in T'), then the matches themselves (EMIT true:
+// keys region << 41 | (y - x + 2^20) << 20 | x at moff[f] on; cnt[f] counts
+// down).  A target position is kept by its start on the forward strand; on
+// strand 1 the query's k-mer is reverse-complemented instead.  A position
+// belongs to the same thread in every round over the target, so cnt needs no
+// atomics (between rounds it holds count << 22 | hash); buckets are in no fixed order, which nothing depends on: the
+// matches of a query position differ in their diagonals.
+// Bound by the instructions of a query position in every round, so an entry is
+// compared without another read (tag and position in one word), four at a
+// time, and the hash is taken once.  Sorting all targets' k-mers and searching
+// them for every query position took 41 ms of 50 Mbp's regions (264 Mbp on
+// either side); this takes 8.9 for the counts and 7.5 for the matches.
+template <bool EMIT>
+__global__ __launch_bounds__(SEED_THREADS, 8) void k_seeds(const IndexView ix, const ARegion *reg,
+                                                        const SeedWork *work, const uint64_t *qoff,
+                                                        uint32_t k, uint32_t *cnt,
+                                                        const uint64_t *moff, uint64_t *mkey) {
+    __shared__ uint32_t start[SEED_BUCKETS / 2 + 1];  // 16 bits per bucket: counts, ends, starts
+    __shared__ uint32_t entry[SEED_Y + 4];            // tag << SEED_POS | position
+    __shared__ uint32_t wsum[SEED_THREADS / 64];
+    const uint32_t tid = threadIdx.x;
+    const SeedWork w = work[blockIdx.x];
+    const ARegion R = reg[w.region];
+    const uint32_t nq = (uint32_t)(R.q1 - R.q0), nt = (uint32_t)(R.t1 - R.t0);
+    const uint64_t f0 = qoff[w.region];
+    const uint32_t starts = nt < k ? 0u : nt - k + 1;  // of target k-mers
+    if (starts == 0) {
+        if constexpr (!EMIT)
+            for (uint32_t x = w.x0 + tid; x < w.x1; x += SEED_THREADS) cnt[f0 + x] = 0;
+        return;
     }
-    // keys before sample lo - 1's are below x; sample lo's (if any) is >= x
-    uint64_t a = lo ? (lo - 1) * TS + 1 : 0, b = min(n, lo * TS);
-    while (a < b) {
-        const uint64_t m = (a + b) >> 1;
-        if (key[m] < x) a = m + 1; else b = m;
-    }
-    return a;
-}
-
-// The query k-mer at x of region R (false when it holds a gap base or ends
-// past the side).
-__device__ __forceinline__ bool q_kmer(const IndexView &ix, const ARegion &R, uint64_t x,
-                                       uint32_t k, uint64_t &code) {
-    if (x + k > R.q1 - R.q0) return false;
-    code = 0;
-    for (uint32_t t = 0; t < k; t++) {
-        const uint32_t c = base_at(ix, R.q0 + x + t);
-        if (c > 3) return false;
-        code = code * 4 + c;
-    }
-    return true;
-}
-
-// 1b. seed matches per query position (0 for seeds above MAXOCC), and where
-// their target keys start (qa, read by k_q_emit)
-__global__ void k_q_count(const IndexView ix, const ARegion *reg, uint32_t nr,
-                          const uint64_t *qoff, uint64_t total, uint32_t k, const uint64_t *tkey,
-                          uint64_t ntk, const uint64_t *smp, uint32_t *cnt, uint64_t *qa) {
-    for (uint64_t f = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; f < total;
-         f += (uint64_t)gridDim.x * blockDim.x) {
-        const uint32_t r = region_of(qoff, nr, f);
-        const ARegion R = reg[r];
-        uint64_t code;
-        uint32_t c = 0;
-        if (q_kmer(ix, R, f - qoff[r], k, code)) {
-            const uint64_t base = ((uint64_t)r << 42) | (code << 20);
-            const uint64_t a = first_at_least_s(tkey, ntk, smp, base);
-            // the occurrences end among the next MAXOCC + 1 keys, or there are too many
-            const uint64_t e = min(ntk, a + MAXOCC + 1);
-            const uint64_t b = a + first_at_least(tkey + a, e - a, base + (1ull << 20));
-            c = (b - a <= MAXOCC) ? (uint32_t)(b - a) : 0u;
-            if (c) qa[f] = a;
+    for (uint32_t g0 = 0; g0 < starts; g0 += SEED_Y) {
+        const uint32_t n = min(SEED_Y, starts - g0);
+        __syncthreads();  // the round before is done with the entries
+        for (uint32_t i = tid; i <= SEED_BUCKETS / 2; i += SEED_THREADS) start[i] = 0;
+        __syncthreads();
+        const auto target_mix = [&](uint32_t y, uint32_t &m) {
+            uint32_t code;
+            if (!kmer_at(ix, R.t0 + g0 + y, k, code)) return false;
+            m = kmer_mix(code);
+            return true;
+        };
+        uint32_t m;
+#pragma unroll 2
+        for (uint32_t y = tid; y < n; y += SEED_THREADS)
+            if (target_mix(y, m)) {
+                const uint32_t b = m >> SEED_TAG;
+                atomicAdd(&start[b >> 1], 1u << (16 * (b & 1)));
+            }
+        __syncthreads();
+        // counts to ends: eight buckets per thread
+        constexpr uint32_t PER = SEED_BUCKETS / 2 / SEED_THREADS;  // words per thread
+        uint32_t c[PER], sum = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < PER; u++) {
+            c[u] = start[tid * PER + u];
+            sum += (c[u] & 0xFFFFu) + (c[u] >> 16);
         }
-        cnt[f] = c;
-    }
-}
-
-// 2a. match keys: region << 41 | (y - x + 2^20) << 20 | x
-__global__ void k_q_emit(uint32_t nr, const uint64_t *qoff, uint64_t total, const uint64_t *tkey,
-                         const uint32_t *cnt, const uint64_t *qa, const uint64_t *moff,
-                         uint64_t *mkey, uint32_t *mval) {
-    for (uint64_t f = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; f < total;
-         f += (uint64_t)gridDim.x * blockDim.x) {
-        if (!cnt[f]) continue;
-        const uint32_t r = region_of(qoff, nr, f);
-        const uint64_t x = f - qoff[r], a = qa[f];
-        for (uint32_t t = 0; t < cnt[f]; t++) {
-            const uint64_t y = tkey[a + t] & 0xFFFFF;
-            const uint64_t d = y + (1ull << 20) - x;
-            mkey[moff[f] + t] = ((uint64_t)r << 41) | (d << 20) | x;
-            mval[moff[f] + t] = 0;
+        uint32_t at = sum;
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t v = __shfl_up(at, d);
+            if ((tid & 63) >= d) at += v;
+        }
+        if ((tid & 63) == 63) wsum[tid >> 6] = at;
+        __syncthreads();
+        at -= sum;
+        for (uint32_t v = 0; v < tid >> 6; v++) at += wsum[v];
+#pragma unroll
+        for (uint32_t u = 0; u < PER; u++) {
+            const uint32_t mid = at + (c[u] & 0xFFFFu);
+            at = mid + (c[u] >> 16);
+            start[tid * PER + u] = mid | (at << 16);
+        }
+        if (tid == SEED_THREADS - 1) start[SEED_BUCKETS / 2] = at;
+        __syncthreads();
+        // entries, from the end of each bucket: its end becomes its start
+#pragma unroll 2
+        for (uint32_t y = tid; y < n; y += SEED_THREADS)
+            if (target_mix(y, m)) {
+                const uint32_t b = m >> SEED_TAG, sh = 16 * (b & 1);
+                const uint32_t e = ((atomicSub(&start[b >> 1], 1u << sh) >> sh) & 0xFFFFu) - 1;
+                entry[e] = ((m & ((1u << SEED_TAG) - 1)) << SEED_POS) | y;
+            }
+        __syncthreads();
+        const bool last = g0 + SEED_Y >= starts;
+#pragma unroll 2
+        for (uint32_t x = w.x0 + tid; x < w.x1; x += SEED_THREADS) {
+            // matches so far (EMIT: to come), and the k-mer's hash
+            uint32_t left = EMIT || g0 ? cnt[f0 + x] : 0u;
+            if (g0 == 0) {
+                uint32_t code;
+                if (EMIT && left == 0) continue;
+                if (x + k > nq || !kmer_at(ix, R.q0 + x, k, code)) {
+                    if constexpr (!EMIT) cnt[f0 + x] = last ? 0u : SEED_NOT;
+                    continue;
+                }
+                m = kmer_mix(R.o ? revcomp_kmer(code, k) : code);
+            } else {
+                m = left & ((1u << 22) - 1);
+                left >>= 22;
+                if (EMIT ? left == 0 : left > MAXOCC) {
+                    if (!EMIT && last) cnt[f0 + x] = 0;
+                    continue;
+                }
+            }
+            const uint32_t b = m >> SEED_TAG, tag = m & ((1u << SEED_TAG) - 1);
+            const uint32_t s0 = start[b >> 1], s1 = start[(b >> 1) + 1];
+            const uint32_t e1 = b & 1 ? s1 & 0xFFFFu : s0 >> 16;
+            bool more = true;
+            for (uint32_t e = b & 1 ? s0 >> 16 : s0 & 0xFFFFu; e < e1 && more; e += 4) {
+                uint32_t v[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; q++) v[q] = entry[e + q];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; q++) {
+                    if (e + q >= e1 || (v[q] >> SEED_POS) != tag || !more) continue;
+                    if constexpr (EMIT) {
+                        const uint32_t y = g0 + (v[q] & ((1u << SEED_POS) - 1));
+                        const uint64_t ty = R.o ? starts - 1 - y : y;
+                        left--;
+                        mkey[moff[f0 + x] + left] =
+                            ((uint64_t)w.region << 41) | ((ty + (1ull << 20) - x) << 20) | x;
+                        more = left != 0;
+                    } else {
+                        more = ++left <= MAXOCC;
+                    }
+                }
+            }
+            if (!last)
+                cnt[f0 + x] = (left << 22) | m;
+            else if (!EMIT)
+                cnt[f0 + x] = left <= MAXOCC ? left : 0u;
         }
     }
 }
@@ -203,17 +265,22 @@ struct Anchors {
     uint32_t *reg, *x, *y, *len;
 };
 
-// 2b. anchors from the runs
-__global__ void k_anchor_emit(const uint64_t *mkey, uint64_t m, const uint32_t *flag,
-                              const uint32_t *pre, uint32_t k, Anchors an) {
+// 2b. the first match of each run, then an anchor per run (a run ends where
+// the next one starts)
+__global__ void k_run_first(const uint32_t *flag, const uint32_t *pre, uint64_t m,
+                            uint64_t *first) {
     const uint64_t f = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= m || !flag[f]) return;
-    uint64_t e = f + 1;
-    while (e < m && mkey[e] == mkey[e - 1] + 1) e++;
+    if (f < m && flag[f]) first[pre[f]] = f;
+}
+
+__global__ void k_anchor_emit(const uint64_t *mkey, uint64_t m, const uint64_t *first, uint64_t na,
+                              uint32_t k, Anchors an) {
+    const uint64_t a = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (a >= na) return;
+    const uint64_t f = first[a], e = a + 1 < na ? first[a + 1] : m;
     const uint64_t key = mkey[f];
     const uint32_t x = (uint32_t)(key & 0xFFFFF);
     const uint64_t d = (key >> 20) & 0x1FFFFF;
-    const uint32_t a = pre[f];
     an.reg[a] = (uint32_t)(key >> 41);
     an.x[a] = x;
     an.y[a] = (uint32_t)(d + x - (1ull << 20));
@@ -1788,7 +1855,6 @@ __global__ void k_u32_to_u64(const uint32_t *a, uint64_t n, uint64_t *b) {
 }
 
 unsigned nb(uint64_t n, unsigned t = 256) { return (unsigned)std::max<uint64_t>(1, (n + t - 1) / t); }
-unsigned grid_stride(uint64_t n) { return (unsigned)std::min<uint64_t>(nb(n), 65536); }
 
 template <class T>
 T read1(const T *d, hipStream_t st) {
@@ -1827,9 +1893,8 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     }
     const uint32_t nr = (uint32_t)n;
     DevBuf<ARegion> dreg(n);
-    DevBuf<uint64_t> toff(n + 1), qoff(n + 1);
+    DevBuf<uint64_t> qoff(n + 1);
     SDF_HIP(hipMemcpyAsync(dreg.p, hr.data(), n * sizeof(ARegion), hipMemcpyHostToDevice, st));
-    SDF_HIP(hipMemcpyAsync(toff.p, hto.data(), (n + 1) * 8, hipMemcpyHostToDevice, st));
     SDF_HIP(hipMemcpyAsync(qoff.p, hqo.data(), (n + 1) * 8, hipMemcpyHostToDevice, st));
     // the regions by falling size: one workgroup or wave takes a region in the
     // chaining kernels, and the largest take longest, so they start first
@@ -1840,51 +1905,43 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     });
     DevBuf<uint32_t> large(n);
     SDF_HIP(hipMemcpyAsync(large.p, hl.data(), n * 4, hipMemcpyHostToDevice, st));
-    const uint64_t TT = hto[n], QT = hqo[n];
+    const uint64_t QT = hqo[n];
     // key bits of a region number: every region number stays below 2^rbits - 1, so
     // no key of a region has all of its bits set like the sentinel ~0
     int rbits = 1;
     while ((1ull << rbits) <= (uint64_t)n) rbits++;
     std::optional<Range> stage;
     stage.emplace("sdf final SDs: seeds");
-    // 1. target keys, sorted
-    DevBuf<uint64_t> tkey(TT + 1);
-    DevBuf<uint32_t> tval(TT + 1);
-    if (TT) {
-        k_t_keys<<<grid_stride(TT), 256, 0, st>>>(ix, dreg.p, nr, toff.p, TT, k, tkey.p, tval.p);
-        SDF_HIP(hipGetLastError());
-        // (region, k-mer): the keys are made in position order, so equal ones keep y ascending
-        radix_sort_u64_bits(tkey.p, tval.p, TT, 20, 42 + rbits, st);
-    }
-    // samples of the target keys, matches per query position, their
-    // offsets, the matches sorted
-    DevBuf<uint64_t> smp((TT + TS - 1) / TS + 1);
-    if (TT) {
-        k_key_samples<<<nb((TT + TS - 1) / TS), 256, 0, st>>>(tkey.p, TT, smp.p);
-        SDF_HIP(hipGetLastError());
-    }
+    // 1. matches per query position, their offsets, the matches sorted
+    // Query positions per workgroup: every part of a large side builds the target's
+    // buckets anew, so parts are as long as leave some 2,048 workgroups (50 Mbp:
+    // 10.1, 8.9, 9.0 ms for the counts with at most 32,768, 65,536, 131,072).
+    const uint64_t xpart =
+        std::clamp<uint64_t>(QT / 2048 / SEED_XLO * SEED_XLO, SEED_XLO, SEED_XHI);
+    std::vector<SeedWork> hw;
+    for (const uint32_t r : hl)
+        for (uint64_t nq = hqo[r + 1] - hqo[r], x = 0; x < nq; x += xpart)
+            hw.push_back(SeedWork{r, (uint32_t)x, (uint32_t)std::min(nq, x + xpart)});
+    DevBuf<SeedWork> work(hw.size() + 1);
     DevBuf<uint32_t> qcnt(QT + 1);
-    DevBuf<uint64_t> moff(QT + 1), qa(QT + 1);
+    DevBuf<uint64_t> moff(QT + 1);
     if (QT) {
-        k_q_count<<<grid_stride(QT), 256, 0, st>>>(ix, dreg.p, nr, qoff.p, QT, k, tkey.p, TT,
-                                                   smp.p, qcnt.p, qa.p);
+        SDF_HIP(hipMemcpyAsync(work.p, hw.data(), hw.size() * sizeof(SeedWork),
+                               hipMemcpyHostToDevice, st));
+        k_seeds<false><<<(unsigned)hw.size(), SEED_THREADS, 0, st>>>(
+            ix, dreg.p, work.p, qoff.p, k, qcnt.p, nullptr, nullptr);
         SDF_HIP(hipGetLastError());
     }
     scan_u32_to_u64(qcnt.p, moff.p, QT, st);
     const uint64_t M = read1(moff.p + QT, st);
     DevBuf<uint64_t> mkey(M + 1);
-    DevBuf<uint32_t> mval(M + 1);
     if (M) {
-        k_q_emit<<<grid_stride(QT), 256, 0, st>>>(nr, qoff.p, QT, tkey.p, qcnt.p, qa.p, moff.p,
-                                                  mkey.p, mval.p);
+        k_seeds<true><<<(unsigned)hw.size(), SEED_THREADS, 0, st>>>(
+            ix, dreg.p, work.p, qoff.p, k, qcnt.p, moff.p, mkey.p);
         SDF_HIP(hipGetLastError());
         // (region, diagonal): the matches are made in x order within a region
-        radix_sort_u64_bits(mkey.p, mval.p, M, 20, 41 + rbits, st);
+        sort_keys_u64_bits(mkey.p, M, 20, 41 + rbits, st);
     }
-    tkey.reset();
-    tval.reset();
-    smp.reset();
-    qa.reset();
     // 2. anchors
     stage.emplace("sdf final SDs: anchors");
     DevBuf<uint32_t> flag(M + 1), fpre(M + 1);
@@ -1897,10 +1954,13 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     if (A == 0) return;
     DevBuf<uint32_t> areg(A), ax(A), ay(A), alen(A);
     Anchors an{areg.p, ax.p, ay.p, alen.p};
-    k_anchor_emit<<<nb(M), 256, 0, st>>>(mkey.p, M, flag.p, fpre.p, k, an);
+    DevBuf<uint64_t> rfirst(A);
+    k_run_first<<<nb(M), 256, 0, st>>>(flag.p, fpre.p, M, rfirst.p);
+    SDF_HIP(hipGetLastError());
+    k_anchor_emit<<<nb(A), 256, 0, st>>>(mkey.p, M, rfirst.p, A, k, an);
     SDF_HIP(hipGetLastError());
     mkey.reset();
-    mval.reset();
+    rfirst.reset();
     // orders by (region, x, y) and by (region, end x, end y)
     DevBuf<uint64_t> kxy(A), kend(A), kbuf(A);
     DevBuf<uint32_t> byxy(A), byend(A), byscore(A), perm(A);

@@ -475,7 +475,8 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_hist(const K *keys, DevCount 
 // a time; lanes with equal digits are ranked with eight ballots.  The tile is
 // first placed in LDS in digit order, then written out so that consecutive
 // threads store consecutive elements of one digit's run (coalesced).
-template <class K>
+// VALS false: keys alone.
+template <class K, bool VALS>
 __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const K *kin, const uint32_t *vin, K *kout,
                                                         uint32_t *vout, DevCount count, int shift,
                                                         const uint64_t *hoff, uint32_t nblocks) {
@@ -486,7 +487,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const K *kin, const u
     __shared__ uint32_t lstart[RS_BINS];  // first tile slot of each digit
     __shared__ uint32_t wsum[RS_WAVES];
     __shared__ K skey[RS_TILE];
-    __shared__ uint32_t sval[RS_TILE];
+    __shared__ uint32_t sval[VALS ? RS_TILE : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int i = threadIdx.x; i < RS_BINS; i += RS_THREADS) {
         boff[i] = hoff[(uint64_t)i * nblocks + blockIdx.x];
@@ -508,7 +509,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const K *kin, const u
         uint32_t d = 0;
         if (valid) {
             kk[r] = kin[idx];
-            vv[r] = vin[idx];
+            if constexpr (VALS) vv[r] = vin[idx];
             d = (uint32_t)(kk[r] >> shift) & (RS_BINS - 1);
         }
         uint64_t m = __ballot(valid);
@@ -559,7 +560,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const K *kin, const u
         if (idx < n) {
             const uint32_t at = lstart[dg[r]] + cnt[wave][dg[r]] + rk[r];
             skey[at] = kk[r];
-            sval[at] = vv[r];
+            if constexpr (VALS) sval[at] = vv[r];
         }
     }
     __syncthreads();
@@ -569,11 +570,11 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const K *kin, const u
         const uint32_t d = (uint32_t)(key >> shift) & (RS_BINS - 1);
         const uint64_t pos = boff[d] + (t - lstart[d]);
         kout[pos] = key;
-        vout[pos] = sval[t];
+        if constexpr (VALS) vout[pos] = sval[t];
     }
 }
 
-template <class K>
+template <class K, bool VALS = true>
 static void radix_impl(K *keys, uint32_t *vals, DevCount cnt, int bits, hipStream_t st,
                        int lo = 0) {
     const uint64_t n = cnt.bound;  // grid and buffer sizes; the kernels stop at cnt.get()
@@ -582,7 +583,7 @@ static void radix_impl(K *keys, uint32_t *vals, DevCount cnt, int bits, hipStrea
     if (nb64 > 0xFFFFFFFFull) throw Error{SDF_EINVAL, "radix sort too large"};
     uint32_t nb = (uint32_t)nb64;
     DevBuf<K> k2(n);
-    DevBuf<uint32_t> v2(n);
+    DevBuf<uint32_t> v2(VALS ? n : 1);
     DevBuf<uint32_t> hist((uint64_t)RS_BINS * nb);
     DevBuf<uint64_t> hoff((uint64_t)RS_BINS * nb + 1);
     K *ka = keys, *kb = k2.p;
@@ -593,14 +594,15 @@ static void radix_impl(K *keys, uint32_t *vals, DevCount cnt, int bits, hipStrea
         k_rs_hist<K><<<nb, RS_THREADS, 0, st>>>(ka, cnt, shift, hist.p, nb);
         SDF_HIP(hipGetLastError());
         scan_u32_to_u64(hist.p, hoff.p, (uint64_t)RS_BINS * nb, st);
-        k_rs_scatter<K><<<nb, RS_THREADS, 0, st>>>(ka, va, kb, vb, cnt, shift, hoff.p, nb);
+        k_rs_scatter<K, VALS><<<nb, RS_THREADS, 0, st>>>(ka, va, kb, vb, cnt, shift, hoff.p, nb);
         SDF_HIP(hipGetLastError());
         std::swap(ka, kb);
         std::swap(va, vb);
     }
     if (ka != keys) {
         SDF_HIP(hipMemcpyAsync(keys, ka, n * sizeof(K), hipMemcpyDeviceToDevice, st));
-        SDF_HIP(hipMemcpyAsync(vals, va, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
+        if constexpr (VALS)
+            SDF_HIP(hipMemcpyAsync(vals, va, n * sizeof(uint32_t), hipMemcpyDeviceToDevice, st));
     }
 }
 
@@ -616,9 +618,8 @@ void radix_sort_u32(uint32_t *keys, uint32_t *vals, uint64_t n, int bits, hipStr
 void radix_sort_u64(uint64_t *keys, uint32_t *vals, uint64_t n, int bits, hipStream_t st) {
     radix_impl<uint64_t>(keys, vals, DevCount{nullptr, n}, bits, st);
 }
-void radix_sort_u64_bits(uint64_t *keys, uint32_t *vals, uint64_t n, int lo, int hi,
-                         hipStream_t st) {
-    radix_impl<uint64_t>(keys, vals, DevCount{nullptr, n}, hi - lo, st, lo);
+void sort_keys_u64_bits(uint64_t *keys, uint64_t n, int lo, int hi, hipStream_t st) {
+    radix_impl<uint64_t, false>(keys, nullptr, DevCount{nullptr, n}, hi - lo, st, lo);
 }
 
 }  // namespace sdf

@@ -46,3 +46,44 @@ def test_wave_aligner_sides(oracle_lib, cells):
     want = oracle_lib.sd_align(b, off, [tuple(r) for r in rows], 11, 1000, 0.25, pad_frac=0.0)
     assert len(want[0]) >= len(GAPS)
     _same(got, want, "sides, cells %s" % cells)
+
+
+@pytest.mark.parametrize("nt", [10, 11, 12, 15_369, 15_370, 15_371, 33_000])
+@pytest.mark.parametrize("strand", [0, 1])
+def test_seed_tiles(oracle_lib, nt, strand):
+    """Target sides around the edges of the seeds' rounds (15,360 starts of 11
+    bases) and query sides around the 16,384 positions of a workgroup: copies
+    across the edge, gap bases, and a k-mer that occurs 32, 33 or far more
+    times, within a round and over two."""
+    from paper_1807_00205_amd import sdf
+    rng = synth.rng_for(nt)
+    t = synth.random_bases(rng, max(nt, 40))
+    q = synth.random_bases(rng, 33_100)
+    unit = synth.random_bases(rng, 11)
+    if nt > 1_000:
+        for u in range(33):                          # 33 in all, the last in a later round
+            at = (u * 211) if u < 32 else nt - 400
+            t[at + 50:at + 61] = unit
+        t[7_000:8_500] = t[7_000]                    # one base: above the limit at once
+        t[9_000:10_200] = np.tile(t[9_000:9_002], 600)
+        t[12_000:12_003] = 4                         # gap bases
+        src = t[nt - 6_000:nt] if nt < 20_000 else t[14_000:20_000]
+        cp = synth.mutate(rng, src, 0.05)
+        q[14_500:14_500 + len(cp)] = cp              # across the query's edge too
+        q[2_000:3_500] = t[6_800:8_300]
+        q[4_000:5_500] = t[8_900:10_400]
+        q[20_500:20_700:100] = 4
+        q[25_000:25_011] = unit
+        q[26_000:28_000] = t[:2_000]
+    t = t[:nt]
+    if strand:
+        t = synth.revcomp(t)
+    seqs = [q, np.concatenate([t, synth.random_bases(rng, 64)])]
+    b = np.concatenate(seqs)
+    off = np.array([0, len(q), len(b)], np.uint64)
+    rows = [(0, nq, len(q), len(q) + nt, strand) for nq in (10, 11, 16_384, 16_385, 16_400, 33_100)]
+    ix = sdf.Index(seqs, 12, 16)
+    got = ix.align_regions(_regions(sdf, rows, off), 11, 200, 0.25, pad_frac=0.0)
+    want = oracle_lib.sd_align(b, off, rows, 11, 200, 0.25, pad_frac=0.0)
+    assert len(want[0]) > 0 or nt < 1_000
+    _same(got, want, "target side %d" % nt)
