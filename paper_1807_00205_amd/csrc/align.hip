@@ -42,8 +42,9 @@ namespace {
 constexpr uint32_t MAXOCC = 32;
 constexpr uint32_t TIER2_GAP = 10000;
 constexpr uint32_t T2_BLOCKS = 4096;  // tier-2 end-order blocks per region with LDS bounds
-constexpr uint32_t T2_WAVES = 8;      // waves of a tier-2 workgroup
-constexpr uint32_t T1_WAVES = 4;      // waves of a tier-1 workgroup
+constexpr uint32_t T2_WAVES = 16;     // waves of a tier-2 workgroup
+constexpr int32_t T2_NEVER = 1 << 29;  // the cost of no link: above any score
+constexpr uint32_t T1_WAVES = 8;      // waves of a tier-1 workgroup
 constexpr uint32_t X_CAP = 1u << 19;  // ids per region with used flags in LDS (64 KiB of bits)
 constexpr uint64_t DP_CELLS = 1ull << 20;
 enum : uint32_t { OP_EQ = 7, OP_X = 8, OP_I = 1, OP_D = 2 };
@@ -355,6 +356,11 @@ __device__ __forceinline__ uint32_t lane_u32(uint32_t v, uint32_t i) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)i);
 }
 
+// A 64-bit value that is the same in every lane, as a scalar.
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
+    return ((uint64_t)lane_u32((uint32_t)(v >> 32), 0) << 32) | lane_u32((uint32_t)v, 0);
+}
+
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     for (int m = 32; m >= 1; m >>= 1) {
         const uint32_t o = __shfl_xor(v, m);
@@ -372,6 +378,12 @@ __device__ __forceinline__ int64_t ld_score(const int64_t *p) {
 __device__ __forceinline__ void st_score(int64_t *p, int64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+__device__ __forceinline__ int32_t ld_score(const int32_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void st_score(int32_t *p, int32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 // 3a. tier-1 scores (the longest chains: a link costs the indel |dx - dy|
 // it implies plus its cut, gaps at most G1), one workgroup of T1_WAVES waves
@@ -386,15 +398,18 @@ __device__ __forceinline__ void st_score(int64_t *p, int64_t v) {
 //     LDS holds the last end x of each of the region's first nblk blocks, so
 //     the window's first block is found without memory reads;
 //  2. predecessors inside the batch (wave 0): anchor k's score is final once
-//     anchors 0..k-1 are done, so k runs from first to last and every later
-//     lane tests anchor k as its predecessor.
+//     anchors 0..k-1 are done, so k runs from first to last over the anchors
+//     that have a later one in reach, and every later lane tests anchor k as
+//     its predecessor.
 // Only positive link values are kept and the choice among equal ones does
 // not depend on the order candidates are met, so this equals scoring the
 // anchors one at a time against every earlier anchor.  Candidates' lengths,
 // scores and anchor ids come from arrays kept in end order.  Bound by the
 // compares of the largest region's chance anchors: an entry no window of the
-// batch holds is left out by its own lane, and a pair too far apart in y after
-// three instructions (50 Mbp, all regions: 25.6 -> 9.8 ms).
+// batch holds is left out by its own lane, a pair too far apart in y after
+// three instructions, and inside the batch only anchors that some later one is
+// in reach of are taken one by one, which all waves find out (50 Mbp, all
+// regions: 25.6 -> 5.9 ms, 6.3 with 4 waves).
 __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, const uint32_t *byxy,
                                               const uint32_t *alen, const uint64_t *endkey,
                                               const uint32_t *byend, const uint32_t *elen,
@@ -405,6 +420,7 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
     extern __shared__ uint32_t t1_lds[];
     uint32_t *const exhi = t1_lds;  // [nblk]
     __shared__ Best2 part[T1_WAVES][64];  // per wave and anchor
+    __shared__ uint64_t rows[T1_WAVES];   // per wave: anchors with a link inside the batch
     if (blockIdx.x >= nr) return;
     const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
@@ -502,19 +518,32 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
             }
             if (mbey) break;
         }
+        // anchors of the batch that some later one of it may follow, whatever
+        // their scores: each wave tests a share of them
+        const auto follows = [&](uint32_t k) {
+            const uint32_t lk = lane_u32(len, k);
+            const uint32_t exk = lane_u32(x, k) + lk, eyk = lane_u32(y, k) + lk;
+            return (lane > k) & mine & (exk < xend) & (exk + G1 >= x) & y_in_reach(eyk, y, len, G1);
+        };
+        uint64_t own = 0;
+        for (uint32_t k = wave; k + 1 < cnt; k += T1_WAVES)
+            if (__ballot(follows(k))) own |= 1ull << k;
+        if (lane == 0) rows[wave] = own;
         part[wave][lane] = B;
         __syncthreads();
         if (wave == 0) {
             for (uint32_t q = 1; q < T1_WAVES; q++) {
                 const Best2 o = part[q][lane];
                 if (better2(o.v, o.x, o.y, B)) B = o;
+                own |= rows[q];
             }
             // 2. predecessors inside the batch
-            for (uint32_t k = 0; k + 1 < cnt; k++) {
+            for (own = uniform_u64(own); own; own &= own - 1) {
+                const uint32_t k = (uint32_t)__builtin_ctzll(own);
                 const int32_t sk = (int32_t)lane_u32((uint32_t)((int32_t)len + B.v), k);
                 const uint32_t xk = lane_u32(x, k), yk = lane_u32(y, k), lk = lane_u32(len, k);
                 const uint32_t exk = xk + lk, eyk = yk + lk;
-                if ((lane > k) & mine & (exk < xend) & (exk + G1 >= x) & y_in_reach(eyk, y, len, G1)) {
+                if (follows(k)) {
                     uint32_t o, dx, dy;
                     if (link_trim(exk, eyk, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1) {
                         const int32_t val = sk - (int32_t)(absdiff(dx, dy) + o);
@@ -785,46 +814,65 @@ __device__ __forceinline__ int32_t tier2_min_cost(uint32_t d) {
     return (int32_t)(d < u ? d : u);
 }
 
-__device__ __forceinline__ int64_t tier2_cost(uint32_t dx, uint32_t dy, uint32_t o) {
+// The cost of a link with gaps dx, dy <= TIER2_GAP and cut o < 2^20.
+__device__ __forceinline__ int32_t tier2_cost(uint32_t dx, uint32_t dy, uint32_t o) {
     const uint32_t g = absdiff(dx, dy);
-    return (int64_t)(dx < dy ? dx : dy) + (g > 0 ? 10 + (int64_t)((g + 9) / 10) : 0) + (int64_t)o;
+    return (int32_t)((dx < dy ? dx : dy) + (g > 0 ? 10 + (g + 9) / 10 : 0) + o);
 }
+
+// A node (tier-1 chain) as tier 2 reads it, in start order.
+struct Node2 {
+    uint32_t x, y, ex, ey;  // its first base and past its last
+    uint32_t flen;          // length of its first anchor
+    int32_t w;
+    uint32_t epos;  // its entry in end order
+    uint32_t slot;
+};
+// A node's best predecessor: value << 32 | start-order entry (among equal
+// values the later start wins, as starts are unique within a region); 0 none.
+__device__ __forceinline__ int32_t best_val(uint64_t b) { return (int32_t)(b >> 32); }
 
 // 4a. tier-2 scores, one workgroup of T2_WAVES waves per region: the
 // region's nodes (tier-1 chains) are the entries [nbnd[r], nbnd[r+1]) of
-// `nodes` (by start, keys xykey = region | x | y) and of `nodes_e` (by end,
-// keys ekey = region | ex | ey, starts ecxy); the predecessors of a node are
-// the earlier ones ending in [x - 10000, x + first anchor length), with the
-// affine cost plus the cut.  Scores are kept by slot (score) and by end
-// order (score_e).  Nodes are scored 64 at a time in start order, node k of
-// a batch in lane k of every wave:
+// `node` (by start) and of ekey (by end, region | ex | ey) with ue (start-order
+// entries); the predecessors of a node are the earlier ones ending in
+// [x - 10000, x + first anchor length), with the affine cost plus the cut.
+// Scores are kept in start order (score_s) and by end order (score_e).  Nodes
+// are scored 64 at a time in start order, node k of a batch in lane k of every
+// wave:
 //  1. predecessors scored before the batch: the end order is cut into
 //     blocks of 64 entries, and LDS holds, for the first nblk blocks of the
 //     region, the last end x of each block (static) and the best score of
 //     its nodes scored so far.  A block that cannot give any node of the
 //     batch a positive link value (its best score does not exceed the least
 //     cost of a link from its last end to the batch's first start) is not
-//     read; the others are dealt round robin to the waves, which read them
-//     four at a time, one entry per lane, and test every entry against
-//     every lane's node; the waves' best predecessors meet in LDS;
-//  2. predecessors inside the batch (wave 0): node k's score is final once
-//     nodes 0..k-1 are done, so k runs from first to last and every later
-//     lane tests node k as its predecessor.
+//     read; the others are dealt round robin to the waves, the last (and
+//     highest scored) first, which read them four at a time, one entry per
+//     lane.  Every entry that is still a candidate is tested against every
+//     lane's node for reach and the least cost; the pairs left are queued and
+//     scored 64 at a time;
+//  2. predecessors inside the batch: the links' costs, which need no scores,
+//     by all waves; then wave 0: node k's score is final once nodes 0..k-1 are
+//     done, so k runs from first to last and every later lane tests node k as
+//     its predecessor.
 // Only positive link values are kept and the choice among equal ones does
 // not depend on the order candidates are met, so this equals scoring the
-// nodes one at a time against every earlier node.  Within a block, an entry
-// whose score the batch's first start is too far for is left out by its own
-// lane (most are chance chains of one anchor), and a pair too far apart in y
-// after three instructions (50 Mbp, all regions: 57 -> 26 ms).
+// nodes one at a time against every earlier node.  Bound by the instructions
+// of the largest region's workgroup: an entry whose score the batch's first
+// start is too far for is left out by its own lane; an entry is in reach of
+// one or two nodes of a batch, so their full scoring is gathered; and a node's
+// inputs come in one load, a batch ahead (50 Mbp, all regions: 25.8 -> 13.5 ms,
+// 16.3 with 8 waves).
 __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
-    const uint32_t *nbnd, uint32_t nr, const uint32_t *nodes, const uint64_t *xykey,
-    const uint64_t *ekey, const uint32_t *nodes_e, const uint2 *ecxy, const uint32_t *pos_e,
-    const Chains1 c, int64_t *score, int64_t *score_e, uint32_t *pred, uint32_t nblk,
+    const uint32_t *nbnd, uint32_t nr, const Node2 *node, const uint64_t *ekey, const uint32_t *ue,
+    int32_t *score_s, int32_t *score_e, uint32_t *pred_s, uint32_t nblk,
     const uint32_t *large_first) {
     extern __shared__ uint32_t t2_lds[];
     uint32_t *const exhi = t2_lds;                                      // [nblk]
     int32_t *const bmax = reinterpret_cast<int32_t *>(t2_lds + nblk);  // [nblk]
-    __shared__ Best2 part[T2_WAVES][64];                                 // per wave and node
+    __shared__ unsigned long long best[2][64];  // per node of the batch, and for the next
+    __shared__ int32_t inner[64][64];  // the cost of node l following node k of the batch
+    __shared__ uint16_t queue[T2_WAVES][128];  // pairs to score: entry << 6 | node
     if (blockIdx.x >= nr) return;
     const uint32_t r = large_first[blockIdx.x];
     const uint32_t lane = threadIdx.x % 64, wave = threadIdx.x / 64;
@@ -839,25 +887,25 @@ __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
         exhi[j] = (uint32_t)(ekey[min(lo + 64 * j + 63, hi - 1)] >> 21) & 0x1FFFFFu;
         bmax[j] = INT32_MIN;
     }
+    if (wave == 0) best[0][lane] = 0;
+    uint32_t odd = 0;  // the batch's half of best
     __syncthreads();
     const uint64_t rk = (uint64_t)r << 42;
+    uint16_t *const wq = queue[wave];
     uint32_t jlo = 0;  // first block that ends at or after the batch's window start
+    Node2 ahead{};     // the next batch's node
+    if (lo + lane < hi) ahead = node[lo + lane];
     for (uint32_t u0 = lo; u0 < hi; u0 += 64) {
         const uint32_t cnt = min(64u, hi - u0);
         const bool mine = lane < cnt;
-        uint32_t a = NONE32, x = 0, y = 0, flen = 0;
-        if (mine) {
-            const uint64_t key = xykey[u0 + lane];
-            a = nodes[u0 + lane];
-            x = (uint32_t)(key >> 21) & 0x1FFFFFu;
-            y = (uint32_t)key & 0x1FFFFFu;
-            flen = c.flen[a];
-        }
+        const Node2 N = ahead;
+        ahead = Node2{};
+        if (u0 + 64 + lane < hi) ahead = node[u0 + 64 + lane];
+        const uint32_t x = N.x, y = N.y, flen = N.flen;
         const uint32_t xend = x + flen;  // this node's window: ends in [x - 10000, xend)
-        const uint32_t x0 = lane_u32(x, 0), y0 = lane_u32(y, 0);  // the batch's first start
+        const uint32_t x0 = lane_u32(x, 0);  // the batch's first start
         const uint32_t xend_max = wave_max_u32(mine ? xend : 0u);
         const uint64_t khi_max = rk | ((uint64_t)xend_max << 21);
-        Best2 B{0, 0, 0, NONE32};
         // 1. predecessors scored before the batch
         const uint32_t xlo = x0 >= TIER2_GAP ? x0 - TIER2_GAP : 0;
         for (;;) {  // blocks ending before every window: a prefix, and x0 only grows
@@ -866,121 +914,167 @@ __global__ __launch_bounds__(64 * T2_WAVES) void k_tier2(
             jlo += cb;
             if (cb < 64) break;
         }
-        const auto scan = [&](uint64_t ek, uint2 exy, int32_t es, uint32_t esl) {
+        const auto scan = [&](uint64_t ek, uint32_t eu, int32_t es) {
             // entries before the windows' end, scored already, whose score exceeds
             // the least cost of a link to the batch's first start (the others are no
-            // nearer), told by their own lanes; then one at a time against every
-            // lane's node
-            const uint32_t lex = (uint32_t)(ek >> 21) & 0x1FFFFFu;
-            uint64_t todo = __ballot(ek < khi_max && es > tier2_min_cost(x0 > lex ? x0 - lex : 0) &&
-                                     (exy.x < x0 || (exy.x == x0 && exy.y < y0)));
-            for (; todo; todo &= todo - 1) {
-                const uint32_t i = (uint32_t)__builtin_ctzll(todo);
-                const uint32_t elo = lane_u32((uint32_t)ek, i), ehi = lane_u32((uint32_t)(ek >> 32), i);
-                const int32_t sb = (int32_t)lane_u32((uint32_t)es, i);
-                const uint32_t bex = (uint32_t)((((uint64_t)ehi << 32) | elo) >> 21) & 0x1FFFFFu;
-                const uint32_t bey = elo & 0x1FFFFFu;
-                const bool pass = mine & (bex < xend) & y_in_reach(bey, y, flen, TIER2_GAP) &
-                                  (sb > tier2_min_cost(x > bex ? x - bex : 0));
-                if (!__ballot(pass)) continue;
-                const uint32_t bx = lane_u32(exy.x, i), by = lane_u32(exy.y, i);
+            // nearer), told by their own lanes
+            const uint32_t lex = (uint32_t)(ek >> 21) & 0x1FFFFFu, ley = (uint32_t)ek & 0x1FFFFFu;
+            uint64_t todo =
+                __ballot(ek < khi_max && eu < u0 && es > tier2_min_cost(x0 > lex ? x0 - lex : 0));
+            const int32_t least = max(best_val(best[odd][lane]), 1);
+            uint32_t nq = 0;  // pairs queued
+            while (todo || nq) {
+                while (todo && nq <= 64) {
+                    const uint32_t i = (uint32_t)__builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const uint32_t bex = lane_u32(lex, i), bey = lane_u32(ley, i);
+                    const int32_t sb = (int32_t)lane_u32((uint32_t)es, i);
+                    const bool pass = mine & (bex < xend) & y_in_reach(bey, y, flen, TIER2_GAP) &
+                                      (sb - tier2_min_cost(x > bex ? x - bex : 0) >= least);
+                    const uint64_t p = __ballot(pass);
+                    if (!p) continue;
+                    if (pass)
+                        wq[nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(p >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)p, 0))] =
+                            (uint16_t)(i << 6 | lane);
+                    nq += (uint32_t)__popcll(p);
+                }
+                if (!nq) break;
+                // the last 64 pairs at most, one per lane
+                const uint32_t m = min(nq, 64u);
+                nq -= m;
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t pr = lane < m ? wq[nq + lane] : 0u;
+                __builtin_amdgcn_wave_barrier();
+                const uint32_t i = pr >> 6, l = pr & 63;
+                const uint32_t bex = __shfl(lex, i), bey = __shfl(ley, i), bu = __shfl(eu, i);
+                const int32_t sb = __shfl(es, i);
+                const uint32_t px = __shfl(x, l), py = __shfl(y, l), pf = __shfl(flen, l);
                 uint32_t o, dx, dy;
-                if (pass && link_trim(bex, bey, x, y, flen, o, dx, dy) &&
+                if (lane < m && link_trim(bex, bey, px, py, pf, o, dx, dy) &&
                     (dx > dy ? dx : dy) <= TIER2_GAP) {
-                    const int32_t val = sb - (int32_t)tier2_cost(dx, dy, o);
-                    if (better2(val, bx, by, B)) B = Best2{val, bx, by, lane_u32(esl, i)};
+                    const int32_t val = sb - tier2_cost(dx, dy, o);
+                    if (val > 0)
+                        atomicMax(&best[odd][l], ((unsigned long long)(uint32_t)val << 32) | bu);
                 }
             }
         };
-        uint32_t dealt = 0;  // needed blocks met so far (dealt round robin)
-        for (uint32_t j0 = jlo; j0 < nbr; j0 += 64) {
-            const uint32_t j = j0 + lane;
-            bool beyond = true, need = false;
-            if (j < nbr) {
-                // block j starts no earlier than block j - 1 ends
-                beyond = j > jlo && block_end(j - 1) >= xend_max;
-                if (!beyond) {
-                    need = true;
-                    if (j < nbl) {
-                        const uint32_t eh = exhi[j];
-                        need = bmax[j] > tier2_min_cost(x0 > eh ? x0 - eh : 0);
-                    }
-                }
+        // the first block past every window: block j starts no earlier than block
+        // j - 1 ends
+        uint32_t jhi = jlo;
+        for (;;) {
+            const uint32_t j = jhi + lane;
+            const uint64_t mbey =
+                __ballot(j >= nbr || (j > jlo && block_end(j - 1) >= xend_max));
+            jhi += mbey ? (uint32_t)__builtin_ctzll(mbey) : 64u;
+            if (mbey) break;
+        }
+        // blocks from the last on: their scores are the highest, and drop entries of
+        // the others
+        uint32_t dealt = 0;  // needed blocks met so far
+        for (uint32_t jt = jhi; jt > jlo; jt -= min(64u, jt - jlo)) {
+            const uint32_t j = jt - 1 - lane;  // lane 0: the last block of the group
+            bool need = lane < jt - jlo;
+            if (need && j < nbl) {
+                const uint32_t eh = exhi[j];
+                need = bmax[j] > tier2_min_cost(x0 > eh ? x0 - eh : 0);
             }
-            uint64_t mneed = __ballot(need);
-            const uint64_t mbey = __ballot(beyond);
-            if (mbey) mneed &= (mbey & (0ull - mbey)) - 1;  // blocks before the first beyond
             // this wave's share: every T2_WAVES-th needed block
             uint64_t mine_b = 0;
-            for (uint64_t m = mneed; m; m &= m - 1, dealt++)
+            for (uint64_t m = __ballot(need); m; m &= m - 1, dealt++)
                 if (dealt % T2_WAVES == wave) mine_b |= m & (0ull - m);
             while (mine_b) {
                 uint32_t jb[4];
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    jb[q] = mine_b ? j0 + (uint32_t)__builtin_ctzll(mine_b) : nbr;
+                    jb[q] = mine_b ? jt - 1 - (uint32_t)__builtin_ctzll(mine_b) : nbr;
                     mine_b &= mine_b - 1;
                 }
                 uint64_t ek[4];
-                uint2 exy[4];
+                uint32_t eu[4];
                 int32_t es[4];
-                uint32_t esl[4];
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
                     const uint32_t v = lo + 64 * jb[q] + lane;
                     const bool ok = jb[q] < nbr && v < hi;
                     ek[q] = ok ? ekey[v] : ~0ull;
-                    exy[q] = ok ? ecxy[v] : make_uint2(0u, 0u);
-                    es[q] = ok ? (int32_t)ld_score(score_e + v) : INT32_MIN;
-                    esl[q] = ok ? nodes_e[v] : NONE32;
+                    eu[q] = ok ? ue[v] : NONE32;
+                    es[q] = ok ? ld_score(score_e + v) : INT32_MIN;
                 }
 #pragma unroll
                 for (int q = 0; q < 4; q++)
-                    if (jb[q] < nbr) scan(ek[q], exy[q], es[q], esl[q]);
+                    if (jb[q] < nbr) scan(ek[q], eu[q], es[q]);
             }
-            if (mbey) break;
         }
-        part[wave][lane] = B;
+        // the costs of the links inside the batch, a share of the rows per wave
+        for (uint32_t k = wave; k + 1 < cnt; k += T2_WAVES) {
+            const uint32_t exk = lane_u32(N.ex, k), eyk = lane_u32(N.ey, k);
+            int32_t cost = T2_NEVER;
+            if ((lane > k) & mine & (exk < xend) & y_in_reach(eyk, y, flen, TIER2_GAP)) {
+                uint32_t o, dx, dy;
+                if (link_trim(exk, eyk, x, y, flen, o, dx, dy) &&
+                    (dx > dy ? dx : dy) <= TIER2_GAP)
+                    cost = tier2_cost(dx, dy, o);
+            }
+            inner[k][lane] = cost;
+        }
         __syncthreads();
         if (wave == 0) {
-            for (uint32_t q = 1; q < T2_WAVES; q++) {
-                const Best2 o = part[q][lane];
-                if (better2(o.v, o.x, o.y, B)) B = o;
-            }
-            uint32_t apos = 0, ex = 0, ey = 0;
-            int32_t w = 0;
-            if (mine) {
-                apos = pos_e[a];
-                ex = c.cex[a];
-                ey = c.cey[a];
-                w = (int32_t)c.w[a];
-            }
-            // 2. predecessors inside the batch
+            const uint64_t b = best[odd][lane];
+            best[odd ^ 1][lane] = 0;
+            int32_t bv = best_val(b);
+            uint32_t bu = bv > 0 ? (uint32_t)b : NONE32;
+            // 2. predecessors inside the batch.  They start after every other one and
+            // in the order of their lanes, so a later one wins among equal values.
+#pragma unroll 8
             for (uint32_t k = 0; k + 1 < cnt; k++) {
-                const int32_t sk = (int32_t)lane_u32((uint32_t)(w + B.v), k);
-                const uint32_t exk = lane_u32(ex, k), eyk = lane_u32(ey, k);
-                if ((lane > k) & mine & (exk < xend) & y_in_reach(eyk, y, flen, TIER2_GAP) &
-                    (sk > tier2_min_cost(x > exk ? x - exk : 0))) {
-                    const uint32_t xk = lane_u32(x, k), yk = lane_u32(y, k);
-                    uint32_t o, dx, dy;
-                    if (link_trim(exk, eyk, x, y, flen, o, dx, dy) &&
-                        (dx > dy ? dx : dy) <= TIER2_GAP) {
-                        const int32_t val = sk - (int32_t)tier2_cost(dx, dy, o);
-                        if (better2(val, xk, yk, B)) B = Best2{val, xk, yk, lane_u32(a, k)};
-                    }
-                }
+                const int32_t val = (int32_t)lane_u32((uint32_t)(N.w + bv), k) - inner[k][lane];
+                const bool take = val >= max(bv, 1);
+                bv = take ? val : bv;
+                bu = take ? u0 + k : bu;
             }
             if (mine) {
-                const int32_t sa = w + B.v;
-                st_score(score + a, (int64_t)sa);
-                st_score(score_e + apos, (int64_t)sa);
-                pred[a] = B.v > 0 ? B.b : NONE32;
-                const uint32_t jp = (apos - lo) / 64;  // the node's block in end order
+                const int32_t sa = N.w + bv;
+                st_score(score_e + N.epos, sa);
+                score_s[u0 + lane] = sa;
+                pred_s[u0 + lane] = bu;
+                const uint32_t jp = (N.epos - lo) / 64;  // the node's block in end order
                 if (jp < nbl) atomicMax(bmax + jp, sa);
             }
         }
+        odd ^= 1;
         __syncthreads();  // scores and block bounds seen by every wave
     }
+}
+
+// Tier 2's inputs by start order, and the start-order entries by end order.
+__global__ void k_node_starts(const uint32_t *nodes, uint64_t na, const uint32_t *nlive,
+                              const uint32_t *pos_e, const Chains1 c, Node2 *node, uint32_t *ue) {
+    const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= na || u >= *nlive) return;
+    const uint32_t s = nodes[u];
+    Node2 n;
+    n.x = c.cx[s];
+    n.y = c.cy[s];
+    n.ex = c.cex[s];
+    n.ey = c.cey[s];
+    n.flen = c.flen[s];
+    n.w = (int32_t)c.w[s];
+    n.epos = pos_e[s];
+    n.slot = s;
+    node[u] = n;
+    ue[n.epos] = (uint32_t)u;
+}
+
+// Tier 2's results by slot.
+__global__ void k_node_results(const Node2 *node, uint64_t na, const uint32_t *nlive,
+                               const int32_t *score_s, const uint32_t *pred_s, int64_t *score,
+                               uint32_t *pred) {
+    const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= na || u >= *nlive) return;
+    const uint32_t s = node[u].slot, p = pred_s[u];
+    score[s] = score_s[u];
+    pred[s] = p == NONE32 ? NONE32 : node[p].slot;
 }
 
 // Most nodes of one region (entries between consecutive region bounds).
@@ -993,12 +1087,6 @@ __global__ void k_max_span(const uint32_t *bnd, uint32_t nr, uint32_t *out) {
 __global__ void k_invert(const uint32_t *nodes_e, uint64_t na, uint32_t *pos_e) {
     const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v < na) pos_e[nodes_e[v]] = (uint32_t)v;
-}
-
-// Starts (x, y) of the nodes in end order.
-__global__ void k_end_starts(const uint32_t *nodes_e, uint64_t na, const Chains1 c, uint2 *ecxy) {
-    const uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v < na) ecxy[v] = make_uint2(c.cx[nodes_e[v]], c.cy[nodes_e[v]]);
 }
 
 // Keys of the node entries: pass 0 by end (region, ex, ey); pass 1 and 2
@@ -2042,11 +2130,11 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     SDF_HIP(hipGetLastError());
     radix_sort_u64(ekey.p, nodes_e.p, A, 42 + rbits, st);
     {
-        DevBuf<uint32_t> pos_e(A);
-        DevBuf<uint2> ecxy(A);
-        DevBuf<int64_t> s2e(A);
+        DevBuf<uint32_t> pos_e(A), ue(A), p2s(A);
+        DevBuf<Node2> node2(A);
+        DevBuf<int32_t> s2s(A), s2e(A);
         k_invert<<<nb(A), 256, 0, st>>>(nodes_e.p, A, pos_e.p);
-        k_end_starts<<<nb(A), 256, 0, st>>>(nodes_e.p, A, c, ecxy.p);
+        k_node_starts<<<nb(A), 256, 0, st>>>(nodes.p, A, nbnd.p + nr, pos_e.p, c, node2.p, ue.p);
         SDF_HIP(hipGetLastError());
         // LDS bounds for up to T2_BLOCKS blocks of 64 nodes per region (align_lds_blocks)
         DevBuf<uint32_t> most(1);
@@ -2056,9 +2144,9 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
         const uint32_t nblk = std::min<uint32_t>(
             std::min(knob(tuning().align_lds_blocks, T2_BLOCKS), T2_BLOCKS),
             (read1(most.p, st) + 63) / 64);
-        k_tier2<<<nr, 64 * T2_WAVES, 8 * nblk, st>>>(nbnd.p, nr, nodes.p, kbuf.p, ekey.p,
-                                                     nodes_e.p, ecxy.p, pos_e.p, c, s2.p, s2e.p,
-                                                     p2.p, nblk, large.p);
+        k_tier2<<<nr, 64 * T2_WAVES, 8 * nblk, st>>>(nbnd.p, nr, node2.p, ekey.p, ue.p, s2s.p,
+                                                     s2e.p, p2s.p, nblk, large.p);
+        k_node_results<<<nb(A), 256, 0, st>>>(node2.p, A, nbnd.p + nr, s2s.p, p2s.p, s2.p, p2.p);
         SDF_HIP(hipGetLastError());
     }
     k_node_keys2<<<nb(A), 256, 0, st>>>(nodes.p, A, nbnd.p + nr, rslot.p, c, s2.p, 1, nullptr,

@@ -1,6 +1,5 @@
-"""Final SDs where the aligner's and the seeds' split can go wrong, against the
-oracle: stretches with the edges of 64, 128, 256 and 512 lines per lane group
-on either side, and long thin ones.  Whole numbers and CIGARs: equality."""
+"""Final SDs where the split of the work can go wrong (aligner, seeds, chaining,
+records), against the oracle.  Whole numbers and CIGARs: equality."""
 import numpy as np
 import pytest
 
@@ -87,3 +86,25 @@ def test_seed_tiles(oracle_lib, nt, strand):
     want = oracle_lib.sd_align(b, off, rows, 11, 200, 0.25, pad_frac=0.0)
     assert len(want[0]) > 0 or nt < 1_000
     _same(got, want, "target side %d" % nt)
+
+
+@pytest.mark.parametrize("unit,copies", [(300, 28), (97, 31), (1_500, 12)])
+@pytest.mark.parametrize("strand", [0, 1])
+def test_crowded_region(oracle_lib, unit, copies, strand):
+    """Diverged copies of a unit in a row on both sides: most pairs of chains
+    are in reach of each other, many with equal values."""
+    from paper_1807_00205_amd import sdf
+    rng = synth.rng_for(unit)
+    one = synth.random_bases(rng, unit)
+    q = np.concatenate([synth.mutate(rng, one, 0.04) for _ in range(copies)])
+    t = np.concatenate([synth.mutate(rng, one, 0.04) for _ in range(copies)])
+    if strand:
+        t = synth.revcomp(t)
+    b = np.concatenate([q, t])
+    off = np.array([0, len(q), len(b)], np.uint64)
+    rows = [(0, len(q), len(q), len(b), strand), (0, len(q) // 2, len(q), len(b), strand)]
+    ix = sdf.Index([q, t], 12, 16)
+    got = ix.align_regions(_regions(sdf, rows, off), 11, 300, 0.25, pad_frac=0.0)
+    want = oracle_lib.sd_align(b, off, rows, 11, 300, 0.25, pad_frac=0.0)
+    assert len(want[0]) > 0
+    _same(got, want, "unit %d" % unit)
