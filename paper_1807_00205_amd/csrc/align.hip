@@ -27,9 +27,10 @@
 //      aligned by one thread each (three-state affine recurrence over two
 //      rolling rows, one byte of traceback per cell), the large ones by one
 //      wave each;
-//   6. one wave per final chain joins anchors and stretches into merged
-//      operations, counts matches, transitions and gaps, applies the report
-//      rule and writes the record and its CIGAR.
+//   6. the shares of the final chains (a stretch and the anchor after it) are
+//      counted one per lane (matches, transitions, gaps, runs of equal
+//      operations), summed up by chain, which applies the report rule, and
+//      written to the CIGARs at the places a prefix sum gives them.
 #include <vector>
 
 #include "sdf_impl.h"
@@ -1700,15 +1701,17 @@ __global__ __launch_bounds__(64) void k_align_wave(const IndexView ix, const ARe
     if (threadIdx.x == 0) ncol[t] = n;
 }
 
-struct SdOut {
-    sdf_sd *sd;
-    uint32_t *cigar;
+// What a final chain's share - the stretch before an anchor and the anchor's
+// '=' run - adds to its chain.
+struct Share {
+    uint32_t runs;  // merged runs, the last always '='; FIRST_EQ: so is the first
+    uint32_t match, mism, opens, ts, tv;
 };
+constexpr uint32_t FIRST_EQ = 1u << 31;
 
-// Counts of a final chain's alignment (the per-column operations of its
-// stretches between the '=' runs of its anchors).
+// A final chain's counts.
 struct ChainStats {
-    uint32_t aln, match, mism, ins, del, opens, ts, tv, nops;
+    uint32_t match, mism, ins, del, opens, ts, tv, nops;
     uint32_t x0, y0, ex, ey;
 };
 
@@ -1717,40 +1720,31 @@ __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
     return v;
 }
 
-// One lane's share of a final chain: the stretch before its anchor (n
-// column ops at col, starting at (qi, ti); none for the chain's first
-// anchor) and then the anchor's '=' run of `keep` bases.  Calls run(op, len)
-// for its runs in order (equal ops next to each other merged) and, when
-// `counts`, adds its columns to the counts (I and D runs that start in the
-// share are counted as opened).
-template <class F>
+// One share (n column ops at col, starting at (qi, ti), then `keep` equal bases)
+// walked by a lane: calls run(op, len) for its runs in order (equal ops next to
+// each other merged) and, when COUNT, adds its columns to c.
+template <bool COUNT, class F>
 __device__ __forceinline__ void walk_share(const IndexView &ix, const ARegion &R, const uint8_t *col,
                                            uint32_t n, uint32_t qi, uint32_t ti, uint32_t keep,
-                                           bool counts, ChainStats &st, F &&run) {
+                                           Share &c, F &&run) {
     uint32_t cur = 0xFFu, len = 0;
     const auto op1 = [&](uint32_t op) {
-        if (counts) {
-            st.aln++;
+        if constexpr (COUNT) {
             if (op == OP_EQ) {  // the aligners write it for equal bases only
-                st.match++;
+                c.match++;
                 qi++;
                 ti++;
             } else if (op == OP_X) {  // unequal bases, or an N on either side
                 const uint32_t x = base_at(ix, R.q0 + qi), y = t_base(ix, R, ti);
-                st.mism++;
+                c.mism++;
                 if (x < 4 && y < 4) {
-                    if ((x ^ y) == 2) st.ts++; else st.tv++;
+                    if ((x ^ y) == 2) c.ts++; else c.tv++;
                 }
                 qi++;
                 ti++;
-            } else if (op == OP_I) {
-                st.ins++;
-                if (cur != OP_I) st.opens++;
-                qi++;
             } else {
-                st.del++;
-                if (cur != OP_D) st.opens++;
-                ti++;
+                if (cur != op) c.opens++;
+                if (op == OP_I) qi++; else ti++;
             }
         }
         if (op == cur) {
@@ -1770,138 +1764,254 @@ __device__ __forceinline__ void walk_share(const IndexView &ix, const ARegion &R
         for (uint32_t q = 0; q < 16; q++)
             if (u0 + q < n) op1(cb[q]);
     }
-    if (keep) {
-        if (counts) {
-            st.aln += keep;
-            st.match += keep;
-        }
-        if (cur == OP_EQ) {
-            len += keep;
-        } else {
-            if (len) run(cur, len);
-            cur = OP_EQ;
-            len = keep;
-        }
+    if (cur == OP_EQ) {
+        len += keep;
+    } else {
+        if (len) run(cur, len);
+        cur = OP_EQ;
+        len = keep;
     }
-    if (len) run(cur, len);
+    if constexpr (COUNT) c.match += keep;
+    run(cur, len);
 }
 
-// 6. records and CIGARs, one 64-lane workgroup per final chain: the chain
-// is its first anchor's '=' run and then its stretches in order (soff[g] ..
-// soff[g + 1]), each followed by its anchor's '=' run after the cut; the
-// lanes take 64 consecutive stretches at a time.  Each lane counts its
-// columns and runs; then, lane after lane in order, the runs at the lanes'
-// borders are merged with the run still open and placed in the CIGAR (the
-// runs inside a lane's share are placed by that lane).  Pass 0 counts (ops,
-// passing), pass 1 writes record and CIGAR.
-__global__ __launch_bounds__(64) void k_assemble(const IndexView ix, const ARegion *reg,
-                                                 const uint64_t *foff, uint32_t nr, uint64_t nf,
-                                                 const uint64_t *soff, const Seg *seg,
-                                                 const uint8_t *cols, const uint32_t *ncol,
-                                                 const uint32_t *fanchor, uint32_t min_len,
-                                                 double delta, int pass, uint32_t *nops_out,
-                                                 uint32_t *pass_out, const uint64_t *wr_off,
-                                                 const uint64_t *op_off, SdOut out) {
-    const uint64_t g = blockIdx.x;
+// The same by a whole wave, 64 columns at a time: chunk(op, starts, valid) for
+// each, with every lane's op, the lanes at which a run starts and the lanes in
+// use.  Returns the last op (0xFF for none).
+template <class F>
+__device__ __forceinline__ uint32_t walk_wave(const uint8_t *col, uint32_t n, F &&chunk) {
+    const uint32_t lane = threadIdx.x % 64;
+    uint32_t last = 0xFFu;
+    for (uint32_t u0 = 0; u0 < n; u0 += 64) {
+        const uint32_t m = min(64u, n - u0);
+        const uint32_t op = lane < m ? (uint32_t)col[u0 + lane] : 0u;
+        const uint32_t prev = (uint32_t)lane_before((int)op, (int)last);
+        chunk(op, __ballot(lane < m && op != prev), m == 64 ? ~0ull : (1ull << m) - 1);
+        last = lane_u32(op, m - 1);
+    }
+    return last;
+}
+
+// Shares of at least this many columns are walked by their wave together: a
+// lane alone takes over 1 us per 16 columns, and its wave waits for it.
+constexpr uint32_t SHARE_WAVE = 96;
+
+// 6a. the shares, one lane each (long ones by the wave), and how many more runs
+// than its predecessors' a share brings to its chain's CIGAR: a first run of
+// equal bases lengthens the run before it.
+// (Before, one wave walked a whole chain, 64 shares at a time, merging them one
+// by one, once for the counts and once for the CIGAR: 16.6 ms for 50 Mbp's
+// regions, where the four kernels now take 3.4.)
+__global__ __launch_bounds__(256) void k_shares(const IndexView ix, const ARegion *reg,
+                                                const Seg *seg, uint64_t ns, const uint8_t *cols,
+                                                const uint32_t *ncol, Share *share,
+                                                uint32_t *more) {
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t lane = threadIdx.x % 64;
+    Seg S{};
+    uint32_t n = 0;
+    if (t < ns) {
+        S = seg[t];
+        n = ncol[t];
+    }
+    Share c{};
+    if (t < ns && n < SHARE_WAVE) {
+        uint32_t first = 0xFFu;
+        walk_share<true>(ix, reg[S.region], cols + S.ops, n, S.qx, S.ty, S.keep, c,
+                         [&](uint32_t op, uint32_t) {
+                             if (!c.runs) first = op;
+                             c.runs++;
+                         });
+        if (first == OP_EQ) c.runs |= FIRST_EQ;
+    }
+    for (uint64_t todo = __ballot(n >= SHARE_WAVE); todo; todo &= todo - 1) {
+        const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+        const Seg W = seg[t - lane + l];
+        const ARegion R = reg[W.region];
+        const uint8_t *col = cols + W.ops;
+        uint32_t qi = W.qx, ti = W.ty;
+        Share w{};
+        const uint32_t last = walk_wave(col, lane_u32(n, l), [&](uint32_t op, uint64_t starts,
+                                                                uint64_t valid) {
+            const uint64_t eq = __ballot(op == OP_EQ), x = __ballot(op == OP_X);
+            const uint64_t ins = __ballot(op == OP_I), del = __ballot(op == OP_D);
+            const uint64_t below = (1ull << lane) - 1;
+            bool ts = false, tv = false;
+            if (op == OP_X) {
+                const uint32_t a =
+                    base_at(ix, R.q0 + qi + (uint32_t)__popcll(valid & ~del & below));
+                const uint32_t b = t_base(ix, R, ti + (uint32_t)__popcll(valid & ~ins & below));
+                if (a < 4 && b < 4) {
+                    ts = (a ^ b) == 2;
+                    tv = !ts;
+                }
+            }
+            w.runs += (uint32_t)__popcll(starts);
+            w.match += (uint32_t)__popcll(eq);
+            w.mism += (uint32_t)__popcll(x);
+            w.opens += (uint32_t)__popcll(starts & (ins | del));
+            w.ts += (uint32_t)__popcll(__ballot(ts));
+            w.tv += (uint32_t)__popcll(__ballot(tv));
+            qi += (uint32_t)__popcll(valid & ~del);
+            ti += (uint32_t)__popcll(valid & ~ins);
+        });
+        w.match += W.keep;
+        if (last != OP_EQ) w.runs++;
+        if (col[0] == OP_EQ) w.runs |= FIRST_EQ;
+        if (lane == l) c = w;
+    }
+    if (t >= ns) return;
+    share[t] = c;
+    more[t] = (c.runs & ~FIRST_EQ) - (c.runs & FIRST_EQ ? 1u : 0u);
+}
+
+// 6b. the chains' counts from their shares and which are reported.  Most
+// chains have a share or two: a lane each; the wave goes through the long ones
+// together.
+__global__ __launch_bounds__(256) void k_chain_counts(const uint64_t *soff, uint64_t nf,
+                                                      const Seg *seg, const Share *share,
+                                                      const uint64_t *moff,
+                                                      const uint32_t *fanchor, uint32_t min_len,
+                                                      double delta, ChainStats *stats,
+                                                      uint32_t *nops_out, uint32_t *pass_out) {
+    constexpr uint64_t LONG = 8;
+    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t lane = threadIdx.x % 64;
+    const uint64_t s0 = g < nf ? soff[g] : 0, s1 = g < nf ? soff[g + 1] : 0;
+    const auto add = [&](ChainStats &st, uint64_t s) {
+        const Share c = share[s];
+        const uint32_t dx = seg[s].dx, dy = seg[s].dy, keep = seg[s].keep;
+        const uint32_t both = c.match - keep + c.mism;  // columns of the stretch on both sides
+        st.match += c.match;
+        st.mism += c.mism;
+        st.ins += dx - both;
+        st.del += dy - both;
+        st.opens += c.opens;
+        st.ts += c.ts;
+        st.tv += c.tv;
+    };
+    ChainStats st = {};
+    if (s1 - s0 <= LONG)
+        for (uint64_t s = s0; s < s1; s++) add(st, s);
+    for (uint64_t todo = __ballot(s1 - s0 > LONG); todo; todo &= todo - 1) {
+        const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+        const uint64_t a = soff[g - lane + l], b = soff[g - lane + l + 1];
+        ChainStats w = {};
+#pragma unroll 2
+        for (uint64_t s = a + lane; s < b; s += 64) add(w, s);
+        w.match = wave_sum_u32(w.match);
+        w.mism = wave_sum_u32(w.mism);
+        w.ins = wave_sum_u32(w.ins);
+        w.del = wave_sum_u32(w.del);
+        w.opens = wave_sum_u32(w.opens);
+        w.ts = wave_sum_u32(w.ts);
+        w.tv = wave_sum_u32(w.tv);
+        if (lane == l) st = w;
+    }
     if (g >= nf) return;
-    const uint32_t lane = threadIdx.x;
-    if (pass == 1 && !pass_out[g]) return;
-    const uint32_t r = region_of(foff, nr, g);
-    const ARegion R = reg[r];
-    const uint64_t s0 = soff[g], ns = soff[g + 1] - s0;
-    uint32_t *const cig = pass == 1 ? out.cigar + op_off[g] : nullptr;
-    ChainStats st = {};  // the chain's counts (the same in every lane)
+    const uint32_t l0 = fanchor[3 * g + 2];
+    st.match += l0;
+    st.nops = 1 + (uint32_t)(moff[s1] - moff[s0]);
     st.x0 = fanchor[3 * g];
     st.y0 = fanchor[3 * g + 1];
-    const uint32_t l0 = fanchor[3 * g + 2];
-    st.aln = st.match = l0;
     st.ex = st.x0 + l0;
     st.ey = st.y0 + l0;
-    uint32_t open_op = OP_EQ, open_len = l0;  // the run still open
-    uint32_t placed = 0;                      // CIGAR runs placed so far
-    int32_t opens_adj = 0;
-    const auto place = [&](uint32_t op, uint32_t len) {  // a complete run (uniform)
-        if (!len) return;
-        if (cig && lane == 0) cig[placed] = (len << 4) | op;
-        placed++;
-    };
-    for (uint64_t j0 = 0; j0 < ns; j0 += 64) {
-        const uint32_t cnt = (uint32_t)min<uint64_t>(64, ns - j0);
-        const bool mine = lane < cnt;
-        Seg S{};
-        uint32_t n = 0;
-        if (mine) {
-            S = seg[s0 + j0 + lane];
-            n = ncol[s0 + j0 + lane];
+    if (s1 > s0) {  // the end of the last stretch's anchor
+        const Seg S = seg[s1 - 1];
+        st.ex = S.qx + S.dx + S.keep;
+        st.ey = S.ty + S.dy + S.keep;
+    }
+    stats[g] = st;
+    const uint32_t aln = st.match + st.mism + st.ins + st.del;
+    const bool ok = aln >= min_len && (double)(st.mism + st.opens) <= delta * (double)aln;
+    pass_out[g] = ok ? 1u : 0u;
+    nops_out[g] = ok ? st.nops : 0u;
+}
+
+// 6c. the CIGARs of the reported chains, share by share (cigar zeroed
+// beforehand, the chain's first anchor's run added by k_records): run i of a
+// share goes to the chain's place for it; a length that grows from several
+// places is added up.
+__global__ __launch_bounds__(256) void k_cigars(const IndexView ix, const ARegion *reg,
+                                                const Seg *seg, uint64_t ns, const uint8_t *cols,
+                                                const uint32_t *ncol, const Share *share,
+                                                const uint64_t *soff, const uint64_t *moff,
+                                                const uint32_t *pass, const uint64_t *op_off,
+                                                uint32_t *cigar) {
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t lane = threadIdx.x % 64;
+    Seg S{};
+    uint32_t n = 0;
+    bool on = false, merged = false;  // merged: the first run lengthens the one before
+    uint64_t at = 0;                  // where the share's run 0 goes
+    if (t < ns) {
+        S = seg[t];
+        on = pass[S.chain] != 0;
+        if (on) {
+            n = ncol[t];
+            merged = (share[t].runs & FIRST_EQ) != 0;
+            at = op_off[S.chain] + 1 + (moff[t] - moff[soff[S.chain]]) - (merged ? 1u : 0u);
         }
-        const uint8_t *col = cols + S.ops;
-        const uint32_t keep = mine ? S.keep : 0u;
-        // the lane's runs: how many, the first and the last
-        ChainStats ls = {};
-        uint32_t nruns = 0, fo = 0, fl = 0, lo = 0, ll = 0;
-        walk_share(ix, R, col, n, S.qx, S.ty, keep, true, ls, [&](uint32_t op, uint32_t len) {
-            if (!nruns) {
-                fo = op;
-                fl = len;
+    }
+    if (on && n < SHARE_WAVE) {
+        const uint32_t runs = share[t].runs & ~FIRST_EQ;
+        uint32_t i = 0;
+        Share unused;
+        walk_share<false>(ix, reg[S.region], cols + S.ops, n, S.qx, S.ty, S.keep, unused,
+                          [&](uint32_t op, uint32_t len) {
+                              const uint32_t v = (len << 4) | (i == 0 && merged ? 0u : op);
+                              if (i == 0 || i + 1 == runs)
+                                  atomicAdd(cigar + at + i, v);
+                              else
+                                  cigar[at + i] = v;
+                              i++;
+                          });
+    }
+    for (uint64_t todo = __ballot(on && n >= SHARE_WAVE); todo; todo &= todo - 1) {
+        const uint32_t l = (uint32_t)__builtin_ctzll(todo);
+        const Seg W = seg[t - lane + l];
+        const bool wm = lane_u32(merged, l) != 0;
+        uint32_t *const cig =
+            cigar + (((uint64_t)lane_u32((uint32_t)(at >> 32), l) << 32) | lane_u32((uint32_t)at, l));
+        uint32_t runs = 0;  // runs started so far
+        const uint32_t last = walk_wave(cols + W.ops, lane_u32(n, l), [&](uint32_t op, uint64_t starts,
+                                                                          uint64_t valid) {
+            // the columns that go on the run before
+            const uint32_t m = (uint32_t)__popcll(valid);
+            const uint32_t on0 = starts ? (uint32_t)__builtin_ctzll(starts) : m;
+            if (lane == 0 && on0) atomicAdd(cig + runs - 1, on0 << 4);
+            if ((starts >> lane) & 1) {
+                const uint64_t later = lane == 63 ? 0ull : starts >> (lane + 1);
+                const uint32_t len = later ? (uint32_t)__builtin_ctzll(later) + 1 : m - lane;
+                const uint32_t i = runs + (uint32_t)__popcll(starts & ((1ull << lane) - 1));
+                const uint32_t v = (len << 4) | (i == 0 && wm ? 0u : op);
+                if (later && i)
+                    cig[i] = v;
+                else
+                    atomicAdd(cig + i, v);
             }
-            lo = op;
-            ll = len;
-            nruns++;
+            runs += (uint32_t)__popcll(starts);
         });
-        // lane by lane: merge at the borders, place the complete runs
-        uint32_t mid = 0;  // where this lane's inner runs go
-        for (uint32_t t = 0; t < cnt; t++) {
-            const uint32_t nt = lane_u32(nruns, t), fot = lane_u32(fo, t), flt = lane_u32(fl, t);
-            const uint32_t lot = lane_u32(lo, t), llt = lane_u32(ll, t);
-            if (!nt) continue;
-            const bool merged = fot == open_op;
-            if (merged && (fot == OP_I || fot == OP_D)) opens_adj--;  // not a new gap
-            if (merged) {
-                open_len += flt;
-            } else {
-                place(open_op, open_len);
-                open_op = fot;
-                open_len = flt;
-            }
-            if (nt >= 2) {
-                place(open_op, open_len);  // the lane's first run is complete
-                if (lane == t) mid = placed;
-                placed += nt - 2;
-                open_op = lot;
-                open_len = llt;
-            }
+        if (lane == 0) {
+            if (last == OP_EQ)
+                atomicAdd(cig + runs - 1, W.keep << 4);
+            else
+                atomicAdd(cig + runs, (W.keep << 4) | OP_EQ);
         }
-        if (cig && nruns > 2) {  // this lane's inner runs
-            uint32_t j = 0;
-            ChainStats unused;
-            walk_share(ix, R, col, n, S.qx, S.ty, keep, false, unused,
-                       [&](uint32_t op, uint32_t len) {
-                           if (j > 0 && j + 1 < nruns) cig[mid + j - 1] = (len << 4) | op;
-                           j++;
-                       });
-        }
-        st.aln += wave_sum_u32(ls.aln);
-        st.match += wave_sum_u32(ls.match);
-        st.mism += wave_sum_u32(ls.mism);
-        st.ins += wave_sum_u32(ls.ins);
-        st.del += wave_sum_u32(ls.del);
-        st.opens += wave_sum_u32(ls.opens);
-        st.ts += wave_sum_u32(ls.ts);
-        st.tv += wave_sum_u32(ls.tv);
-        // the end of the last stretch's anchor
-        st.ex = lane_u32(S.qx + S.dx + keep, cnt - 1);
-        st.ey = lane_u32(S.ty + S.dy + keep, cnt - 1);
     }
-    place(open_op, open_len);  // the last run
-    st.opens = (uint32_t)((int32_t)st.opens + opens_adj);
-    st.nops = placed;
-    if (lane != 0) return;
-    const bool ok = st.aln >= min_len && (double)(st.mism + st.opens) <= delta * (double)st.aln;
-    if (pass == 0) {
-        pass_out[g] = ok ? 1u : 0u;
-        nops_out[g] = ok ? st.nops : 0u;
-        return;
-    }
+}
+
+// 6d. the records of the reported chains
+__global__ void k_records(const IndexView ix, const ARegion *reg, const uint64_t *foff, uint32_t nr,
+                          uint64_t nf, const ChainStats *stats, const uint32_t *fanchor,
+                          const uint32_t *pass, const uint64_t *wr_off, const uint64_t *op_off,
+                          sdf_sd *sd, uint32_t *cigar) {
+    const uint64_t g = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g >= nf || !pass[g]) return;
+    const uint32_t r = region_of(foff, nr, g);
+    const ARegion R = reg[r];
+    const ChainStats st = stats[g];
+    atomicAdd(cigar + op_off[g], (fanchor[3 * g + 2] << 4) | OP_EQ);
     sdf_sd d;
     d.region = r;
     d.strand = R.o;
@@ -1918,7 +2028,7 @@ __global__ __launch_bounds__(64) void k_assemble(const IndexView ix, const ARegi
         d.t_begin = R.t1 - st.ey - to;
         d.t_end = R.t1 - st.y0 - to;
     }
-    d.aln_len = st.aln;
+    d.aln_len = st.match + st.mism + st.ins + st.del;
     d.matches = st.match;
     d.mismatches = st.mism;
     d.ins = st.ins;
@@ -1934,7 +2044,7 @@ __global__ __launch_bounds__(64) void k_assemble(const IndexView ix, const ARegi
     d.jc = (al > 0 && a3 > 0) ? -0.75 * log(a3) : -1.0;
     d.cigar_off = op_off[g];
     d.cigar_len = st.nops;
-    out.sd[wr_off[g]] = d;
+    sd[wr_off[g]] = d;
 }
 
 __global__ void k_u32_to_u64(const uint32_t *a, uint64_t n, uint64_t *b) {
@@ -2223,10 +2333,18 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     // 6. records and CIGAR
     stage.emplace("sdf final SDs: records");
     DevBuf<uint32_t> aops(NF + 1), apass(NF + 1);
-    SdOut none{nullptr, nullptr};
-    k_assemble<<<(unsigned)NF, 64, 0, st>>>(ix, dreg.p, foff.p, nr, NF, soff.p, seg.p, cols.p,
-                                            ncol.p, fanchor.p, min_len, delta, 0, aops.p, apass.p,
-                                            nullptr, nullptr, none);
+    DevBuf<Share> share(NS + 1);
+    DevBuf<uint32_t> more(NS + 1);
+    DevBuf<uint64_t> mroff(NS + 1);
+    DevBuf<ChainStats> stats(NF);
+    if (NS) {
+        k_shares<<<nb(NS, 256), 256, 0, st>>>(ix, dreg.p, seg.p, NS, cols.p, ncol.p, share.p,
+                                              more.p);
+        SDF_HIP(hipGetLastError());
+    }
+    scan_u32_to_u64(more.p, mroff.p, NS, st);
+    k_chain_counts<<<nb(NF), 256, 0, st>>>(soff.p, NF, seg.p, share.p, mroff.p, fanchor.p,
+                                                min_len, delta, stats.p, aops.p, apass.p);
     SDF_HIP(hipGetLastError());
     DevBuf<uint64_t> woff(NF + 1), opoff(NF + 1);
     scan_u32_to_u64(apass.p, woff.p, NF, st);
@@ -2241,10 +2359,14 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     res.sd.alloc(NSD + 1);
     res.cigar.alloc(NOPS + 1);
     if (NSD) {
-        k_assemble<<<(unsigned)NF, 64, 0, st>>>(ix, dreg.p, foff.p, nr, NF, soff.p, seg.p,
-                                                cols.p, ncol.p, fanchor.p, min_len, delta, 1,
-                                                aops.p, apass.p, woff.p, opoff.p,
-                                                SdOut{res.sd.p, res.cigar.p});
+        fill_u32(res.cigar.p, 0u, NOPS, st);
+        if (NS) {
+            k_cigars<<<nb(NS, 256), 256, 0, st>>>(ix, dreg.p, seg.p, NS, cols.p, ncol.p, share.p,
+                                                  soff.p, mroff.p, apass.p, opoff.p, res.cigar.p);
+            SDF_HIP(hipGetLastError());
+        }
+        k_records<<<nb(NF), 256, 0, st>>>(ix, dreg.p, foff.p, nr, NF, stats.p, fanchor.p, apass.p,
+                                          woff.p, opoff.p, res.sd.p, res.cigar.p);
         SDF_HIP(hipGetLastError());
     }
     SDF_HIP(hipStreamSynchronize(st));
