@@ -339,17 +339,25 @@ __device__ __forceinline__ bool y_in_reach(uint32_t bey, uint32_t ay, uint32_t a
     return ay - bey + (alen - 1) < G + alen;
 }
 
-// The best predecessor seen by a lane: largest value, then (for values
-// above 0) the larger start (x, then y).  Starts are unique within a
+// The best predecessor seen by a lane: largest value, then the larger start (x,
+// then y) as one key, value << 42 | x << 21 | y (0 for values not above 0), so
+// that taking a better one is a plain selection.  (Written as nested conditions
+// on the three, with the members assigned under them, the compiler lost the
+// predecessor's number where values were equal.)  Starts are unique within a
 // region, so the choice does not depend on the order candidates are met.
-// Values fit 32 bits: scores lie in (-2^21, 2^21).
-struct Best2 {
-    int32_t v;
-    uint32_t x, y, b;
+// Values lie in (-2^21, 2^21).
+struct Best1 {
+    uint64_t key;
+    uint32_t b;
+    __device__ __forceinline__ int32_t value() const { return (int32_t)(key >> 42); }
+    __device__ __forceinline__ void take(uint64_t k, uint32_t id) {
+        const bool better = k > key;
+        key = better ? k : key;
+        b = better ? id : b;
+    }
 };
-
-__device__ __forceinline__ bool better2(int32_t v, uint32_t x, uint32_t y, const Best2 &B) {
-    return v > B.v || (v == B.v && v > 0 && (x > B.x || (x == B.x && y > B.y)));
+__device__ __forceinline__ uint64_t best_key(int32_t v, uint32_t x, uint32_t y) {
+    return v > 0 ? ((uint64_t)v << 42) | ((uint64_t)x << 21) | y : 0;
 }
 
 // A 32-bit value of lane i (i the same in every lane).
@@ -420,7 +428,7 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
                                               const uint32_t *large_first) {
     extern __shared__ uint32_t t1_lds[];
     uint32_t *const exhi = t1_lds;  // [nblk]
-    __shared__ Best2 part[T1_WAVES][64];  // per wave and anchor
+    __shared__ Best1 part[T1_WAVES][64];  // per wave and anchor
     __shared__ uint64_t rows[T1_WAVES];   // per wave: anchors with a link inside the batch
     if (blockIdx.x >= nr) return;
     const uint32_t r = large_first[blockIdx.x];
@@ -453,7 +461,7 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
         const uint32_t x0 = lane_u32(x, 0), y0 = lane_u32(y, 0);  // the batch's first start
         const uint32_t xend_max = wave_max_u32(mine ? xend : 0u);
         const uint64_t khi_max = rk | ((uint64_t)xend_max << 21);
-        Best2 B{0, 0, 0, NONE32};
+        Best1 B{0, NONE32};
         // 1. predecessors scored before the batch
         const uint32_t xlo = x0 >= G1 ? x0 - G1 : 0;
         for (;;) {  // blocks ending before every window: a prefix, and x0 only grows
@@ -476,12 +484,11 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
                 const bool pass = mine & (bex < xend) & (bex + G1 >= x) & y_in_reach(bey, y, len, G1);
                 if (!__ballot(pass)) continue;
                 const uint32_t bl = lane_u32(el, i), bx = bex - bl, by = bey - bl;
+                const int32_t sb = (int32_t)lane_u32((uint32_t)es, i);
+                const uint32_t b = lane_u32(esl, i);
                 uint32_t o, dx, dy;
-                if (pass && link_trim(bex, bey, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1) {
-                    const int32_t val =
-                        (int32_t)lane_u32((uint32_t)es, i) - (int32_t)(absdiff(dx, dy) + o);
-                    if (better2(val, bx, by, B)) B = Best2{val, bx, by, lane_u32(esl, i)};
-                }
+                if (pass && link_trim(bex, bey, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1)
+                    B.take(best_key(sb - (int32_t)(absdiff(dx, dy) + o), bx, by), b);
             }
         };
         uint32_t dealt = 0;  // blocks met so far (dealt round robin to the waves)
@@ -534,29 +541,27 @@ __global__ __launch_bounds__(64 * T1_WAVES) void k_tier1(const uint64_t *xykey, 
         __syncthreads();
         if (wave == 0) {
             for (uint32_t q = 1; q < T1_WAVES; q++) {
-                const Best2 o = part[q][lane];
-                if (better2(o.v, o.x, o.y, B)) B = o;
+                const Best1 o = part[q][lane];
+                B.take(o.key, o.b);
                 own |= rows[q];
             }
             // 2. predecessors inside the batch
             for (own = uniform_u64(own); own; own &= own - 1) {
                 const uint32_t k = (uint32_t)__builtin_ctzll(own);
-                const int32_t sk = (int32_t)lane_u32((uint32_t)((int32_t)len + B.v), k);
+                const int32_t sk = (int32_t)lane_u32((uint32_t)((int32_t)len + B.value()), k);
                 const uint32_t xk = lane_u32(x, k), yk = lane_u32(y, k), lk = lane_u32(len, k);
-                const uint32_t exk = xk + lk, eyk = yk + lk;
+                const uint32_t exk = xk + lk, eyk = yk + lk, ak = lane_u32(a, k);
                 if (follows(k)) {
                     uint32_t o, dx, dy;
-                    if (link_trim(exk, eyk, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1) {
-                        const int32_t val = sk - (int32_t)(absdiff(dx, dy) + o);
-                        if (better2(val, xk, yk, B)) B = Best2{val, xk, yk, lane_u32(a, k)};
-                    }
+                    if (link_trim(exk, eyk, x, y, len, o, dx, dy) && (dx > dy ? dx : dy) <= G1)
+                        B.take(best_key(sk - (int32_t)(absdiff(dx, dy) + o), xk, yk), ak);
                 }
             }
             if (mine) {
-                const int64_t sa = (int64_t)len + B.v;  // scores < 2^21
+                const int64_t sa = (int64_t)len + B.value();  // scores < 2^21
                 st_score(t1.score + a, sa);
                 st_score(score_e + apos, sa);
-                t1.pred[a] = B.v > 0 ? B.b : NONE32;
+                t1.pred[a] = B.b;
             }
         }
         __syncthreads();  // scores seen by every wave

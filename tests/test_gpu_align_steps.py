@@ -108,3 +108,26 @@ def test_crowded_region(oracle_lib, unit, copies, strand):
     want = oracle_lib.sd_align(b, off, rows, 11, 300, 0.25, pad_frac=0.0)
     assert len(want[0]) > 0
     _same(got, want, "unit %d" % unit)
+
+
+@pytest.mark.parametrize("seed", [919, 923, 962, 965, 966, 992, 996])
+def test_equal_values_far_apart(oracle_lib, seed):
+    """Copies apart by 8,000 unlike bases: the best chain goes over chance matches
+    in between, and at some of them two predecessors that different waves meet
+    give the same value.  The one that starts later is taken."""
+    from paper_1807_00205_amd import sdf
+    rng = synth.rng_for(seed)
+    q, t = [], []
+    for _ in range(8):
+        cp = synth.random_bases(rng, 9_000)
+        q += [cp, synth.random_bases(rng, 8_000)]
+        t += [cp, synth.random_bases(rng, 8_000)]
+    q, t = np.concatenate(q), np.concatenate(t + [synth.random_bases(rng, 100_000)])
+    b = np.concatenate([q, t])
+    off = np.array([0, len(q), len(b)], np.uint64)
+    rows = [(0, len(q), len(q), len(b), 0)]
+    ix = sdf.Index([q, t], 12, 16)
+    got = ix.align_regions(_regions(sdf, rows, off), 11, 1000, 0.25, pad_frac=0.0)
+    want = oracle_lib.sd_align(b, off, rows, 11, 1000, 0.25, pad_frac=0.0)
+    assert len(want[0]) > 0
+    _same(got, want, "equal values")
