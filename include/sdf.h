@@ -428,9 +428,7 @@ typedef struct {
                                      region whose bounds the chaining tiers keep in LDS
                                      (at most 4,096; later blocks are read from memory and
                                      never skipped) */
-    uint32_t align_lds_ids;       /* final SDs: the most anchors of a region whose used flags
-                                     chain extraction keeps in LDS (at most 2^19; larger
-                                     regions are extracted by one thread from memory) */
+    uint32_t align_lds_ids;       /* without effect: chain extraction keeps no flags in LDS */
 } sdf_tuning;
 
 /* Every field of *t set to SDF_AUTO. */

@@ -17,8 +17,8 @@
 //      or inside the anchor itself (a link then cuts the overlap from the
 //      later anchor's start), a window of a second order, by end, and then
 //      the links inside the batch; the anchors are then ordered by (region,
-//      score descending, x, y) and one wave per region takes the chains
-//      out; the chains become nodes, ordered by (region, x, y) and by
+//      score descending, x, y), and every anchor finds the chain it is taken
+//      out with; the chains become nodes, ordered by (region, x, y) and by
 //      (region, end);
 //   4. tier 2: the same scoring over the nodes (affine cost, gaps up to
 //      10 kbp, blocks of candidates that cannot give a positive link
@@ -46,7 +46,6 @@ constexpr uint32_t T2_BLOCKS = 4096;  // tier-2 end-order blocks per region with
 constexpr uint32_t T2_WAVES = 16;     // waves of a tier-2 workgroup
 constexpr int32_t T2_NEVER = 1 << 29;  // the cost of no link: above any score
 constexpr uint32_t T1_WAVES = 8;      // waves of a tier-1 workgroup
-constexpr uint32_t X_CAP = 1u << 19;  // ids per region with used flags in LDS (64 KiB of bits)
 constexpr uint64_t DP_CELLS = 1ull << 20;
 enum : uint32_t { OP_EQ = 7, OP_X = 8, OP_I = 1, OP_D = 2 };
 
@@ -604,187 +603,86 @@ struct Chains1 {
     uint32_t *flen;                 // length of each node's first anchor
 };
 
-// has_child[p] = 1 for every p that is the kept predecessor of an entry:
-// ids[u] for u < *n (or u itself without ids), the array zeroed beforehand.
-__global__ void k_child_flags(const uint32_t *pred, const uint32_t *ids, uint64_t cap,
-                              const uint32_t *n, uint8_t *has_child) {
+// 3b, 4b. Chains by score: entries (anchors, then nodes) are taken in extraction
+// order; one not yet used starts a chain that follows kept predecessors until
+// a used one (or none); the chain's entries in start order are its members.  So
+// an entry belongs to the chain of the first entry, in extraction order, among
+// itself and all that reach it over kept predecessors: what is used earlier on
+// the way there is used by one of these too.  That minimum is taken over paths
+// of 1, 2, 4, ... predecessors, for all regions at once; sorted by it, stably
+// from start order, the entries are the members of the chains in the order in
+// which these are taken out.
+// (Before, one wave per region followed the chains one after another: 18.5 ms
+// for both tiers of 50 Mbp's regions, where this takes 4.5.)
+
+// own[id] = the entry's place in extraction order, jump[id] = its predecessor.
+__global__ void k_own_init(const uint32_t *order, uint64_t na, const uint32_t *nlive,
+                           const uint32_t *pred, uint32_t *own, uint32_t *jump) {
+    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= na || (nlive && e >= *nlive)) return;
+    const uint32_t id = order[e];
+    own[id] = (uint32_t)e;
+    jump[id] = pred[id];
+}
+
+// One doubling: jin leads 2^i predecessors on, jout twice as far.  own only
+// falls, to places of entries that reach the entry, so a value that is already
+// this round's does no harm.
+__global__ void k_own_double(const uint32_t *list, uint64_t na, const uint32_t *nlive,
+                             uint32_t *own, const uint32_t *jin, uint32_t *jout) {
     const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= cap || (n && u >= *n)) return;
-    const uint32_t p = pred[ids ? ids[u] : (uint32_t)u];
-    if (p != NONE32) has_child[p] = 1;
+    if (u >= na || (nlive && u >= *nlive)) return;
+    const uint32_t id = list[u], p = jin[id];
+    uint32_t next = NONE32;
+    if (p != NONE32) {
+        atomicMin(own + p, own[id]);
+        next = jin[p];
+    }
+    jout[id] = next;
 }
 
-// 3b. tier-1 chains of a region: anchors in score order; an anchor not yet
-// used starts a chain that follows kept predecessors until a used one (or
-// none); the chain's anchors in x order are its members.  The region owns
-// the slots [bnd[r], bnd[r+1]) of every per-anchor array (members, nodes,
-// tmp); its anchors are the ids [bnd[r], bnd[r+1]) too (anchors are made in
-// region order).  One thread, the used flags in global memory: the
-// reference form, kept for regions with more anchors than LDS holds flags.
-__device__ void extract1_serial(const Anchors &an, const uint32_t *byscore, uint32_t r,
-                                uint32_t lo, uint32_t hi, const Tier1 &t1, uint8_t *used,
-                                uint32_t *tmp, const Chains1 &c) {
-    uint32_t pos = lo, nc = 0;
-    for (uint32_t u = lo; u < hi; u++) {
-        uint32_t a = byscore[u];
-        if (used[a]) continue;
-        uint32_t m = 0;
-        while (a != NONE32 && !used[a]) {
-            used[a] = 1;
-            tmp[lo + m++] = a;
-            a = t1.pred[a];
-        }
-        const uint32_t node = lo + nc;
-        c.start[node] = pos;
-        int64_t w = 0;
-        for (uint32_t v = m; v > 0; v--) {
-            const uint32_t b = tmp[lo + v - 1];
-            c.member[pos++] = b;
-            w += an.len[b];
-            if (v < m) {
-                const uint32_t p = tmp[lo + v];
-                uint32_t o = 0, dx = 0, dy = 0;
-                link_trim(an.x[p] + an.len[p], an.y[p] + an.len[p], an.x[b], an.y[b], an.len[b], o,
-                          dx, dy);
-                w -= (int64_t)absdiff(dx, dy) + o;
-            }
-        }
-        c.end[node] = pos;
-        const uint32_t f = tmp[lo + m - 1], l = tmp[lo];
-        c.cx[node] = an.x[f];
-        c.cy[node] = an.y[f];
-        c.cex[node] = an.x[l] + an.len[l];
-        c.cey[node] = an.y[l] + an.len[l];
-        c.w[node] = w;
-        c.flen[node] = an.len[f];
-        nc++;
-    }
-    c.count[r] = nc;
+__global__ void k_own_keys(const uint32_t *list, uint64_t na, const uint32_t *nlive,
+                           const uint32_t *own, uint32_t *key, uint32_t *val) {
+    const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= na) return;
+    const bool live = !nlive || u < *nlive;
+    key[u] = live ? own[list[u]] : ~0u;  // its low bits sort after every place
+    val[u] = live ? list[u] : NONE32;
 }
 
-// The used flags of a region's ids [base, base + n) as bits in LDS (one
-// wave: lane 0 sets, every lane reads).
-struct UsedBits {
-    uint32_t *bits;
-    uint32_t base;
-    __device__ bool get(uint32_t a) const {
-        const uint32_t i = a - base;
-        return (__hip_atomic_load(bits + (i >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >>
-                (i & 31)) & 1u;
-    }
-    __device__ void set(uint32_t a) const {
-        const uint32_t i = a - base;
-        if (threadIdx.x == 0)
-            __hip_atomic_fetch_or(bits + (i >> 5), 1u << (i & 31), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-};
+__global__ void k_own_heads(const uint32_t *key, uint64_t na, const uint32_t *nlive,
+                            uint32_t *flag) {
+    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= na) return;
+    flag[j] = (!nlive || j < *nlive) && (j == 0 || key[j - 1] != key[j]) ? 1u : 0u;
+}
 
-// The same chains, one 64-lane workgroup per region with the used flags in
-// LDS (regions of at most cap anchors): the lanes load the next 64 anchors
-// in score order with their predecessors and coordinates at once, and the
-// wave takes them in order; a predecessor costs one memory round trip only
-// when the chain goes on through it.  A chain's members (the walk
-// reversed) are written by the lanes together.
-__global__ __launch_bounds__(64) void k_extract1(Anchors an, const uint32_t *byscore,
-                                                 const uint32_t *bnd, uint32_t nr, const Tier1 t1,
-                                                 const uint8_t *has_child, uint8_t *used,
-                                                 uint32_t *tmp, Chains1 c, uint32_t cap, const uint32_t *large_first) {
-    extern __shared__ uint32_t x1_bits[];
-    if (blockIdx.x >= nr) return;
-    const uint32_t r = large_first[blockIdx.x];
-    const uint32_t lane = threadIdx.x;
-    const uint32_t lo = bnd[r], hi = bnd[r + 1];
-    if (hi - lo > cap) {
-        if (lane == 0) extract1_serial(an, byscore, r, lo, hi, t1, used, tmp, c);
-        return;
-    }
-    for (uint32_t j = lane; j < (hi - lo + 31) / 32; j += 64) x1_bits[j] = 0;
-    __syncthreads();
-    const UsedBits U{x1_bits, lo};
-    uint32_t pos = lo, nc = 0;
-    for (uint32_t u0 = lo; u0 < hi; u0 += 64) {
-        const uint32_t cnt = min(64u, hi - u0);
-        uint32_t ma = 0, mp = NONE32, mx = 0, my = 0, ml = 0;
-        bool lone = false;  // no predecessor and no successor: a chain of its own
-        if (lane < cnt) {
-            ma = byscore[u0 + lane];
-            mp = t1.pred[ma];
-            mx = an.x[ma];
-            my = an.y[ma];
-            ml = an.len[ma];
-            lone = mp == NONE32 && !has_child[ma];
-        }
-        const uint64_t mlone = __ballot(lone);
-        uint32_t lone_node = 0, lone_pos = 0;  // this lane's, when lone
-        for (uint32_t i = 0; i < cnt; i++) {
-            if ((mlone >> i) & 1) {  // no walk reaches it and it reaches none: no flag needed
-                if (lane == i) {
-                    lone_node = nc;
-                    lone_pos = pos;
-                }
-                pos++;
-                nc++;
-                continue;
-            }
-            const uint32_t a = lane_u32(ma, i);
-            if (U.get(a)) continue;
-            uint32_t cur = a, p = lane_u32(mp, i);
-            uint32_t x = lane_u32(mx, i), y = lane_u32(my, i), l = lane_u32(ml, i);
-            const uint32_t ex = x + l, ey = y + l;  // the chain's end (its last anchor)
-            int64_t w = 0;
-            uint32_t m = 0;
-            for (;;) {
-                U.set(cur);
-                if (lane == 0) tmp[lo + m] = cur;
-                m++;
-                w += l;
-                if (p == NONE32 || U.get(p)) break;
-                // the predecessor, linked to cur with its trim
-                const uint32_t px = an.x[p], py = an.y[p], pl = an.len[p], pp = t1.pred[p];
-                uint32_t o = 0, dx = 0, dy = 0;
-                link_trim(px + pl, py + pl, x, y, l, o, dx, dy);
-                w -= (int64_t)absdiff(dx, dy) + o;
-                cur = p;
-                x = px;
-                y = py;
-                l = pl;
-                p = pp;
-            }
-            if (m == 1) {
-                if (lane == 0) c.member[pos] = a;
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // tmp, written by lane 0
-                for (uint32_t t = lane; t < m; t += 64) c.member[pos + m - 1 - t] = tmp[lo + t];
-            }
-            if (lane == 0) {
-                const uint32_t node = lo + nc;
-                c.start[node] = pos;
-                c.end[node] = pos + m;
-                c.cx[node] = x;  // the first anchor: the walk's last
-                c.cy[node] = y;
-                c.cex[node] = ex;
-                c.cey[node] = ey;
-                c.w[node] = w;
-                c.flen[node] = l;
-            }
-            pos += m;
-            nc++;
-        }
-        if (lone) {  // the batch's lone anchors, written by their lanes
-            const uint32_t node = lo + lone_node;
-            c.member[lone_pos] = ma;
-            c.start[node] = lone_pos;
-            c.end[node] = lone_pos + 1;
-            c.cx[node] = mx;
-            c.cy[node] = my;
-            c.cex[node] = mx + ml;
-            c.cey[node] = my + ml;
-            c.w[node] = ml;
-            c.flen[node] = ml;
-        }
-    }
-    if (lane == 0) c.count[r] = nc;
+// Chains per region, from the chains before each member position.
+__global__ void k_chain_count(const uint32_t *bnd, uint32_t nr, const uint32_t *pre,
+                              uint32_t *count) {
+    const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < nr) count[r] = pre[bnd[r + 1]] - pre[bnd[r]];
+}
+
+// 3c. the tier-1 chains as nodes: a region's in the slots from bnd[r] on.  A
+// chain's weight is what its scores grew by, its links' costs included.
+__global__ void k_nodes1(const Anchors an, const uint32_t *bnd, uint64_t na, const uint32_t *flag,
+                         const uint32_t *pre, const uint64_t *first, const int64_t *score,
+                         Chains1 c) {
+    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= na || !flag[j]) return;
+    const uint32_t i = pre[j];
+    const uint64_t end = i + 1 < pre[na] ? first[i + 1] : na;
+    const uint32_t f = c.member[j], l = c.member[end - 1];
+    const uint32_t lo = bnd[an.reg[f]], node = lo + (i - pre[lo]);
+    c.start[node] = (uint32_t)j;
+    c.end[node] = (uint32_t)end;
+    c.cx[node] = an.x[f];
+    c.cy[node] = an.y[f];
+    c.cex[node] = an.x[l] + an.len[l];
+    c.cey[node] = an.y[l] + an.len[l];
+    c.w[node] = score[l] - score[f] + an.len[f];
+    c.flen[node] = an.len[f];
 }
 
 __global__ void k_slot_regions(const Anchors an, const uint32_t *byxy, uint64_t na,
@@ -1121,105 +1019,16 @@ __global__ void k_node_keys2(const uint32_t *nodes, uint64_t na, const uint32_t 
     }
 }
 
-// 4b. final chains of a region: nodes in extraction order, each not yet
-// used starting a chain that follows kept predecessors until a used one.
-// Final chains of the region use entries from nbnd[r] on; its nodes are
-// the slots [bnd[r], bnd[r] + live nodes).  One thread, the used flags in
-// global memory: the reference form, kept for regions with more slots than
-// LDS holds flags.
-__device__ void extract2_serial(uint32_t r, uint32_t lo, uint32_t hi, const uint32_t *order,
-                                const uint32_t *pred, uint8_t *used, uint32_t *tmp,
-                                const Final &fin) {
-    uint32_t pos = lo, nf = 0;
-    for (uint32_t u = lo; u < hi; u++) {
-        uint32_t a = order[u];
-        if (used[a]) continue;
-        uint32_t m = 0;
-        while (a != NONE32 && !used[a]) {
-            used[a] = 1;
-            tmp[lo + m++] = a;
-            a = pred[a];
-        }
-        fin.start[lo + nf] = pos;
-        for (uint32_t v = m; v > 0; v--) fin.member[pos++] = tmp[lo + v - 1];
-        fin.end[lo + nf] = pos;
-        nf++;
-    }
-    fin.count[r] = nf;
-}
-
-// The same chains, one 64-lane workgroup per region with the used flags in
-// LDS (regions of at most cap slots), as for the tier-1 chains.
-__global__ __launch_bounds__(64) void k_extract2(const uint32_t *nbnd, const uint32_t *bnd,
-                                                 uint32_t nr, const uint32_t *order,
-                                                 const uint32_t *pred, const uint8_t *has_child,
-                                                 uint8_t *used, uint32_t *tmp, Final fin,
-                                                 uint32_t cap, const uint32_t *large_first) {
-    extern __shared__ uint32_t x2_bits[];
-    if (blockIdx.x >= nr) return;
-    const uint32_t r = large_first[blockIdx.x];
-    const uint32_t lane = threadIdx.x;
-    const uint32_t lo = nbnd[r], hi = nbnd[r + 1], base = bnd[r], ns = bnd[r + 1] - base;
-    if (ns > cap) {
-        if (lane == 0) extract2_serial(r, lo, hi, order, pred, used, tmp, fin);
-        return;
-    }
-    for (uint32_t j = lane; j < (ns + 31) / 32; j += 64) x2_bits[j] = 0;
-    __syncthreads();
-    const UsedBits U{x2_bits, base};
-    uint32_t pos = lo, nf = 0;
-    for (uint32_t u0 = lo; u0 < hi; u0 += 64) {
-        const uint32_t cnt = min(64u, hi - u0);
-        uint32_t ma = 0, mp = NONE32;
-        bool lone = false;  // no predecessor and no successor: a chain of its own
-        if (lane < cnt) {
-            ma = order[u0 + lane];
-            mp = pred[ma];
-            lone = mp == NONE32 && !has_child[ma];
-        }
-        const uint64_t mlone = __ballot(lone);
-        uint32_t lone_f = 0, lone_pos = 0;  // this lane's, when lone
-        for (uint32_t i = 0; i < cnt; i++) {
-            if ((mlone >> i) & 1) {
-                if (lane == i) {
-                    lone_f = nf;
-                    lone_pos = pos;
-                }
-                pos++;
-                nf++;
-                continue;
-            }
-            const uint32_t a = lane_u32(ma, i);
-            if (U.get(a)) continue;
-            uint32_t cur = a, p = lane_u32(mp, i), m = 0;
-            for (;;) {
-                U.set(cur);
-                if (lane == 0) tmp[lo + m] = cur;
-                m++;
-                if (p == NONE32 || U.get(p)) break;
-                cur = p;
-                p = pred[p];
-            }
-            if (m == 1) {
-                if (lane == 0) fin.member[pos] = a;
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // tmp, written by lane 0
-                for (uint32_t t = lane; t < m; t += 64) fin.member[pos + m - 1 - t] = tmp[lo + t];
-            }
-            if (lane == 0) {
-                fin.start[lo + nf] = pos;
-                fin.end[lo + nf] = pos + m;
-            }
-            pos += m;
-            nf++;
-        }
-        if (lone) {  // the batch's lone nodes, written by their lanes
-            fin.member[lone_pos] = ma;
-            fin.start[lo + lone_f] = lone_pos;
-            fin.end[lo + lone_f] = lone_pos + 1;
-        }
-    }
-    if (lane == 0) fin.count[r] = nf;
+// 4c. the final chains: a region's entries from nbnd[r] on.
+__global__ void k_finals(const uint32_t *reg_of_slot, const uint32_t *nbnd, uint64_t na,
+                         const uint32_t *nlive, const uint32_t *flag, const uint32_t *pre,
+                         const uint64_t *first, Final fin) {
+    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= na || !flag[j]) return;
+    const uint32_t i = pre[j];
+    const uint32_t lo = nbnd[reg_of_slot[fin.member[j]]], at = lo + (i - pre[lo]);
+    fin.start[at] = (uint32_t)j;
+    fin.end[at] = i + 1 < pre[na] ? (uint32_t)first[i + 1] : *nlive;
 }
 
 // Final chain g (global, in region order) as (region, entry).
@@ -2059,6 +1868,35 @@ __global__ void k_u32_to_u64(const uint32_t *a, uint64_t n, uint64_t *b) {
 
 unsigned nb(uint64_t n, unsigned t = 256) { return (unsigned)std::max<uint64_t>(1, (n + t - 1) / t); }
 
+// Chains taken out by score (see k_own_init): the members of all chains, chain
+// after chain (member), the chains' heads (flag), the chains before each
+// position (pre, na + 1) and each chain's first position (first).  order, list:
+// the entries in extraction and in start order, the first *nlive of them (all
+// na without); most: the most entries of a region.
+void take_chains(const uint32_t *order, const uint32_t *list, const uint32_t *pred, uint64_t na,
+                 const uint32_t *nlive, uint32_t most, uint32_t *member, uint32_t *flag,
+                 uint32_t *pre, uint64_t *first, hipStream_t st) {
+    DevBuf<uint32_t> own(na), key(na), ja(na), jb(na);
+    k_own_init<<<nb(na), 256, 0, st>>>(order, na, nlive, pred, own.p, ja.p);
+    SDF_HIP(hipGetLastError());
+    uint32_t *jin = ja.p, *jout = jb.p;
+    for (uint64_t reach = 1; reach < most; reach *= 2) {
+        k_own_double<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, jin, jout);
+        SDF_HIP(hipGetLastError());
+        std::swap(jin, jout);
+    }
+    k_own_keys<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, key.p, member);
+    SDF_HIP(hipGetLastError());
+    int bits = 1;
+    while ((1ull << bits) <= na) bits++;
+    radix_sort_u32(key.p, member, na, bits, st);
+    k_own_heads<<<nb(na), 256, 0, st>>>(key.p, na, nlive, flag);
+    SDF_HIP(hipGetLastError());
+    scan_u32(flag, pre, na, st);
+    k_run_first<<<nb(na), 256, 0, st>>>(flag, pre, na, first);
+    SDF_HIP(hipGetLastError());
+}
+
 template <class T>
 T read1(const T *d, hipStream_t st) {
     T h{};
@@ -2210,21 +2048,15 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     k_score_keys<<<nb(A), 256, 0, st>>>(an, A, t1, 1, kbuf.p, byscore.p, perm.p);
     SDF_HIP(hipGetLastError());
     radix_sort_u64(kbuf.p, byscore.p, A, 41 + rbits, st);
-    DevBuf<uint8_t> used(A + 4);
-    fill_u32(reinterpret_cast<uint32_t *>(used.p), 0u, (A + 3) / 4, st);
-    DevBuf<uint32_t> tmp(A), mem1(A), cst(A), cend(A), ccount(n), cx(A), cy(A), cex(A), cey(A),
-        cfl(A);
+    DevBuf<uint32_t> mem1(A), cst(A), cend(A), ccount(n), cx(A), cy(A), cex(A), cey(A), cfl(A);
     DevBuf<int64_t> cw(A);
     Chains1 c{mem1.p, cst.p, cend.p, ccount.p, cx.p, cy.p, cex.p, cey.p, cw.p, cfl.p};
-    // used flags of up to X_CAP ids per region as LDS bits (align_lds_ids)
-    const uint32_t xcap =
-        (uint32_t)std::min<uint64_t>(std::min(knob(tuning().align_lds_ids, X_CAP), X_CAP) / 32 * 32,
-                                     (most_anchors + 31) / 32 * 32);
-    DevBuf<uint8_t> child(A + 4);  // anchors (then node slots) that are some entry's predecessor
-    fill_u32(reinterpret_cast<uint32_t *>(child.p), 0u, (A + 3) / 4, st);
-    k_child_flags<<<nb(A), 256, 0, st>>>(t1.pred, nullptr, A, nullptr, child.p);
-    k_extract1<<<nr, 64, std::max<uint32_t>(4, xcap / 8), st>>>(an, byscore.p, bnd.p, nr, t1,
-                                                                child.p, used.p, tmp.p, c, xcap, large.p);
+    DevBuf<uint32_t> cpre(A + 1);  // chains before each member position
+    DevBuf<uint64_t> cfirst(A);    // each chain's first
+    take_chains(byscore.p, byxy.p, t1.pred, A, nullptr, most_anchors, c.member, flag.p, cpre.p,
+                cfirst.p, st);
+    k_chain_count<<<nb(n), 256, 0, st>>>(bnd.p, nr, cpre.p, c.count);
+    k_nodes1<<<nb(A), 256, 0, st>>>(an, bnd.p, A, flag.p, cpre.p, cfirst.p, t1.score, c);
     SDF_HIP(hipGetLastError());
     // nodes ordered by (region, x, y)
     DevBuf<uint32_t> rslot(A), nodes(A), nbnd(n + 1);
@@ -2244,6 +2076,7 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
                                         ekey.p, nodes_e.p);
     SDF_HIP(hipGetLastError());
     radix_sort_u64(ekey.p, nodes_e.p, A, 42 + rbits, st);
+    uint32_t most_nodes = 0;  // nodes of the largest region
     {
         DevBuf<uint32_t> pos_e(A), ue(A), p2s(A);
         DevBuf<Node2> node2(A);
@@ -2256,9 +2089,10 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
         fill_u32(most.p, 0u, 1, st);
         k_max_span<<<nb(n), 256, 0, st>>>(nbnd.p, nr, most.p);
         SDF_HIP(hipGetLastError());
-        const uint32_t nblk = std::min<uint32_t>(
-            std::min(knob(tuning().align_lds_blocks, T2_BLOCKS), T2_BLOCKS),
-            (read1(most.p, st) + 63) / 64);
+        most_nodes = read1(most.p, st);
+        const uint32_t nblk =
+            std::min<uint32_t>(std::min(knob(tuning().align_lds_blocks, T2_BLOCKS), T2_BLOCKS),
+                               (most_nodes + 63) / 64);
         k_tier2<<<nr, 64 * T2_WAVES, 8 * nblk, st>>>(nbnd.p, nr, node2.p, ekey.p, ue.p, s2s.p,
                                                      s2e.p, p2s.p, nblk, large.p);
         k_node_results<<<nb(A), 256, 0, st>>>(node2.p, A, nbnd.p + nr, s2s.p, p2s.p, s2.p, p2.p);
@@ -2272,12 +2106,11 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
                                         kbuf.p, order.p);
     SDF_HIP(hipGetLastError());
     radix_sort_u64(kbuf.p, order.p, A, 42 + rbits, st);
-    fill_u32(reinterpret_cast<uint32_t *>(used.p), 0u, (A + 3) / 4, st);
     Final fin{fmem.p, fst.p, fend.p, fcount.p};
-    fill_u32(reinterpret_cast<uint32_t *>(child.p), 0u, (A + 3) / 4, st);
-    k_child_flags<<<nb(A), 256, 0, st>>>(p2.p, order.p, A, nbnd.p + nr, child.p);
-    k_extract2<<<nr, 64, std::max<uint32_t>(4, xcap / 8), st>>>(nbnd.p, bnd.p, nr, order.p, p2.p,
-                                                                child.p, used.p, tmp.p, fin, xcap, large.p);
+    take_chains(order.p, nodes.p, p2.p, A, nbnd.p + nr, most_nodes, fin.member, flag.p, cpre.p,
+                cfirst.p, st);
+    k_chain_count<<<nb(n), 256, 0, st>>>(nbnd.p, nr, cpre.p, fin.count);
+    k_finals<<<nb(A), 256, 0, st>>>(rslot.p, nbnd.p, A, nbnd.p + nr, flag.p, cpre.p, cfirst.p, fin);
     SDF_HIP(hipGetLastError());
     DevBuf<uint64_t> foff(n + 1);
     scan_u32_to_u64(fcount.p, foff.p, n, st);
