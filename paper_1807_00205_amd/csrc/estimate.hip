@@ -36,10 +36,11 @@ namespace sdf {
 
 constexpr int EW = 3;         // runs (waves) per workgroup
 constexpr int FMAX = 256;     // minimizers of a window and of a run, first launch
-// Runs per wave of the first launch: their seeds leave with one atomic, since
+// Most runs per wave of the first launch: their seeds leave with one atomic, since
 // the seed counter takes one about every 12 ns from all CUs together (one per
 // run: 14.2 ms for 1.2 million seeds, whatever the kernel did besides).
 constexpr uint32_t ERUNS = 32;
+constexpr uint64_t EWAVES = 4096;  // 256 CUs with four waves per SIMD
 constexpr int AMAX_L = 1024, TCAP_L = 512;  // second launch
 constexpr uint16_t TR_IN = 0x8000, TR_SHARED = 0x4000, TR_RANK = 0x3FF;
 
@@ -682,7 +683,7 @@ __device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L,
 
 template <class K>
 __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const uint32_t *runs,
-                                                            uint64_t nruns, uint32_t n,
+                                                            uint64_t nruns, uint32_t per, uint32_t n,
                                                             const uint16_t *T, uint32_t *seeds,
                                                             uint64_t cap, unsigned long long *nseeds,
                                                             uint32_t *err, uint32_t amax,
@@ -692,8 +693,8 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
     const uint32_t lane = e_lane(), wv = threadIdx.x >> 6;
     EstFirst &L = W[wv];
     const uint32_t k = ix.k;
-    const uint64_t r0 = ((uint64_t)blockIdx.x * EW + wv) * ERUNS;  // (no workgroup barrier below)
-    const uint64_t r1 = min(r0 + ERUNS, nruns);
+    const uint64_t r0 = ((uint64_t)blockIdx.x * EW + wv) * per;  // (no workgroup barrier below)
+    const uint64_t r1 = min(r0 + per, nruns);
     uint32_t nbuf = 0;
     // minimizers [first, first + count) at positions [from, to]; above `most`: most + 1
     auto count = [&](uint64_t first, uint64_t to, uint32_t most, uint32_t *pos) {
@@ -764,8 +765,12 @@ void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nr
     // hash and index in 32 bits while the hash has at most 24 (k <= 12): half the
     // instructions per exchange of a sort
     const auto first = 2 * ix.k <= 24 ? k_estimate_runs<uint32_t> : k_estimate_runs<uint64_t>;
-    first<<<(unsigned)((nruns + EW * ERUNS - 1) / (EW * ERUNS)), EW * 64, 0, st>>>(
-        ix, runs, nruns, n, T, seeds, cap, nseeds, err, amax, tmax, over.p, nover.p);
+    // a run takes its wave some 14 us, so few runs are spread over the waves the
+    // chip holds before any takes several (0.8 Mbp: 1,377 us a call with 32 runs
+    // per wave, 471 spread)
+    const uint32_t per = (uint32_t)std::clamp<uint64_t>((nruns + EWAVES - 1) / EWAVES, 1, ERUNS);
+    first<<<(unsigned)((nruns + EW * per - 1) / (EW * per)), EW * 64, 0, st>>>(
+        ix, runs, nruns, per, n, T, seeds, cap, nseeds, err, amax, tmax, over.p, nover.p);
     SDF_HIP(hipGetLastError());
     unsigned long long no = 0;
     {
