@@ -1868,6 +1868,17 @@ __global__ void k_u32_to_u64(const uint32_t *a, uint64_t n, uint64_t *b) {
 
 unsigned nb(uint64_t n, unsigned t = 256) { return (unsigned)std::max<uint64_t>(1, (n + t - 1) / t); }
 
+// launch(first, blocks) for n workgroups of `threads` threads, in parts of fewer
+// than the 2^32 threads a launch may have.
+template <class F>
+void by_parts(uint64_t n, uint64_t threads, F &&launch) {
+    const uint64_t most = ((1ull << 32) - 1) / threads;
+    for (uint64_t first = 0; first < n; first += most) {
+        launch(first, (unsigned)std::min(most, n - first));
+        SDF_HIP(hipGetLastError());
+    }
+}
+
 // Chains taken out by score (see k_own_init): the members of all chains, chain
 // after chain (member), the chains' heads (flag), the chains before each
 // position (pre, na + 1) and each chain's first position (first).  order, list:
@@ -1969,17 +1980,19 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     if (QT) {
         SDF_HIP(hipMemcpyAsync(work.p, hw.data(), hw.size() * sizeof(SeedWork),
                                hipMemcpyHostToDevice, st));
-        k_seeds<false><<<(unsigned)hw.size(), SEED_THREADS, 0, st>>>(
-            ix, dreg.p, work.p, qoff.p, k, qcnt.p, nullptr, nullptr);
-        SDF_HIP(hipGetLastError());
+        by_parts(hw.size(), SEED_THREADS, [&](uint64_t first, unsigned blocks) {
+            k_seeds<false><<<blocks, SEED_THREADS, 0, st>>>(ix, dreg.p, work.p + first, qoff.p, k,
+                                                            qcnt.p, nullptr, nullptr);
+        });
     }
     scan_u32_to_u64(qcnt.p, moff.p, QT, st);
     const uint64_t M = read1(moff.p + QT, st);
     DevBuf<uint64_t> mkey(M + 1);
     if (M) {
-        k_seeds<true><<<(unsigned)hw.size(), SEED_THREADS, 0, st>>>(
-            ix, dreg.p, work.p, qoff.p, k, qcnt.p, moff.p, mkey.p);
-        SDF_HIP(hipGetLastError());
+        by_parts(hw.size(), SEED_THREADS, [&](uint64_t first, unsigned blocks) {
+            k_seeds<true><<<blocks, SEED_THREADS, 0, st>>>(ix, dreg.p, work.p + first, qoff.p, k,
+                                                           qcnt.p, moff.p, mkey.p);
+        });
         // (region, diagonal): the matches are made in x order within a region
         sort_keys_u64_bits(mkey.p, M, 20, 41 + rbits, st);
     }
@@ -2163,10 +2176,10 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
             k_align_segs<<<nb(nthread, 64), 64, 0, st>>>(ix, dreg.p, seg.p, order.p, nthread, tb.p,
                                                         rows.p, cols.p, ncol.p);
         SDF_HIP(hipGetLastError());
-        if (NS > nthread)
-            k_align_wave<<<(unsigned)(NS - nthread), 64, 0, st>>>(
-                ix, dreg.p, seg.p, order.p + nthread, NS - nthread, tb.p, cols.p, ncol.p);
-        SDF_HIP(hipGetLastError());
+        by_parts(NS - nthread, 64, [&](uint64_t first, unsigned blocks) {
+            k_align_wave<<<blocks, 64, 0, st>>>(ix, dreg.p, seg.p, order.p + nthread + first, blocks,
+                                                tb.p, cols.p, ncol.p);
+        });
     }
     // 6. records and CIGAR
     stage.emplace("sdf final SDs: records");
