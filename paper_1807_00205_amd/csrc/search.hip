@@ -9,7 +9,8 @@
 // hits of the tile stay on chip:
 //   1. gather: every hit (p, p', o) is loaded once, increments a small counter
 //      for its (orientation, target bin of 2^SB >= n bases) in an LDS table
-//      indexed by the bin modulo the table size, and stays in a register;
+//      indexed by the bin modulo the table size, and the first ones of a lane
+//      stay in registers;
 //   2. the counters become flags: a slot is hot when some pair of adjacent
 //      bins around it holds at least T_min hits;
 //   3. a hit is kept only if its slot is hot.  Bins that share a slot only
@@ -28,15 +29,15 @@
 // of the phase sequence.  Counters have 4 bits while the tile has many hits
 // (131,072 slots in 64 KiB: fewer chance hits in a slot than 16-bit counters
 // in a quarter of the slots, so the whole tile fits one partition and every
-// list is read once, in one piece), 8 bits when it has few or when a 4-bit
+// list is searched once, in one piece), 8 bits when it has few or when a 4-bit
 // counter overflows, 16 bits when an 8-bit one does.  An overflow shows in
 // the sum of the counters, taken while they become flags: it equals the
 // number of hits counted exactly when none wrapped.
 //
 // Measured against 16-bit counters in 32 KiB, partitions of 16,384 hits, a
 // search per hit for its list and hits gathered twice (tile kernel): 3.1 Gbp
-// all-vs-all 538 -> 205 ms, 4,096 spans on 250 Mbp 4.06 -> 1.65 ms, 50 Mbp
-// 1.31 -> 0.94 ms.
+// all-vs-all 538 -> 170 ms, 4,096 spans on 250 Mbp 4.06 -> 1.38 ms, 50 Mbp
+// 1.31 -> 0.84 ms.
 //
 // The file is compiled twice, for two workgroup layouts (SDF_TILE_THREADS):
 // 1,024 threads, one workgroup per CU, and 512 threads with 80 KB of LDS, two
@@ -439,7 +440,12 @@ __device__ __forceinline__ uint32_t list_of(const TileLds &L, uint32_t e) {
 }
 
 constexpr int HU = 8;  // chunks gathered per round: their loads are all in flight together
-constexpr int SG = 6;  // rounds whose hits stay in registers (48 per lane)
+// Rounds whose hits stay in registers (24 per lane); those of later rounds are
+// gathered again.  More of them spill: 6 rounds wrote 224 GB of scratch per
+// 3.1 Gbp search (tile kernel 206, 197, 176, 170, 173 ms at 6, 5, 4, 3, 2
+// rounds; 4,096 spans 1.63, 1.61, 1.51, 1.38, 1.48 ms; 50 Mbp 0.95, 0.95, 0.90,
+// 0.84, 0.85 ms).
+constexpr int SG = 3;
 
 // Hits of the chunks [c, c + HU): pv = target position, bit u of the result =
 // orientation.  Lists and chunks are exact, so every load is in range; lanes
