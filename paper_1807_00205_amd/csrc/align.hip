@@ -626,8 +626,8 @@ __global__ void k_own_init(const uint32_t *order, uint64_t na, const uint32_t *n
 }
 
 // One doubling: jin leads 2^i predecessors on, jout twice as far.  own only
-// falls, to places of entries that reach the entry, so a value that is already
-// this round's does no harm.
+// falls, to places of entries that reach the entry, so a value that has
+// fallen in the same launch already does no harm.
 __global__ void k_own_double(const uint32_t *list, uint64_t na, const uint32_t *nlive,
                              uint32_t *own, const uint32_t *jin, uint32_t *jout) {
     const uint64_t u = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
