@@ -410,9 +410,10 @@ typedef struct {
     uint32_t cand_sort_general;   /* 1: candidates ordered by the record sort alone */
     uint32_t cand_sort_small_max; /* most candidates sorted by one workgroup */
     uint32_t cand_tie_max;        /* longest run of equal sort prefixes ordered in place */
-    uint32_t est_lds_cap;         /* estimate mode: most hashes of a run held in LDS */
+    uint32_t est_lds_cap;         /* estimate mode: most minimizers of a run held on chip */
     uint32_t est_reg_cap;         /* estimate mode: most held in registers */
-    uint32_t est_first_amax;      /* estimate mode: largest window of the first launch */
+    uint32_t est_first_amax;      /* estimate mode: largest window taken in registers (0: every
+                                     run goes to the last launch) */
     uint32_t ext_h0;              /* extension: steps gathered per phase and attempt */
     uint32_t ext_lds_words;       /* extension: ordered-set cells kept in LDS */
     uint32_t ext_hb0;             /* extension: backward steps gathered early */

@@ -16,17 +16,26 @@
 // belongs to it.  One wave takes one run and emits the seed of its largest m
 // (earliest j on ties) when m reaches the threshold T[s].
 //
-// First launch (windows and runs of up to 256 minimizers): the run's target
-// minimizers are classified against the sorted query hashes and sorted by
-// hash once, in registers.  In that order a candidate needs no sort of its
-// own: the distinct outside hashes of its window are the lanes whose
-// occurrence lies in it and whose previous occurrence does not (a compare and
-// a ballot), the number of them below a lane is the popcount of the ballot
-// below it, and y, the shared count and m are popcounts too.  Bound by the
-// instructions of the two sorts and of the steps: 5.9 ms for the 1.5 million
-// runs of the 50 Mbp workload, where a sort per candidate, shared ranks marked
-// in LDS and a global atomic per seed took 14.2.  A second launch takes the
-// runs that do not fit, with the window of each candidate sorted by itself.
+// Runs whose target minimizers fit a wave's registers: they are classified
+// against the sorted query hashes and sorted by hash once, in registers.  In
+// that order a candidate needs no sort of its own: the distinct outside hashes
+// of its window are the lanes whose occurrence lies in it and whose previous
+// occurrence does not (a compare and a ballot), the number of them below a lane
+// is the popcount of the ballot below it, and y, the shared count and m are
+// popcounts too.  Bound by the instructions of the two sorts and of the steps.
+// A run's target minimizers are about twice its window's, so three sizes cover
+// the windows in use; each launch hands the runs past its size on:
+//   1. windows and runs of up to 256 minimizers (2 or 4 keys per lane);
+//   2. runs of up to 512 (8 per lane);
+//   3. windows of up to 512, runs of up to 1,024 (16 per lane).
+// The rest (tandem arrays, longer windows) have the window of each candidate
+// sorted by itself.  Whole calls over 50 Mbp with duplications (k = 12), against
+// 256 as the only size with the rest left to the last launch, and against a sort
+// per candidate throughout (LDS marks, a global atomic per seed):
+//   min_len 1,000, w 16 ( 88 minimizers a window)   7.1 ms     7.2     15.9
+//           2,000, w 16 (176)                      17.4      288      169
+//           2,000, w 12 (231)                      32.1    1,521      589
+//           2,000, w 12, error 0.15, k 14 (262)    61.4    2,187    1,642
 #include <algorithm>
 #include <cstdlib>
 
@@ -35,13 +44,18 @@
 namespace sdf {
 
 constexpr int EW = 3;         // runs (waves) per workgroup
-constexpr int FMAX = 256;     // minimizers of a window and of a run, first launch
-// Most runs per wave of the first launch: their seeds leave with one atomic, since
-// the seed counter takes one about every 12 ns from all CUs together (one per
-// run: 14.2 ms for 1.2 million seeds, whatever the kernel did besides).
+// Most runs per wave of a register launch: their seeds leave with one atomic, and
+// so do the runs handed on, since a counter takes one atomic about every 12 ns
+// from all CUs together (one per run: 14.2 ms for 1.2 million seeds, whatever the
+// kernel did besides).
 constexpr uint32_t ERUNS = 32;
 constexpr uint64_t EWAVES = 4096;  // 256 CUs with four waves per SIMD
-constexpr int AMAX_L = 1024, TCAP_L = 512;  // second launch
+constexpr int AMAX_M = 256, TCAP_M = 64;    // minimizers held where a candidate's window is
+constexpr int AMAX_L = 1024, TCAP_L = 512;  // sorted by itself: of a window, of a run
+// Listed runs that the register launches leave: with a window of up to AMAX_M
+// minimizers, and the others.
+constexpr uint32_t RUN_MID = 1u << 30, RUN_LAST = 1u << 31;
+constexpr uint64_t RUNS_MAX = 1ull << 30;  // runs listed at once
 constexpr uint16_t TR_IN = 0x8000, TR_SHARED = 0x4000, TR_RANK = 0x3FF;
 
 template <int AMAX, int TC>
@@ -251,15 +265,16 @@ __device__ uint32_t estimate_at(const IndexView &ix, W &L, uint32_t s, uint32_t 
     __builtin_amdgcn_wave_barrier();
     uint32_t nb = 0;
     for (uint64_t base = tj;; base += 64) {
-        const uint64_t tm = base + lane;
-        const bool v = tm < ix.nm && (uint64_t)ix.mpos[tm] <= jend;
+        // (position, hash and flags loaded together: a candidate is bound by the
+        // latency of its loads)
+        const uint64_t tm = base + lane, tc = min(tm, ix.nm - 1);
+        const uint32_t pos = ix.mpos[tc], h = ix.mhash[tc];
+        const uint8_t fl = ix.mflags[tc];
+        const bool v = tm < ix.nm && (uint64_t)pos <= jend;
         bool outside = false;
-        uint32_t h = 0;
         if (v) {
-            h = ix.mhash[tm];
             const uint32_t r = rank_below(L.ahash, s, h);
             if (r < s && L.ahash[r] == h) {
-                const uint8_t fl = ix.mflags[tm];
                 if ((fl & 2) && pairs(L, r, fl & 1, o, tm, q0, na))  // eligible and pairs
                     atomicOr(&L.cbits[r >> 6], 1ull << (r & 63));
             } else {
@@ -305,23 +320,28 @@ __device__ uint32_t estimate_lds(W &L, uint32_t s, uint32_t xs, uint32_t xe, boo
     return estimate_finish(L, out, L.u.run.first, s, nb, have, beat, reg_cap);  // nb <= W::tcap
 }
 
-// The runs listed in `list`, with windows of up to 1,024 minimizers.
+// The runs of `list` marked MARK, with windows of up to AMAX minimizers (of the
+// query, and outside hashes of a target window).  RUN_MID: one that does not fit
+// is left to the launch of the RUN_LAST ones (the smaller form has 39 waves per CU,
+// the larger nine; a run of thousands of candidates, as along a tandem array, is
+// bound by their latency).
+template <int AMAX, int TC, uint32_t MARK>
 __global__ void __launch_bounds__(EW * 64) k_estimate_long(IndexView ix, const uint32_t *runs,
-                                                            uint64_t nruns, const uint32_t *list,
+                                                            uint64_t nruns, uint32_t *list,
                                                             uint32_t n, const uint16_t *T,
                                                             uint32_t *seeds, uint64_t cap,
                                                             unsigned long long *nseeds,
                                                             uint32_t *err, uint32_t lds_cap,
                                                             uint32_t reg_cap) {
-    constexpr int AMAX = AMAX_L, TC = TCAP_L;
-    constexpr uint32_t amax_rt = AMAX_L;
+    constexpr uint32_t amax_rt = AMAX;
     using Wave = EstWave<AMAX, TC>;
     __shared__ Wave W[EW];
     const uint32_t lane = e_lane(), wv = threadIdx.x >> 6;
     Wave &L = W[wv];
     const uint64_t slot = (uint64_t)blockIdx.x * EW + wv;
     if (slot >= nruns) return;  // whole wave; no workgroup barrier below
-    const uint64_t r = list[slot];
+    if (!(list[slot] & MARK)) return;
+    const uint64_t r = list[slot] & ~MARK;
     const uint64_t ltmask = lane ? (~0ull >> (64 - lane)) : 0ull;
     const uint32_t *rec = runs + r * 6;
     const uint32_t qid = rec[0], i = rec[1], jf = rec[2], o = rec[3], jl = rec[4], s = rec[5];
@@ -459,7 +479,10 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_long(IndexView ix, const u
             const uint32_t m =
                 estimate_at(ix, L, s, o, base + l, (uint64_t)j + n - k, have, best_m, reg_cap, q0, na);
             if (m == NONE32) {
-                if (lane == 0) atomicOr(err, 1u);
+                if (lane == 0) {
+                    if (MARK == RUN_MID) list[slot] = (uint32_t)r | RUN_LAST;
+                    else atomicOr(err, 1u);
+                }
                 return;
             }
             if (!have || m > best_m) {
@@ -479,7 +502,7 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_long(IndexView ix, const u
     }
 }
 
-// ------------------------------------------------------- first launch --
+// ---------------------------------------------------- register launches --
 // Ascending bitonic sort of 64 E keys in registers, element e * 64 + lane.
 template <class K, int E>
 __device__ __forceinline__ void wave_sort_keys(K (&x)[E], uint32_t lane) {
@@ -512,79 +535,92 @@ __device__ __forceinline__ void wave_sort_keys(K (&x)[E], uint32_t lane) {
     }
 }
 
-struct EstFirst {
-    uint32_t ahash[FMAX];  // distinct query hashes, ascending (W_i)
-    uint32_t acnt[FMAX];   // eligible occurrences per hash: strand 0 low 16 bits, strand 1 high
-    uint32_t tp[FMAX];     // the run's target minimizers: position,
-    uint16_t tr[FMAX];     // TR_* and rank, or the hashes of W_i below it when outside
-    uint64_t sorted[FMAX]; // their keys in order
+// What a wave of a register launch holds: windows of up to AM minimizers, runs
+// of up to TM.  Sort keys are a hash above the bits of an index below TM.
+template <int AM, int TM>
+struct EstRun {
+    static constexpr int amax = AM, tmax = TM;
+    static constexpr int ibits = __builtin_ctz(TM);
+    uint32_t ahash[AM];  // distinct query hashes, ascending (W_i)
+    uint32_t acnt[AM];   // eligible occurrences per hash: strand 0 low 16 bits, strand 1 high
+    union {
+        uint32_t tp[TM];    // the run's target minimizers: positions;
+        uint32_t cand[TM];  // then its candidates in order: place | end of its window's places << 16
+    };
+    uint16_t tr[TM];     // TR_* and rank, or the hashes of W_i below it when outside
+    uint16_t ord[TM];    // in hash order: place in the run | ORD_SAME
     uint32_t seeds[ERUNS * 6];
 };
+constexpr uint32_t ORD_SAME = 0x8000;  // the hash of the one before
+
+// The keys before x's own in sorted order (lane 0 of register 0: 0).
+template <class K, int E>
+__device__ __forceinline__ K key_before(const K (&x)[E], int e, uint32_t lane) {
+    K p, b = 0;
+    if constexpr (sizeof(K) == 8) {
+        p = ((K)(uint32_t)__shfl_up((int)(uint32_t)(x[e] >> 32), 1, 64) << 32) |
+            (uint32_t)__shfl_up((int)(uint32_t)x[e], 1, 64);
+        if (e) b = ((K)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x[e ? e - 1 : 0] >> 32), 63) << 32) |
+                   (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x[e ? e - 1 : 0], 63);
+    } else {
+        p = (K)__shfl_up((int)x[e], 1, 64);
+        if (e) b = (K)__builtin_amdgcn_readlane((int)x[e ? e - 1 : 0], 63);
+    }
+    return lane == 0 ? b : p;
+}
 
 // Query hashes of a window in order: distinct ones and their eligible
-// occurrences; the number of distinct ones.  Keys are hash << 8 | index of
-// the minimizer in the window.
-template <class K, int E>
-__device__ __forceinline__ uint32_t sort_query(const IndexView &ix, EstFirst &L, uint64_t q0,
-                                               uint32_t na, uint32_t lane) {
+// occurrences; the number of distinct ones.  Keys: hash over the index of the
+// minimizer in the window.
+template <class K, int E, class W>
+__device__ __forceinline__ uint32_t sort_query(const IndexView &ix, W &L, uint64_t q0, uint32_t na,
+                                               uint32_t lane) {
+    constexpr int IB = W::ibits;
     K x[E];
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const uint32_t t = e * 64 + lane;
-        x[e] = t < na ? ((K)ix.mhash[q0 + t] << 8) | t : (K)~(K)0;
+        x[e] = t < na ? ((K)ix.mhash[q0 + t] << IB) | t : (K)~(K)0;
     }
     wave_sort_keys<K, E>(x, lane);
     for (uint32_t t = lane; t < na; t += 64) L.acnt[t] = 0;
     __builtin_amdgcn_wave_barrier();
     const uint64_t le = lane == 63 ? ~0ull : (1ull << (lane + 1)) - 1;
     uint32_t nd = 0;
-    K before = 0;
 #pragma unroll
     for (int e = 0; e < E; e++) {
-        K p = x[e];
-        if constexpr (sizeof(K) == 8)
-            p = ((K)(uint32_t)__shfl_up((int)(uint32_t)(x[e] >> 32), 1, 64) << 32) |
-                (uint32_t)__shfl_up((int)(uint32_t)x[e], 1, 64);
-        else
-            p = (K)__shfl_up((int)x[e], 1, 64);
-        if (lane == 0) p = before;
+        const K p = key_before<K, E>(x, e, lane);
         const uint32_t t = e * 64 + lane;
-        const bool first = t < na && (t == 0 || (p >> 8) != (x[e] >> 8));
+        const bool first = t < na && (t == 0 || (p >> IB) != (x[e] >> IB));
         const uint64_t fm = __ballot(first);
         const uint32_t rk = nd + (uint32_t)__popcll(fm & le) - 1;
         if (t < na) {
-            if (first) L.ahash[rk] = (uint32_t)(x[e] >> 8);
-            const uint8_t fl = ix.mflags[q0 + (uint32_t)(x[e] & 255)];
+            if (first) L.ahash[rk] = (uint32_t)(x[e] >> IB);
+            const uint8_t fl = ix.mflags[q0 + (uint32_t)(x[e] & (W::tmax - 1))];
             if (fl & 2) atomicAdd(&L.acnt[rk], (fl & 1) ? 0x10000u : 1u);
         }
         nd += (uint32_t)__popcll(fm);
-        if constexpr (sizeof(K) == 8)
-            before = ((K)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x[e] >> 32), 63) << 32) |
-                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x[e], 63);
-        else
-            before = (K)__builtin_amdgcn_readlane((int)x[e], 63);
     }
     __builtin_amdgcn_wave_barrier();
     return nd;
 }
 
 // The candidate of the largest m among the run's nt <= 64 E target minimizers
-// [t0, t0 + nt), whose positions are in tp: best_m, best_j; false: none.
-template <class K, int E>
-__device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L, uint64_t t0,
-                                               uint32_t nt, uint64_t q0, uint32_t na, uint32_t s,
-                                               uint32_t o, uint32_t n, uint32_t jl, uint32_t lane,
-                                               uint32_t &best_m, uint32_t &best_j) {
+// [t0, t0 + nt), whose positions are in tp: best_m and its place; false: none.
+template <class K, int E, class W>
+__device__ __forceinline__ bool best_candidate(const IndexView &ix, W &L, uint64_t t0, uint32_t nt,
+                                               uint64_t q0, uint32_t na, uint32_t s, uint32_t o,
+                                               uint32_t n, uint32_t jl, uint32_t lane,
+                                               uint32_t &best_m, uint32_t &best_x) {
+    constexpr int IB = W::ibits;
     const uint32_t k = ix.k;
     K x[E];
-    uint64_t cand[E];
-    uint32_t wend[E];
+    uint32_t wend[E];  // 0: no candidate
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const uint32_t t = e * 64 + lane;
         x[e] = (K)~(K)0;
         wend[e] = 0;
-        bool c = false;
         if (t < nt) {
             const uint32_t h = ix.mhash[t0 + t], pos = L.tp[t];
             const uint8_t fl = ix.mflags[t0 + t];
@@ -595,9 +631,9 @@ __device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L,
                 if ((fl & 2) && pairs(L, rk, fl & 1, o, t0 + t, q0, na)) tr |= TR_SHARED;
             }
             L.tr[t] = (uint16_t)tr;
-            x[e] = ((K)h << 8) | t;
-            c = pos <= jl && (tr & TR_SHARED) && window_ok(ix, pos, n, nullptr);
-            if (c) {  // the end of its window's minimizers
+            x[e] = ((K)h << IB) | t;
+            if (pos <= jl && (tr & TR_SHARED) && window_ok(ix, pos, n, nullptr)) {
+                // the end of its window's minimizers
                 uint32_t lo = t, hi = nt;
                 const uint64_t lim = (uint64_t)pos + n - k;
                 while (lo < hi) {
@@ -607,48 +643,58 @@ __device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L,
                 wend[e] = lo;
             }
         }
-        cand[e] = __ballot(c);
+    }
+    __builtin_amdgcn_wave_barrier();
+    uint32_t nc = 0;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint64_t cm = __ballot(wend[e] != 0);
+        if (wend[e])
+            L.cand[__builtin_amdgcn_mbcnt_hi((uint32_t)(cm >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)cm, nc))] =
+                (e * 64 + lane) | (wend[e] << 16);
+        nc += (uint32_t)__popcll(cm);
     }
     wave_sort_keys<K, E>(x, lane);
-#pragma unroll
-    for (int e = 0; e < E; e++) L.sorted[e * 64 + lane] = x[e];
-    __builtin_amdgcn_wave_barrier();
     // each occurrence, in hash order: its place t in the run, the place of the
     // occurrence before it + 1 (of the shared one before it, if it is shared;
-    // FMAX: it never counts), and its rank among the query hashes
+    // NEVER: it does not count), and its rank among the query hashes
+    constexpr uint32_t NEVER = 0xFFFF;
     uint32_t at[E], prev[E], rank[E];
     uint64_t outside[E];
 #pragma unroll
     for (int e = 0; e < E; e++) {
         const uint32_t y = e * 64 + lane;
-        const bool v = y < nt;
-        const uint32_t t = v ? (uint32_t)(x[e] & 255) : 0u;
-        const uint32_t tr = v ? L.tr[t] : (uint32_t)TR_IN;
+        const K p = key_before<K, E>(x, e, lane);  // (by all lanes: a shift reads active ones only)
+        const bool same = y > 0 && (p >> IB) == (x[e] >> IB);
+        at[e] = y < nt ? (uint32_t)x[e] & (W::tmax - 1) : 0u;
+        L.ord[y] = (uint16_t)(at[e] | (same ? ORD_SAME : 0u));
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const uint32_t y = e * 64 + lane;
+        const uint32_t tr = y < nt ? L.tr[at[e]] : (uint32_t)TR_IN;
         uint32_t pv = 0;
-        if (v) {
-            for (uint32_t z = y; z > 0; z--) {
-                const K b = (K)L.sorted[z - 1];
-                if ((b >> 8) != (x[e] >> 8)) break;
-                const uint32_t tb = (uint32_t)(b & 255);
+        if (y < nt) {
+            for (uint32_t z = y; L.ord[z] & ORD_SAME; z--) {
+                const uint32_t tb = L.ord[z - 1] & (ORD_SAME - 1);
                 if (!(tr & TR_SHARED) || (L.tr[tb] & TR_SHARED)) {
                     pv = tb + 1;
                     break;
                 }
             }
         }
-        at[e] = t;
-        prev[e] = (tr & TR_IN) && !(tr & TR_SHARED) ? (uint32_t)FMAX : pv;
+        prev[e] = (tr & TR_IN) && !(tr & TR_SHARED) ? NEVER : pv;
         rank[e] = tr & TR_RANK;
         outside[e] = __ballot(!(tr & TR_IN));
     }
     bool have = false;
-#pragma unroll
-    for (int ec = 0; ec < E; ec++) {
-        uint64_t cm = cand[ec];
-        while (cm) {
-            const uint32_t l = (uint32_t)__ffsll((long long)cm) - 1;
-            cm &= cm - 1;
-            const uint32_t xs = ec * 64 + l, len = (uint32_t)__builtin_amdgcn_readlane((int)wend[ec], (int)l) - xs;
+    for (uint32_t c0 = 0; c0 < nc; c0 += 64) {
+        const uint32_t mine = c0 + lane < nc ? L.cand[c0 + lane] : 0u, cn = min(64u, nc - c0);
+        for (uint32_t u = 0; u < cn; u++) {
+            const uint32_t cd = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)u);
+            const uint32_t xs = cd & 0xFFFFu, len = (cd >> 16) - xs;
             uint64_t live[E];
             uint32_t c = 0;
 #pragma unroll
@@ -673,7 +719,7 @@ __device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L,
                 m += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(rank[e] < s - y) & live[e] & ~outside[e]);
             if (!have || m > best_m) {
                 best_m = m;
-                best_j = L.tp[xs];
+                best_x = xs;
                 have = true;
             }
         }
@@ -681,21 +727,45 @@ __device__ __forceinline__ bool best_candidate(const IndexView &ix, EstFirst &L,
     return have;
 }
 
-template <class K>
+// The sizes of the register launches (the settings may lower them).
+struct EstSizes {
+    uint32_t a[3], t[3];  // minimizers of a window, of a run
+};
+// (The largest size only while the run is at most three of its windows long, as
+// between copies: along a tandem array most of the registers' elements lie
+// outside a candidate's window, and such runs go better with the longer ones of
+// their array, whose launch waits for one of them.  1 Mbp with arrays of 30 kbp, units
+// of 900 bases: 37.1 -> 31.4 ms a call.)
+__device__ __forceinline__ uint32_t size_class(const EstSizes &z, uint32_t na, uint32_t nt) {
+    return na <= z.a[0] && nt <= z.t[0] ? 0u
+           : na <= z.a[1] && nt <= z.t[1] ? 1u
+           : na <= z.a[2] && nt <= z.t[2] && nt <= 3 * na ? 2u
+           : na <= z.a[1] ? 3u : 4u;
+}
+
+// Register launch LEVEL.  Level 0 takes all runs, and hands those past its size
+// on: `over` receives the next level's from its front and the others from its
+// end, with their marks (nover: how many of each, and how many of the latter are
+// marked).  The later ones take the unmarked runs of `list`.
+template <class K, int LEVEL, int AM, int TM>
 __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const uint32_t *runs,
-                                                            uint64_t nruns, uint32_t per, uint32_t n,
+                                                            const uint32_t *list, uint64_t nruns,
+                                                            uint32_t per, uint32_t n,
                                                             const uint16_t *T, uint32_t *seeds,
                                                             uint64_t cap, unsigned long long *nseeds,
-                                                            uint32_t *err, uint32_t amax,
-                                                            uint32_t tmax, uint32_t *over,
+                                                            uint32_t *err, EstSizes sizes,
+                                                            uint32_t *over,
                                                             unsigned long long *nover) {
-    __shared__ EstFirst W[EW];
+    using Run = EstRun<AM, TM>;
+    static_assert(TM <= ORD_SAME && AM <= TR_RANK + 1 && AM <= TM, "fields of tr and ord");
+    __shared__ Run W[EW];
     const uint32_t lane = e_lane(), wv = threadIdx.x >> 6;
-    EstFirst &L = W[wv];
+    Run &L = W[wv];
     const uint32_t k = ix.k;
     const uint64_t r0 = ((uint64_t)blockIdx.x * EW + wv) * per;  // (no workgroup barrier below)
     const uint64_t r1 = min(r0 + per, nruns);
     uint32_t nbuf = 0;
+    uint32_t handed = 0;  // lane u: size class of run r0 + u, if it is handed on
     // minimizers [first, first + count) at positions [from, to]; above `most`: most + 1
     auto count = [&](uint64_t first, uint64_t to, uint32_t most, uint32_t *pos) {
         uint32_t c = 0;
@@ -703,39 +773,69 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
             const uint64_t m = first + c + lane;
             const uint32_t p = m < ix.nm ? ix.mpos[m] : 0xFFFFFFFFu;
             const bool v = m < ix.nm && (uint64_t)p <= to;
-            if (pos && v && c + lane < FMAX) pos[c + lane] = p;
+            if (pos && v && c + lane < (uint32_t)TM) pos[c + lane] = p;
             const uint64_t bv = __ballot(v);  // a prefix of the lanes
             c += (uint32_t)__popcll(bv);
             if (bv != ~0ull) return c;
         }
         return most + 1;
     };
-    for (uint64_t r = r0; r < r1; r++) {
+    for (uint64_t ri = r0; ri < r1; ri++) {
+        if (LEVEL > 0 && (list[ri] & (RUN_MID | RUN_LAST))) continue;
+        const uint64_t r = LEVEL > 0 ? list[ri] : ri;
         const uint32_t *rec = runs + r * 6;
         const uint32_t qid = rec[0], i = rec[1], jf = rec[2], o = rec[3], jl = rec[4], s = rec[5];
         const uint64_t q0 = wave_lower_bound(ix.mpos, ix.nm, i);
-        const uint32_t na = count(q0, (uint64_t)i + n - k, amax, nullptr);
+        const uint32_t na = count(q0, (uint64_t)i + n - k, sizes.a[2], nullptr);
         const uint64_t t0 = wave_lower_bound(ix.mpos, ix.nm, jf);
-        const uint32_t nt = na > amax ? 0u : count(t0, (uint64_t)jl + n - k, tmax, L.tp);
-        if (na > amax || nt > tmax) {  // the second launch takes it
-            if (lane == 0) over[atomicAdd(nover, 1ull)] = (uint32_t)r;
-            continue;
+        const uint32_t nt = na > sizes.a[2] ? 0u : count(t0, (uint64_t)jl + n - k, sizes.t[2], L.tp);
+        if constexpr (LEVEL == 0) {
+            const uint32_t cls = size_class(sizes, na, nt);
+            if (cls) {
+                handed = lane == (uint32_t)(ri - r0) ? cls : handed;
+                continue;
+            }
         }
         __builtin_amdgcn_wave_barrier();
-        const uint32_t nd = na <= 128 ? sort_query<K, 2>(ix, L, q0, na, lane)
-                                      : sort_query<K, 4>(ix, L, q0, na, lane);
+        uint32_t nd;
+        if (LEVEL < 2 && na <= 128) nd = sort_query<K, 2>(ix, L, q0, na, lane);
+        else if (LEVEL < 2 || na <= 256) nd = sort_query<K, 4>(ix, L, q0, na, lane);
+        else nd = sort_query<K, AM / 64>(ix, L, q0, na, lane);
         if (nd != s || s == 0) {
             if (lane == 0) atomicOr(err, 2u);
             continue;
         }
-        uint32_t best_m = 0, best_j = 0;
-        const bool have = nt <= 128 ? best_candidate<K, 2>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_j)
-                                    : best_candidate<K, 4>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_j);
+        uint32_t best_m = 0, best_x = 0;
+        bool have;
+        if (LEVEL != 1 && nt <= (uint32_t)TM / 2)
+            have = best_candidate<K, TM / 128>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_x);
+        else
+            have = best_candidate<K, TM / 64>(ix, L, t0, nt, q0, na, s, o, n, jl, lane, best_m, best_x);
         if (have && best_m >= T[s]) {
+            const uint32_t best_j = ix.mpos[t0 + best_x];
             if (lane < 6)
                 L.seeds[nbuf * 6 + lane] =
                     lane == 0 ? qid : lane == 1 ? i : lane == 2 ? best_j : lane == 3 ? o : lane == 4 ? best_m : s;
             nbuf++;
+        }
+    }
+    if constexpr (LEVEL == 0) {
+        const uint64_t next = __ballot(handed == 1), rest = __ballot(handed > 1);
+        const uint64_t marked = __ballot(handed > 2);
+        if (next | rest) {
+            unsigned long long f = 0, b = 0;
+            if (lane == 0) {
+                if (next) f = atomicAdd(nover, (unsigned long long)__popcll(next));
+                if (rest) b = atomicAdd(nover + 1, (unsigned long long)__popcll(rest));
+                if (marked) atomicAdd(nover + 2, (unsigned long long)__popcll(marked));
+            }
+            f = __shfl(f, 0, 64);
+            b = __shfl(b, 0, 64);
+            const uint64_t lt = (1ull << lane) - 1;
+            const uint32_t r = (uint32_t)r0 + lane;
+            if (handed == 1) over[f + (uint32_t)__popcll(next & lt)] = r;
+            if (handed > 1)
+                over[nruns - 1 - (b + (uint32_t)__popcll(rest & lt))] = r | (handed == 3 ? RUN_MID : handed == 4 ? RUN_LAST : 0u);
         }
     }
     if (nbuf == 0) return;
@@ -747,42 +847,68 @@ __global__ void __launch_bounds__(EW * 64) k_estimate_runs(IndexView ix, const u
         if (at + t / 6 < cap) seeds[at * 6 + t] = L.seeds[t];
 }
 
-void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nruns, uint32_t n,
+static void estimate_part(const IndexView &ix, const uint32_t *runs, uint64_t nruns, uint32_t n,
                           const uint16_t *T, uint32_t *seeds, uint64_t cap,
                           unsigned long long *nseeds, uint32_t *err, hipStream_t st) {
-    if (nruns == 0) return;
     // the settings may lower the sizes held in LDS and registers (0 sends
-    // every run down the general paths) and the window size of the first
-    // launch (0 hands every run to the second)
+    // every run down the general paths) and the window size of the register
+    // launches (0 hands every run to the last)
     const sdf_tuning &tu = tuning();
-    const uint32_t lds_cap = std::min<uint32_t>(TCAP_L, knob(tu.est_lds_cap, TCAP_L));
+    const uint32_t lds_cap = knob(tu.est_lds_cap, 1024), first = knob(tu.est_first_amax, 512);
     const uint32_t reg_cap = std::min<uint32_t>(128, knob(tu.est_reg_cap, 128));
-    const uint32_t amax = std::min<uint32_t>(FMAX, knob(tu.est_first_amax, FMAX));
-    const uint32_t tmax = std::min<uint32_t>(FMAX, lds_cap);
+    EstSizes z;
+    const uint32_t am[3] = {256, 256, 512}, tm[3] = {256, 512, 1024};
+    for (int l = 0; l < 3; l++) {
+        z.a[l] = std::min(am[l], first);
+        z.t[l] = std::min(tm[l], lds_cap);
+    }
     DevBuf<uint32_t> over(nruns);
-    DevBuf<unsigned long long> nover(1);
-    SDF_HIP(hipMemsetAsync(nover.p, 0, 8, st));
-    // hash and index in 32 bits while the hash has at most 24 (k <= 12): half the
-    // instructions per exchange of a sort
-    const auto first = 2 * ix.k <= 24 ? k_estimate_runs<uint32_t> : k_estimate_runs<uint64_t>;
+    DevBuf<unsigned long long> nover(3);
+    SDF_HIP(hipMemsetAsync(nover.p, 0, 24, st));
     // a run takes its wave some 14 us, so few runs are spread over the waves the
     // chip holds before any takes several (0.8 Mbp: 1,377 us a call with 32 runs
     // per wave, 471 spread)
-    const uint32_t per = (uint32_t)std::clamp<uint64_t>((nruns + EWAVES - 1) / EWAVES, 1, ERUNS);
-    first<<<(unsigned)((nruns + EW * per - 1) / (EW * per)), EW * 64, 0, st>>>(
-        ix, runs, nruns, per, n, T, seeds, cap, nseeds, err, amax, tmax, over.p, nover.p);
-    SDF_HIP(hipGetLastError());
-    unsigned long long no = 0;
+    const auto launch = [&](auto kernel, const uint32_t *list, uint64_t m) {
+        const uint32_t per = (uint32_t)std::clamp<uint64_t>((m + EWAVES - 1) / EWAVES, 1, ERUNS);
+        kernel<<<(unsigned)((m + EW * per - 1) / (EW * per)), EW * 64, 0, st>>>(
+            ix, runs, list, m, per, n, T, seeds, cap, nseeds, err, z, over.p, nover.p);
+        SDF_HIP(hipGetLastError());
+    };
+    // hash and index in 32 bits where they fit: half the instructions per exchange of
+    // a sort
+    const uint32_t hbits = 2 * ix.k;
+    launch(hbits + 8 <= 32 ? k_estimate_runs<uint32_t, 0, 256, 256> : k_estimate_runs<uint64_t, 0, 256, 256>,
+           nullptr, nruns);
+    unsigned long long no[3] = {0, 0, 0};
     {
         Readback rb(st);
-        rb.add(&no, nover.p, 8);
+        rb.add(no, nover.p, 24);
         rb.wait();
     }
-    if (no == 0) return;
-    k_estimate_long<<<(unsigned)((no + EW - 1) / EW), EW * 64, 0, st>>>(
-        ix, runs, no, over.p, n, T, seeds, cap, nseeds, err, lds_cap, reg_cap);
-    SDF_HIP(hipGetLastError());
-    SDF_HIP(hipStreamSynchronize(st));  // `over` is released on return
+    if (no[0])
+        launch(hbits + 9 <= 32 ? k_estimate_runs<uint32_t, 1, 256, 512> : k_estimate_runs<uint64_t, 1, 256, 512>,
+               over.p, no[0]);
+    uint32_t *const rest = over.p + (nruns - no[1]);
+    if (no[1] > no[2])
+        launch(hbits + 10 <= 32 ? k_estimate_runs<uint32_t, 2, 512, 1024> : k_estimate_runs<uint64_t, 2, 512, 1024>,
+               rest, no[1]);
+    if (no[2]) {
+        const unsigned grid = (unsigned)((no[1] + EW - 1) / EW);
+        k_estimate_long<AMAX_M, TCAP_M, RUN_MID><<<grid, EW * 64, 0, st>>>(
+            ix, runs, no[1], rest, n, T, seeds, cap, nseeds, err, std::min<uint32_t>(TCAP_M, lds_cap), reg_cap);
+        SDF_HIP(hipGetLastError());
+        k_estimate_long<AMAX_L, TCAP_L, RUN_LAST><<<grid, EW * 64, 0, st>>>(
+            ix, runs, no[1], rest, n, T, seeds, cap, nseeds, err, std::min<uint32_t>(TCAP_L, lds_cap), reg_cap);
+        SDF_HIP(hipGetLastError());
+    }
+    if (no[0] + no[1]) SDF_HIP(hipStreamSynchronize(st));  // `over` is released on return
+}
+
+void launch_estimate_runs(const IndexView &ix, const uint32_t *runs, uint64_t nruns, uint32_t n,
+                          const uint16_t *T, uint32_t *seeds, uint64_t cap,
+                          unsigned long long *nseeds, uint32_t *err, hipStream_t st) {
+    for (uint64_t r = 0; r < nruns; r += RUNS_MAX)
+        estimate_part(ix, runs + 6 * r, std::min(RUNS_MAX, nruns - r), n, T, seeds, cap, nseeds, err, st);
 }
 
 }  // namespace sdf
