@@ -1119,14 +1119,25 @@ k_extend(ExtArgs a) {
                         } else if (rank_big(L, tmp, c0, c1, rank)) {
                             if (threadIdx.x == 0) atomicAdd(&a.stats[6], 1ull);
                         } else {
-                            if (threadIdx.x == 0) { atomicOr(a.err, (uint32_t)XE_HASH); L.flag = 1; }
+                            if (threadIdx.x == 0) L.flag = 1;
                             __syncthreads();
                             break;
                         }
                     }
                 __syncthreads();
             }
-            if (L.flag) { failed = true; break; }
+            if (L.flag) {
+                // a bucket holds too many hashes: shorten the horizon as above (the
+                // backward phase's share of it had such regions refused: sides of 1 Mbp
+                // with w = 64 gather 4.5 sides' minimizers instead of 4)
+                if (want <= 1) {
+                    if (threadIdx.x == 0) atomicOr(a.err, (uint32_t)XE_HASH);
+                    failed = true;
+                    break;
+                }
+                hcut = want / 2;
+                continue;
+            }
             const uint32_t nr = (uint32_t)E;  // ranks, gaps included
             const uint32_t nw = (nr + 7) / 8;
             uint32_t *nib = (nw <= a.lds_words) ? L.w : gnib;

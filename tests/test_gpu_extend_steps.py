@@ -43,3 +43,35 @@ def test_extend_steps(oracle_lib, k, w, length, batch_min):
                  ("m", want["m"]), ("s", want["s"]), ("stop", want["stop"])):
         assert np.array_equal(got[f].astype(np.uint64), x.astype(np.uint64)), f
     ix.close()
+
+
+@pytest.mark.parametrize("strand", [0, 1])
+def test_crowded_bucket_shortens_the_horizon(strand):
+    """Sides of 1 Mbp under a wide winnowing window: the minimizers that both
+    phases can reach crowd the lowest of 2,048 buckets of hashes (some 2,190 of
+    them, most distinct, where 2,048 are held), so the horizon is shortened, as it
+    is for too many minimizers, instead of the region being refused.  The result
+    does not depend on the horizon: with 1/64 of the side never more than 1,970
+    are gathered."""
+    from paper_1807_00205_amd import sdf
+    rng = np.random.default_rng(77)
+    n, side, at = 2_500_000, 1_050_000, 350_000
+    a, b = synth.random_bases(rng, n), synth.random_bases(rng, n)
+    copy = a[at:at + side + 30_000].copy()
+    hit = rng.random(len(copy)) < 0.02
+    copy[hit] = synth.random_bases(rng, int(hit.sum()))
+    t0 = n - at - len(copy) if strand else at
+    b[t0:t0 + len(copy)] = synth.revcomp(copy) if strand else copy
+    ix = sdf.Index([a, b], 12, 64)
+    reg = np.zeros(1, sdf.REGION_DTYPE)
+    reg["strand"], reg["t_seq"] = strand, 1
+    reg["q_begin"], reg["q_end"] = at + 100, at + 100 + side
+    reg["t_begin"] = t0 + (len(copy) - 100 - side if strand else 100)
+    reg["t_end"] = reg["t_begin"] + side
+    got = ix.extend(reg, 0.25, max_len=1_980_000)
+    with sdf.tuning(ext_hdiv=64):
+        want = ix.extend(reg, 0.25, max_len=1_980_000)
+    for f in ("q_begin", "q_end", "t_begin", "t_end", "m", "s", "stop"):
+        assert np.array_equal(got[f], want[f]), f
+    assert got["q_end"][0] - got["q_begin"][0] > side + 20_000
+    ix.close()
