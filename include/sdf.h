@@ -418,7 +418,8 @@ typedef struct {
     uint32_t ext_lds_words;       /* extension: ordered-set cells kept in LDS */
     uint32_t ext_hb0;             /* extension: backward steps gathered early */
     uint32_t ext_hdiv;            /* extension: horizon as 1/hdiv of the longer side */
-    uint32_t ext_batch_min;       /* extension: smallest batch of insertions */
+    uint32_t ext_batch_min;       /* extension: 0: one step at a time; otherwise steps are tried
+                                     in batches, whatever the value */
     uint32_t ext_ecap;            /* extension: scratch elements per workgroup (>= 64) */
     uint32_t ext_stats;           /* 1: one line of extension counters on stderr per call */
     uint32_t align_wave_cells;    /* final SDs: stretches of at least this many cells are

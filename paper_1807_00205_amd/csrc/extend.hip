@@ -94,7 +94,7 @@ struct ExtArgs {
     uint32_t *gnib;         // per workgroup: ecap / 8 + 1
     uint64_t ecap;
     uint32_t lds_words;     // cells kept in LDS up to 8 * lds_words ranks
-    uint32_t batch_min;     // fewest insertions applied as one batch (0: never)
+    uint32_t batches;       // 0: one step at a time
     uint32_t hdiv;          // horizon per attempt: at least the longer side / hdiv
     uint64_t hb0;           // backward horizon while the forward phase is pending (0: same)
     uint32_t *err;
@@ -702,7 +702,7 @@ __device__ __forceinline__ void run_phase(const ExtArgs &a, Shared &L, uint32_t 
         }
         const int32_t v = L.v;
         const uint32_t s0 = L.s, m0 = L.m;
-        const bool batch = L.ok && s0 > 0 && a.batch_min;
+        const bool batch = L.ok && s0 > 0 && a.batches;
         if (tid == 0) L.dark = L.refused = NONE32;
         if (batch && wave < 2)
             near_v(L, nib, nw, v, s0 < 512 ? 8u : s0 < 8192 ? 16u : s0 < 32768 ? 32u : 63u, o, (int)wave);
@@ -1255,14 +1255,14 @@ void launch_extend(const IndexView &ix, const sdf_region *in, uint64_t n, double
     // each attempt gathers max(h0, longer side / hdiv) steps per phase; a
     // phase that runs through them continues in the next attempt.  The
     // settings may change the horizon (h0, hdiv), the cells kept in LDS (0
-    // keeps L in global memory), the elements per workgroup, the smallest
-    // batch (0: one step at a time) and the backward horizon gathered while
-    // the forward phase is pending (hb0)
+    // keeps L in global memory), the elements per workgroup, whether steps are
+    // tried in batches and the backward horizon gathered while the forward phase
+    // is pending (hb0)
     const sdf_tuning &tu = tuning();
     const uint64_t h0 = knob(tu.ext_h0, 4096);
     const uint64_t ecap = std::max<uint64_t>(64, knob(tu.ext_ecap, 1u << 18));
     const uint32_t ldsw = std::min<uint32_t>(LDS_WORDS, knob(tu.ext_lds_words, LDS_WORDS));
-    const uint32_t batch_min = knob(tu.ext_batch_min, 4);
+    const uint32_t batches = knob(tu.ext_batch_min, 1);
     const uint32_t hdiv = std::max<uint32_t>(1, knob(tu.ext_hdiv, 1));
     const uint64_t hb0 = knob(tu.ext_hb0, 512);
     // as many workgroups as fit a CU's LDS; each keeps its own scratch
@@ -1288,7 +1288,7 @@ void launch_extend(const IndexView &ix, const sdf_region *in, uint64_t n, double
     a.gnib = gnib.p;
     a.ecap = ecap;
     a.lds_words = ldsw;
-    a.batch_min = batch_min;
+    a.batches = batches;
     a.hdiv = hdiv;
     a.hb0 = hb0;
     a.err = work.p + 1;
