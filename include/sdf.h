@@ -447,13 +447,14 @@ sdf_status sdf_get_tuning(sdf_tuning *t);
  * turn, timing the tile kernel (second of two runs each, HIP events).  The
  * schedules, in order: 1,024-thread workgroups (one per CU) at 512 to 1,024
  * window starts per tile in steps of 64, then 512-thread workgroups (two
- * per CU) at 512 window starts when a window of p's length holds at most
- * 1,024 minimizers (length <= 1,023 + k).  *out receives the calling
+ * per CU) at 512 window starts when a seed window (n bases) holds at most
+ * 1,024 minimizers (n <= 1,023 + k), then the schedule that a search by
+ * the calling thread takes without it, if that is none of these.  *out receives the calling
  * thread's settings with tile_core and tile_threads set to the fastest
  * schedule: install it with sdf_set_tuning in every thread that searches
  * (the index is not changed, so autotuning may run beside other searches on
  * it).  ms_out (may be NULL) receives up to n_ms kernel times in that order
- * (10 at most).  n == 0 times nothing and returns the settings unchanged.
+ * (11 at most).  n == 0 times nothing and returns the settings unchanged.
  * Errors as for sdf_search_batch. */
 sdf_status sdf_autotune(sdf_index ix, const sdf_span *spans, uint32_t n,
                         const sdf_search_params *p, void *hip_stream, sdf_tuning *out,

@@ -1020,31 +1020,38 @@ sdf_status sdf_autotune(sdf_index ix, const sdf_span *qs, uint32_t n, const sdf_
         const Params P = derive(&q, ix->k, ix->w);
         // schedules tried: 1,024-thread workgroups at 512 .. 1,024 window
         // starts, then 512-thread workgroups (two per CU) at 512 when the
-        // windows fit them
+        // windows fit them, then the one a search takes by itself (0, 0) if it is
+        // none of these
         std::vector<std::pair<uint32_t, uint32_t>> sched;
         for (uint32_t c = 512; c <= tile1024::tile_core_max(); c += 64) sched.push_back({1024u, c});
         if (fits_tile512(P.n, ix->k)) sched.push_back({512u, tile512::tile_core_max()});
-        uint32_t best = 0, best_threads = 0;
+        const size_t listed = sched.size();
+        sched.push_back({0u, 0u});
+        std::pair<uint32_t, uint32_t> best;
         float best_ms = 0.f;
+        bool own_listed = false;
         for (uint32_t t = 0; t < (uint32_t)sched.size(); t++) {
             float ms = 0.f;
-            for (int rep = 0; rep < 2; rep++) {  // the first run warms the memory pool
+            for (int rep = 0; rep < 2 && !own_listed; rep++) {  // the first run warms the memory pool
                 sdf_result_s r;
                 r.device = ix->device;
                 r.st = st;
                 run_search(ix, qs, n, &q, st, &r, sched[t].second, sched[t].first);
                 ms = r.ms[1];
                 SDF_HIP(hipStreamSynchronize(st));
+                sched[t] = {r.threads, r.core};
+                own_listed = t == listed && std::find(sched.begin(), sched.begin() + listed, sched[t]) !=
+                                                sched.begin() + listed;
             }
+            if (own_listed) break;
             if (ms_out && t < n_ms) ms_out[t] = ms;
-            if (best == 0 || ms < best_ms) {
-                best = sched[t].second;
-                best_threads = sched[t].first;
+            if (t == 0 || ms < best_ms) {
+                best = sched[t];
                 best_ms = ms;
             }
         }
-        out->tile_core = best;
-        out->tile_threads = best_threads;
+        out->tile_threads = best.first;
+        out->tile_core = best.second;
     });
 }
 

@@ -9,6 +9,7 @@ from __future__ import annotations
 import contextlib
 import ctypes
 import itertools
+import math
 import os
 from typing import Iterable, List, Optional, Sequence, Tuple
 
@@ -539,8 +540,9 @@ class Index:
                  min_len: int = 1000, stream=None):
         """Times the tile kernel on these spans with every schedule
         (``sdf_autotune``); returns (window starts, workgroup threads,
-        {(threads, window starts): ms}) of the fastest.  The index is not
-        changed: searches use the schedule where the caller installs it
+        {(threads, window starts): ms}) of the fastest.  The schedule that a
+        search takes without it is timed too, and is among the times where it is
+        the fastest.  The index is not changed: searches use the schedule where the caller installs it
         (``set_tuning(tile_core=..., tile_threads=...)`` or ``tuning(...)``).
         No spans: the calling thread's settings, nothing timed."""
         arr, nspans = _span_array(spans)
@@ -551,9 +553,11 @@ class Index:
                                   ctypes.byref(p), _stream_ptr(stream), ctypes.byref(out), ms,
                                   16))
         sched = [(1024, c) for c in range(512, 1025, 64)]
-        if min_len <= 1023 + self.k:
+        if math.ceil(min_len * (1.0 - max_error)) <= 1023 + self.k:  # bases of a window
             sched.append((512, 512))
         times = {k: float(ms[i]) for i, k in enumerate(sched)} if spans else {}
+        if times and (out.tile_threads, out.tile_core) not in times:
+            times[int(out.tile_threads), int(out.tile_core)] = float(ms[len(sched)])
         return int(out.tile_core), int(out.tile_threads), times
 
     def qgram_filter(self, regions: np.ndarray, q: int, gap_rate: float,

@@ -71,3 +71,29 @@ def test_estimate_windows(oracle_lib, k, w, min_len):
     _same(r.candidates(), oc, CAND_F, "candidates")
     assert len(oc) > 0
     ix.close()
+
+
+@pytest.mark.parametrize("min_len", [1000, 1200, 2000])
+def test_autotune_times_the_schedule_in_use(min_len):
+    """The schedule that a search takes by itself is among the timed ones, after
+    the listed ones where it is none of these, and the fastest of all is returned
+    (windows of 1,035 bases are the longest that the 512-thread layout holds)."""
+    import ctypes
+    from paper_1807_00205_amd import sdf
+    g = synth.config1()
+    ix = sdf.Index(g.seqs, 12, 16)
+    listed = [(1024, c) for c in range(512, 1025, 64)] + [(512, 512)] * (min_len * 0.75 <= 1035)
+    for core in (192, 512):
+        with sdf.tuning(tile_threads=1024, tile_core=core):
+            ms = (ctypes.c_float * 16)(*[-1.0] * 16)
+            out, p = sdf._Tuning(), sdf._SearchParams(0.25, min_len, 0)
+            arr, n = sdf._span_array([(0, 0, 300_000)])
+            sdf._check(sdf.lib().sdf_autotune(ix._h, arr.ctypes.data_as(ctypes.c_void_p), n,
+                                              ctypes.byref(p), None, ctypes.byref(out), ms, 16))
+            all_ = listed + ([(1024, core)] if core == 192 else [])
+            assert sum(m > 0 for m in ms) == len(all_)
+            assert (out.tile_threads, out.tile_core) == all_[int(np.argmin(ms[:len(all_)]))]
+            best_core, best_threads, times = ix.autotune([(0, 0, 300_000)], 0.25, min_len)
+            assert times[best_threads, best_core] == min(times.values())
+            assert set(listed) <= set(times)
+    ix.close()
