@@ -364,6 +364,7 @@ struct Prepared {
     uint64_t qbases = 0;
     uint32_t threads = 1024, core = 512, halo = 1, hpart = 16384, sb = 0, grid = 1;
     DevBuf<unsigned char> dup;
+    std::optional<Upload> up;  // returned to its pool once the stream has been waited for
     const uint16_t *dT = nullptr;
     SpanDesc *dsd = nullptr;
     DevBuf<uint32_t> ntiles, tile0;
@@ -422,9 +423,9 @@ void prepare(sdf_index_s *ix, const sdf_span *qs, uint32_t nq, const Params &P, 
         }
     } else {
         // the table and the span descriptors go to the device in one upload
-        Upload up(up_bytes);
-        fill_upload(ix, qs, nq, P, smax, t_bytes, up.host());
-        up.send(pr.dup.p, st);
+        pr.up.emplace(up_bytes);
+        fill_upload(ix, qs, nq, P, smax, t_bytes, pr.up->host());
+        pr.up->send(pr.dup.p, st);
     }
     // tile layout and window starts per tile: the autotuner's trial
     // schedule, else the calling thread's settings (sdf_set_tuning, where
@@ -581,6 +582,7 @@ void run_search(sdf_index_s *ix, const sdf_span *qs, uint32_t nq, const sdf_sear
             if (nq) rb.add(&total_tiles, tile0.p + nq, 4);
             rb.wait();
         }
+        if (pr.up) pr.up->done();
         if (herr == ERR_DENSE_LIST && dense_cap < dense_capacity(qbases, true)) {
             // more dense windows than the short list holds: once more with room
             dense_cap = dense_capacity(qbases, true);

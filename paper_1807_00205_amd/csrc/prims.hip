@@ -195,7 +195,6 @@ struct Stage {
     unsigned char *p = nullptr;
     size_t cap = 0;
     int dev = 0;
-    hipEvent_t ev = nullptr;  // recorded after the last upload out of p, if any
 };
 
 namespace {
@@ -203,7 +202,7 @@ std::mutex g_stage_mu;
 std::map<int, std::vector<Stage *>> g_stage_free;  // per device
 
 // A free block of at least `bytes` on the current device (a new one when none
-// fits), with any upload still reading from it finished.
+// fits).
 Stage *stage_acquire(size_t bytes) {
     int dev = 0;
     SDF_HIP(hipGetDevice(&dev));
@@ -233,14 +232,6 @@ Stage *stage_acquire(size_t bytes) {
         s->p = static_cast<unsigned char *>(p);
         s->cap = cap;
         s->dev = dev;
-        return s;
-    }
-    if (s->ev) {
-        const hipError_t e = hipEventSynchronize(s->ev);
-        if (e != hipSuccess) {
-            // the block may still be read by a failed copy: keep it out of the pool
-            throw Error{SDF_EDEVICE, std::string("hipEventSynchronize: ") + hipGetErrorString(e)};
-        }
     }
     return s;
 }
@@ -289,14 +280,22 @@ void Readback::wait() {
 
 Upload::Upload(size_t bytes) : stage_(stage_acquire(bytes)), bytes_(bytes) {}
 
-Upload::~Upload() { stage_release(stage_); }
+Upload::~Upload() {
+    // a block that a failed stream may still read from is not returned to the pool
+    if (stage_ && (!sent_ || hipStreamSynchronize(st_) == hipSuccess)) stage_release(stage_);
+}
+
+void Upload::done() {
+    if (stage_) stage_release(stage_);
+    stage_ = nullptr;
+}
 
 unsigned char *Upload::host() const { return stage_->p; }
 
 void Upload::send(void *dev_dst, hipStream_t st) {
-    if (!stage_->ev) SDF_HIP(hipEventCreateWithFlags(&stage_->ev, hipEventDisableTiming));
+    st_ = st;
+    sent_ = true;
     if (bytes_) SDF_HIP(hipMemcpyAsync(dev_dst, stage_->p, bytes_, hipMemcpyHostToDevice, st));
-    SDF_HIP(hipEventRecord(stage_->ev, st));
 }
 
 // ---------------------------------------------------------------- fills --

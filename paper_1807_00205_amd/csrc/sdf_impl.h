@@ -129,9 +129,11 @@ class Readback {
 };
 
 // Host-to-device upload through a borrowed staging block of at least `bytes`:
-// host() is filled by the caller, send() queues one copy and records an event;
-// the block goes back to the pool with that event, and its next borrower waits
-// on it before writing.  A pageable source would block the host for the copy.
+// host() is filled by the caller and send() queues one copy.  The block goes back
+// to the pool when the caller knows the stream to be past the copy (done()), or
+// else after a wait in the destructor.  It carries no event: the runtime refuses a
+// wait for one whose stream another thread is capturing, or has destroyed and
+// whose successor is.  A pageable source would block the host for the copy.
 class Upload {
   public:
     explicit Upload(size_t bytes);
@@ -140,10 +142,13 @@ class Upload {
     Upload &operator=(const Upload &) = delete;
     unsigned char *host() const;
     void send(void *dev_dst, hipStream_t st);
+    void done();
 
   private:
     Stage *stage_;
     size_t bytes_;
+    hipStream_t st_ = nullptr;
+    bool sent_ = false;
 };
 
 template <class T>

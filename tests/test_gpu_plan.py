@@ -78,3 +78,44 @@ def test_plan_errors():
     with pytest.raises(sdf.SdfError) as e:
         ix.plan([(0, 0, 3000)], 0.25, 10)
     assert e.value.code == sdf.SDF_EINVAL
+
+
+def test_search_beside_a_capture_of_an_earlier_stream():
+    """Searches of one thread while another captures a stream that searches ran
+    on before: the staging blocks that those left in the pool carry nothing of
+    that stream."""
+    import threading
+    from paper_1807_00205_amd import sdf
+    g = synth.config1()
+    ix = sdf.Index(g.seqs, 12, 16)
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    want = ix.search(g.spans[0], stream=a).candidates()
+    for _ in range(8):  # every block that is in turn
+        ix.search(g.spans[0], stream=a).close()
+    got = []
+
+    def searches():
+        for _ in range(3):
+            try:
+                r = ix.search(g.spans[0], stream=b)
+                got.append(r.candidates())
+                r.close()
+            except sdf.SdfError as e:
+                got.append(e)
+
+    x = torch.zeros(64, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=a, capture_error_mode="thread_local"):
+        x += 1
+        t = threading.Thread(target=searches)
+        t.start()
+        t.join()
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    assert float(x[0]) == 3.0
+    for c in got:
+        assert not isinstance(c, Exception), c
+        _same(c, want, CAND_F, "candidates")
+    ix.close()
