@@ -131,3 +131,102 @@ def test_equal_values_far_apart(oracle_lib, seed):
     want = oracle_lib.sd_align(b, off, rows, 11, 1000, 0.25, pad_frac=0.0)
     assert len(want[0]) > 0
     _same(got, want, "equal values")
+
+
+def _sides_with_copies(seed, length, strand):
+    """Random sides with three copies of 8 to 20 kbp at 4, 10 and 16%."""
+    rng = synth.rng_for(seed)
+    q, t = synth.random_bases(rng, length), synth.random_bases(rng, length)
+    for u, (ln, rate) in enumerate(((20_000, 0.10), (8_000, 0.16), (12_000, 0.04))):
+        at, to = (2 * u + 1) * length // 7, (2 * u + 2) * length // 8
+        cp = synth.mutate(rng, q[at:at + ln], rate)
+        t[to:to + len(cp)] = cp
+    return q, synth.revcomp(t) if strand else t
+
+
+@pytest.mark.parametrize("length,strand", [(600_000, 0), (450_000, 1)])
+def test_large_region(oracle_lib, length, strand):
+    """A region of some 86,000 and 48,000 chance anchors: more than a thousand
+    blocks per tier, and chains taken out over 17 doublings."""
+    from paper_1807_00205_amd import sdf
+    q, t = _sides_with_copies(length, length, strand)
+    b = np.concatenate([q, t])
+    off = np.array([0, length, 2 * length], np.uint64)
+    ix = sdf.Index([q, t], 12, 16)
+    reg = np.zeros(1, sdf.REGION_DTYPE)
+    reg[0] = (strand, 0, 1, 0, 0, length, 0, length, 0, 0)
+    rows = np.array([[0, length, length, 2 * length, strand]], np.uint64)
+    _same(ix.align_regions(reg, pad_frac=0.0),
+          oracle_lib.sd_align(b, off, rows, 11, 1000, 0.25, pad_frac=0.0), "large region")
+    ix.close()
+
+
+@pytest.mark.parametrize("strand", [0, 1])
+def test_largest_side_records(oracle_lib, strand):
+    """The largest sides (2^20 - 1 bases, some 260,000 chance anchors), which no
+    plain restatement chains in seconds: every record's counts follow from its
+    CIGAR and the bases, and the records are those that the oracle finds in
+    pieces of 40 kbp around each copy (chains reach over 10 kbp at most)."""
+    from paper_1807_00205_amd import sdf
+    length = (1 << 20) - 1
+    q, t = _sides_with_copies(5, length, strand)
+    ix = sdf.Index([q, t], 12, 16)
+    reg = np.zeros(1, sdf.REGION_DTYPE)
+    reg[0] = (strand, 0, 1, 0, 0, length, 0, length, 0, 0)
+    sd, ops = ix.align_regions(reg, pad_frac=0.0)
+    ts = synth.revcomp(t) if strand else t
+    code = np.zeros(256, np.uint8)
+    code[list(b"ACGT")] = np.arange(4)
+    for d in sd:
+        x = int(d["q_begin"])
+        y = int(length - d["t_end"] if strand else d["t_begin"])
+        n = dict.fromkeys(("matches", "mismatches", "ins", "dels", "gap_opens", "transitions",
+                           "transversions"), 0)
+        last = None
+        for v in ops[int(d["cigar_off"]):int(d["cigar_off"]) + int(d["cigar_len"])]:
+            op, ln = int(v) & 15, int(v) >> 4
+            assert ln > 0 and op != last
+            a, c = code[q[x:x + ln]], code[ts[y:y + ln]]
+            if op == 7:
+                assert np.array_equal(a, c)
+                n["matches"] += ln
+            elif op == 8:
+                assert np.all(a != c)
+                n["mismatches"] += ln
+                n["transitions"] += int(np.sum((a ^ c) == 2))
+                n["transversions"] += int(np.sum((a ^ c) != 2))
+            else:
+                n["ins" if op == 1 else "dels"] += ln
+                n["gap_opens"] += 1
+            x += ln if op != 2 else 0
+            y += ln if op != 1 else 0
+            last = op
+        assert x == d["q_end"] and y == (length - d["t_begin"] if strand else d["t_end"])
+        assert all(int(d[f]) == n[f] for f in n), (n, d)
+        assert d["aln_len"] == sum(n[f] for f in ("matches", "mismatches", "ins", "dels")) >= 1000
+    # around each copy: what the oracle finds in the two pieces
+    whole = ("aln_len", "matches", "mismatches", "ins", "dels", "gap_opens", "transitions",
+             "transversions", "cigar_len")
+    found = 0
+    for u, ln in ((0, 20_000), (1, 8_000), (2, 12_000)):
+        at, to = (2 * u + 1) * length // 7, (2 * u + 2) * length // 8
+        a, e = at - 40_000, at + ln + 40_000
+        c, f = to - 40_000, to + ln + 40_000
+        if strand:
+            c, f = length - f, length - c
+        want, wops = oracle_lib.sd_align(
+            np.concatenate([q[a:e], t[c:f]]), np.array([0, e - a, e - a + f - c], np.uint64),
+            np.array([[0, e - a, e - a, e - a + f - c, strand]], np.uint64), 11, 1000, 0.25,
+            pad_frac=0.0)
+        for w in want:
+            d = sd[sd["q_begin"] == w["q_begin"] + a]
+            assert len(d) == 1
+            for v, base in (("q_end", a), ("t_begin", c), ("t_end", c)):
+                assert int(d[v][0]) == int(w[v]) + base, v
+            assert all(int(d[v][0]) == int(w[v]) for v in whole)
+            at_ = int(d["cigar_off"][0])
+            assert np.array_equal(ops[at_:at_ + int(d["cigar_len"][0])],
+                                  wops[int(w["cigar_off"]):int(w["cigar_off"]) + int(w["cigar_len"])])
+            found += 1
+    assert found == len(sd) == 3
+    ix.close()
