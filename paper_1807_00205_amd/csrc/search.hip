@@ -689,12 +689,16 @@ __device__ __forceinline__ void run_step(const SearchArgs &a, TileLds &L, SeedBu
 // j + n - k has entered before candidate j): one at or past the candidate means
 // that the minimizer has a hit in [j, j + n - k], so a ballot per r is the
 // candidate's bitmask over the block's minimizers, and a window's count the
-// popcount of it over the window's own.
-template <int R>
+// popcount of it over the window's own.  DUP: a hash repeats within the tile.
+// Each lane then looks for the earlier ones of its own minimizers (four arrays of
+// 30 kbp with units of 350 bases: 148 ms a search, 319 with one look at a time,
+// 199 with a wave per window); a form of its own, as other tiles ran 1.5%
+// slower with it in theirs.
+template <int R, bool DUP>
 __device__ __forceinline__ void eval_masks(const SearchArgs &a, TileLds &L, SeedBuf &sbuf,
                                            const Block &bk, RunState &rs, EndedRuns &er,
                                            uint32_t ob, uint32_t oe,
-                                           uint32_t lane, bool dup, uint32_t &n_evals,
+                                           uint32_t lane, uint32_t &n_evals,
                                            uint32_t &n_scan) {
     const PostLds &F = L.u.post;
     const uint32_t qlo = bk.qlo, nq = bk.qhi - bk.qlo;
@@ -708,7 +712,7 @@ __device__ __forceinline__ void eval_masks(const SearchArgs &a, TileLds &L, Seed
         if (to < 64) m = to <= 0 ? 0ull : m & ((1ull << to) - 1);
         wm[r] = m;
         const uint32_t q = lane + 64 * r;
-        if (dup) again[r] = __builtin_amdgcn_ballot_w64(q < nq && L.qprev[min(qlo + q, (uint32_t)QCAP - 1)] >= (int)qlo);
+        if (DUP) again[r] = __builtin_amdgcn_ballot_w64(q < nq && L.qprev[min(qlo + q, (uint32_t)QCAP - 1)] >= (int)qlo);
     }
     // the next hit to enter, its chunk, the chunk's minimizers and the hits of it
     // still to enter
@@ -784,22 +788,24 @@ __device__ __forceinline__ void eval_masks(const SearchArgs &a, TileLds &L, Seed
             for (int r = 0; r < R; r++) rep |= M[r] & again[r];
             if (rep) {
                 // a marked minimizer that repeats the hash of an earlier marked one
-                // does not count in the windows that hold the nearest such one too
+                // does not count in the windows that hold the nearest such one too:
+                // each lane looks for that of its own minimizers
 #pragma unroll
                 for (int r = 0; r < R; r++) {
-                    uint64_t dm = M[r] & again[r];
-                    while (dm) {
-                        const uint32_t dq = qlo + 64 * r + (uint32_t)__ffsll((long long)dm) - 1;
-                        dm &= dm - 1;
-                        int x = (int)uni((uint32_t)(int)L.qprev[dq]);
-                        for (; x >= (int)qlo; x = (int)uni((uint32_t)(int)L.qprev[x])) {
-                            const uint32_t rx = (uint32_t)x - qlo;
-                            uint64_t m = 0;
+                    const uint64_t am = M[r] & again[r];
+                    if (!am) continue;
+                    int x = (am >> lane) & 1 ? (int)L.qprev[qlo + 64 * r + lane] : -1;
+                    while (x >= (int)qlo) {
+                        const uint32_t rx = (uint32_t)x - qlo, half = rx >> 5;
+                        uint32_t m = 0;
 #pragma unroll
-                            for (int v = 0; v < R; v++) m = (rx >> 6) == (uint32_t)v ? M[v] : m;
-                            if ((m >> (rx & 63)) & 1) break;
-                        }
-                        if (x >= (int)qlo && dq < bk.qc + bk.len && (uint32_t)x >= bk.qc) cnt--;
+                        for (int v = 0; v < 2 * R; v++) m = half == (uint32_t)v ? (uint32_t)(M[v / 2] >> (32 * (v & 1))) : m;
+                        if ((m >> (rx & 31)) & 1) break;
+                        x = L.qprev[x];
+                    }
+                    for (uint64_t dm = __builtin_amdgcn_ballot_w64(x >= (int)qlo); dm; dm &= dm - 1) {
+                        const uint32_t l = (uint32_t)__builtin_ctzll(dm);
+                        if (qlo + 64 * r + l < bk.qc + bk.len && lane_read((uint32_t)x, l) >= bk.qc) cnt--;
                     }
                 }
             }
@@ -1747,10 +1753,14 @@ k_tile_search(SearchArgs) {
                     }
                     EndedRuns er{0, 0, 0};
                     const uint32_t nq = bk.qhi - bk.qlo;
-                    if (nq <= 192)
-                        eval_masks<3>(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
+                    if (nq <= 192 && !dup)
+                        eval_masks<3, false>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
+                    else if (nq <= 192)
+                        eval_masks<3, true>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
+                    else if (nq <= 256 && !dup)
+                        eval_masks<4, false>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
                     else if (nq <= 256)
-                        eval_masks<4>(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
+                        eval_masks<4, true>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
                     else
                         eval_events(a, L, sbuf, bk, rs, er, ob, oe, lane, dup, n_evals, n_scan);
                     if (multi) {

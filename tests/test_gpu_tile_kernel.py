@@ -97,3 +97,30 @@ def test_autotune_times_the_schedule_in_use(min_len):
             assert times[best_threads, best_core] == min(times.values())
             assert set(listed) <= set(times)
     ix.close()
+
+
+# windows of 750 and 1,050 bases over diverged copies of a unit in a row: a block's
+# minimizers repeat hashes one to four units back, through copies that lost them
+@pytest.mark.parametrize("unit,min_len,w", [(171, 1000, 16), (350, 1000, 16), (600, 1000, 16),
+                                            (350, 1400, 16), (350, 1400, 12)])
+def test_rows_of_copies(oracle_lib, unit, min_len, w):
+    from paper_1807_00205_amd import sdf
+    rng = synth.rng_for(unit + min_len + w)
+    seqs = [synth.random_bases(rng, 9_000) for _ in range(2)]
+    one = synth.random_bases(rng, unit)
+    row = np.concatenate([synth.mutate(rng, one, 0.06) for _ in range(5_000 // unit)])
+    seqs[0][1_000:1_000 + len(row)] = row
+    half = np.concatenate([synth.mutate(rng, one, 0.06) for _ in range(2_500 // unit)])
+    seqs[1][3_000:3_000 + len(half)] = synth.revcomp(half)
+    g = synth.Genome(seqs, [], [(0, 0, 9_000), (1, 0, 9_000)], "rows")
+    b, off = g.concat()
+    ix = sdf.Index(g.seqs, 12, w)
+    os_, oc = oracle_lib.OracleIndex(b, off, 12, w).search(g.spans, 0.25, min_len)
+    for threads in (512, 1024):
+        with sdf.tuning(tile_threads=threads):
+            r = ix.search_batch(g.spans, 0.25, min_len)
+        _same(r.seeds(), os_, SEED_F, "seeds")
+        _same(r.candidates(), oc, CAND_F, "candidates")
+        r.close()
+    assert len(oc) > 0
+    ix.close()
