@@ -650,6 +650,40 @@ __global__ void k_own_keys(const uint32_t *list, uint64_t na, const uint32_t *nl
     val[u] = live ? list[u] : NONE32;
 }
 
+// The three for few entries, by one workgroup in LDS: a small call is bound by its
+// launches (one region of 1.5 kbp: 1,031 us a call; 1,066 with a launch per doubling).
+constexpr uint32_t OWN_SMALL = 4096;
+__global__ __launch_bounds__(1024) void k_own_small(const uint32_t *order, const uint32_t *list,
+                                                    uint32_t na, const uint32_t *nlive,
+                                                    const uint32_t *pred, uint32_t most,
+                                                    uint32_t *key, uint32_t *val) {
+    __shared__ uint32_t own[OWN_SMALL], jump[2][OWN_SMALL];
+    const uint32_t live = nlive ? min(na, *nlive) : na;
+    for (uint32_t e = threadIdx.x; e < live; e += 1024) {
+        const uint32_t id = order[e];
+        own[id] = e;
+        jump[0][id] = pred[id];
+    }
+    __syncthreads();
+    uint32_t from = 0;
+    for (uint32_t reach = 1; reach < most; reach *= 2, from ^= 1) {
+        for (uint32_t u = threadIdx.x; u < live; u += 1024) {
+            const uint32_t id = list[u], p = jump[from][id];
+            uint32_t next = NONE32;
+            if (p != NONE32) {
+                atomicMin(&own[p], own[id]);
+                next = jump[from][p];
+            }
+            jump[from ^ 1][id] = next;
+        }
+        __syncthreads();
+    }
+    for (uint32_t u = threadIdx.x; u < na; u += 1024) {
+        key[u] = u < live ? own[list[u]] : ~0u;
+        val[u] = u < live ? list[u] : NONE32;
+    }
+}
+
 __global__ void k_own_heads(const uint32_t *key, uint64_t na, const uint32_t *nlive,
                             uint32_t *flag) {
     const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1887,17 +1921,23 @@ void by_parts(uint64_t n, uint64_t threads, F &&launch) {
 void take_chains(const uint32_t *order, const uint32_t *list, const uint32_t *pred, uint64_t na,
                  const uint32_t *nlive, uint32_t most, uint32_t *member, uint32_t *flag,
                  uint32_t *pre, uint64_t *first, hipStream_t st) {
-    DevBuf<uint32_t> own(na), key(na), ja(na), jb(na);
-    k_own_init<<<nb(na), 256, 0, st>>>(order, na, nlive, pred, own.p, ja.p);
-    SDF_HIP(hipGetLastError());
-    uint32_t *jin = ja.p, *jout = jb.p;
-    for (uint64_t reach = 1; reach < most; reach *= 2) {
-        k_own_double<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, jin, jout);
+    DevBuf<uint32_t> key(na);
+    if (na <= OWN_SMALL) {
+        k_own_small<<<1, 1024, 0, st>>>(order, list, (uint32_t)na, nlive, pred, most, key.p, member);
         SDF_HIP(hipGetLastError());
-        std::swap(jin, jout);
+    } else {
+        DevBuf<uint32_t> own(na), ja(na), jb(na);
+        k_own_init<<<nb(na), 256, 0, st>>>(order, na, nlive, pred, own.p, ja.p);
+        SDF_HIP(hipGetLastError());
+        uint32_t *jin = ja.p, *jout = jb.p;
+        for (uint64_t reach = 1; reach < most; reach *= 2) {
+            k_own_double<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, jin, jout);
+            SDF_HIP(hipGetLastError());
+            std::swap(jin, jout);
+        }
+        k_own_keys<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, key.p, member);
+        SDF_HIP(hipGetLastError());
     }
-    k_own_keys<<<nb(na), 256, 0, st>>>(list, na, nlive, own.p, key.p, member);
-    SDF_HIP(hipGetLastError());
     int bits = 1;
     while ((1ull << bits) <= na) bits++;
     radix_sort_u32(key.p, member, na, bits, st);

@@ -230,3 +230,31 @@ def test_largest_side_records(oracle_lib, strand):
             found += 1
     assert found == len(sd) == 3
     ix.close()
+
+
+def test_regions_alone_and_together(oracle_lib):
+    """Regions of a few to a few thousand anchors one at a time (their chains
+    taken out by one workgroup), in pairs, and all in one call: the same records
+    each time, the oracle's."""
+    from paper_1807_00205_amd import sdf
+    rng = synth.rng_for(31)
+    sizes = (40, 400, 1_200, 4_000, 12_000, 30_000, 60_000, 90_000, 110_000, 130_000, 131_000, 132_000)
+    q, t, rows, at = [], [], [], 0
+    for u, ln in enumerate(sizes):
+        a = synth.random_bases(rng, ln)
+        b = synth.random_bases(rng, ln)
+        cp = synth.mutate(rng, a[ln // 4:ln // 4 + min(ln // 2, 3_000)], 0.03 * (u % 4))[:ln // 2]
+        b[ln // 3:ln // 3 + len(cp)] = cp
+        q.append(a)
+        t.append(synth.revcomp(b) if u % 2 else b)
+        rows.append((at, at + ln, at, at + ln, u % 2))
+        at += ln
+    q, t = np.concatenate(q), np.concatenate(t)
+    b = np.concatenate([q, t])
+    off = np.array([0, at, 2 * at], np.uint64)
+    rows = [(qb, qe, tb + at, te + at, o) for qb, qe, tb, te, o in rows]
+    ix = sdf.Index([q, t], 12, 16)
+    for part in [[r] for r in rows] + [rows[i:i + 2] for i in range(6, 12, 2)] + [rows]:
+        got = ix.align_regions(_regions(sdf, part, off), 11, 300, 0.25, pad_frac=0.0)
+        _same(got, oracle_lib.sd_align(b, off, part, 11, 300, 0.25, pad_frac=0.0), "%d regions" % len(part))
+    ix.close()
