@@ -515,15 +515,16 @@ sdf_status sdf_result_seeds(sdf_result r, sdf_seed *dst, uint64_t cap, uint64_t 
  * SDF_EXTEND). */
 sdf_status sdf_result_timing(sdf_result r, float *ms, uint32_t n_ms);
 
-/* Work counters of the search: [0] query windows, [1] hits gathered
- * (both passes count once), [2] hits kept by the prefilter, [3] tiles,
- * [4] target partitions, [5] seeds, [6] candidate target starts evaluated,
- * [7] 64-hit words scanned by the per-window sweeps; with SDF_EXTEND also
- * [8] minimizers inserted by the extension, [9] attempts that continued a
- * phase past its gathered horizon, [10] distinct hashes ranked, [11] and
- * [12] workgroup microseconds spent gathering and ranking, and in the
- * phases, [13] microseconds of the slowest region; [14] window starts per
- * tile and [15] tile workgroup threads of the schedule the search ran. */
+/* Work counters of the search: [0] query windows, [1] hits of the partitions'
+ * lists (each once, however often it is loaded), [2] hits kept by the
+ * prefilter, [3] tiles, [4] target partitions, [5] seeds, [6] candidate target
+ * starts evaluated, [7] 64-hit words of kept hits that blocks of 64 windows
+ * went through; with SDF_EXTEND also [8] minimizers inserted by the extension,
+ * [9] attempts that continued a phase past its gathered horizon, [10] distinct
+ * hashes ranked, [11] and [12] workgroup microseconds spent gathering and
+ * ranking, and in the phases, [13] microseconds of the slowest region; [14]
+ * window starts per tile and [15] tile workgroup threads of the schedule the
+ * search ran. */
 sdf_status sdf_result_stats(sdf_result r, uint64_t *v, uint32_t n_v);
 
 void sdf_result_free(sdf_result r);

@@ -2175,9 +2175,9 @@ void sd_align(const IndexView &ix, const uint64_t *h_off, const sdf_region *regi
     DevBuf<uint64_t> ncell(NF + 1), nops(NF + 1), nrow(NF + 1);
     // Stretches a thread takes: a thread needs about 0.25 us per cell whatever
     // else runs, so a call of few stretches waits for its longest; a wave is
-    // idle in most lanes on a small one (50 Mbp, all regions: 161, 155.3, 151.2,
-    // 150.2, 149.7, 149.8, 150.1, 151.3 ms from 4,096, 2,048, 1,024, 512, 256,
-    // 128, 64, 1 cells up; 3 Mbp: 6.3, 5.7, 5.3, 5.0, 4.9, 4.8, 4.8, 4.8 ms).
+    // idle in most lanes on a small one (50 Mbp, all regions: 85.5, 79.4, 75.0,
+    // 73.5, 73.2, 73.3, 73.9, 74.9 ms from 4,096, 2,048, 1,024, 512, 256, 128,
+    // 64, 1 cells up; 3 Mbp: 4.53, 3.90, 3.42, 3.20, 3.10, 3.05, 3.02, 2.98 ms).
     const uint32_t wave_cells = knob(tuning().align_wave_cells, 1u << 8);
     k_seg_count<<<nb(NF), 256, 0, st>>>(an, c, fin, foff.p, nr, nbnd.p, NF, wave_cells, nseg.p,
                                         ncell.p, nops.p, nrow.p);

@@ -438,9 +438,12 @@ void prepare(sdf_index_s *ix, const sdf_span *qs, uint32_t nq, const Params &P, 
     const double hits_per_min = ix->hbar * (double)ix->ne / (double)std::max<uint64_t>(ix->nm, 1);
     // 512 threads, two workgroups per CU, while a tile of 256 window starts and
     // its halo keeps its hits in one partition of that layout's smaller table,
-    // else 1,024 threads, one per CU (measured: 250 Mbp at 20.7 hits per
-    // minimizer 1.65 against 1.95 ms, 3.1 Gbp at 93 hits 199 ms at 320 starts
-    // in two partitions each against 206 ms at 512 in one)
+    // else 1,024 threads, one per CU.  Tile kernel of an assembly against itself
+    // at 9.1, 21.2, 36.1, 60.3 and 93.6 hits per minimizer, both layouts with the
+    // starts of the rule below: 512 threads 3.84, 9.95, 26.9, 70.7, 182.1 ms,
+    // 1,024 threads 4.43, 11.2, 27.9, 70.7, 170.2 ms.  (Fixed starts in two
+    // partitions per tile do a little better at the end, 512 threads at 384
+    // starts 165.4 ms, but not at 60.3 hits: 70.0 with 1.4 partitions a tile.)
     const TileLimits lim512 = tile512::tile_limits();
     const bool sparse = hits_per_min * (256.0 + per_win) <= 0.85 * auto_hits_per_part(lim512, t_min);
     uint32_t threads = threads_override ? threads_override : knob(tu.tile_threads, sparse ? 512u : 1024u);

@@ -1258,6 +1258,8 @@ void launch_extend(const IndexView &ix, const sdf_region *in, uint64_t n, double
     // keeps L in global memory), the elements per workgroup, whether steps are
     // tried in batches and the backward horizon gathered while the forward phase
     // is pending (hb0)
+    // (at least 4,096 or 16,384 steps: 13.8 and 13.6 ms a call for 9,157 regions of
+    // 50 Mbp with copies of up to 50 kbp, 2.77 and 2.88 with copies of up to 4)
     const sdf_tuning &tu = tuning();
     const uint64_t h0 = knob(tu.ext_h0, 4096);
     const uint64_t ecap = std::max<uint64_t>(64, knob(tu.ext_ecap, 1u << 18));
