@@ -1755,7 +1755,9 @@ k_tile_search(SearchArgs) {
                     const uint32_t nq = bk.qhi - bk.qlo;
                     if (nq <= 192 && !dup)
                         eval_masks<3, false>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
-                    else if (nq <= 192)
+                    // (a fourth form costs the 1,024-thread layout, for dense indexes, more
+                    // than it gives: 3.1 Gbp 170.3 against 169.8 ms)
+                    else if (TB == 512 && nq <= 192)
                         eval_masks<3, true>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
                     else if (nq <= 256 && !dup)
                         eval_masks<4, false>(a, L, sbuf, bk, rs, er, ob, oe, lane, n_evals, n_scan);
