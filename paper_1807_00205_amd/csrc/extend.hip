@@ -50,6 +50,7 @@
 
 #include "extend.h"
 #include "search.h"
+#include "wave.h"
 
 namespace sdf {
 
@@ -376,18 +377,6 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
     return __builtin_amdgcn_readlane(wave_incl_sum(v), 63);
 }
 
-// The value of lane ^ j (a constant power of two).
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v, uint32_t j) {
-    switch (j) {
-    case 1: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xf, 0xf, false);
-    case 2: return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xf, 0xf, false);
-    case 4: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (4 << 10) | 0x1F);
-    case 8: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (8 << 10) | 0x1F);
-    case 16: return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (16 << 10) | 0x1F);
-    default: return (uint32_t)__shfl_xor((int)v, (int)j, 64);
-    }
-}
-
 // Keys [b, e) of src (whole buckets, so no hash continues outside, and at most
 // 64 N): one wave sorts them in registers (bitonic, key t * 64 + lane in x[t])
 // and gives every element its rank, equal hashes sharing one.  Ranks of the
@@ -405,28 +394,7 @@ __device__ __forceinline__ void rank_chunk(const uint64_t *src, uint32_t b, uint
         const uint32_t i = t * 64 + lane;
         x[t] = b + i < e ? ((K)((uint32_t)(src[b + i] >> 32) - hbase) << 10) | i : (K)~(K)0;
     }
-#pragma unroll
-    for (uint32_t size = 2; size <= 64u * N; size <<= 1) {
-#pragma unroll
-        for (uint32_t j = size >> 1; j > 0; j >>= 1) {
-#pragma unroll
-            for (int t = 0; t < N; t++) {
-                if (j >= 64) {  // between registers: each pair once
-                    const int f = t ^ (int)(j >> 6);
-                    if (f < t) continue;
-                    const bool up = ((uint32_t)(t * 64) & size) == 0;
-                    const K lo = std::min(x[t], x[f]), hi = std::max(x[t], x[f]);
-                    x[t] = up ? lo : hi;
-                    x[f] = up ? hi : lo;
-                } else {
-                    K y = (K)lane_xor((uint32_t)x[t], j);
-                    if constexpr (sizeof(K) == 8) y |= (K)lane_xor((uint32_t)(x[t] >> 32), j) << 32;
-                    const bool up = (((uint32_t)(t * 64) | lane) & size) == 0, lower = (lane & j) == 0;
-                    x[t] = lower == up ? std::min(x[t], y) : std::max(x[t], y);
-                }
-            }
-        }
-    }
+    wave_sort_keys<K, N>(x, lane);
     uint32_t eid[N];
 #pragma unroll
     for (int t = 0; t < N; t++)
