@@ -56,7 +56,8 @@ constexpr int AMAX_L = 1024, TCAP_L = 512;  // sorted by itself: of a window, of
 // Listed runs that the register launches leave: with a window of up to AMAX_M
 // minimizers, and the others.
 constexpr uint32_t RUN_MID = 1u << 30, RUN_LAST = 1u << 31;
-constexpr uint64_t RUNS_MAX = 1ull << 30;  // runs listed at once
+// Runs taken at once: a launch of a wave per run stays below 2^32 threads.
+constexpr uint64_t RUNS_MAX = 1ull << 25;
 constexpr uint16_t TR_IN = 0x8000, TR_SHARED = 0x4000, TR_RANK = 0x3FF;
 
 template <int AMAX, int TC>

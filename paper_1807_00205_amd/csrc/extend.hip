@@ -30,8 +30,9 @@
 //     from prefix sums over them and from the elements of L next to v, so all
 //     their steps are checked together, and they are inserted up to the first
 //     step refused.
-// The horizon of one attempt is max(h0, longer side) steps per phase.  A
-// phase that runs through it stops at its last step; the next attempt
+// The horizon of one attempt is max(h0, longer side) steps per phase, half of
+// that, and again half, while the minimizers within it are more than the scratch
+// or a hash bucket holds.  A phase that runs through it stops at its last step; the next attempt
 // gathers and ranks again around the region reached and continues the same
 // phase from there (the state is a function of the region, so nothing is
 // repeated).
